@@ -242,6 +242,7 @@ FmmPlan *fmm_plan(superdc_batch *b, int leaf, int crossover) {
     fp->nupper = (int)upper_box.size();
     fp->nupper_item = (int)upper_item.size();
     fp->nsplit = (int)split_box.size();
+    fp->nslot = nslot;
     // work items (64-root pieces of the target leaves) in problem order and longest-first
     std::vector<Tile> lnat, llpt;
     fp->item_off_h.push_back(0);
@@ -288,8 +289,6 @@ FmmPlan *fmm_plan(superdc_batch *b, int leaf, int crossover) {
               fmm_upload(fp, &fp->box_fmm, box_fmm) && fmm_upload(fp, &fp->leaf_fmm, leaf_fmm) &&
               fmm_upload(fp, &fp->leaf_box, leaf_box) && fmm_upload(fp, &fp->upper_box, upper_box) &&
               fmm_upload(fp, &fp->upper_item, upper_item) && fmm_upload(fp, &fp->split_box, split_box) &&
-              fmm_upload(fp, &fp->vpart, std::vector<double>(),
-                         (size_t)nslot * FMM_P * FMMV_MAX_M) &&
               fmm_upload(fp, &fp->leaf_nat, lnat) && fmm_upload(fp, &fp->leaf_lpt, llpt) &&
               fmm_upload(fp, &fp->sitem_nat, snat) && fmm_upload(fp, &fp->sitem_lpt, slpt) &&
               fmm_upload(fp, &fp->eq, std::vector<double2>(), (size_t)fp->nboxes * FMM_P) &&
@@ -307,9 +306,6 @@ FmmPlan *fmm_plan(superdc_batch *b, int leaf, int crossover) {
               fmm_upload(fp, &fp->loc, std::vector<double>(), (size_t)fp->nleaves * FMM_LOC) &&
               fmm_upload(fp, &fp->used, std::vector<int32_t>(), fp->nboxes) &&
               fmm_upload(fp, &fp->vnode, std::vector<double>(), (size_t)fp->nboxes * FMM_P) &&
-              fmm_upload(fp, &fp->vw, std::vector<double>(),
-                         (size_t)fp->nboxes * FMM_P * FMMV_MAX_M) &&
-              fmm_upload(fp, &fp->tail, std::vector<double>(), b->nprob) &&
               fmm_upload(fp, &fp->lgeo, std::vector<double2>(), fp->nboxes) &&
               fmm_upload(fp, &fp->lmom, std::vector<double>(), (size_t)fp->nboxes * FMML_K) &&
               fmm_upload(fp, &fp->t_near_lo, std::vector<int32_t>(), (size_t)fp->nleaves * FMM_NEAR_MAX) &&
@@ -388,29 +384,30 @@ FmmArgs fmm_args(const FmmPlan *fp, const superdc_batch *b, const SolveArgs &a,
     f.nupper_item = fp->nupper_item;
     f.split_box = fp->split_box;
     f.nsplit = fp->nsplit;
-    f.vpart = fp->vpart;
     (void)o;
     return f;
 }
-// The eigenvector-side FMM of one call: the list geometry comes from `pairs` (written by
-// the pack kernel from this call's d) and the last roots' offsets.
-FmmArgs fmm_vec_args(const FmmPlan *fp, const superdc_batch *b, const double2 *pairs,
-                     const int32_t *status) {
+// The eigenvector-side FMM of one call: the list geometry comes from this call's poles and
+// its last roots.
+FmmArgs fmm_vec_args(const FmmPlan *fp, const superdc_batch *b, const double *d,
+                     const double *eta, const int32_t *origin, const int32_t *status) {
     SolveArgs a{};
-    a.dw = const_cast<double2 *>(pairs);
     a.status = const_cast<int32_t *>(status);
     superdc_opts o;
     superdc_opts_default(&o);
     FmmArgs f = fmm_args(fp, b, a, o);
-    f.tail = fp->tail;
+    f.pos = d;
+    f.tail = nullptr;
+    f.teta = eta;
+    f.torg = origin;
     return f;
 }
 
 // The FMM of the sums over the roots (Y = Qhat X): its own lists and use flags, the
-// sources' positions in `pairs` (the roots), the targets at the poles d.
-FmmArgs fmm_roots_args(const FmmPlan *fp, const superdc_batch *b, const double2 *pairs,
+// sources' positions in `pos` (the roots), the targets at the poles d.
+FmmArgs fmm_roots_args(const FmmPlan *fp, const superdc_batch *b, const double *pos,
                        const int32_t *status, const double *d) {
-    FmmArgs f = fmm_vec_args(fp, b, pairs, status);
+    FmmArgs f = fmm_vec_args(fp, b, pos, nullptr, nullptr, status);
     f.tpos = d;
     f.near_lo = fp->t_near_lo;
     f.near_hi = fp->t_near_hi;
@@ -440,22 +437,35 @@ FmmPlan *fmm_for(superdc_ctx *ctx, superdc_batch *b, const superdc_opts &o, int 
     return fp->nfmm > 0 ? fp : nullptr;
 }
 
-// Run the eigenvector-side FMM over every FMM problem of the batch for columns
-// [pk.c0, pk.c0 + v.m): pack the sources, build the lists (first pass only), compress the
-// used boxes, evaluate at the roots (one persistent launch, or one launch per problem).
+// Columns per set of launches for m columns: in small batches up to FMMV_MAX_PASS at once, so
+// that the 16-column groups fill the chip together (one 8192-root problem has 128 items for
+// 256 CUs: 64 columns in four sets of launches took 264 us, in one 88 us; of one 65536-root
+// problem, 560 and 354 us);
+// 16 where the wider pass's equivalent weights (2 KiB a box and group) would exceed 64 MiB --
+// such a batch has items enough for every CU.
+int fmmv_pass(const FmmPlan *fp, int m) {
+    const int64_t groups = ((int64_t)64 << 20) / ((int64_t)std::max(1, fp->nboxes) * FMM_P * FMMV_MAX_M * 8);
+    return std::min<int64_t>(m, FMMV_MAX_M * std::min<int64_t>(FMMV_MAX_PASS / FMMV_MAX_M,
+                                                               std::max<int64_t>(1, groups)));
+}
+
+// workspace for the equivalent weights of a pass of `cols` columns; false: out of memory
+bool fmmv_space(superdc_ctx *ctx, const FmmPlan *fp, int cols, FmmArgs &f, FmmVec &v) {
+    const int ng = (cols + FMMV_MAX_M - 1) / FMMV_MAX_M;
+    v.vnode = fp->vnode;
+    v.vw = (double *)ws_get(ctx, WS_VW, sizeof(double) * fp->nboxes * FMM_P * cols);
+    f.vpart = (double *)ws_get(ctx, WS_VPART, sizeof(double) * fp->nslot * ng * FMM_P * FMMV_MAX_M);
+    return v.vw && f.vpart;
+}
+
+// Run the eigenvector-side FMM over every FMM problem of the batch for the v.m columns of
+// v.X: build the lists (first pass only), compress the used boxes, evaluate at the targets
+// (one persistent launch, or one launch per problem).
 hipError_t fmmv_run(superdc_ctx *ctx, const superdc_batch *b, const FmmPlan *fp,
-                    const FmmArgs &f, FmmvPackArgs pk, const FmmVec &v, bool lists,
-                    bool persistent, hipStream_t s) {
-    pk.tiles = fp->leaf_nat;
-    pk.ntiles = fp->nitems;
-    hipError_t e = hipSuccess;
-    if (lists) {  // the lists need the packed positions first
-        e = launch_fmmv_pack(pk, v, s);
-        if (e == hipSuccess) e = launch_fmm_lists(f, s);
-        if (e == hipSuccess) e = launch_fmmv_sources(f, v, nullptr, s);
-    } else {  // the leaves' launch packs the sources itself
-        e = launch_fmmv_sources(f, v, &pk, s);
-    }
+                    const FmmArgs &f, const FmmVec &v, bool lists, bool persistent,
+                    hipStream_t s) {
+    hipError_t e = lists ? launch_fmm_lists(f, s) : hipSuccess;
+    if (e == hipSuccess) e = launch_fmmv_sources(f, v, s);
     if (e != hipSuccess) return e;
     SolveArgs it{};
     it.off = b->off_d;
@@ -541,30 +551,26 @@ int loewner_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const
     FmmlArgs lf{};
     if (fp) {
         double2 *pairs = (double2 *)ws_get(ctx, WS_VPAIR, sizeof(double2) * b->total);
-        double *src = (double *)ws_get(ctx, WS_VSRC, sizeof(double) * b->total);
-        if (!pairs || !src) return SUPERDC_ENOMEM;
+        if (!pairs) return SUPERDC_ENOMEM;
         pk.off = b->off_d;
         pk.tiles = fp->leaf_nat;
         pk.ntiles = fp->nitems;
         pk.d = d;
-        pk.zhat = zhat;
         pk.eta = eta;
         pk.origin = origin;
         pk.pairs = pairs;
-        pk.tail = fp->tail;
         // every problem uses the FMM: the Loewner packing writes ke as well
         pk.ke = fp->nfmm == b->nprob ? a.ke : nullptr;
         v.m = 1;
         v.kern = 2;
-        v.src = src;
-        v.vnode = fp->vnode;
-        v.vw = fp->vw;
+        v.scale = zhat;
         v.d = d;
         v.origin = origin;
         v.eta = eta;
         v.bout = bnorm;
         v.zh = zhat;
-        f = fmm_vec_args(fp, b, pairs, status);
+        f = fmm_vec_args(fp, b, d, eta, origin, status);
+        if (fmm_b && !fmmv_space(ctx, fp, 1, f, v)) return SUPERDC_ENOMEM;
         lf.pd = pairs;
         lf.geo = fp->lgeo;
         lf.mom = fp->lmom;
@@ -581,7 +587,6 @@ int loewner_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const
             lf.eta = eta;
             lf.origin = origin;
             lf.ke = pk.ke;
-            lf.tail = fp->tail;
         }
         SDC_HIP(launch_fmml_moments(f, lf, s));
     }
@@ -607,7 +612,7 @@ int loewner_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const
         if (fmm_b)
             SDC_HIP(launch_bnorm(a, S, ctx->queues + Q_BNORM,
                                  persistent_grid(ctx, a.ntiles, std::max(1, 32 / S)), s));
-        if (fp && fmm_b) SDC_HIP(fmmv_run(ctx, b, fp, f, pk, v, false, true, s));
+        if (fp && fmm_b) SDC_HIP(fmmv_run(ctx, b, fp, f, v, false, true, s));
     } else {
         for (int p = 0; p < b->nprob; ++p) {
             const int64_t np = b->off_h[p + 1] - b->off_h[p];
@@ -625,7 +630,7 @@ int loewner_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const
             SDC_HIP(launch_loewner(a, S, nullptr, 0, s, false));
             if (fmm_b) SDC_HIP(launch_bnorm(a, S, nullptr, 0, s));
         }
-        if (fp && fmm_b) SDC_HIP(fmmv_run(ctx, b, fp, f, pk, v, false, false, s));
+        if (fp && fmm_b) SDC_HIP(fmmv_run(ctx, b, fp, f, v, false, false, s));
     }
     return SUPERDC_OK;
 }
@@ -678,90 +683,58 @@ int apply_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const d
     if (o.persistent) {
         a.tiles = fp ? fp->dir_lpt[0] : L->lpt;
         a.ntiles = fp ? fp->dir_count[0] : L->count;
-        SDC_HIP(launch_apply(a, use_mfma, ctx->queues + Q_APPLY,
-                             persistent_grid(ctx, a.ntiles, use_mfma ? 4 : 8), s));
+        SDC_HIP(launch_apply(a, use_mfma, ctx->queues + Q_APPLY, ctx->num_cu, s));
     } else {
         for (int p = 0; p < b->nprob; ++p) {
             if (fp && fp->fmm_of_h[p] >= 0) continue;
             a.tiles = L->nat + L->begin[p];
             a.ntiles = L->begin[p + 1] - L->begin[p];
-            SDC_HIP(launch_apply(a, use_mfma, nullptr, 0, s));
+            SDC_HIP(launch_apply(a, use_mfma, nullptr, ctx->num_cu, s));
         }
     }
-    if (fp && trans == 0) {
-        const int mc = std::min(m, FMMV_MAX_M);
-        double2 *pairs = (double2 *)ws_get(ctx, WS_VPAIR, sizeof(double2) * b->total);
-        double *src = (double *)ws_get(ctx, WS_VSRC, sizeof(double) * b->total * mc);
-        if (!pairs || !src) return SUPERDC_ENOMEM;
+    if (!fp) return SUPERDC_OK;
+    FmmVec v{};
+    v.trans = trans;
+    v.kern = 1;
+    v.ldx = ldx;
+    v.scale = trans ? zhat : bnorm;
+    v.d = d;
+    v.origin = origin;
+    v.eta = eta;
+    v.post = trans ? bnorm : zhat;
+    v.ldy = ldy;
+    v.fuse_b = fuse_b ? 1 : 0;
+    v.zh = zhat;
+    v.bout = const_cast<double *>(bnorm);  // written only with fuse_b
+    bool lists = !reuse_lists;
+    FmmArgs f{};
+    if (trans == 0) {
+        double *pos = (double *)ws_get(ctx, WS_VPAIR, sizeof(double) * b->total);
+        if (!pos) return SUPERDC_ENOMEM;
         FmmvPackArgs pk{};
         pk.off = b->off_d;
+        pk.tiles = fp->leaf_nat;
+        pk.ntiles = fp->nitems;
         pk.d = d;
-        pk.zhat = zhat;
-        pk.bnorm = bnorm;
         pk.eta = eta;
         pk.origin = origin;
-        pk.X = X;
-        pk.ldx = ldx;
-        pk.pairs = pairs;
-        pk.tail = fp->tail;
-        FmmVec v{};
-        v.trans = 0;
-        v.kern = 1;
-        v.src = src;
-        v.vnode = fp->vnode;
-        v.vw = fp->vw;
-        v.d = d;
-        v.origin = origin;
-        v.eta = eta;
-        v.post = zhat;
-        v.ldy = ldy;
-        v.zh = zhat;
-        FmmArgs f = fmm_roots_args(fp, b, pairs, status, d);
+        pk.pos = pos;
+        SDC_HIP(launch_fmmv_pos(pk, s));
+        f = fmm_roots_args(fp, b, pos, status, d);
         f.gen = ++fp->t_gen;  // built with the first columns below
-        for (int c0 = 0; c0 < m; c0 += FMMV_MAX_M) {
-            pk.c0 = c0;
-            v.m = std::min(FMMV_MAX_M, m - c0);
-            v.Y = Y + (int64_t)c0 * ldy;
-            // the lists depend on the roots' positions, packed with the first columns
-            SDC_HIP(fmmv_run(ctx, b, fp, f, pk, v, c0 == 0, o.persistent != 0, s));
-        }
-    } else if (fp) {
-        const int mc = std::min(m + (fuse_b ? 1 : 0), FMMV_MAX_M);
-        double2 *pairs = (double2 *)ws_get(ctx, WS_VPAIR, sizeof(double2) * b->total);
-        double *src = (double *)ws_get(ctx, WS_VSRC, sizeof(double) * b->total * mc);
-        if (!pairs || !src) return SUPERDC_ENOMEM;
-        FmmvPackArgs pk{};
-        pk.off = b->off_d;
-        pk.d = d;
-        pk.zhat = zhat;
-        pk.eta = eta;
-        pk.origin = origin;
-        pk.X = X;
-        pk.ldx = ldx;
-        pk.pairs = pairs;
-        pk.tail = fp->tail;
-        FmmVec v{};
-        v.trans = 1;
-        v.kern = 1;
-        v.src = src;
-        v.vnode = fp->vnode;
-        v.vw = fp->vw;
-        v.d = d;
-        v.origin = origin;
-        v.eta = eta;
-        v.post = bnorm;
-        v.ldy = ldy;
-        v.fuse_b = fuse_b ? 1 : 0;
-        v.zh = zhat;
-        v.bout = const_cast<double *>(bnorm);  // written only with fuse_b
-        FmmArgs f = fmm_vec_args(fp, b, pairs, status);
-        if (!reuse_lists) f.gen = ++fp->gen;  // built with the first columns below
-        for (int c0 = 0; c0 < m; c0 += FMMV_MAX_M) {
-            pk.c0 = c0;
-            v.m = std::min(FMMV_MAX_M, m - c0) + v.fuse_b;  // one chunk when fused
-            v.Y = Y + (int64_t)c0 * ldy;
-            SDC_HIP(fmmv_run(ctx, b, fp, f, pk, v, c0 == 0 && !reuse_lists, o.persistent != 0, s));
-        }
+        lists = true;
+    } else {
+        f = fmm_vec_args(fp, b, d, eta, origin, status);
+        if (lists) f.gen = ++fp->gen;  // built with the first columns below
+    }
+    const int pass = fmmv_pass(fp, m + v.fuse_b);  // one pass when fused
+    if (!fmmv_space(ctx, fp, pass, f, v)) return SUPERDC_ENOMEM;
+    for (int c0 = 0; c0 < m; c0 += pass) {
+        v.m = std::min(pass, m + v.fuse_b - c0);
+        v.X = X + (int64_t)c0 * ldx;
+        v.Y = Y + (int64_t)c0 * ldy;
+        SDC_HIP(fmmv_run(ctx, b, fp, f, v, lists, o.persistent != 0, s));
+        lists = false;
     }
     return SUPERDC_OK;
 }

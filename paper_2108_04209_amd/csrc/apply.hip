@@ -82,19 +82,21 @@ __device__ __forceinline__ void apply_store(const ApplyStage<NCT> &st, double *X
     }
 }
 
-// NCT: 16-column blocks per pass (the pass width is 16 NCT columns)
+// NCT: 16-column blocks per pass (the pass width is 16 NCT columns); this item's pass starts
+// at column c0
 template <int TRANS, int NCT>
-__device__ void apply_tile_mfma(const ApplyArgs &a, Tile t, double *Xs, double2 *Sd) {
+__device__ void apply_tile_mfma(const ApplyArgs &a, Tile t, int c0, double *Xs, double2 *Sd) {
     const int p = t.prob;
     const int64_t base = a.off[p];
     const int n = (int)(a.off[p + 1] - base);
     const int lane = lane_id();
     const int wv = threadIdx.x / WAVE;
     const int o0 = t.row0;
+    const int ncols = min(16 * NCT, a.m - c0);
     if (a.status[p] & ~SUPERDC_ST_NOCONV) {
         const double nan = __builtin_nan("");
-        for (int e = threadIdx.x; e < AP_ROWS * a.m; e += blockDim.x) {
-            const int r = o0 + (e % AP_ROWS), c = e / AP_ROWS;
+        for (int e = threadIdx.x; e < AP_ROWS * ncols; e += blockDim.x) {
+            const int r = o0 + (e % AP_ROWS), c = c0 + e / AP_ROWS;
             if (r < n) a.Y[base + r + (int64_t)c * a.ldy] = nan;
         }
         if (TRANS == 1 && a.fuse_b && threadIdx.x < AP_ROWS && o0 + (int)threadIdx.x < n)
@@ -112,80 +114,76 @@ __device__ void apply_tile_mfma(const ApplyArgs &a, Tile t, double *Xs, double2 
         ra = a.d[base + clamp_idx(a.origin[base + oc], n)];
         rb = a.eta[base + oc];
     }
-    constexpr int PW = 16 * NCT;  // columns per pass
-    for (int c0 = 0; c0 < a.m; c0 += PW) {
-        const int ncols = min(PW, a.m - c0);
-        const int nct = (ncols + 15) / 16;
-        v4d acc[NCT];
+    const int nct = (ncols + 15) / 16;
+    v4d acc[NCT];
 #pragma unroll
-        for (int ct = 0; ct < NCT; ++ct) acc[ct] = v4d{0.0, 0.0, 0.0, 0.0};
-        // fuse_b (one pass of at most 15 columns): b = sum (zhat_s / t)^2, each term squared
-        // after the division as the b kernel does (zhat^2 and 1/t^2 apart can leave the
-        // exponent range); each lane sums the terms of the entries it generates, on the
-        // VALU beside the multiply (one column does not need the MFMA)
-        const bool fb = TRANS == 1 && NCT == 1 && a.fuse_b;
-        double bsum = 0.0;
-        ApplyStage<NCT> st;
-        apply_fetch<TRANS, NCT>(a, base, n, 0, c0, ncols, st);
-        for (int s0 = 0; s0 < n; s0 += AP_K) {
-            __syncthreads();  // the previous chunk's reads of Xs/Sd are done
-            apply_store<NCT>(st, Xs, Sd);
-            __syncthreads();
-            // the next chunk's loads are in flight while this one is multiplied
-            if (s0 + AP_K < n) apply_fetch<TRANS, NCT>(a, base, n, s0 + AP_K, c0, ncols, st);
-            // one slice of 4 sources: this lane's Cauchy entry (one reciprocal with a Newton
-            // step) into the MFMA of every column tile; MASK: padding entries past the
-            // problem's end are zeroed.  A row past the end (ovalid false) only feeds its own
-            // output row, never written.
+    for (int ct = 0; ct < NCT; ++ct) acc[ct] = v4d{0.0, 0.0, 0.0, 0.0};
+    // fuse_b (one pass of at most 15 columns): b = sum (zhat_s / t)^2, each term squared
+    // after the division as the b kernel does (zhat^2 and 1/t^2 apart can leave the
+    // exponent range); each lane sums the terms of the entries it generates, on the
+    // VALU beside the multiply (one column does not need the MFMA)
+    const bool fb = TRANS == 1 && NCT == 1 && a.fuse_b;
+    double bsum = 0.0;
+    ApplyStage<NCT> st;
+    apply_fetch<TRANS, NCT>(a, base, n, 0, c0, ncols, st);
+    for (int s0 = 0; s0 < n; s0 += AP_K) {
+        __syncthreads();  // the previous chunk's reads of Xs/Sd are done
+        apply_store<NCT>(st, Xs, Sd);
+        __syncthreads();
+        // the next chunk's loads are in flight while this one is multiplied
+        if (s0 + AP_K < n) apply_fetch<TRANS, NCT>(a, base, n, s0 + AP_K, c0, ncols, st);
+        // one slice of 4 sources: this lane's Cauchy entry (one reciprocal with a Newton
+        // step) into the MFMA of every column tile; MASK: padding entries past the
+        // problem's end are zeroed.  A row past the end (ovalid false) only feeds its own
+        // output row, never written.
 #define SDC_AP_SLICE(MASK)                                                                 \
-    {                                                                                      \
-        const int sl = kk + (lane >> 4);                                                   \
-        const double2 sd = Sd[sl];                                                         \
-        const double tt = TRANS ? (sd.x - ra) - rb : (ra - sd.x) - sd.y;                   \
-        const double av = (!(MASK) || s0 + sl < n) ? rcp_nr1(tt) : 0.0;                   \
-        _Pragma("unroll") for (int ct = 0; ct < NCT; ++ct) {                               \
-            if (ct < nct) {                                                                \
-                const double bv = Xs[(ct * 16 + (lane & 15)) * AP_LD + sl];                \
-                acc[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc[ct], 0, 0, 0);  \
-                if (fb) {                                                                  \
-                    const double qv = av * sd.y;                                           \
-                    bsum = fma(qv, qv, bsum);                                              \
-                }                                                                          \
-            }                                                                              \
-        }                                                                                  \
-    }
+{                                                                                      \
+    const int sl = kk + (lane >> 4);                                                   \
+    const double2 sd = Sd[sl];                                                         \
+    const double tt = TRANS ? (sd.x - ra) - rb : (ra - sd.x) - sd.y;                   \
+    const double av = (!(MASK) || s0 + sl < n) ? rcp_nr1(tt) : 0.0;                   \
+    _Pragma("unroll") for (int ct = 0; ct < NCT; ++ct) {                               \
+        if (ct < nct) {                                                                \
+            const double bv = Xs[(ct * 16 + (lane & 15)) * AP_LD + sl];                \
+            acc[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc[ct], 0, 0, 0);  \
+            if (fb) {                                                                  \
+                const double qv = av * sd.y;                                           \
+                bsum = fma(qv, qv, bsum);                                              \
+            }                                                                          \
+        }                                                                              \
+    }                                                                                  \
+}
 #pragma unroll 4
-            for (int kk = 0; kk < AP_K; kk += 4) SDC_AP_SLICE(true)
+        for (int kk = 0; kk < AP_K; kk += 4) SDC_AP_SLICE(true)
 #undef SDC_AP_SLICE
-            mfma_drain();  // before any copy of the accumulators between chunks
-        }
-        if (fb) {  // the four lanes of a Cauchy row (lane % 16) hold its partial sums
-            bsum += __shfl_xor(bsum, 16);
-            bsum += __shfl_xor(bsum, 32);
-        }
-        if (a.work && threadIdx.x == 0) {  // kernel timing: this pass's algorithmic flops
-            const unsigned long long rows = (unsigned long long)min(AP_ROWS, n - o0);
-            const unsigned long long me = (unsigned long long)(ncols + (fb ? 1 : 0));
-            atomicAdd(a.work, rows * (unsigned long long)n * (2 * me + 3) + 2 * rows * me);
-        }
-        mfma_drain();
-        // v_mfma_f64_16x16x4f64 returns D[4 v + lane/16][lane % 16] in accumulator v
+        mfma_drain();  // before any copy of the accumulators between chunks
+    }
+    if (fb) {  // the four lanes of a Cauchy row (lane % 16) hold its partial sums
+        bsum += __shfl_xor(bsum, 16);
+        bsum += __shfl_xor(bsum, 32);
+    }
+    if (a.work && threadIdx.x == 0) {  // kernel timing: this pass's algorithmic flops
+        const unsigned long long rows = (unsigned long long)min(AP_ROWS, n - o0);
+        const unsigned long long me = (unsigned long long)(ncols + (fb ? 1 : 0));
+        atomicAdd(a.work, rows * (unsigned long long)n * (2 * me + 3) + 2 * rows * me);
+    }
+    mfma_drain();
+    // v_mfma_f64_16x16x4f64 returns D[4 v + lane/16][lane % 16] in accumulator v
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int row = o0 + wv * 16 + 4 * v + (lane >> 4);
-            double postb = 0.0;
-            if (fb) {  // b's sum of this row is held by the lanes that generated its entries
-                postb = 1.0 / sqrt(__shfl(bsum, 4 * v + (lane >> 4)));
-                if (row < n && (lane & 15) == 0) a.bout[base + row] = postb;
-            }
-            if (row < n) {
-                const double post = fb ? postb : (TRANS ? a.bnorm[base + row] : a.zhat[base + row]);
+    for (int v = 0; v < 4; ++v) {
+        const int row = o0 + wv * 16 + 4 * v + (lane >> 4);
+        double postb = 0.0;
+        if (fb) {  // b's sum of this row is held by the lanes that generated its entries
+            postb = 1.0 / sqrt(__shfl(bsum, 4 * v + (lane >> 4)));
+            if (row < n && (lane & 15) == 0) a.bout[base + row] = postb;
+        }
+        if (row < n) {
+            const double post = fb ? postb : (TRANS ? a.bnorm[base + row] : a.zhat[base + row]);
 #pragma unroll
-                for (int ct = 0; ct < NCT; ++ct) {
-                    const int col = ct * 16 + (lane & 15);
-                    if (ct < nct && col < ncols)
-                        a.Y[base + row + (int64_t)(c0 + col) * a.ldy] = post * acc[ct][v];
-                }
+            for (int ct = 0; ct < NCT; ++ct) {
+                const int col = ct * 16 + (lane & 15);
+                if (ct < nct && col < ncols)
+                    a.Y[base + row + (int64_t)(c0 + col) * a.ldy] = post * acc[ct][v];
             }
         }
     }
@@ -196,8 +194,9 @@ __global__ __launch_bounds__(256) void k_apply_mfma(ApplyArgs a, Queue *q) {
     __shared__ double Xs[16 * NCT * AP_LD];
     __shared__ double2 Sd[AP_K];
     __shared__ int slot;
-    for_each_item(q, a.ntiles, &slot, [&](int item) {
-        apply_tile_mfma<TRANS, NCT>(a, a.tiles[item], Xs, Sd);
+    const int np = (a.m + 16 * NCT - 1) / (16 * NCT);  // passes of a tile: neighbouring items
+    for_each_item(q, a.ntiles * np, &slot, [&](int item) {
+        apply_tile_mfma<TRANS, NCT>(a, a.tiles[item / np], item % np * (16 * NCT), Xs, Sd);
     });
 }
 
@@ -303,14 +302,17 @@ __global__ __launch_bounds__(WAVE * AV_W) void k_apply_valu(ApplyArgs a, Queue *
     });
 }
 
-hipError_t launch_apply(const ApplyArgs &a0, int use_mfma, Queue *q, int grid, hipStream_t s) {
+hipError_t launch_apply(const ApplyArgs &a0, int use_mfma, Queue *q, int num_cu, hipStream_t s) {
     if (a0.ntiles <= 0) return hipSuccess;
     ApplyArgs a = a0;
     a.work = trace_work(use_mfma ? KID_APPLY_MFMA : KID_APPLY_VALU);
-    const dim3 g(q ? grid : a.ntiles);
     if (use_mfma) {
-        // the pass width: 16, 32 or 64 columns, the smallest that covers m (64 beyond)
-        const int nct = a.m <= 16 ? 1 : (a.m <= 32 ? 2 : 4);
+        // the pass width: 16, 32 or 64 columns, the smallest that covers m (64 beyond), and
+        // narrower while the items (64 rows x a pass) are fewer than two per CU
+        int nct = a.m <= 16 ? 1 : (a.m <= 32 ? 2 : 4);
+        auto items = [&] { return a.ntiles * ((a.m + 16 * nct - 1) / (16 * nct)); };
+        while (nct > 1 && items() < 2 * num_cu) nct /= 2;
+        const dim3 g(q ? min(items(), num_cu * 4) : items());
 #define SDC_APPLY_MFMA(T, C) \
     SDC_LAUNCH(KID_APPLY_MFMA, (k_apply_mfma<T, C>), g, dim3(256), 0, s, a, q)
         if (a.trans) {
@@ -324,6 +326,7 @@ hipError_t launch_apply(const ApplyArgs &a0, int use_mfma, Queue *q, int grid, h
         }
 #undef SDC_APPLY_MFMA
     } else {
+        const dim3 g(q ? min(a.ntiles, num_cu * 8) : a.ntiles);
         if (a.trans)
             SDC_LAUNCH(KID_APPLY_VALU, k_apply_valu<1>, g, dim3(WAVE * AV_W), 0, s, a, q);
         else

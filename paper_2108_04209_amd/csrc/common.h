@@ -201,8 +201,8 @@ class TraceScope {
 
 enum WsSlot {
     WS_DW = 0, WS_KE = 1, WS_DZ = 2, WS_Z2 = 3, WS_BK = 4, WS_BP = 5, WS_TMP = 6, WS_VPAIR = 7,
-    WS_VSRC = 8, WS_DEFL_VAL = 9, WS_DEFL_FLAG = 10, WS_DEFL_T = 11, WS_DEFL_SEGI = 12,
-    WS_DEFL_SEGD = 13, kNumWs
+    WS_VW = 8, WS_DEFL_VAL = 9, WS_DEFL_FLAG = 10, WS_DEFL_T = 11, WS_DEFL_SEGI = 12,
+    WS_DEFL_SEGD = 13, WS_VPART = 14, kNumWs
 };
 
 struct superdc_ctx {
@@ -354,7 +354,8 @@ struct ApplyArgs {
     unsigned long long *work;  // kernel timing on: algorithmic flops of the launch, (2m + 3)
                                // per Cauchy entry plus 2m per output row (set by launch_apply)
 };
-hipError_t launch_apply(const ApplyArgs &a, int use_mfma, Queue *q, int grid, hipStream_t s);
+// persistent (q != nullptr) launches size themselves from num_cu
+hipError_t launch_apply(const ApplyArgs &a, int use_mfma, Queue *q, int num_cu, hipStream_t s);
 
 struct BwdArgs {
     const int64_t *off;

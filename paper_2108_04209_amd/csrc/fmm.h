@@ -38,7 +38,10 @@ struct FmmArgs {
     const int32_t *leaf_off;  // [nfmm + 1]
     const int32_t *height;    // [nfmm] tree height H (levels 0..H)
     const double2 *dw;        // (d_j, w_j) of the batch (from validation); .x alone for geometry
-    const double *tail;       // [nprob] bound of the last root above d_{n-1}
+    const double *pos;        // when set, the points' positions (instead of dw's .x)
+    const double *tail;       // [nprob] bound of the last root above d_{n-1}; nullptr: taken
+    const double *teta;       // from the last root itself (its gap and origin; the poles are
+    const int32_t *torg;      // pos)
     const int32_t *status;
     int32_t *used;            // [nboxes] == gen if some target leaf of the current lists lists
                               // the box as far field
@@ -73,7 +76,7 @@ struct FmmArgs {
     int nupper_item;
     const int2 *split_box;    // [nsplit]
     int nsplit;
-    double *vpart;            // [slots][FMM_P][FMMV_MAX_M]
+    double *vpart;            // [slots][column groups][FMM_P][FMMV_MAX_M]
     // targets of the lists: nullptr, the roots of the solver (a target leaf's roots lie in
     // [d_first, d_next]); else the positions of the target points themselves (the poles, for
     // sums over the roots), a leaf spanning [tpos[first], tpos[last]]
@@ -92,8 +95,7 @@ struct FmmPlan {
     int nupper = 0;
     int4 *upper_item = nullptr;
     int2 *split_box = nullptr;
-    int nupper_item = 0, nsplit = 0;
-    double *vpart = nullptr;
+    int nupper_item = 0, nsplit = 0, nslot = 0;
     double2 *eq = nullptr;
     int32_t *near_lo = nullptr, *near_hi = nullptr, *far_l = nullptr, *far_r = nullptr;
     int32_t *cnt = nullptr, *near_lf = nullptr;
@@ -119,8 +121,7 @@ struct FmmPlan {
     std::vector<int32_t> dir_count;
     int32_t *used = nullptr;           // [nboxes], zeroed at creation
     int gen = 0, t_gen = 0;            // numbers of the last lists built (solver's, roots')
-    double *vnode = nullptr, *vw = nullptr;  // eigenvector-side equivalent sources
-    double *tail = nullptr;            // [nprob] per-call bound of the last root
+    double *vnode = nullptr;           // eigenvector-side equivalent sources' positions
     double2 *lgeo = nullptr;           // Loewner far field: box geometry and moments
     double *lmom = nullptr;
     // the lists of the sums over the roots (Y = Qhat X: sources at the roots, targets at the
@@ -139,12 +140,17 @@ struct FmmPlan {
 // with trans = 0, sums over the roots j for every pole i, sum_j src_j,c / (d_i - lambda_j)
 // (the apply Y = Qhat X: src = b_j X_j,c, scaled by zhat_i), sources at the roots.
 struct FmmVec {
-    int m;                    // columns of src (<= FMMV_MAX_M)
+    int m;                    // weight columns (<= FMMV_MAX_PASS), in groups of FMMV_MAX_M
     int kern;                 // 1: 1/t, 2: 1/t^2
     int trans;                // 1: sums over the poles (targets the roots); 0: over the roots
-                              // (source positions lambda_j = d_{K_j} + eta_j, in the .x of
-                              // the pairs the pack kernel writes)
-    double *src;              // [total][m] pole-major source weights
+                              // (source positions lambda_j = d_{K_j} + eta_j, written by
+                              // launch_fmmv_pos)
+    // The sources' weights are read from X itself, src_s,c = scale_s X_s,c (kern 2: scale_s^2;
+    // scale: zhat, or b for trans 0): X is column-major, so 64 sources of a column are one
+    // 512-byte run, and no packed copy of it has to be written and read back
+    const double *X;
+    int64_t ldx;
+    const double *scale;
     double *vnode;            // [boxes][FMM_P] equivalent source nodes
     double *vw;               // [boxes][FMM_P][m] equivalent source weights
     const double *d;          // poles
@@ -162,7 +168,8 @@ struct FmmVec {
                               // launch_fmmv_eval): (2m + 3) per near pole or far source of a
                               // root for kern 1, 6 for kern 2, plus the output scaling
 };
-constexpr int FMMV_MAX_M = 16;
+constexpr int FMMV_MAX_M = 16;       // columns per group (the MFMA tile)
+constexpr int FMMV_MAX_PASS = 64;    // columns per set of launches
 constexpr int FMMV_PART_PTS = 512;   // points per part of an upper box's sources (2 chunks)
 
 // Loewner far field (Sec. 4.3, eqs. lowner2 and logv with local shifting): for a far box B
@@ -181,32 +188,28 @@ struct FmmlArgs {
     double *mom;              // [boxes][FMML_K] moments M_1 .. M_K
     // pack != 0: the leaves' launch packs its poles itself (when the lists already exist, as
     // the separate packing launch would): (d_j, delta_j) into pd, (d_{K_j}, eta_j) into ke
-    // when ke is set, and the last delta of each problem into tail
+    // when ke is set
     int pack;
     const double *d, *eta;
     const int32_t *origin;
     double2 *ke;
-    double *tail;
 };
 hipError_t launch_fmml_moments(const FmmArgs &f, const FmmlArgs &l, hipStream_t s);
 
-// packing of the source weights of the FMM problems (and the list geometry)
+// per-entry packing for the FMM problems: launch_fmml_pack the (d_j, delta_j) pairs of the
+// Loewner far field, launch_fmmv_pos the roots' positions
 struct FmmvPackArgs {
     const int64_t *off;
     const Tile *tiles;   // 64-entry tiles of the FMM problems
     int ntiles;
-    const double *d, *zhat, *eta;
-    const double *bnorm; // trans 0: b_j, the sources' scale
+    const double *d, *eta;
     const int32_t *origin;
-    const double *X;     // kern 1: right-hand sides (column-major, ld ldx), columns c0..c0+m-1
-    int64_t ldx;
-    int c0;
-    double2 *pairs;      // (d_i, zhat_i) for the list geometry; trans 0: (lambda_j, b_j)
-    double *tail;        // [nprob] lambda_{n-1} - d_{n-1}
+    double2 *pairs;
+    double *pos;         // launch_fmmv_pos: lambda_j = d_{K_j} + eta_j
     double2 *ke;         // Loewner packing, when every problem of the batch uses the FMM:
                          // also (d_{K_j}, eta_j) for every root (else nullptr)
 };
-hipError_t launch_fmmv_pack(const FmmvPackArgs &a, const FmmVec &v, hipStream_t s);
+hipError_t launch_fmmv_pos(const FmmvPackArgs &a, hipStream_t s);
 // Loewner far field: (d_j, delta_j) pairs and the last roots' offsets, then the products
 hipError_t launch_fmml_pack(const FmmvPackArgs &a, hipStream_t s);
 hipError_t launch_loewner_fmm(const VecArgs &a, const FmmArgs &f, const FmmlArgs &l, int split,
@@ -216,10 +219,7 @@ hipError_t launch_loewner_fmm(const VecArgs &a, const FmmArgs &f, const FmmlArgs
 hipError_t launch_fmm_build(const FmmArgs &f, hipStream_t s);
 // interaction lists only (no secular equivalent sources)
 hipError_t launch_fmm_lists(const FmmArgs &f, hipStream_t s);
-// pk: when set, the leaves' launch packs the sources itself (pk.pairs non-null; the lists
-// must exist already), in place of launch_fmmv_pack
-hipError_t launch_fmmv_sources(const FmmArgs &f, const FmmVec &v, const FmmvPackArgs *pk,
-                               hipStream_t s);
+hipError_t launch_fmmv_sources(const FmmArgs &f, const FmmVec &v, hipStream_t s);
 // grid: persistent (q != nullptr) launches size themselves from num_cu
 hipError_t launch_fmmv_eval(const SolveArgs &items, const FmmArgs &f, const FmmVec &v, int split,
                             Queue *q, int num_cu, hipStream_t s);

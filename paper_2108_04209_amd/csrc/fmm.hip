@@ -165,12 +165,22 @@ __global__ __launch_bounds__(EQ ? 2 * WAVE : WAVE) void k_fmm_lists(FmmArgs f) {
         if (lane == 0) cnt[0] = -1;
         return;
     }
-    const double2 *dw = f.dw + base;
+    auto at = [&](int i) { return f.pos ? f.pos[base + i] : f.dw[base + i].x; };
     // the target leaf's span: its roots lie in [d_first, d_next] (the solver's targets), or
     // the target points themselves (poles, for the sums over the roots)
-    const double xa = f.tpos ? f.tpos[base + i0] : dw[i0].x;
-    const double xb = f.tpos ? f.tpos[base + i1 - 1]
-                             : (i1 < n ? dw[i1].x : dw[n - 1].x + fmax(f.tail[p], 0.0));
+    const double xa = f.tpos ? f.tpos[base + i0] : at(i0);
+    double xb;
+    if (f.tpos) {
+        xb = f.tpos[base + i1 - 1];
+    } else if (i1 < n) {
+        xb = at(i1);
+    } else {
+        const double last = at(n - 1);
+        const double tail =
+            f.tail ? f.tail[p]
+                   : (at(clamp_idx(f.torg[base + n - 1], n)) - last) + f.teta[base + n - 1];
+        xb = last + fmax(tail, 0.0);
+    }
     int32_t *far_l = f.far_l + (int64_t)L * FMM_FAR_MAX;
     int32_t *far_r = f.far_r + (int64_t)L * FMM_FAR_MAX;
     int32_t *near_lo = f.near_lo + (int64_t)L * FMM_NEAR_MAX;
@@ -186,7 +196,7 @@ __global__ __launch_bounds__(EQ ? 2 * WAVE : WAVE) void k_fmm_lists(FmmArgs f) {
         const int lo = (int)min((int64_t)n, i * span), hi = (int)min((int64_t)n, (i + 1) * span);
         const bool live = valid && lo < hi;  // empty boxes are dropped
         // the box's span: its first and last point
-        const double2 ab = live ? make_double2(dw[lo].x, dw[hi - 1].x) : make_double2(0.0, 0.0);
+        const double2 ab = live ? make_double2(at(lo), at(hi - 1)) : make_double2(0.0, 0.0);
         const double width = ab.y - ab.x;
         const bool fl = live && ab.y < xa && xa - ab.y >= f.sep * width && hi <= i0 - TILE;
         const bool fr = live && !fl && ab.x > xb && ab.x - xb >= f.sep * width && lo >= i1 + TILE;

@@ -18,42 +18,13 @@ namespace sdc {
 typedef double v4d_f __attribute__((ext_vector_type(4)));
 
 
-// src_i,c = zhat_i X_i,c0+c (kern 1) or zhat_i^2 (kern 2) for pole i of problem p (entries
-// from base).  trans 0: src_j,c = b_j X_j,c0+c at the root lambda_j (positions in pairs[j].x)
-__device__ __forceinline__ void fmmv_pack_entry(const FmmvPackArgs &a, const FmmVec &v, int p,
-                                                int64_t base, int n, int i) {
-    if (v.trans == 0) {
-        const int K = clamp_idx(a.origin[base + i], n);
-        const double bj = a.bnorm[base + i];
-        a.pairs[base + i] = make_double2(a.d[base + K] + a.eta[base + i], bj);
-        double *src = v.src + (base + i) * v.m;
-        for (int c = 0; c < v.m; ++c) src[c] = bj * a.X[base + i + (int64_t)(a.c0 + c) * a.ldx];
-        return;
-    }
-    const double zh = a.zhat[base + i];
-    const double di = a.d[base + i];
-    a.pairs[base + i] = make_double2(di, zh);
-    double *src = v.src + (base + i) * v.m;
-    if (v.kern == 1) {
-        const int mx = v.m - v.fuse_b;
-        for (int c = 0; c < mx; ++c) src[c] = zh * a.X[base + i + (int64_t)(a.c0 + c) * a.ldx];
-        if (v.fuse_b) src[mx] = zh * zh;
-    } else {
-        src[0] = zh * zh;
-    }
-    if (i == n - 1) {
-        const int K = clamp_idx(a.origin[base + i], n);
-        a.tail[p] = (a.d[base + K] + a.eta[base + i]) - di;
-    }
-}
-
-// one lane per pole (per root for trans 0)
-__global__ __launch_bounds__(64) void k_fmmv_pack(FmmvPackArgs a, FmmVec v) {
+// lambda_j = d_{K_j} + eta_j, the positions of the sums over the roots; one lane per root
+__global__ __launch_bounds__(64) void k_fmmv_pos(FmmvPackArgs a) {
     const Tile t = a.tiles[blockIdx.x];
     const int64_t base = a.off[t.prob];
     const int n = (int)(a.off[t.prob + 1] - base);
-    const int i = t.row0 + lane_id();
-    if (i < n) fmmv_pack_entry(a, v, t.prob, base, n, i);
+    const int j = t.row0 + lane_id();
+    if (j < n) a.pos[base + j] = a.d[base + clamp_idx(a.origin[base + j], n)] + a.eta[base + j];
 }
 
 // Equivalent sources, one workgroup (256 threads) per box, in two launches: LEAVES = true
@@ -63,11 +34,12 @@ __global__ __launch_bounds__(64) void k_fmmv_pack(FmmvPackArgs a, FmmVec v) {
 // interpolation accuracy, and the box's nodes interpolate it again).  Points are taken a
 // chunk at a time: each of the chunk's threads forms the 16 Lagrange values of one point in
 // LDS, then W_q,c += sum_k L_q(x_k) w_k,c over the chunk runs on the FP64 MFMA, its weight
-// operands loaded straight from memory (they are point-major: the 4 points x m columns of
-// one step are consecutive) before the Lagrange values are formed.
+// operands loaded straight from memory before the Lagrange values are formed: a leaf's from
+// the columns of X (each lane the 16 consecutive points of one column that it feeds), an
+// upper box's from the leaves' weights (point-major: the 4 points x 16 columns of one step
+// are 128-byte runs).  blockIdx.y is the group of FMMV_MAX_M columns.
 template <bool LEAVES>
-__global__ __launch_bounds__(LEAVES ? 64 : 256, LEAVES ? 1 : 4) void k_fmmv_sources(FmmArgs f, FmmVec v,
-                                                                              FmmvPackArgs pk) {
+__global__ __launch_bounds__(LEAVES ? 64 : 256, LEAVES ? 1 : 4) void k_fmmv_sources(FmmArgs f, FmmVec v) {
     // leaves: one wavefront, 64 points per chunk; upper boxes (up to 16 sources per leaf
     // below): four wavefronts, 256 points per chunk
     constexpr int NW = LEAVES ? 1 : 4;
@@ -92,23 +64,26 @@ __global__ __launch_bounds__(LEAVES ? 64 : 256, LEAVES ? 1 : 4) void k_fmmv_sour
     const int lo = (int)min((int64_t)n, bi * span), hi = (int)min((int64_t)n, (bi + 1) * span);
     if (lo >= hi) return;  // empty box (never listed)
     const int tid = threadIdx.x;
-    if (LEAVES && pk.pairs) {  // the leaf's poles packed here, as k_fmmv_pack would
-        for (int i = lo + tid; i < hi; i += blockDim.x) fmmv_pack_entry(pk, v, p, base, n, i);
-        __syncthreads();
-    }
     const int m = v.m;
-    const double2 *d2 = f.dw + base;  // the points' positions in .x (poles, or roots)
-    auto d = [&](int i) { return d2[i].x; };
-    const double *src = v.src + base * m;
-    const double a = d(lo), b = d(hi - 1);
+    const int g0 = blockIdx.y * FMMV_MAX_M;       // this group's columns [g0, g0 + mg)
+    const int mg = min(FMMV_MAX_M, m - g0);
+    const int mx = v.kern == 2 ? 0 : min(mg, m - v.fuse_b - g0);  // those that are X's
+    const double *d = f.pos + base;               // the points' positions (poles, or roots)
+    const double *sc = v.scale + base;
+    const double *X = v.kern == 2 ? nullptr : v.X + base + (int64_t)g0 * v.ldx;
+    // weight of point i in column c of the group: scale X, or scale^2 for the b sum's column
+    auto weight = [&](int i, int c) {
+        return c < mx ? sc[i] * X[i + (int64_t)c * v.ldx] : (c < mg ? sc[i] * sc[i] : 0.0);
+    };
+    const double a = d[lo], b = d[hi - 1];
     const double cc = 0.5 * (a + b), hw = 0.5 * (b - a);
     double *node = v.vnode + (int64_t)g * FMM_P;
-    double *w = v.vw + (int64_t)g * FMM_P * m;
+    double *w = v.vw + (int64_t)g * FMM_P * m + g0;
     if (LEAVES && hi - lo <= FMM_P) {  // few poles: they are their own equivalent sources
         if (tid < FMM_P) {
             const bool in = lo + tid < hi;
-            node[tid] = in ? d(lo + tid) : cc;
-            for (int c = 0; c < m; ++c) w[tid * m + c] = in ? src[(int64_t)(lo + tid) * m + c] : 0.0;
+            if (blockIdx.y == 0) node[tid] = in ? d[lo + tid] : cc;
+            for (int c = 0; c < mg; ++c) w[tid * m + c] = in ? weight(lo + tid, c) : 0.0;
         }
         return;
     }
@@ -128,23 +103,36 @@ __global__ __launch_bounds__(LEAVES ? 64 : 256, LEAVES ? 1 : 4) void k_fmmv_sour
     }
     const double ihw = 1.0 / hw;
     v4d_f acc = v4d_f{0.0, 0.0, 0.0, 0.0};
-    // the points' weights, m per point: the leaf's poles in src, or the sources of the
-    // box's leaves
-    const double *wsrc = LEAVES ? src + (int64_t)lo * m
-                                : v.vw + (int64_t)(f.box_off[qf] + leaf0) * FMM_P * m;
+    // an upper box's points' weights, m per point: the sources of the box's leaves
+    const double *wsrc = v.vw + (int64_t)(f.box_off[qf] + leaf0) * FMM_P * m + g0;
     for (int k0 = pk0; k0 < pk1; k0 += FV_CHUNK) {
         // W (16 nodes x 16 columns) += L (16 x chunk) S (chunk x 16) on the FP64 MFMA: each
-        // wavefront takes 64 points of the chunk, 4 per step
-        // (A lane l = L[l % 16][k + l / 16], B lane l = S[k + l / 16][l % 16])
+        // wavefront takes 64 points of the chunk, 4 per step (A lane l = L[l % 16][point],
+        // B lane l = S[point][l % 16]): step st of lane l takes point 16 (l / 16) + st for a
+        // leaf, 4 st + l / 16 for an upper box
         double bs[16];
+        const int c = lane & 15;
+        if (LEAVES) {
+            const int p0 = k0 + 16 * (lane >> 4);
+            if (c < mx && p0 + 16 <= pk1) {
+                const double *xc = X + lo + p0 + (int64_t)c * v.ldx, *sp = sc + lo + p0;
 #pragma unroll
-        for (int st = 0; st < 16; ++st) {
-            const int pt = k0 + wv * 64 + 4 * st + (lane >> 4), c = lane & 15;
-            bs[st] = pt < pk1 && c < m ? wsrc[(int64_t)pt * m + c] : 0.0;
+                for (int st = 0; st < 16; ++st) bs[st] = sp[st] * xc[st];
+            } else {
+#pragma unroll
+                for (int st = 0; st < 16; ++st)
+                    bs[st] = p0 + st < pk1 ? weight(lo + p0 + st, c) : 0.0;
+            }
+        } else {
+#pragma unroll
+            for (int st = 0; st < 16; ++st) {
+                const int pt = k0 + wv * 64 + 4 * st + (lane >> 4);
+                bs[st] = pt < pk1 && c < mg ? wsrc[(int64_t)pt * m + c] : 0.0;
+            }
         }
         const int k = k0 + tid;
         if (k < pk1) {
-            const double x = LEAVES ? d(lo + k)
+            const double x = LEAVES ? d[lo + k]
                                     : v.vnode[(int64_t)(f.box_off[qf] + leaf0) * FMM_P + k];
             const double t = fmin(1.0, fmax(-1.0, (x - cc) * ihw));
             int hit = -1;
@@ -167,7 +155,7 @@ __global__ __launch_bounds__(LEAVES ? 64 : 256, LEAVES ? 1 : 4) void k_fmmv_sour
         __syncthreads();
 #pragma unroll
         for (int st = 0; st < 16; ++st) {
-            const int kk = wv * 64 + 4 * st + (lane >> 4);
+            const int kk = LEAVES ? 16 * (lane >> 4) + st : wv * 64 + 4 * st + (lane >> 4);
             acc = __builtin_amdgcn_mfma_f64_16x16x4f64(Lq[kk][lane & 15], bs[st], acc, 0, 0, 0);
         }
         __syncthreads();
@@ -188,16 +176,16 @@ __global__ __launch_bounds__(LEAVES ? 64 : 256, LEAVES ? 1 : 4) void k_fmmv_sour
             for (int u = 0; u < NW - 1; ++u) s2 += red[(u * 4 + r) * WAVE + lane];
             const int qn = 4 * r + (lane >> 4), cn = lane & 15;
             if (it.w >= 0)  // one part of several: its partial weights, summed afterwards
-                f.vpart[((int64_t)it.w * FMM_P + qn) * FMMV_MAX_M + cn] = s2;
-            else if (cn < m)
+                f.vpart[(((int64_t)it.w * gridDim.y + blockIdx.y) * FMM_P + qn) * FMMV_MAX_M + cn] = s2;
+            else if (cn < mg)
                 w[qn * m + cn] = s2;
         }
     }
-    if (it.y == 0 && tid < FMM_P) node[tid] = cc + hw * tq[tid];
+    if (it.y == 0 && blockIdx.y == 0 && tid < FMM_P) node[tid] = cc + hw * tq[tid];
 }
 
 // The weights of the upper boxes computed in several parts: the parts' partial weights
-// added in part order.  One workgroup per such box, thread (node q, column c).
+// added in part order.  One workgroup per such box and column group, thread (node q, column c).
 __global__ __launch_bounds__(FMM_P * FMMV_MAX_M) void k_fmmv_sources_sum(FmmArgs f, FmmVec v) {
     const int2 sb = f.split_box[blockIdx.x];
     const int g = sb.x;
@@ -216,10 +204,12 @@ __global__ __launch_bounds__(FMM_P * FMMV_MAX_M) void k_fmmv_sources_sum(FmmArgs
     const int nleaf = (hi - lo + f.leaf - 1) / f.leaf;
     const int parts = (nleaf * FMM_P + FMMV_PART_PTS - 1) / FMMV_PART_PTS;
     const int q = threadIdx.x / FMMV_MAX_M, c = threadIdx.x % FMMV_MAX_M;
-    if (c >= v.m) return;
+    const int gy = blockIdx.y, col = gy * FMMV_MAX_M + c;
+    if (col >= v.m) return;
     double s = 0.0;
-    for (int u = 0; u < parts; ++u) s += f.vpart[((int64_t)(sb.y + u) * FMM_P + q) * FMMV_MAX_M + c];
-    v.vw[((int64_t)g * FMM_P + q) * v.m + c] = s;
+    for (int u = 0; u < parts; ++u)
+        s += f.vpart[(((int64_t)(sb.y + u) * gridDim.y + gy) * FMM_P + q) * FMMV_MAX_M + c];
+    v.vw[((int64_t)g * FMM_P + q) * v.m + col] = s;
 }
 
 // Evaluation at the roots: work items are 64-root pieces of the target leaves; S
@@ -256,8 +246,8 @@ __device__ void fmmv_item(const SolveArgs &it, const FmmArgs &f, const FmmVec &v
     const int nl = wave_uniform(f.cnt[3 * (int64_t)L + 1]);
     const int nr = wave_uniform(f.cnt[3 * (int64_t)L + 2]);
     const const_double_ptr dd = as_const(v.d + base);
-    const const_double_ptr src = as_const(v.src + base * m);
-    const const_double_ptr zhv = as_const((KERN == 2 ? v.zh : v.d) + base);
+    const const_double_ptr sc = as_const(v.scale + base);  // zhat
+    const const_double_ptr X = as_const(KERN == 1 ? v.X + base : v.d + base);
     double acc[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) acc[c] = 0.0;
@@ -267,12 +257,12 @@ __device__ void fmmv_item(const SolveArgs &it, const FmmArgs &f, const FmmVec &v
         ent += hi > lo ? hi - lo : 0;
         for (int i = lo; i < hi; ++i) {
             const double r = rcp_nr((dd[i] - dK) - eta);
+            const double qv = r * sc[i];
             if (KERN == 1) {
 #pragma unroll
                 for (int c = 0; c < NC; ++c)
-                    if (c < m) acc[c] = __builtin_fma(r, src[(int64_t)i * m + c], acc[c]);
+                    if (c < m) acc[c] = __builtin_fma(qv, X[i + (int64_t)c * v.ldx], acc[c]);
             } else {  // (zhat / t)^2, squared after the division (r^2 zhat^2 can leave range)
-                const double qv = r * zhv[i];
                 acc[0] = __builtin_fma(qv, qv, acc[0]);
             }
         }
@@ -371,19 +361,20 @@ static_assert(FV_K * 16 == 4 * 256, "a chunk's 64 sources x 16 columns: four per
 struct FvStage {
     double2 sd;    // source position and, with fuse_b, zhat (near poles) or the weight of
                    // zhat^2 (far equivalent sources) (threads < 64)
-    double w[4];   // weights: element e = tid + 256 i -> source e / 16, column e % 16 (the
-                   // weights are stored source-major, so 16 threads read a source's row)
+    double w[4];   // weights: near poles, source tid % 64 in column tid / 64 + 4 i (a
+                   // wavefront reads 64 consecutive entries of a column of X); far sources,
+                   // source tid / 16 of box i in column tid % 16 (their weights are
+                   // source-major, so 16 threads read a source's row)
 };
 
 // TRANS 0 (sums over the roots): a near source is root j, staged as (d_{K_j}, eta_j) for
 // the shifted difference (d_i - d_{K_j}) - eta_j; a far one as (node, 0)
+// columns [g0, g0 + mg) of the pass, of which the first mx are X's
 template <int TRANS>
 __device__ __forceinline__ void fv_fetch(const FmmVec &v, int64_t base, int n, const int *fbox,
-                                         int4 ch, FvStage &st) {
+                                         int4 ch, int g0, int mg, int mx, FvStage &st) {
     const int tid = threadIdx.x;
     const int m = v.m;
-    // weight element i of this thread: source r16 + 16 i of the chunk, column c
-    const int c = tid & 15, r16 = tid >> 4;
     if (ch.x == 0) {
         if (tid < FV_K) {
             const int j = ch.y + tid;
@@ -393,10 +384,13 @@ __device__ __forceinline__ void fv_fetch(const FmmVec &v, int64_t base, int n, c
             else
                 st.sd = make_double2(v.d[base + j], v.fuse_b ? v.zh[base + j] : 0.0);
         }
-        const double *srow = v.src + (base + ch.y + r16) * m + c;
+        const int sl = tid & (FV_K - 1), c0 = tid / FV_K;
+        const bool in = sl < ch.z;
+        const double sv = in ? v.scale[base + ch.y + sl] : 0.0;
+        const double *xs = v.X + base + ch.y + sl + (int64_t)(g0 + c0) * v.ldx;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            st.w[i] = (r16 + 16 * i < ch.z && c < m) ? srow[(int64_t)16 * i * m] : 0.0;
+            st.w[i] = in && c0 + 4 * i < mx ? sv * xs[(int64_t)(4 * i) * v.ldx] : 0.0;
     } else {
         // far chunk: box i of the chunk holds its FMM_P = 16 sources r16
         if (tid < FV_K) {
@@ -405,10 +399,11 @@ __device__ __forceinline__ void fv_fetch(const FmmVec &v, int64_t base, int n, c
             st.sd = sq >= 0 ? make_double2(v.vnode[sq], v.fuse_b ? v.vw[sq * m + m - 1] : 0.0)
                             : make_double2(0.0, 0.0);
         }
+        const int c = tid & 15, r16 = tid >> 4;
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            st.w[i] = (i < ch.z && c < m)
-                          ? v.vw[((int64_t)fbox[ch.y + i] * FMM_P + r16) * m + c]
+            st.w[i] = (i < ch.z && c < mg)
+                          ? v.vw[((int64_t)fbox[ch.y + i] * FMM_P + r16) * m + g0 + c]
                           : 0.0;
     }
 }
@@ -421,21 +416,23 @@ struct FvShared {
     int nch;
 };
 
+// gi: the group of FMMV_MAX_M columns of the pass
 template <int TRANS>
 __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmVec &v, Tile t,
-                               FvShared &sh) {
+                               int gi, FvShared &sh) {
     const int p = t.prob;
     const int64_t base = it.off[p];
     const int n = (int)(it.off[p + 1] - base);
     const int lane = lane_id();
     const int wv = threadIdx.x / WAVE;
     const int o0 = t.row0;
-    const int m = v.m;
-    const int mo = m - v.fuse_b;  // output columns
+    const int g0 = gi * FMMV_MAX_M;
+    const int mg = min(FMMV_MAX_M, v.m - g0);  // columns of the group
+    const int mo = mg - v.fuse_b;              // output columns
     if (f.status[p] & ~SUPERDC_ST_NOCONV) {
         const double nan = __builtin_nan("");
         for (int e = threadIdx.x; e < FV_K * mo; e += blockDim.x) {
-            const int r = o0 + (e % FV_K), c = e / FV_K;
+            const int r = o0 + (e % FV_K), c = g0 + e / FV_K;
             if (r < n) v.Y[base + r + (int64_t)c * v.ldy] = nan;
         }
         if (v.fuse_b && threadIdx.x < FV_K && o0 + (int)threadIdx.x < n)
@@ -484,15 +481,19 @@ __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmV
     const bool fb = v.fuse_b != 0;
     FvStage st;
     int4 cur = chunk(0);
-    fv_fetch<TRANS>(v, base, n, sh.fbox, cur, st);
+    fv_fetch<TRANS>(v, base, n, sh.fbox, cur, g0, mg, mo, st);
     int64_t ent = 0;  // near poles and far sources summed per root (kernel timing)
     for (int ci = 0; ci < nch; ++ci) {
         __syncthreads();  // the previous chunk's reads of Xs/Sd are done
         if (threadIdx.x < FV_K) sh.Sd[threadIdx.x] = st.sd;
+        if (cur.x == 0) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int e = threadIdx.x + 256 * i;
-            sh.Xs[(e & 15) * FV_LD + (e >> 4)] = st.w[i];
+            for (int i = 0; i < 4; ++i)
+                sh.Xs[(threadIdx.x / FV_K + 4 * i) * FV_LD + (threadIdx.x & (FV_K - 1))] = st.w[i];
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                sh.Xs[(threadIdx.x & 15) * FV_LD + (threadIdx.x >> 4) + 16 * i] = st.w[i];
         }
         __syncthreads();
         const int nvalid = wave_uniform(cur.x == 0 ? cur.z : cur.z * FMM_P);
@@ -500,7 +501,8 @@ __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmV
         ent += nvalid;
         if (ci + 1 < nch) {
             cur = chunk(ci + 1);
-            fv_fetch<TRANS>(v, base, n, sh.fbox, cur, st);  // in flight during the multiply
+            // in flight during the multiply
+            fv_fetch<TRANS>(v, base, n, sh.fbox, cur, g0, mg, mo, st);
         }
         // one slice of 4 sources: the Cauchy entries of this lane's row (one reciprocal
         // with a Newton step each) into the MFMA; MASK: a partial chunk, whose padding
@@ -539,7 +541,7 @@ __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmV
     }
     if (v.work && threadIdx.x == 0) {  // kernel timing: the item's algorithmic flops
         const unsigned long long rows = (unsigned long long)min(FV_K, n - o0);
-        atomicAdd(v.work, rows * (unsigned long long)ent * (2 * (unsigned long long)m + 3) +
+        atomicAdd(v.work, rows * (unsigned long long)ent * (2 * (unsigned long long)mg + 3) +
                               2 * rows * (unsigned long long)mo);
     }
     mfma_drain();
@@ -555,7 +557,7 @@ __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmV
         } else {
             post = row < n ? v.post[base + row] : 0.0;
         }
-        if (row < n && col < mo) v.Y[base + row + (int64_t)col * v.ldy] = post * acc[r];
+        if (row < n && col < mo) v.Y[base + row + (int64_t)(g0 + col) * v.ldy] = post * acc[r];
     }
 }
 
@@ -564,8 +566,10 @@ __global__ __launch_bounds__(256) void k_fmmv_eval_mfma(SolveArgs it, FmmArgs f,
                                                         Queue *q) {
     __shared__ FvShared sh;
     __shared__ int slot;
-    for_each_item(q, it.ntiles, &slot, [&](int item) {
-        fmmv_item_mfma<TRANS>(it, f, v, it.tiles[item], sh);
+    // the column groups of a tile are neighbouring items: they read the same lists and poles
+    const int ng = (v.m + FMMV_MAX_M - 1) / FMMV_MAX_M;
+    for_each_item(q, it.ntiles * ng, &slot, [&](int item) {
+        fmmv_item_mfma<TRANS>(it, f, v, it.tiles[item / ng], item % ng, sh);
     });
 }
 
@@ -612,7 +616,6 @@ __global__ __launch_bounds__(LEAVES ? 64 : 256, LEAVES ? 1 : 4) void k_fmml_mome
             const double delta = (dK - dj) + ej;
             l.pd[base + j] = make_double2(dj, delta);
             if (l.ke) l.ke[base + j] = make_double2(dK, ej);
-            if (j == n - 1) l.tail[p] = delta;
         }
         __syncthreads();
     }
@@ -731,7 +734,6 @@ __global__ __launch_bounds__(64) void k_fmml_pack(FmmvPackArgs a) {
     const double delta = (dK - dj) + ej;
     a.pairs[base + j] = make_double2(dj, delta);
     if (a.ke) a.ke[base + j] = make_double2(dK, ej);
-    if (j == n - 1) a.tail[t.prob] = delta;
 }
 
 hipError_t launch_fmml_pack(const FmmvPackArgs &a, hipStream_t s) {
@@ -740,24 +742,22 @@ hipError_t launch_fmml_pack(const FmmvPackArgs &a, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_fmmv_pack(const FmmvPackArgs &a, const FmmVec &v, hipStream_t s) {
+hipError_t launch_fmmv_pos(const FmmvPackArgs &a, hipStream_t s) {
     if (a.ntiles <= 0) return hipSuccess;
-    SDC_LAUNCH(KID_FMMV_PACK, k_fmmv_pack, dim3(a.ntiles), dim3(64), 0, s, a, v);
+    SDC_LAUNCH(KID_FMMV_PACK, k_fmmv_pos, dim3(a.ntiles), dim3(64), 0, s, a);
     return hipGetLastError();
 }
 
-hipError_t launch_fmmv_sources(const FmmArgs &f, const FmmVec &v, const FmmvPackArgs *pk,
-                               hipStream_t s) {
+hipError_t launch_fmmv_sources(const FmmArgs &f, const FmmVec &v, hipStream_t s) {
     if (f.nboxes <= 0) return hipSuccess;
-    FmmvPackArgs none{};
-    SDC_LAUNCH(KID_FMMV_SOURCES, k_fmmv_sources<true>, dim3(f.nleaves), dim3(64), 0, s, f, v,
-               pk ? *pk : none);
+    const int ng = (v.m + FMMV_MAX_M - 1) / FMMV_MAX_M;
+    SDC_LAUNCH(KID_FMMV_SOURCES, k_fmmv_sources<true>, dim3(f.nleaves, ng), dim3(64), 0, s, f, v);
     if (f.nupper_item > 0)
-        SDC_LAUNCH(KID_FMMV_SOURCES, k_fmmv_sources<false>, dim3(f.nupper_item), dim3(256), 0, s,
-                   f, v, none);
+        SDC_LAUNCH(KID_FMMV_SOURCES, k_fmmv_sources<false>, dim3(f.nupper_item, ng), dim3(256), 0,
+                   s, f, v);
     if (f.nsplit > 0)
-        SDC_LAUNCH(KID_FMMV_SOURCES, k_fmmv_sources_sum, dim3(f.nsplit), dim3(FMM_P * FMMV_MAX_M),
-                   0, s, f, v);
+        SDC_LAUNCH(KID_FMMV_SOURCES, k_fmmv_sources_sum, dim3(f.nsplit, ng),
+                   dim3(FMM_P * FMMV_MAX_M), 0, s, f, v);
     return hipGetLastError();
 }
 
@@ -769,21 +769,22 @@ hipError_t launch_fmmv_eval(const SolveArgs &it, const FmmArgs &f, const FmmVec 
     const bool mfma = v.kern == 1 && (v.m >= 4 || v.fuse_b || v.trans == 0);
     v.work = trace_work(mfma ? KID_FMMV_EVAL_MFMA : KID_FMMV_EVAL);
     if (mfma) {
-        const dim3 g(q ? min(it.ntiles, num_cu * 4) : it.ntiles);
+        const int items = it.ntiles * ((v.m + FMMV_MAX_M - 1) / FMMV_MAX_M);
+        const dim3 g(q ? min(items, num_cu * 4) : items);
         if (v.trans == 0)
             SDC_LAUNCH(KID_FMMV_EVAL_MFMA, k_fmmv_eval_mfma<0>, g, dim3(256), 0, s, it, f, v, q);
         else
             SDC_LAUNCH(KID_FMMV_EVAL_MFMA, k_fmmv_eval_mfma<1>, g, dim3(256), 0, s, it, f, v, q);
         return hipGetLastError();
     }
-    if (v.trans == 0) return hipErrorInvalidValue;
+    if (v.trans == 0 || v.m >= 4) return hipErrorInvalidValue;
     const dim3 g(q ? min(it.ntiles, num_cu * max(1, 32 / split)) : it.ntiles), blk(WAVE * split);
     if (v.kern == 2) {
         const size_t lds = sizeof(double) * WAVE * (split - 1) * 1;
         SDC_LAUNCH(KID_FMMV_EVAL, (k_fmmv_eval<2, 1>), g, blk, lds, s, it, f, v, q);
     } else {
-        const size_t lds = sizeof(double) * WAVE * (split - 1) * 8;
-        SDC_LAUNCH(KID_FMMV_EVAL, (k_fmmv_eval<1, 8>), g, blk, lds, s, it, f, v, q);
+        const size_t lds = sizeof(double) * WAVE * (split - 1) * 3;
+        SDC_LAUNCH(KID_FMMV_EVAL, (k_fmmv_eval<1, 3>), g, blk, lds, s, it, f, v, q);
     }
     return hipGetLastError();
 }
