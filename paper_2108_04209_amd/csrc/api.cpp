@@ -439,8 +439,8 @@ FmmPlan *fmm_for(superdc_ctx *ctx, superdc_batch *b, const superdc_opts &o, int 
 
 // Columns per set of launches for m columns: in small batches up to FMMV_MAX_PASS at once, so
 // that the 16-column groups fill the chip together (one 8192-root problem has 128 items for
-// 256 CUs: 64 columns in four sets of launches took 264 us, in one 88 us; of one 65536-root
-// problem, 560 and 354 us);
+// 256 CUs: 64 columns in four sets of launches took 264 us, in one 73 us; of one 65536-root
+// problem, 560 and 317 us);
 // 16 where the wider pass's equivalent weights (2 KiB a box and group) would exceed 64 MiB --
 // such a batch has items enough for every CU.
 int fmmv_pass(const FmmPlan *fp, int m) {
@@ -710,7 +710,8 @@ int apply_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const d
     FmmArgs f{};
     if (trans == 0) {
         double *pos = (double *)ws_get(ctx, WS_VPAIR, sizeof(double) * b->total);
-        if (!pos) return SUPERDC_ENOMEM;
+        double2 *ke = (double2 *)ws_get(ctx, WS_KE, sizeof(double2) * b->total);
+        if (!pos || !ke) return SUPERDC_ENOMEM;
         FmmvPackArgs pk{};
         pk.off = b->off_d;
         pk.tiles = fp->leaf_nat;
@@ -719,6 +720,8 @@ int apply_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const d
         pk.eta = eta;
         pk.origin = origin;
         pk.pos = pos;
+        pk.ke = ke;
+        v.ke = ke;
         SDC_HIP(launch_fmmv_pos(pk, s));
         f = fmm_roots_args(fp, b, pos, status, d);
         f.gen = ++fp->t_gen;  // built with the first columns below

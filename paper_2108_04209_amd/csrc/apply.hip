@@ -20,8 +20,7 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 
 constexpr int AP_ROWS = 64;   // output rows per workgroup
 constexpr int AP_K = 64;      // reduction chunk
-constexpr int AP_C = 64;      // right-hand sides per pass
-constexpr int AP_LD = AP_K + 1;
+constexpr int AP_LD = AP_K + 4;  // the 16 columns x 4 rows of an MFMA step on different banks
 
 // per-entry data of the reduction index s
 template <int TRANS>
@@ -42,9 +41,12 @@ __device__ __forceinline__ void stage_entry(const ApplyArgs &a, int64_t base, in
 }
 
 // raw data of one reduction chunk, held in registers while the previous chunk is
-// multiplied: threads < 64 hold entry s0 + tid's pole data and scale; every thread holds
-// NCT * 4 right-hand-side values, element e = tid + 256 i (row e % 64 of the chunk,
-// column e / 64 of the pass)
+// multiplied: the first wavefront's threads hold the pole data of entry s0 + tid; every
+// thread holds NCT * 4 right-hand-side values, element e = tid + 256 i (row e % 64 of the
+// chunk, column e / 64 of the pass), and the scale of their row.  Every lane loads (rows and
+// columns clamped into the problem and the pass), so that a chunk's loads are one run without
+// branches, and nothing uses them before the chunk is stored: padding is set to zero and the
+// scale multiplied in there.
 template <int NCT>
 struct ApplyStage {
     double2 sd;
@@ -56,35 +58,38 @@ template <int TRANS, int NCT>
 __device__ __forceinline__ void apply_fetch(const ApplyArgs &a, int64_t base, int n, int s0,
                                             int c0, int ncols, ApplyStage<NCT> &st) {
     const int tid = threadIdx.x;
-    if (tid < AP_K) stage_entry<TRANS>(a, base, n, s0 + tid, st.sd, st.sc);
+    const int64_t s = base + min(s0 + tid % AP_K, n - 1);
+    const double *x = a.X + s + (int64_t)c0 * a.ldx;
+    st.sc = (TRANS == 0 ? a.bnorm : a.zhat)[s];
 #pragma unroll
-    for (int i = 0; i < NCT * 4; ++i) {
-        const int e = tid + 256 * i;
-        const int sl = e % AP_K, c = e / AP_K;
-        const int s = s0 + sl;
-        double v = 0.0;
-        if (s < n && c < ncols) {
-            const double sc = TRANS == 0 ? a.bnorm[base + s] : a.zhat[base + s];
-            v = sc * a.X[base + s + (int64_t)(c0 + c) * a.ldx];
-        }
-        st.x[i] = v;
+    for (int i = 0; i < NCT * 4; ++i)
+        st.x[i] = x[(int64_t)min(tid / AP_K + 4 * i, ncols - 1) * a.ldx];
+    if (wave_uniform(tid / WAVE) == 0) {
+        if (TRANS == 0)  // s runs over roots: (d_{K_s}, eta_s)
+            st.sd = make_double2(a.d[base + clamp_idx(a.origin[s], n)], a.eta[s]);
+        else             // s runs over poles: (d_s, zhat_s)
+            st.sd = make_double2(a.d[s], st.sc);
     }
 }
 
-template <int NCT>
-__device__ __forceinline__ void apply_store(const ApplyStage<NCT> &st, double *Xs, double2 *Sd) {
+template <int TRANS, int NCT>
+__device__ __forceinline__ void apply_store(int n, int s0, int ncols, const ApplyStage<NCT> &st,
+                                            double *Xs, double2 *Sd) {
     const int tid = threadIdx.x;
-    if (tid < AP_K) Sd[tid] = st.sd;
+    const bool in = s0 + tid % AP_K < n;
+    if (wave_uniform(tid / WAVE) == 0)
+        Sd[tid] = make_double2(st.sd.x, TRANS && !in ? 0.0 : st.sd.y);
 #pragma unroll
     for (int i = 0; i < NCT * 4; ++i) {
         const int e = tid + 256 * i;
-        Xs[(e / AP_K) * AP_LD + e % AP_K] = st.x[i];
+        Xs[(e / AP_K) * AP_LD + e % AP_K] =
+            in && tid / AP_K + 4 * i < ncols ? st.sc * st.x[i] : 0.0;
     }
 }
 
 // NCT: 16-column blocks per pass (the pass width is 16 NCT columns); this item's pass starts
-// at column c0
-template <int TRANS, int NCT>
+// at column c0.  FB: form b beside the columns
+template <int TRANS, int NCT, bool FB>
 __device__ void apply_tile_mfma(const ApplyArgs &a, Tile t, int c0, double *Xs, double2 *Sd) {
     const int p = t.prob;
     const int64_t base = a.off[p];
@@ -99,72 +104,63 @@ __device__ void apply_tile_mfma(const ApplyArgs &a, Tile t, int c0, double *Xs, 
             const int r = o0 + (e % AP_ROWS), c = c0 + e / AP_ROWS;
             if (r < n) a.Y[base + r + (int64_t)c * a.ldy] = nan;
         }
-        if (TRANS == 1 && a.fuse_b && threadIdx.x < AP_ROWS && o0 + (int)threadIdx.x < n)
+        if (FB && threadIdx.x < AP_ROWS && o0 + (int)threadIdx.x < n)
             a.bout[base + o0 + threadIdx.x] = nan;
         return;
     }
-    // row data for the entries of C this lane generates: row o = o0 + 16 wv + lane%16
-    const int orow = o0 + wv * 16 + (lane & 15);
-    const bool ovalid = orow < n;
-    const int oc = ovalid ? orow : n - 1;
-    double ra, rb = 0.0;
-    if (TRANS == 0) {
-        ra = a.d[base + oc];
-    } else {
-        ra = a.d[base + clamp_idx(a.origin[base + oc], n)];
-        rb = a.eta[base + oc];
-    }
-    const int nct = (ncols + 15) / 16;
+    // row data for the entries of C this lane generates: row o = o0 + 16 wv + lane%16 (a row
+    // past the end only feeds its own output row, never written)
+    const int oc = min(o0 + wv * 16 + (lane & 15), n - 1);
+    double ra = TRANS ? a.d[base + clamp_idx(a.origin[base + oc], n)] : a.d[base + oc];
+    double rb = TRANS ? a.eta[base + oc] : 0.0;
     v4d acc[NCT];
 #pragma unroll
     for (int ct = 0; ct < NCT; ++ct) acc[ct] = v4d{0.0, 0.0, 0.0, 0.0};
-    // fuse_b (one pass of at most 15 columns): b = sum (zhat_s / t)^2, each term squared
+    // FB (one pass of at most 15 columns): b = sum (zhat_s / t)^2, each term squared
     // after the division as the b kernel does (zhat^2 and 1/t^2 apart can leave the
     // exponent range); each lane sums the terms of the entries it generates, on the
     // VALU beside the multiply (one column does not need the MFMA)
-    const bool fb = TRANS == 1 && NCT == 1 && a.fuse_b;
     double bsum = 0.0;
     ApplyStage<NCT> st;
+    __syncthreads();  // the previous item's reads of the buffers are done
     apply_fetch<TRANS, NCT>(a, base, n, 0, c0, ncols, st);
-    for (int s0 = 0; s0 < n; s0 += AP_K) {
-        __syncthreads();  // the previous chunk's reads of Xs/Sd are done
-        apply_store<NCT>(st, Xs, Sd);
+    asm volatile("" : "+v"(ra), "+v"(rb));  // loaded here, not inside the loop
+    // one barrier per chunk: a buffer is stored again two chunks later, behind the barrier
+    // that every wavefront reaches after its last read of it
+    for (int s0 = 0, buf = 0; s0 < n; s0 += AP_K, buf ^= 1) {
+        double *Xb = Xs + buf * (16 * NCT * AP_LD);
+        double2 *Sb = Sd + buf * AP_K;
+        apply_store<TRANS, NCT>(n, s0, ncols, st, Xb, Sb);
         __syncthreads();
         // the next chunk's loads are in flight while this one is multiplied
         if (s0 + AP_K < n) apply_fetch<TRANS, NCT>(a, base, n, s0 + AP_K, c0, ncols, st);
-        // one slice of 4 sources: this lane's Cauchy entry (one reciprocal with a Newton
-        // step) into the MFMA of every column tile; MASK: padding entries past the
-        // problem's end are zeroed.  A row past the end (ovalid false) only feeds its own
-        // output row, never written.
-#define SDC_AP_SLICE(MASK)                                                                 \
-{                                                                                      \
-    const int sl = kk + (lane >> 4);                                                   \
-    const double2 sd = Sd[sl];                                                         \
-    const double tt = TRANS ? (sd.x - ra) - rb : (ra - sd.x) - sd.y;                   \
-    const double av = (!(MASK) || s0 + sl < n) ? rcp_nr1(tt) : 0.0;                   \
-    _Pragma("unroll") for (int ct = 0; ct < NCT; ++ct) {                               \
-        if (ct < nct) {                                                                \
-            const double bv = Xs[(ct * 16 + (lane & 15)) * AP_LD + sl];                \
-            acc[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc[ct], 0, 0, 0);  \
-            if (fb) {                                                                  \
-                const double qv = av * sd.y;                                           \
-                bsum = fma(qv, qv, bsum);                                              \
-            }                                                                          \
-        }                                                                              \
-    }                                                                                  \
-}
+        // one step of 4 sources: this lane's Cauchy entry (one reciprocal with a Newton
+        // step) into the MFMA of every column tile; padding entries have weight zero at the
+        // position of the problem's last source
 #pragma unroll 4
-        for (int kk = 0; kk < AP_K; kk += 4) SDC_AP_SLICE(true)
-#undef SDC_AP_SLICE
+        for (int kk = 0; kk < AP_K; kk += 4) {
+            const int sl = kk + (lane >> 4);
+            const double2 sd = Sb[sl];
+            const double av = rcp_nr1(TRANS ? (sd.x - ra) - rb : (ra - sd.x) - sd.y);
+#pragma unroll
+            for (int ct = 0; ct < NCT; ++ct) {
+                const double bv = Xb[(ct * 16 + (lane & 15)) * AP_LD + sl];
+                acc[ct] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc[ct], 0, 0, 0);
+            }
+            if (FB) {
+                const double qv = av * sd.y;
+                bsum = fma(qv, qv, bsum);
+            }
+        }
         mfma_drain();  // before any copy of the accumulators between chunks
     }
-    if (fb) {  // the four lanes of a Cauchy row (lane % 16) hold its partial sums
+    if (FB) {  // the four lanes of a Cauchy row (lane % 16) hold its partial sums
         bsum += __shfl_xor(bsum, 16);
         bsum += __shfl_xor(bsum, 32);
     }
     if (a.work && threadIdx.x == 0) {  // kernel timing: this pass's algorithmic flops
         const unsigned long long rows = (unsigned long long)min(AP_ROWS, n - o0);
-        const unsigned long long me = (unsigned long long)(ncols + (fb ? 1 : 0));
+        const unsigned long long me = (unsigned long long)(ncols + (FB ? 1 : 0));
         atomicAdd(a.work, rows * (unsigned long long)n * (2 * me + 3) + 2 * rows * me);
     }
     mfma_drain();
@@ -173,30 +169,30 @@ __device__ void apply_tile_mfma(const ApplyArgs &a, Tile t, int c0, double *Xs, 
     for (int v = 0; v < 4; ++v) {
         const int row = o0 + wv * 16 + 4 * v + (lane >> 4);
         double postb = 0.0;
-        if (fb) {  // b's sum of this row is held by the lanes that generated its entries
+        if (FB) {  // b's sum of this row is held by the lanes that generated its entries
             postb = 1.0 / sqrt(__shfl(bsum, 4 * v + (lane >> 4)));
             if (row < n && (lane & 15) == 0) a.bout[base + row] = postb;
         }
         if (row < n) {
-            const double post = fb ? postb : (TRANS ? a.bnorm[base + row] : a.zhat[base + row]);
+            const double post = FB ? postb : (TRANS ? a.bnorm[base + row] : a.zhat[base + row]);
 #pragma unroll
             for (int ct = 0; ct < NCT; ++ct) {
                 const int col = ct * 16 + (lane & 15);
-                if (ct < nct && col < ncols)
+                if (col < ncols)
                     a.Y[base + row + (int64_t)(c0 + col) * a.ldy] = post * acc[ct][v];
             }
         }
     }
 }
 
-template <int TRANS, int NCT>
+template <int TRANS, int NCT, bool FB>
 __global__ __launch_bounds__(256) void k_apply_mfma(ApplyArgs a, Queue *q) {
-    __shared__ double Xs[16 * NCT * AP_LD];
-    __shared__ double2 Sd[AP_K];
+    __shared__ double Xs[2 * 16 * NCT * AP_LD];
+    __shared__ double2 Sd[2 * AP_K];
     __shared__ int slot;
     const int np = (a.m + 16 * NCT - 1) / (16 * NCT);  // passes of a tile: neighbouring items
     for_each_item(q, a.ntiles * np, &slot, [&](int item) {
-        apply_tile_mfma<TRANS, NCT>(a, a.tiles[item / np], item % np * (16 * NCT), Xs, Sd);
+        apply_tile_mfma<TRANS, NCT, FB>(a, a.tiles[item / np], item % np * (16 * NCT), Xs, Sd);
     });
 }
 
@@ -313,16 +309,17 @@ hipError_t launch_apply(const ApplyArgs &a0, int use_mfma, Queue *q, int num_cu,
         auto items = [&] { return a.ntiles * ((a.m + 16 * nct - 1) / (16 * nct)); };
         while (nct > 1 && items() < 2 * num_cu) nct /= 2;
         const dim3 g(q ? min(items(), num_cu * 4) : items());
-#define SDC_APPLY_MFMA(T, C) \
-    SDC_LAUNCH(KID_APPLY_MFMA, (k_apply_mfma<T, C>), g, dim3(256), 0, s, a, q)
+#define SDC_APPLY_MFMA(T, C, FB) \
+    SDC_LAUNCH(KID_APPLY_MFMA, (k_apply_mfma<T, C, FB>), g, dim3(256), 0, s, a, q)
         if (a.trans) {
-            if (nct == 1) SDC_APPLY_MFMA(1, 1);
-            else if (nct == 2) SDC_APPLY_MFMA(1, 2);
-            else SDC_APPLY_MFMA(1, 4);
+            if (a.fuse_b) SDC_APPLY_MFMA(1, 1, true);
+            else if (nct == 1) SDC_APPLY_MFMA(1, 1, false);
+            else if (nct == 2) SDC_APPLY_MFMA(1, 2, false);
+            else SDC_APPLY_MFMA(1, 4, false);
         } else {
-            if (nct == 1) SDC_APPLY_MFMA(0, 1);
-            else if (nct == 2) SDC_APPLY_MFMA(0, 2);
-            else SDC_APPLY_MFMA(0, 4);
+            if (nct == 1) SDC_APPLY_MFMA(0, 1, false);
+            else if (nct == 2) SDC_APPLY_MFMA(0, 2, false);
+            else SDC_APPLY_MFMA(0, 4, false);
         }
 #undef SDC_APPLY_MFMA
     } else {

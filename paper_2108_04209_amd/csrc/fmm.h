@@ -156,6 +156,7 @@ struct FmmVec {
     const double *d;          // poles
     const int32_t *origin;    // roots' origins (local indices)
     const double *eta;        // roots' offsets
+    const double2 *ke;        // trans 0: (d_{K_j}, eta_j) per root (launch_fmmv_pos)
     const double *post;       // kern 1: per-root scale (b); unused for kern 2
     double *Y;                // kern 1: output columns, ld ldy
     int64_t ldy;
@@ -197,7 +198,7 @@ struct FmmlArgs {
 hipError_t launch_fmml_moments(const FmmArgs &f, const FmmlArgs &l, hipStream_t s);
 
 // per-entry packing for the FMM problems: launch_fmml_pack the (d_j, delta_j) pairs of the
-// Loewner far field, launch_fmmv_pos the roots' positions
+// Loewner far field, launch_fmmv_pos the roots' positions and (d_K, eta)
 struct FmmvPackArgs {
     const int64_t *off;
     const Tile *tiles;   // 64-entry tiles of the FMM problems
@@ -206,8 +207,8 @@ struct FmmvPackArgs {
     const int32_t *origin;
     double2 *pairs;
     double *pos;         // launch_fmmv_pos: lambda_j = d_{K_j} + eta_j
-    double2 *ke;         // Loewner packing, when every problem of the batch uses the FMM:
-                         // also (d_{K_j}, eta_j) for every root (else nullptr)
+    double2 *ke;         // (d_{K_j}, eta_j) per root; Loewner packing: when every problem of
+                         // the batch uses the FMM (else nullptr)
 };
 hipError_t launch_fmmv_pos(const FmmvPackArgs &a, hipStream_t s);
 // Loewner far field: (d_j, delta_j) pairs and the last roots' offsets, then the products

@@ -17,14 +17,22 @@ namespace sdc {
 
 typedef double v4d_f __attribute__((ext_vector_type(4)));
 
+// compile-time flags for generic lambdas
+struct fv_true { static constexpr bool value = true; };
+struct fv_false { static constexpr bool value = false; };
 
-// lambda_j = d_{K_j} + eta_j, the positions of the sums over the roots; one lane per root
+
+// lambda_j = d_{K_j} + eta_j, the positions of the sums over the roots, and (d_{K_j}, eta_j)
+// for their near sources; one lane per root
 __global__ __launch_bounds__(64) void k_fmmv_pos(FmmvPackArgs a) {
     const Tile t = a.tiles[blockIdx.x];
     const int64_t base = a.off[t.prob];
     const int n = (int)(a.off[t.prob + 1] - base);
     const int j = t.row0 + lane_id();
-    if (j < n) a.pos[base + j] = a.d[base + clamp_idx(a.origin[base + j], n)] + a.eta[base + j];
+    if (j >= n) return;
+    const double dK = a.d[base + clamp_idx(a.origin[base + j], n)], e = a.eta[base + j];
+    a.pos[base + j] = dK + e;
+    a.ke[base + j] = make_double2(dK, e);
 }
 
 // Equivalent sources, one workgroup (256 threads) per box, in two launches: LEAVES = true
@@ -336,128 +344,176 @@ __global__ __launch_bounds__(512) void k_fmmv_eval(SolveArgs it, FmmArgs f, FmmV
 }
 
 // ---------------------------------------------------------------------------------------
-// Y = Qhat^T X through the FMM on MFMA: for a 64-root work item the near poles and the far
-// boxes' equivalent sources form one gathered reduction dimension, and the product
+// Y = Qhat^T X (or Qhat X, sums over the roots) through the FMM on MFMA: for a 64-row work
+// item the near sources and the far boxes' equivalent sources form one gathered reduction
+// dimension, and the product
 //     Y_j,c = b_j sum_k 1/((s_k - d_{K_j}) - eta_j) W_k,c
-// (s_k a pole or a Chebyshev node, W_k,c its weight) is the dense contraction of the
-// direct apply: 64-source chunks are staged through LDS (the next chunk's data in
-// registers while the current one is multiplied), each wavefront generates its 16 x 4
-// slices of the Cauchy block and feeds v_mfma_f64_16x16x4f64.  Every source uses the
-// shifted difference, never less accurate than the lambda-form.
+// (s_k a pole or a Chebyshev node, W_k,c its weight) is the dense contraction of the direct
+// apply: each wavefront generates its 16 x 4 slices of the Cauchy block and feeds
+// v_mfma_f64_16x16x4f64.  Every source uses the shifted difference, never less accurate than
+// the lambda-form.
+//
+// The bound is the FP64 pipe: on gfx950 the FP64 MFMA (72 cycles each, measured) and FP64 VALU
+// instructions share it and do not overlap (two wavefronts of each on one SIMD took the sum of
+// their times), so a step of 4 sources x 16 rows x 16 columns costs 72 cycles and about 36 for
+// its Cauchy entries, and a 65536-root launch (1024 items, about 20 chunks each) 62 us.  What
+// kept the kernel from it (it took 95 us) was waiting, so a chunk goes through two LDS buffers with one
+// barrier, its loads issued before the previous chunk is multiplied and used only when it is
+// stored; every lane loads (indices clamped to the chunk's own sources, padding set to zero
+// at the store), so that the loads of a chunk are one run without branches; and the values
+// loaded once per item are taken before the loop, since a first use inside it made the
+// compiler wait there for the next chunk's loads as well.  Now 80 us; in a level of 4096 problems
+// (16 columns) 4.08 -> 3.25 ms.  A launch with too few items to give every CU two workgroups
+// gives each item TEAMS teams of four wavefronts, which take the chunks in turn and add their
+// sums in team order (n = 1024, 16 items: 23 -> 12 us).
 // ---------------------------------------------------------------------------------------
 constexpr int FV_K = 64;            // sources per chunk
-constexpr int FV_LD = FV_K + 1;
+constexpr int FV_LD = FV_K + 4;     // LDS row: the 16 columns x 4 sources of a step fall on
+                                    // different banks
 
-// The chunks of an item (built once per item in LDS): near ranges in 64-pole chunks, then
-// the far boxes 4 at a time (64 equivalent sources).  kind 0: poles [a, a + cnt); kind 1:
-// far boxes fbox[a .. a + cnt).
+// The chunks of an item (built once per item in LDS): near ranges in 64-source chunks, then
+// the far boxes 4 at a time (64 equivalent sources).  x = 0: sources [y, y + z); x = 1: far
+// boxes fbox[y .. y + z).
 // (at most FMM_NEAR_MAX near leaves of at most 1024 poles, the largest leaf the options
 // allow; a run of adjacent leaves has no more chunks than its leaves, since every leaf but
 // a problem's last holds a multiple of 64 poles)
 constexpr int FV_MAXCH = FMM_NEAR_MAX * (1024 / FV_K) + (2 * FMM_FAR_MAX + 3) / 4;
 
 static_assert(FV_K * 16 == 4 * 256, "a chunk's 64 sources x 16 columns: four per thread");
+static_assert(FMM_NEAR_MAX <= WAVE, "a lane per near range");
 
+// A chunk's data on its way from memory to LDS, raw: masks and scales are applied at the
+// store.  Near sources: thread t holds source t % 64 in columns t / 64 + 4 i (a wavefront
+// reads 64 consecutive entries of a column of X) and its scale; far sources: source t / 16 of
+// box i in column t % 16 (their weights are source-major: 16 threads read a source's row).
 struct FvStage {
-    double2 sd;    // source position and, with fuse_b, zhat (near poles) or the weight of
-                   // zhat^2 (far equivalent sources) (threads < 64)
-    double w[4];   // weights: near poles, source tid % 64 in column tid / 64 + 4 i (a
-                   // wavefront reads 64 consecutive entries of a column of X); far sources,
-                   // source tid / 16 of box i in column tid % 16 (their weights are
-                   // source-major, so 16 threads read a source's row)
+    double2 sd;    // (first wavefront) source position and, with b formed beside the columns,
+                   // zhat (near) or the weight of zhat^2 (far); TRANS 0: (d_K, eta) (near) or
+                   // (node, 0) (far)
+    double w[4];
+    double sc;
 };
 
-// TRANS 0 (sums over the roots): a near source is root j, staged as (d_{K_j}, eta_j) for
-// the shifted difference (d_i - d_{K_j}) - eta_j; a far one as (node, 0)
-// columns [g0, g0 + mg) of the pass, of which the first mx are X's
-template <int TRANS>
-__device__ __forceinline__ void fv_fetch(const FmmVec &v, int64_t base, int n, const int *fbox,
-                                         int4 ch, int g0, int mg, int mx, FvStage &st) {
-    const int tid = threadIdx.x;
+template <int TRANS, bool FB>
+__device__ __forceinline__ void fv_fetch(const FmmVec &v, int64_t base, const int *fbox,
+                                         int4 ch, int tid, int g0, int mg, int mx, FvStage &st) {
     const int m = v.m;
+    const bool first = wave_uniform(tid / WAVE) == 0;
     if (ch.x == 0) {
-        if (tid < FV_K) {
-            const int j = ch.y + tid;
-            if (tid >= ch.z) st.sd = make_double2(0.0, 0.0);
-            else if (TRANS == 0)
-                st.sd = make_double2(v.d[base + clamp_idx(v.origin[base + j], n)], v.eta[base + j]);
-            else
-                st.sd = make_double2(v.d[base + j], v.fuse_b ? v.zh[base + j] : 0.0);
-        }
-        const int sl = tid & (FV_K - 1), c0 = tid / FV_K;
-        const bool in = sl < ch.z;
-        const double sv = in ? v.scale[base + ch.y + sl] : 0.0;
-        const double *xs = v.X + base + ch.y + sl + (int64_t)(g0 + c0) * v.ldx;
+        const int64_t j = base + ch.y + min(tid & (FV_K - 1), ch.z - 1);
+        const double *xs = v.X + j + (int64_t)g0 * v.ldx;
+        st.sc = v.scale[j];
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            st.w[i] = in && c0 + 4 * i < mx ? sv * xs[(int64_t)(4 * i) * v.ldx] : 0.0;
+            st.w[i] = xs[(int64_t)min(tid / FV_K + 4 * i, mx - 1) * v.ldx];
+        if (first) {
+            if (TRANS == 0) st.sd = v.ke[j];
+            else st.sd = make_double2(v.d[j], FB ? v.zh[j] : 0.0);
+        }
     } else {
         // far chunk: box i of the chunk holds its FMM_P = 16 sources r16
-        if (tid < FV_K) {
-            const int bx = tid / FMM_P, qn = tid % FMM_P;
-            const int64_t sq = bx < ch.z ? (int64_t)fbox[ch.y + bx] * FMM_P + qn : -1;
-            st.sd = sq >= 0 ? make_double2(v.vnode[sq], v.fuse_b ? v.vw[sq * m + m - 1] : 0.0)
-                            : make_double2(0.0, 0.0);
-        }
-        const int c = tid & 15, r16 = tid >> 4;
+        const int c = min(tid & 15, mg - 1), r16 = tid >> 4;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            st.w[i] = (i < ch.z && c < mg)
-                          ? v.vw[((int64_t)fbox[ch.y + i] * FMM_P + r16) * m + g0 + c]
-                          : 0.0;
+        for (int i = 0; i < 4; ++i) {
+            const int64_t sq = (int64_t)fbox[ch.y + min(i, ch.z - 1)] * FMM_P + r16;
+            st.w[i] = v.vw[sq * m + g0 + c];
+        }
+        if (first) {
+            const int64_t sq = (int64_t)fbox[ch.y + min(tid / FMM_P, ch.z - 1)] * FMM_P + tid % FMM_P;
+            st.sd = make_double2(v.vnode[sq], FB ? v.vw[sq * m + m - 1] : 0.0);
+        }
     }
 }
 
+// Padding (past a partial chunk's sources or the group's columns) is stored as weight zero at
+// the position of one of the chunk's own sources.
+template <bool FB>
+__device__ __forceinline__ void fv_store(int4 ch, int tid, int mg, int mx, const FvStage &st,
+                                         double *Xs, double2 *Sd) {
+    const int cnt = ch.x == 0 ? ch.z : ch.z * FMM_P;
+    if (ch.x == 0) {
+        const int sl = tid & (FV_K - 1), c0 = tid / FV_K;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            Xs[(c0 + 4 * i) * FV_LD + sl] =
+                sl < ch.z && c0 + 4 * i < mx ? st.sc * st.w[i] : 0.0;
+    } else {
+        const int c = tid & 15, r16 = tid >> 4;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            Xs[c * FV_LD + r16 + 16 * i] = i < ch.z && c < mg ? st.w[i] : 0.0;
+    }
+    if (wave_uniform(tid / WAVE) == 0)
+        Sd[tid] = make_double2(st.sd.x, FB && tid >= cnt ? 0.0 : st.sd.y);
+}
+
+struct FvTeam {
+    double Xs[2][16 * FV_LD];
+    double2 Sd[2][FV_K];
+};
+
+template <int TEAMS>
 struct FvShared {
-    double Xs[16 * FV_LD];
-    double2 Sd[FV_K];
+    FvTeam team[TEAMS];
     int4 ctab[FV_MAXCH];
     int fbox[2 * FMM_FAR_MAX];
     int nch;
 };
 
 // gi: the group of FMMV_MAX_M columns of the pass
-template <int TRANS>
+template <int TRANS, bool FB, int TEAMS>
 __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmVec &v, Tile t,
-                               int gi, FvShared &sh) {
+                               int gi, FvShared<TEAMS> &sh) {
     const int p = t.prob;
     const int64_t base = it.off[p];
     const int n = (int)(it.off[p + 1] - base);
     const int lane = lane_id();
-    const int wv = threadIdx.x / WAVE;
+    const int wave = wave_uniform((int)(threadIdx.x / WAVE));
+    const int tm = wave >> 2, wv = wave & 3;      // team, wavefront of the team
+    const int tid = threadIdx.x & 255;            // thread of the team
     const int o0 = t.row0;
     const int g0 = gi * FMMV_MAX_M;
     const int mg = min(FMMV_MAX_M, v.m - g0);  // columns of the group
-    const int mo = mg - v.fuse_b;              // output columns
+    const int mo = mg - (FB ? 1 : 0);          // output columns
     if (f.status[p] & ~SUPERDC_ST_NOCONV) {
         const double nan = __builtin_nan("");
         for (int e = threadIdx.x; e < FV_K * mo; e += blockDim.x) {
             const int r = o0 + (e % FV_K), c = g0 + e / FV_K;
             if (r < n) v.Y[base + r + (int64_t)c * v.ldy] = nan;
         }
-        if (v.fuse_b && threadIdx.x < FV_K && o0 + (int)threadIdx.x < n)
+        if (FB && threadIdx.x < FV_K && o0 + (int)threadIdx.x < n)
             v.bout[base + o0 + threadIdx.x] = nan;
         return;
     }
     const int qf = f.fmm_of[p];
     const int L = wave_uniform(f.leaf_off[qf] + t.row0 / f.leaf);
     const int nn = wave_uniform(f.cnt[3 * (int64_t)L]);
-    const bool direct = nn < 0;  // overflowed lists: every pole, 64 at a time
-    __syncthreads();  // the previous item's reads of the tables are done
+    const bool direct = nn < 0;  // overflowed lists: every source, 64 at a time
+    __syncthreads();  // the previous item's reads of the tables and buffers are done
     if (!direct) {
-        const int nl = f.cnt[3 * (int64_t)L + 1], nr = f.cnt[3 * (int64_t)L + 2];
+        const int nl = wave_uniform(f.cnt[3 * (int64_t)L + 1]);
+        const int nr = wave_uniform(f.cnt[3 * (int64_t)L + 2]);
         for (int e = threadIdx.x; e < nl + nr; e += blockDim.x)
             sh.fbox[e] = e < nl ? f.far_l[(int64_t)L * FMM_FAR_MAX + e]
                                 : f.far_r[(int64_t)L * FMM_FAR_MAX + e - nl];
-        if (threadIdx.x == 0) {
-            int c = 0;
-            for (int e = 0; e < nn; ++e) {
-                const int lo = f.near_lo[(int64_t)L * FMM_NEAR_MAX + e];
-                const int hi = f.near_hi[(int64_t)L * FMM_NEAR_MAX + e];
-                for (int a = lo; a < hi; a += FV_K) sh.ctab[c++] = make_int4(0, a, min(FV_K, hi - a), 0);
+        if (wave == 0) {  // a lane per near range, its chunks after those of the lanes below
+            int lo = 0, hi = 0;
+            if (lane < nn) {
+                lo = f.near_lo[(int64_t)L * FMM_NEAR_MAX + lane];
+                hi = f.near_hi[(int64_t)L * FMM_NEAR_MAX + lane];
             }
-            for (int a = 0; a < nl + nr; a += 4) sh.ctab[c++] = make_int4(1, a, min(4, nl + nr - a), 0);
-            sh.nch = c;
+            int end = (hi - lo + FV_K - 1) / FV_K;
+            const int mine = end;
+            for (int o = 1; o < FMM_NEAR_MAX; o *= 2) {
+                const int up = __shfl_up(end, o);
+                if (lane >= o) end += up;
+            }
+            int c = end - mine;
+            for (int a = lo; a < hi; a += FV_K) sh.ctab[c++] = make_int4(0, a, min(FV_K, hi - a), 0);
+            const int near = __shfl(end, FMM_NEAR_MAX - 1), far = (nl + nr + 3) / 4;
+            for (int e = lane; e < far; e += WAVE)
+                sh.ctab[near + e] = make_int4(1, 4 * e, min(4, nl + nr - 4 * e), 0);
+            if (lane == 0) sh.nch = near + far;
         }
     } else if (threadIdx.x == 0) {
         sh.nch = (n + FV_K - 1) / FV_K;
@@ -465,93 +521,105 @@ __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmV
     __syncthreads();
     const int nch = wave_uniform(sh.nch);
     auto chunk = [&](int ci) -> int4 {
-        return direct ? make_int4(0, ci * FV_K, min(FV_K, n - ci * FV_K), 0) : sh.ctab[ci];
+        if (direct) return make_int4(0, ci * FV_K, min(FV_K, n - ci * FV_K), 0);
+        const int4 ch = sh.ctab[ci];
+        return make_int4(wave_uniform(ch.x), wave_uniform(ch.y), wave_uniform(ch.z), 0);
     };
-    // the root of the Cauchy rows this lane generates: row o0 + 16 wv + lane%16
-    const int orow = o0 + wv * 16 + (lane & 15);
-    const bool ovalid = orow < n;
-    const int oc = ovalid ? orow : n - 1;
-    // the target of the Cauchy row: root (d_K, eta), or (TRANS 0) pole d_i
-    const double ra = TRANS ? v.d[base + clamp_idx(v.origin[base + oc], n)] : v.d[base + oc];
-    const double rb = TRANS ? v.eta[base + oc] : 0.0;
+    // the target of the Cauchy rows this lane generates: row o0 + 16 wv + lane%16, a root
+    // (d_K, eta) or (TRANS 0) a pole d_i.  A row past the end only feeds its own output row,
+    // never written.
+    const int oc = min(o0 + wv * 16 + (lane & 15), n - 1);
+    double ra = TRANS ? v.d[base + clamp_idx(v.origin[base + oc], n)] : v.d[base + oc];
+    double rb = TRANS ? v.eta[base + oc] : 0.0;
     v4d_f acc = v4d_f{0.0, 0.0, 0.0, 0.0};
-    // fuse_b: this lane's share of b's sum for its Cauchy row (the sources it generates
-    // entries for), on the VALU beside the multiply: one column does not need the MFMA
+    // FB: this lane's share of b's sum for its Cauchy row (the sources it generates entries
+    // for), on the VALU beside the multiply: one column does not need the MFMA
     double bsum = 0.0;
-    const bool fb = v.fuse_b != 0;
     FvStage st;
-    int4 cur = chunk(0);
-    fv_fetch<TRANS>(v, base, n, sh.fbox, cur, g0, mg, mo, st);
-    int64_t ent = 0;  // near poles and far sources summed per root (kernel timing)
-    for (int ci = 0; ci < nch; ++ci) {
-        __syncthreads();  // the previous chunk's reads of Xs/Sd are done
-        if (threadIdx.x < FV_K) sh.Sd[threadIdx.x] = st.sd;
-        if (cur.x == 0) {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                sh.Xs[(threadIdx.x / FV_K + 4 * i) * FV_LD + (threadIdx.x & (FV_K - 1))] = st.w[i];
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i)
-                sh.Xs[(threadIdx.x & 15) * FV_LD + (threadIdx.x >> 4) + 16 * i] = st.w[i];
-        }
-        __syncthreads();
-        const int nvalid = wave_uniform(cur.x == 0 ? cur.z : cur.z * FMM_P);
-        const bool cur_near = cur.x == 0;
-        ent += nvalid;
-        if (ci + 1 < nch) {
-            cur = chunk(ci + 1);
-            // in flight during the multiply
-            fv_fetch<TRANS>(v, base, n, sh.fbox, cur, g0, mg, mo, st);
-        }
-        // one slice of 4 sources: the Cauchy entries of this lane's row (one reciprocal
-        // with a Newton step each) into the MFMA; MASK: a partial chunk, whose padding
-        // entries are zeroed (a padding source may sit on a row's target).  A row past the
-        // problem's end (ovalid false) only feeds its own output row, never written.
-#define SDC_FV_SLICE(MASK)                                                              \
-    {                                                                                   \
-        const int sl = kk + (lane >> 4);                                                \
-        const double2 sdv = sh.Sd[sl];                                                  \
-        const double tt = TRANS ? (sdv.x - ra) - rb : (ra - sdv.x) - sdv.y;             \
-        const double av = (!(MASK) || sl < nvalid) ? rcp_nr1(tt) : 0.0;                 \
-        const double bv = sh.Xs[(lane & 15) * FV_LD + sl];                              \
-        acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);               \
-        if (fb) {                                                                       \
-            if (cur_near) { /* (zhat / t)^2: squared after the division */              \
-                const double qv = av * sdv.y;                                           \
-                bsum = fma(qv, qv, bsum);                                               \
-            } else { /* far sources: weights of zhat^2, t bounded away from 0 */        \
-                bsum = fma(av * av, sdv.y, bsum);                                       \
-            }                                                                           \
-        }                                                                               \
+    const int rounds = (nch + TEAMS - 1) / TEAMS;
+    int4 cur = make_int4(0, 0, 0, 0);
+    if (tm < nch) {
+        cur = chunk(tm);
+        fv_fetch<TRANS, FB>(v, base, sh.fbox, cur, tid, g0, mg, mo, st);
     }
-        if (nvalid == FV_K) {
-#pragma unroll 4
-            for (int kk = 0; kk < FV_K; kk += 4) SDC_FV_SLICE(false)
-        } else {
-#pragma unroll 4
-            for (int kk = 0; kk < FV_K; kk += 4) SDC_FV_SLICE(true)
+    asm volatile("" : "+v"(ra), "+v"(rb));  // loaded here, not inside the loop
+    for (int rd = 0; rd < rounds; ++rd) {
+        double *Xs = sh.team[tm].Xs[rd & 1];
+        double2 *Sd = sh.team[tm].Sd[rd & 1];
+        const int ci = rd * TEAMS + tm;
+        const bool live = ci < nch;
+        if (live) fv_store<FB>(cur, tid, mg, mo, st, Xs, Sd);
+        __syncthreads();
+        const bool near = cur.x == 0;
+        if (ci + TEAMS < nch) {  // the next chunk's loads, in flight during the multiply
+            cur = chunk(ci + TEAMS);
+            fv_fetch<TRANS, FB>(v, base, sh.fbox, cur, tid, g0, mg, mo, st);
         }
-#undef SDC_FV_SLICE
+        if (!live) continue;
+        // a step of 4 sources: the Cauchy entry of this lane's row (one reciprocal with a
+        // Newton step) into the MFMA
+        auto multiply = [&](auto is_near) {
+#pragma unroll 4
+            for (int kk = 0; kk < FV_K; kk += 4) {
+                const int sl = kk + (lane >> 4);
+                const double2 sd = Sd[sl];
+                const double av = rcp_nr1(TRANS ? (sd.x - ra) - rb : (ra - sd.x) - sd.y);
+                const double bv = Xs[(lane & 15) * FV_LD + sl];
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
+                if (FB) {
+                    if (is_near.value) {  // (zhat / t)^2: squared after the division
+                        const double qv = av * sd.y;
+                        bsum = fma(qv, qv, bsum);
+                    } else {  // far sources: weights of zhat^2, t bounded away from 0
+                        bsum = fma(av * av, sd.y, bsum);
+                    }
+                }
+            }
+        };
+        if (!FB || near) multiply(fv_true{});
+        else multiply(fv_false{});
         mfma_drain();  // before any copy of the accumulators between chunks
     }
-    if (fb) {  // the four lanes of a Cauchy row (lane % 16) hold its partial sums
+    if (FB) {  // the four lanes of a Cauchy row (lane % 16) hold its partial sums
         bsum += __shfl_xor(bsum, 16);
         bsum += __shfl_xor(bsum, 32);
     }
     if (v.work && threadIdx.x == 0) {  // kernel timing: the item's algorithmic flops
+        unsigned long long ent = 0;  // near and far sources summed per row
+        for (int ci = 0; ci < nch; ++ci) {
+            const int4 ch = chunk(ci);
+            ent += ch.x == 0 ? ch.z : ch.z * FMM_P;
+        }
         const unsigned long long rows = (unsigned long long)min(FV_K, n - o0);
-        atomicAdd(v.work, rows * (unsigned long long)ent * (2 * (unsigned long long)mg + 3) +
+        atomicAdd(v.work, rows * ent * (2 * (unsigned long long)mg + 3) +
                               2 * rows * (unsigned long long)mo);
     }
     mfma_drain();
+    if (TEAMS > 1) {  // the teams' sums through their own buffers, added in team order
+        double *mine = &sh.team[tm].Xs[0][0] + wv * 5 * WAVE;
+        static_assert(4 * 5 * WAVE <= 2 * 16 * FV_LD, "a team's sums fit its buffers");
+        __syncthreads();
+        if (tm > 0) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) mine[r * WAVE + lane] = acc[r];
+            if (FB) mine[4 * WAVE + lane] = bsum;
+        }
+        __syncthreads();
+        if (tm > 0) return;
+        for (int u = 1; u < TEAMS; ++u) {
+            const double *o = &sh.team[u].Xs[0][0] + wv * 5 * WAVE;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) acc[r] += o[r * WAVE + lane];
+            if (FB) bsum += o[4 * WAVE + lane];
+        }
+    }
     // v_mfma_f64_16x16x4f64 returns D[4 r + lane/16][lane % 16] in accumulator r
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int row = o0 + wv * 16 + 4 * r + (lane >> 4);
         const int col = lane & 15;
         double post;
-        if (fb) {  // b's sum of this row is held by the lanes that generated its entries
+        if (FB) {  // b's sum of this row is held by the lanes that generated its entries
             post = 1.0 / sqrt(__shfl(bsum, 4 * r + (lane >> 4)));
             if (row < n && col == 0) v.bout[base + row] = post;
         } else {
@@ -561,15 +629,15 @@ __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmV
     }
 }
 
-template <int TRANS>
-__global__ __launch_bounds__(256) void k_fmmv_eval_mfma(SolveArgs it, FmmArgs f, FmmVec v,
-                                                        Queue *q) {
-    __shared__ FvShared sh;
+template <int TRANS, bool FB, int TEAMS>
+__global__ __launch_bounds__(256 * TEAMS, 4) void k_fmmv_eval_mfma(SolveArgs it, FmmArgs f,
+                                                                   FmmVec v, Queue *q) {
+    __shared__ FvShared<TEAMS> sh;
     __shared__ int slot;
     // the column groups of a tile are neighbouring items: they read the same lists and poles
     const int ng = (v.m + FMMV_MAX_M - 1) / FMMV_MAX_M;
     for_each_item(q, it.ntiles * ng, &slot, [&](int item) {
-        fmmv_item_mfma<TRANS>(it, f, v, it.tiles[item / ng], item % ng, sh);
+        fmmv_item_mfma<TRANS, FB, TEAMS>(it, f, v, it.tiles[item / ng], item % ng, sh);
     });
 }
 
@@ -770,11 +838,22 @@ hipError_t launch_fmmv_eval(const SolveArgs &it, const FmmArgs &f, const FmmVec 
     v.work = trace_work(mfma ? KID_FMMV_EVAL_MFMA : KID_FMMV_EVAL);
     if (mfma) {
         const int items = it.ntiles * ((v.m + FMMV_MAX_M - 1) / FMMV_MAX_M);
-        const dim3 g(q ? min(items, num_cu * 4) : items);
-        if (v.trans == 0)
-            SDC_LAUNCH(KID_FMMV_EVAL_MFMA, k_fmmv_eval_mfma<0>, g, dim3(256), 0, s, it, f, v, q);
-        else
-            SDC_LAUNCH(KID_FMMV_EVAL_MFMA, k_fmmv_eval_mfma<1>, g, dim3(256), 0, s, it, f, v, q);
+        // teams per item: one once the items give every CU two workgroups
+        const int teams = items >= 2 * num_cu ? 1 : items >= num_cu ? 2 : 4;
+        const dim3 g(q ? min(items, num_cu * 4 / teams) : items);
+#define SDC_FV(T, FB, K) \
+    SDC_LAUNCH(KID_FMMV_EVAL_MFMA, (k_fmmv_eval_mfma<T, FB, K>), g, dim3(256 * K), 0, s, it, f, v, q)
+#define SDC_FV_TEAMS(T, FB)              \
+    {                                    \
+        if (teams == 1) SDC_FV(T, FB, 1);     \
+        else if (teams == 2) SDC_FV(T, FB, 2); \
+        else SDC_FV(T, FB, 4);           \
+    }
+        if (v.trans == 0) SDC_FV_TEAMS(0, false)
+        else if (v.fuse_b) SDC_FV_TEAMS(1, true)
+        else SDC_FV_TEAMS(1, false)
+#undef SDC_FV_TEAMS
+#undef SDC_FV
         return hipGetLastError();
     }
     if (v.trans == 0 || v.m >= 4) return hipErrorInvalidValue;
