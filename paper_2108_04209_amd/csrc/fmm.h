@@ -164,6 +164,8 @@ struct FmmVec {
     int fuse_b;               // kern 1 on the MFMA: the last of the m weight columns is zhat^2;
                               // the evaluation forms b from it with the kernel 1/t^2, writes
                               // it to bout and scales the other m - 1 columns by it
+    int expand;               // VALU evaluation: far boxes through the targets' interval (set
+                              // by launch_fmmv_eval)
     const double *zh;         // fuse_b: zhat, for b's near terms (zhat / t)^2
     unsigned long long *work; // kernel timing on: algorithmic flops of the launch (set by
                               // launch_fmmv_eval): (2m + 3) per near pole or far source of a

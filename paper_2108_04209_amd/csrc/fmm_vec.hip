@@ -220,12 +220,109 @@ __global__ __launch_bounds__(FMM_P * FMMV_MAX_M) void k_fmmv_sources_sum(FmmArgs
     v.vw[((int64_t)g * FMM_P + q) * v.m + col] = s;
 }
 
+// ---------------------------------------------------------------------------------------
+// The far field of one work item (64 neighbouring targets) as a function on the targets'
+// interval.  Instead of meeting every target, a far box's 16 equivalent sources meet the 16
+// Chebyshev nodes of the interval, and each target interpolates the boxes' sum there: a
+// quarter of the Cauchy entries plus one 16-term series.  Only boxes at least FV_SEP_T interval
+// widths away take part -- interpolating 1/(s - x) at that distance converges like
+// (4 + sqrt 15)^-16 = 5e-15, the separation at which a box's own sources stand for its poles --
+// the others stay with the direct sums (entries per row, level of 4096 problems: 541 -> 387;
+// evaluation 3.25 -> 2.60 ms, b 1.75 -> 1.54 ms).  Node positions are kept as offsets from the
+// interval's centre, so a difference s - x_m = (s - centre) - offset_m is as accurate as the
+// shifted differences of the targets themselves.
+constexpr double FV_SEP_T = 1.5;
+constexpr int FV_MIN_EXP = 4;  // fewer boxes: the interpolation costs more than it saves
+// A launch uses the expansion once its items give every CU two workgroups: from there the
+// FP64 pipe is the bound (1024 items, one problem of 65536 with 64 columns: 232 -> 173 us with
+// the expansion), below the latency of one item, which it lengthens (16 items, n = 1024: 17
+// -> 20 us for 16 columns, 13 -> 18 us for b).
+constexpr int FV_EXPAND_PER_CU = 2;
+
+// cos((2q + 1) pi / 32) and (-1)^q sin((2q + 1) pi / 32): the nodes and barycentric weights
+__constant__ double FV_NODE[FMM_P] = {
+    0.99518472667219693, 0.95694033573220882, 0.88192126434835505, 0.77301045336273699,
+    0.63439328416364549, 0.47139673682599781, 0.29028467725446233, 0.09801714032956077,
+    -0.098017140329560645, -0.29028467725446216, -0.4713967368259977, -0.63439328416364538,
+    -0.77301045336273699, -0.88192126434835494, -0.95694033573220882, -0.99518472667219682
+};
+__constant__ double FV_BARY[FMM_P] = {
+    0.098017140329560604, -0.29028467725446233, 0.47139673682599764, -0.63439328416364549,
+    0.77301045336273699, -0.88192126434835494, 0.95694033573220894, -0.99518472667219682,
+    0.99518472667219693, -0.95694033573220894, 0.88192126434835505, -0.7730104533627371,
+    0.63439328416364549, -0.47139673682599786, 0.29028467725446239, -0.098017140329560826
+};
+
+// centre and half-width of an item's targets, rows r0 .. r1 of the problem's n (targets are
+// ascending: roots d_K + eta, or with trans 0 the poles); hw = 0: no expansion (one target, or
+// targets so close together that the centre's rounding would show)
+__device__ __forceinline__ double2 fv_interval(const FmmVec &v, int64_t base, int n, int r0, int r1) {
+    double da = v.d[base + r0], db = v.d[base + r1], ea = 0.0, eb = 0.0;
+    if (v.trans) {
+        da = v.d[base + clamp_idx(v.origin[base + r0], n)];
+        db = v.d[base + clamp_idx(v.origin[base + r1], n)];
+        ea = v.eta[base + r0];
+        eb = v.eta[base + r1];
+    }
+    const double c = 0.5 * ((da + ea) + (db + eb)), h = 0.5 * ((db - da) + (eb - ea));
+    return make_double2(c, h >= 0x1p-44 * fabs(c) ? h : 0.0);
+}
+
+// The far boxes of leaf L (nl left, nr right ones) into fbox: those summed directly from the
+// front, those of the expansion from the back; returns how many of the latter (none with
+// expand false).  One wavefront, all lanes.
+__device__ __forceinline__ int fv_split_far(const FmmArgs &f, const FmmVec &v, int L, int nl, int nr,
+                                            double2 iv, bool expand, int *fbox) {
+    const int lane = lane_id();
+    int nd = 0, ne = 0;
+    for (int e0 = 0; e0 < nl + nr; e0 += WAVE) {
+        const int e = e0 + lane;
+        const bool in = e < nl + nr;
+        int g = 0;
+        bool ex = false;
+        if (in) {
+            g = e < nl ? f.far_l[(int64_t)L * FMM_FAR_MAX + e]
+                       : f.far_r[(int64_t)L * FMM_FAR_MAX + e - nl];
+            // the box's end sources: its nodes descend (a leaf of few poles keeps them
+            // ascending instead, but that is a problem's last leaf, whose nearest is the first)
+            const double *nd2 = v.vnode + (int64_t)g * FMM_P;
+            const double dist = fmin(fabs(nd2[0] - iv.x), fabs(nd2[FMM_P - 1] - iv.x)) - iv.y;
+            ex = expand && iv.y > 0.0 && dist >= FV_SEP_T * 2.0 * iv.y;
+        }
+        const unsigned long long md = __ballot(in && !ex), me = __ballot(ex);
+        auto rank = [&](unsigned long long mk) {
+            return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mk >> 32),
+                                                  __builtin_amdgcn_mbcnt_lo((unsigned)mk, 0u));
+        };
+        if (ex) fbox[2 * FMM_FAR_MAX - 1 - (ne + rank(me))] = g;
+        else if (in) fbox[nd + rank(md)] = g;
+        nd += __popcll(md);
+        ne += __popcll(me);
+    }
+    if (ne > 0 && ne < FV_MIN_EXP) {  // too few: back among the direct ones
+        if (lane < ne) {
+            const int g = fbox[2 * FMM_FAR_MAX - 1 - lane];
+            fbox[nd + lane] = g;
+        }
+        ne = 0;
+    }
+    return wave_uniform(ne);
+}
+
 // Evaluation at the roots: work items are 64-root pieces of the target leaves; S
 // wavefronts per item split the near ranges and the far boxes, and their partial sums are
-// added in wavefront order.  NC >= m accumulators per lane.
+// added in wavefront order.  NC >= m accumulators per lane.  In the expansion a lane holds
+// node lane % 16 and every fourth source of a box.
+template <int NC>
+struct FvEvalShared {
+    int fbox[2 * FMM_FAR_MAX];
+    int nexp;
+    double gsum[8][NC][FMM_P];  // far field at the nodes, per wavefront (at most 8)
+};
+
 template <int KERN, int NC>
 __device__ void fmmv_item(const SolveArgs &it, const FmmArgs &f, const FmmVec &v, Tile t,
-                          double *red) {
+                          FvEvalShared<NC> &sh, double *red) {
     const int p = t.prob;
     const int64_t base = it.off[p];
     const int n = (int)(it.off[p + 1] - base);
@@ -260,10 +357,35 @@ __device__ void fmmv_item(const SolveArgs &it, const FmmArgs &f, const FmmVec &v
 #pragma unroll
     for (int c = 0; c < NC; ++c) acc[c] = 0.0;
     int64_t ent = 0;  // pole or source entries this wavefront sums per root (kernel timing)
-    // one near range [lo, hi) of poles, shifted form, two Newton steps
+    // one near range [lo, hi) of poles, shifted form, two Newton steps; two poles share one
+    // reciprocal (it issues at a quarter of the FMA rate), as in the direct b kernel, while
+    // every |t| of the wavefront's roots lies inside [2^-300, 2^300]: the smallest is |eta| (a
+    // root's origin is its nearest pole), the largest at an end of the problem (b of a level of
+    // 4096 problems: 1.54 -> 1.45 ms)
+    const bool pair = __ballot(fabs(eta) < 0x1p-300 ||
+                               fmax(fabs((dd[0] - dK) - eta), fabs((dd[n - 1] - dK) - eta)) > 0x1p300) == 0ull;
     auto near = [&](int lo, int hi) {
         ent += hi > lo ? hi - lo : 0;
-        for (int i = lo; i < hi; ++i) {
+        int i = lo;
+        if (pair) {
+#pragma unroll 2
+            for (; i + 2 <= hi; i += 2) {
+                const double t0 = (dd[i] - dK) - eta, t1 = (dd[i + 1] - dK) - eta;
+                const double R = rcp_nr(t0 * t1);
+                const double u0 = sc[i] * t1, u1 = sc[i + 1] * t0;  // scale_i / t_i = u_i R
+                if (KERN == 1) {
+#pragma unroll
+                    for (int c = 0; c < NC; ++c)
+                        if (c < m) {
+                            const const_double_ptr x = X + i + (int64_t)c * v.ldx;
+                            acc[c] = __builtin_fma(__builtin_fma(u0, x[0], u1 * x[1]), R, acc[c]);
+                        }
+                } else {  // u0^2 + u1^2 over (t0 t1)^2, applied as (num R) R
+                    acc[0] = __builtin_fma(__builtin_fma(u0, u0, u1 * u1) * R, R, acc[0]);
+                }
+            }
+        }
+        for (; i < hi; ++i) {
             const double r = rcp_nr((dd[i] - dK) - eta);
             const double qv = r * sc[i];
             if (KERN == 1) {
@@ -285,9 +407,66 @@ __device__ void fmmv_item(const SolveArgs &it, const FmmArgs &f, const FmmVec &v
                  lo0 + (int)(((int64_t)(hi0 - lo0) * (wv + 1)) / S));
         }
         // far boxes of both sides, lambda-form, one Newton step
-        for (int e = wv; e < nl + nr; e += S) {
-            const int g = wave_uniform(e < nl ? f.far_l[(int64_t)L * FMM_FAR_MAX + e]
-                                              : f.far_r[(int64_t)L * FMM_FAR_MAX + e - nl]);
+        const double2 iv = fv_interval(v, base, n, t.row0, min(t.row0 + WAVE, n) - 1);
+        __syncthreads();  // the previous item's reads of the lists are done
+        if (wv == 0) {
+            const int k = fv_split_far(f, v, L, nl, nr, iv, v.expand != 0, sh.fbox);
+            if (lane == 0) sh.nexp = k;
+        }
+        __syncthreads();
+        const int ne = wave_uniform(sh.nexp);
+        if (ne > 0) {
+            const double off = iv.y * FV_NODE[lane & 15];
+            double gs[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) gs[c] = 0.0;
+            for (int e = wv; e < ne; e += S) {
+                const int64_t g = sh.fbox[2 * FMM_FAR_MAX - 1 - e];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int64_t sq = g * FMM_P + 4 * k + (lane >> 4);
+                    const double r = rcp_nr1((v.vnode[sq] - iv.x) - off);
+                    if (KERN == 1) {
+#pragma unroll
+                        for (int c = 0; c < NC; ++c)
+                            if (c < m) gs[c] = __builtin_fma(r, v.vw[sq * m + c], gs[c]);
+                    } else {
+                        gs[0] = __builtin_fma(r * r, v.vw[sq], gs[0]);
+                    }
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                gs[c] += __shfl_xor(gs[c], 16);
+                gs[c] += __shfl_xor(gs[c], 32);
+                if (lane < FMM_P) sh.gsum[wv][c][lane] = gs[c];
+            }
+            wave_sync();
+            // this wavefront's share of the far field at the targets
+            const double tau = ((dK - iv.x) + eta) / iv.y;
+            double num[NC], den = 0.0;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) num[c] = 0.0;
+            for (int q = 0; q < FMM_P; ++q) {
+                const double dl = tau - FV_NODE[q];
+                // a target on a node: that node's term outweighs the others
+                const double b = FV_BARY[q] * rcp_nr(dl == 0.0 ? 0x1p-200 : dl);
+                den += b;
+#pragma unroll
+                for (int c = 0; c < NC; ++c)
+                    if (c < m) num[c] = __builtin_fma(b, sh.gsum[wv][c][q], num[c]);
+            }
+            const double iden = 1.0 / den;
+#pragma unroll
+            for (int c = 0; c < NC; ++c) acc[c] = __builtin_fma(num[c], iden, acc[c]);
+            if (v.work && lane == 0) {  // kernel timing: the expansion's algorithmic flops
+                const unsigned long long per = KERN == 1 ? 2 * (unsigned long long)m + 3 : 6;
+                atomicAdd(v.work, (unsigned long long)((ne - wv + S - 1) / S) * FMM_P * FMM_P * per +
+                                      (unsigned long long)(WAVE * FMM_P * 2 * m));
+            }
+        }
+        for (int e = wv; e < nl + nr - ne; e += S) {
+            const int g = wave_uniform(sh.fbox[e]);
             const const_double_ptr nd = as_const(v.vnode + (int64_t)g * FMM_P);
             const const_double_ptr ww = as_const(v.vw + (int64_t)g * FMM_P * m);
             ent += FMM_P;
@@ -337,9 +516,10 @@ __device__ void fmmv_item(const SolveArgs &it, const FmmArgs &f, const FmmVec &v
 template <int KERN, int NC>
 __global__ __launch_bounds__(512) void k_fmmv_eval(SolveArgs it, FmmArgs f, FmmVec v, Queue *q) {
     extern __shared__ double red[];
+    __shared__ FvEvalShared<NC> sh;
     __shared__ int slot;
     for_each_item(q, it.ntiles, &slot, [&](int item) {
-        fmmv_item<KERN, NC>(it, f, v, it.tiles[item], red);
+        fmmv_item<KERN, NC>(it, f, v, it.tiles[item], sh, red);
     });
 }
 
@@ -362,8 +542,9 @@ __global__ __launch_bounds__(512) void k_fmmv_eval(SolveArgs it, FmmArgs f, FmmV
 // stored; every lane loads (indices clamped to the chunk's own sources, padding set to zero
 // at the store), so that the loads of a chunk are one run without branches; and the values
 // loaded once per item are taken before the loop, since a first use inside it made the
-// compiler wait there for the next chunk's loads as well.  Now 80 us; in a level of 4096 problems
-// (16 columns) 4.08 -> 3.25 ms.  A launch with too few items to give every CU two workgroups
+// compiler wait there for the next chunk's loads as well: 80 us, and in a level of 4096 problems
+// (16 columns) 4.08 -> 3.25 ms.  The far boxes go through the targets' interval (fv_split_far),
+// which left 5 chunks and 41 boxes an item on average: 73 us, and 2.60 ms.  A launch with too few items to give every CU two workgroups
 // gives each item TEAMS teams of four wavefronts, which take the chunks in turn and add their
 // sums in team order (n = 1024, 16 items: 23 -> 12 us).
 // ---------------------------------------------------------------------------------------
@@ -457,7 +638,8 @@ struct FvShared {
     FvTeam team[TEAMS];
     int4 ctab[FV_MAXCH];
     int fbox[2 * FMM_FAR_MAX];
-    int nch;
+    int nch, nexp;
+    double node[FMM_P], bary[FMM_P];  // FV_NODE and FV_BARY (read by lane)
 };
 
 // gi: the group of FMMV_MAX_M columns of the pass
@@ -489,19 +671,18 @@ __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmV
     const int L = wave_uniform(f.leaf_off[qf] + t.row0 / f.leaf);
     const int nn = wave_uniform(f.cnt[3 * (int64_t)L]);
     const bool direct = nn < 0;  // overflowed lists: every source, 64 at a time
+    double2 iv = fv_interval(v, base, n, o0, min(o0 + FV_K, n) - 1);
     __syncthreads();  // the previous item's reads of the tables and buffers are done
     if (!direct) {
-        const int nl = wave_uniform(f.cnt[3 * (int64_t)L + 1]);
-        const int nr = wave_uniform(f.cnt[3 * (int64_t)L + 2]);
-        for (int e = threadIdx.x; e < nl + nr; e += blockDim.x)
-            sh.fbox[e] = e < nl ? f.far_l[(int64_t)L * FMM_FAR_MAX + e]
-                                : f.far_r[(int64_t)L * FMM_FAR_MAX + e - nl];
         if (wave == 0) {  // a lane per near range, its chunks after those of the lanes below
+            const int nl = wave_uniform(f.cnt[3 * (int64_t)L + 1]);
+            const int nr = wave_uniform(f.cnt[3 * (int64_t)L + 2]);
             int lo = 0, hi = 0;
             if (lane < nn) {
                 lo = f.near_lo[(int64_t)L * FMM_NEAR_MAX + lane];
                 hi = f.near_hi[(int64_t)L * FMM_NEAR_MAX + lane];
             }
+            const int ne = fv_split_far(f, v, L, nl, nr, iv, TEAMS == 1, sh.fbox), nd = nl + nr - ne;
             int end = (hi - lo + FV_K - 1) / FV_K;
             const int mine = end;
             for (int o = 1; o < FMM_NEAR_MAX; o *= 2) {
@@ -510,16 +691,20 @@ __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmV
             }
             int c = end - mine;
             for (int a = lo; a < hi; a += FV_K) sh.ctab[c++] = make_int4(0, a, min(FV_K, hi - a), 0);
-            const int near = __shfl(end, FMM_NEAR_MAX - 1), far = (nl + nr + 3) / 4;
+            const int near = __shfl(end, FMM_NEAR_MAX - 1), far = (nd + 3) / 4;
             for (int e = lane; e < far; e += WAVE)
-                sh.ctab[near + e] = make_int4(1, 4 * e, min(4, nl + nr - 4 * e), 0);
-            if (lane == 0) sh.nch = near + far;
+                sh.ctab[near + e] = make_int4(1, 4 * e, min(4, nd - 4 * e), 0);
+            if (lane == 0) {
+                sh.nch = near + far;
+                sh.nexp = ne;
+            }
         }
     } else if (threadIdx.x == 0) {
         sh.nch = (n + FV_K - 1) / FV_K;
+        sh.nexp = 0;
     }
     __syncthreads();
-    const int nch = wave_uniform(sh.nch);
+    const int nch = wave_uniform(sh.nch), nexp = wave_uniform(sh.nexp);
     auto chunk = [&](int ci) -> int4 {
         if (direct) return make_int4(0, ci * FV_K, min(FV_K, n - ci * FV_K), 0);
         const int4 ch = sh.ctab[ci];
@@ -542,7 +727,7 @@ __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmV
         cur = chunk(tm);
         fv_fetch<TRANS, FB>(v, base, sh.fbox, cur, tid, g0, mg, mo, st);
     }
-    asm volatile("" : "+v"(ra), "+v"(rb));  // loaded here, not inside the loop
+    asm volatile("" : "+v"(ra), "+v"(rb), "+v"(iv.x), "+v"(iv.y));  // loaded here, not in the loop
     for (int rd = 0; rd < rounds; ++rd) {
         double *Xs = sh.team[tm].Xs[rd & 1];
         double2 *Sd = sh.team[tm].Sd[rd & 1];
@@ -580,6 +765,87 @@ __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmV
         else multiply(fv_false{});
         mfma_drain();  // before any copy of the accumulators between chunks
     }
+    if (TEAMS == 1 && nexp > 0) {
+        // The expansion: the Cauchy rows are the interval's nodes.  Wavefront w takes the boxes
+        // w, w + 4, ..., their operands straight from memory (step s of a box: source
+        // 4 s + lane / 16, column lane % 16), the next box's in flight.
+        const int c = min(lane & 15, mg - 1);
+        const double off = iv.y * sh.node[lane & 15];
+        v4d_f g = v4d_f{0.0, 0.0, 0.0, 0.0};
+        double gb = 0.0;  // FB: sum of W / t^2 at this lane's node over its sources
+        struct Box {
+            double w[4], x[4], b[4];
+        };
+        auto fetch = [&](int e, Box &o) {
+            const int64_t s0 = (int64_t)sh.fbox[2 * FMM_FAR_MAX - 1 - e] * FMM_P + (lane >> 4);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                o.x[k] = v.vnode[s0 + 4 * k];
+                o.w[k] = v.vw[(s0 + 4 * k) * v.m + g0 + c];
+                if (FB) o.b[k] = v.vw[(s0 + 4 * k) * v.m + v.m - 1];
+            }
+        };
+        auto add = [&](const Box &o) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const double t = (o.x[k] - iv.x) - off;
+                const double av = rcp_nr1(TRANS ? t : -t);
+                g = __builtin_amdgcn_mfma_f64_16x16x4f64(av, o.w[k], g, 0, 0, 0);
+                if (FB) gb = fma(av * av, o.b[k], gb);
+            }
+            mfma_drain();
+        };
+        Box b0, b1;  // in turn: one in flight while the other is added
+        if (wv < nexp) fetch(wv, b0);
+        for (int e = wv; e < nexp; e += 8) {
+            if (e + 4 < nexp) fetch(e + 4, b1);
+            add(b0);
+            if (e + 4 >= nexp) break;
+            if (e + 8 < nexp) fetch(e + 8, b0);
+            add(b1);
+        }
+        // the wavefronts add their sums through the buffer that the last round left free;
+        // accumulator s of lane l (node 4 s + l / 16, column l % 16) is the operand that step s
+        // of the interpolation feeds
+        double *part = sh.team[0].Xs[rounds & 1];
+        double *pb = (double *)sh.team[0].Sd[rounds & 1];
+        static_assert(4 * 4 * WAVE <= 16 * FV_LD && 4 * FMM_P <= 2 * FV_K, "the sums fit the buffer");
+#pragma unroll
+        for (int k = 0; k < 4; ++k) part[(wv * 4 + k) * WAVE + lane] = g[k];
+        if (FB) {
+            gb += __shfl_xor(gb, 16);
+            gb += __shfl_xor(gb, 32);
+            if (lane < FMM_P) pb[wv * FMM_P + lane] = gb;
+        }
+        __syncthreads();
+        // Lagrange values of this lane's row at the nodes 4 k + lane / 16 (barycentric form; a
+        // target on a node: that node's term outweighs the others)
+        const double tau = ((ra - iv.x) + rb) / iv.y;
+        double lq[4], den = 0.0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const double dl = tau - sh.node[4 * k + (lane >> 4)];
+            lq[k] = sh.bary[4 * k + (lane >> 4)] * rcp_nr(dl == 0.0 ? 0x1p-200 : dl);
+            den += lq[k];
+        }
+        den += __shfl_xor(den, 16);
+        den += __shfl_xor(den, 32);
+        const double iden = 1.0 / den;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            double gk = part[k * WAVE + lane];
+#pragma unroll
+            for (int u = 1; u < 4; ++u) gk += part[(u * 4 + k) * WAVE + lane];
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(lq[k] * iden, gk, acc, 0, 0, 0);
+            if (FB) {
+                const int q = 4 * k + (lane >> 4);
+                double bk = pb[q];
+#pragma unroll
+                for (int u = 1; u < 4; ++u) bk += pb[u * FMM_P + q];
+                bsum = fma(lq[k] * iden, bk, bsum);
+            }
+        }
+    }
     if (FB) {  // the four lanes of a Cauchy row (lane % 16) hold its partial sums
         bsum += __shfl_xor(bsum, 16);
         bsum += __shfl_xor(bsum, 32);
@@ -591,8 +857,9 @@ __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmV
             ent += ch.x == 0 ? ch.z : ch.z * FMM_P;
         }
         const unsigned long long rows = (unsigned long long)min(FV_K, n - o0);
-        atomicAdd(v.work, rows * ent * (2 * (unsigned long long)mg + 3) +
-                              2 * rows * (unsigned long long)mo);
+        const unsigned long long per = 2 * (unsigned long long)mg + 3;
+        atomicAdd(v.work, rows * ent * per + 2 * rows * (unsigned long long)mo +
+                              (nexp > 0 ? FMM_P * (nexp * FMM_P * per + rows * 2 * mg) : 0));
     }
     mfma_drain();
     if (TEAMS > 1) {  // the teams' sums through their own buffers, added in team order
@@ -634,6 +901,10 @@ __global__ __launch_bounds__(256 * TEAMS, 4) void k_fmmv_eval_mfma(SolveArgs it,
                                                                    FmmVec v, Queue *q) {
     __shared__ FvShared<TEAMS> sh;
     __shared__ int slot;
+    if (TEAMS == 1 && threadIdx.x < FMM_P) {
+        sh.node[threadIdx.x] = FV_NODE[threadIdx.x];
+        sh.bary[threadIdx.x] = FV_BARY[threadIdx.x];
+    }
     // the column groups of a tile are neighbouring items: they read the same lists and poles
     const int ng = (v.m + FMMV_MAX_M - 1) / FMMV_MAX_M;
     for_each_item(q, it.ntiles * ng, &slot, [&](int item) {
@@ -838,8 +1109,7 @@ hipError_t launch_fmmv_eval(const SolveArgs &it, const FmmArgs &f, const FmmVec 
     v.work = trace_work(mfma ? KID_FMMV_EVAL_MFMA : KID_FMMV_EVAL);
     if (mfma) {
         const int items = it.ntiles * ((v.m + FMMV_MAX_M - 1) / FMMV_MAX_M);
-        // teams per item: one once the items give every CU two workgroups
-        const int teams = items >= 2 * num_cu ? 1 : items >= num_cu ? 2 : 4;
+        const int teams = items >= FV_EXPAND_PER_CU * num_cu ? 1 : items >= num_cu ? 2 : 4;
         const dim3 g(q ? min(items, num_cu * 4 / teams) : items);
 #define SDC_FV(T, FB, K) \
     SDC_LAUNCH(KID_FMMV_EVAL_MFMA, (k_fmmv_eval_mfma<T, FB, K>), g, dim3(256 * K), 0, s, it, f, v, q)
@@ -857,6 +1127,7 @@ hipError_t launch_fmmv_eval(const SolveArgs &it, const FmmArgs &f, const FmmVec 
         return hipGetLastError();
     }
     if (v.trans == 0 || v.m >= 4) return hipErrorInvalidValue;
+    v.expand = it.ntiles >= FV_EXPAND_PER_CU * num_cu;
     const dim3 g(q ? min(it.ntiles, num_cu * max(1, 32 / split)) : it.ntiles), blk(WAVE * split);
     if (v.kern == 2) {
         const size_t lds = sizeof(double) * WAVE * (split - 1) * 1;

@@ -33,3 +33,33 @@ def test_wide_apply(orc, m, method):
             Qa = np.abs(Q.T if trans else Q)
             tol = 1e-12 * (Qa @ np.abs(X[a:e]))
             assert np.all(np.abs(Y[a:e] - Yo) <= tol), (p, trans)
+
+
+@pytest.mark.parametrize("n", [40000, 40001])
+def test_interval_expansion(orc, n):
+    """Far boxes through the targets' interval (launches with two items per CU and more): b, and
+    3 and 16 columns of both products, in problems whose last item holds 64 targets or one
+    (no interval), clustered poles, on sampled rows."""
+    from paper_2108_04209_amd import native
+    from tests import gpu_pipeline as gp
+    batch, X = gen.small_batch([n], seed=68, kind="clustered", m=16)
+    res = gp.run(batch, opts=native.default_opts(method=2))
+    pr = batch.problem(0)
+    zo, bo, eta, org = (res[k] for k in ("zhat", "b", "eta", "origin"))
+    rng = np.random.default_rng(5)
+    rows = np.unique(np.r_[0, 63, 64, n - 2, n - 1, rng.choice(n, 48, replace=False)])
+    ob = orc.bnorm(pr.d, zo, eta, org, roots=rows)
+    assert np.all(np.abs(bo[rows] - ob) <= 1e-12 * ob)
+    for trans in (0, 1):
+        if trans:
+            t = (pr.d[None, :] - pr.d[org[rows]][:, None]) - eta[rows][:, None]
+            Q = zo[None, :] * bo[rows][:, None] / t
+        else:
+            t = (pr.d[rows][:, None] - pr.d[org][None, :]) - eta[None, :]
+            Q = zo[rows][:, None] * bo[None, :] / t
+        for m in (3, 16):
+            Y = gp.apply_from(batch, zo, bo, eta, org, X[:, :m], trans,
+                              opts=native.default_opts(method=2))
+            Yo = orc.cauchy_apply(pr.d, zo, bo, eta, org, X[:, :m], trans=trans, rows=rows)
+            tol = 1e-12 * (np.abs(Q) @ np.abs(X[:, :m]))
+            assert np.all(np.abs(Y[rows] - Yo) <= tol), (trans, m)
