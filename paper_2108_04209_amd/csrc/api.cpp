@@ -1,8 +1,8 @@
 // api.cpp -- C ABI of the gfx950 conquering-stage library (declared in include/superdc.h).
 //
 // Host responsibilities only: argument checks, batch plans (work tiles ordered
-// longest-problem-first for the persistent launches), grow-only workspace, and the choice
-// between one persistent launch per phase and one launch per problem.
+// longest-problem-first for the batched launches), grow-only workspace, and the choice
+// between one launch per phase and one launch per problem.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -59,12 +59,6 @@ int fmm_crossover_of(const superdc_ctx *ctx, const superdc_opts &o) {
            : o.method == 2 ? 2 * o.fmm_leaf
            : o.fmm_crossover > 0 ? o.fmm_crossover
                                 : ctx->fmm_crossover;
-}
-
-// persistent grid: enough single-wave workgroups to fill every CU several times
-int persistent_grid(const superdc_ctx *ctx, int ntiles, int per_cu) {
-    const long g = (long)ctx->num_cu * per_cu;
-    return (int)std::max(1L, std::min<long>(g, ntiles));
 }
 
 const TileList *tile_list(superdc_batch *b, int chunk) {
@@ -460,7 +454,7 @@ bool fmmv_space(superdc_ctx *ctx, const FmmPlan *fp, int cols, FmmArgs &f, FmmVe
 
 // Run the eigenvector-side FMM over every FMM problem of the batch for the v.m columns of
 // v.X: build the lists (first pass only), compress the used boxes, evaluate at the targets
-// (one persistent launch, or one launch per problem).
+// (one launch, or one launch per problem).
 hipError_t fmmv_run(superdc_ctx *ctx, const superdc_batch *b, const FmmPlan *fp,
                     const FmmArgs &f, const FmmVec &v, bool lists, bool persistent,
                     hipStream_t s) {
@@ -472,12 +466,12 @@ hipError_t fmmv_run(superdc_ctx *ctx, const superdc_batch *b, const FmmPlan *fp,
     if (persistent) {
         it.tiles = fp->leaf_lpt;
         it.ntiles = fp->nitems;
-        return launch_fmmv_eval(it, f, v, fp->split, ctx->queues + Q_FMMV, ctx->num_cu, s);
+        return launch_fmmv_eval(it, f, v, fp->split, ctx->num_cu, s);
     }
     for (int q = 0; q < fp->nfmm && e == hipSuccess; ++q) {
         it.tiles = fp->leaf_nat + fp->item_off_h[q];
         it.ntiles = fp->item_off_h[q + 1] - fp->item_off_h[q];
-        e = launch_fmmv_eval(it, f, v, fp->split, nullptr, ctx->num_cu, s);
+        e = launch_fmmv_eval(it, f, v, fp->split, ctx->num_cu, s);
     }
     return e;
 }
@@ -599,19 +593,15 @@ int loewner_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const
             a.tiles = fp->dir_lpt[0];
             a.ntiles = fp->dir_count[0];
         }
-        SDC_HIP(launch_loewner(a, S, ctx->queues + Q_LOEWNER,
-                               persistent_grid(ctx, a.ntiles, std::max(1, 32 / S)), s, false));
+        SDC_HIP(launch_loewner(a, S, s, false));
         if (fp) {
             VecArgs af = a;
             af.tiles = fp->leaf_lpt;
             af.ntiles = fp->nitems;
-            SDC_HIP(launch_loewner_fmm(af, f, lf, fp->split, ctx->queues + Q_LOEWNER,
-                                       persistent_grid(ctx, af.ntiles, std::max(1, 32 / fp->split)),
-                                       s));
+            SDC_HIP(launch_loewner_fmm(af, f, lf, fp->split, s));
         }
         if (fmm_b)
-            SDC_HIP(launch_bnorm(a, S, ctx->queues + Q_BNORM,
-                                 persistent_grid(ctx, a.ntiles, std::max(1, 32 / S)), s));
+            SDC_HIP(launch_bnorm(a, S, s));
         if (fp && fmm_b) SDC_HIP(fmmv_run(ctx, b, fp, f, v, false, true, s));
     } else {
         for (int p = 0; p < b->nprob; ++p) {
@@ -622,13 +612,13 @@ int loewner_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const
                 VecArgs af = a;
                 af.tiles = fp->leaf_nat + fp->item_off_h[q];
                 af.ntiles = fp->item_off_h[q + 1] - fp->item_off_h[q];
-                SDC_HIP(launch_loewner_fmm(af, f, lf, fp->split, nullptr, 0, s));
+                SDC_HIP(launch_loewner_fmm(af, f, lf, fp->split, s));
                 continue;
             }
             a.tiles = L->nat + L->begin[p];
             a.ntiles = L->begin[p + 1] - L->begin[p];
-            SDC_HIP(launch_loewner(a, S, nullptr, 0, s, false));
-            if (fmm_b) SDC_HIP(launch_bnorm(a, S, nullptr, 0, s));
+            SDC_HIP(launch_loewner(a, S, s, false));
+            if (fmm_b) SDC_HIP(launch_bnorm(a, S, s));
         }
         if (fp && fmm_b) SDC_HIP(fmmv_run(ctx, b, fp, f, v, false, false, s));
     }
@@ -683,13 +673,13 @@ int apply_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const d
     if (o.persistent) {
         a.tiles = fp ? fp->dir_lpt[0] : L->lpt;
         a.ntiles = fp ? fp->dir_count[0] : L->count;
-        SDC_HIP(launch_apply(a, use_mfma, ctx->queues + Q_APPLY, ctx->num_cu, s));
+        SDC_HIP(launch_apply(a, use_mfma, ctx->num_cu, s));
     } else {
         for (int p = 0; p < b->nprob; ++p) {
             if (fp && fp->fmm_of_h[p] >= 0) continue;
             a.tiles = L->nat + L->begin[p];
             a.ntiles = L->begin[p + 1] - L->begin[p];
-            SDC_HIP(launch_apply(a, use_mfma, nullptr, ctx->num_cu, s));
+            SDC_HIP(launch_apply(a, use_mfma, ctx->num_cu, s));
         }
     }
     if (!fp) return SUPERDC_OK;
@@ -791,14 +781,6 @@ int superdc_create(superdc_ctx **out) {
             return rc;
         }
     }
-    hipError_t e = hipMalloc(&ctx->queues, sizeof(Queue) * kNumQueues);
-    if (e == hipSuccess) e = hipMemset(ctx->queues, 0, sizeof(Queue) * kNumQueues);
-    if (e == hipSuccess) e = hipDeviceSynchronize();
-    if (e != hipSuccess) {
-        if (ctx->queues) (void)hipFree(ctx->queues);
-        delete ctx;
-        return hip_fail(e);
-    }
     *out = ctx;
     return SUPERDC_OK;
 }
@@ -808,7 +790,6 @@ void superdc_destroy(superdc_ctx *ctx) {
     (void)hipDeviceSynchronize();
     for (int i = 0; i < kNumWs; ++i)
         if (ctx->ws[i]) (void)hipFree(ctx->ws[i]);
-    if (ctx->queues) (void)hipFree(ctx->queues);
     delete ctx;
 }
 
@@ -849,7 +830,7 @@ int superdc_batch_create(superdc_ctx *ctx, int32_t nprob, const int64_t *off_hos
         superdc_batch_destroy(b);
         return hip_fail(e);
     }
-    // launch shapes for the persistent launches (the autotuner may replace them)
+    // launch shapes for the batched launches (the autotuner may replace them)
     b->sec = choose_shape(ctx, b, SEC_CHUNK);
     // the solver's tile list for that shape is built now, so that a later solve (the
     // allocation-free entry point in particular) finds it ready
@@ -922,7 +903,7 @@ int superdc_secular_solve(superdc_ctx *ctx, const superdc_batch *b, const double
         f.gen = ++fp->gen;  // the lists this solve builds
     }
     if (o.persistent) {
-        // one persistent launch over the chunks of the direct problems, longest first,
+        // one launch over the chunks of the direct problems, longest first,
         // and one over the target leaves of the FMM problems
         const LaunchShape sh = b->sec;
         const TileList *L = tile_list(bm, sh.chunk);
@@ -938,8 +919,7 @@ int superdc_secular_solve(superdc_ctx *ctx, const superdc_batch *b, const double
         SDC_HIP(launch_validate(a, 0, b->nprob, b->max_n, s, b->vsplit, b->vsum, b->vst));
         if (fp) SDC_HIP(launch_fmm_build(f, s));
         a.work = trace_work(KID_SECULAR);
-        SDC_HIP(launch_secular(a, sh.split, ctx->queues + Q_SECULAR,
-                               persistent_grid(ctx, a.ntiles, std::max(1, 32 / sh.split)), s));
+        SDC_HIP(launch_secular(a, sh.split, s));
         if (fp) {
             SolveArgs af = a;
             af.tiles = fp->sitem_lpt;
@@ -947,8 +927,7 @@ int superdc_secular_solve(superdc_ctx *ctx, const superdc_batch *b, const double
             af.chunk = fp->ssub;
             af.work = trace_work(KID_SECULAR_FMM);
             const int ss = b->fmm_ssplit > 0 ? b->fmm_ssplit : fp->ssplit;  // tuned or heuristic
-            SDC_HIP(launch_secular_fmm(af, f, ss, ctx->queues + Q_SECULAR_FMM,
-                                       persistent_grid(ctx, af.ntiles, std::max(1, 32 / ss)), s));
+            SDC_HIP(launch_secular_fmm(af, f, ss, s));
         }
     } else {
         // one launch per problem, cut into 64-root chunks (split if the problem is large),
@@ -967,7 +946,7 @@ int superdc_secular_solve(superdc_ctx *ctx, const superdc_batch *b, const double
                 af.ntiles = fp->sitem_off_h[q + 1] - fp->sitem_off_h[q];
                 af.chunk = fp->ssub;
                 af.work = trace_work(KID_SECULAR_FMM);
-                SDC_HIP(launch_secular_fmm(af, f, fp->ssplit, nullptr, 0, s));
+                SDC_HIP(launch_secular_fmm(af, f, fp->ssplit, s));
                 continue;
             }
             const LaunchShape sh = shape_for(ctx, &np, 1, TILE);
@@ -977,7 +956,7 @@ int superdc_secular_solve(superdc_ctx *ctx, const superdc_batch *b, const double
             a.ntiles = L->begin[p + 1] - L->begin[p];
             a.chunk = sh.chunk;
             a.work = trace_work(KID_SECULAR);
-            SDC_HIP(launch_secular(a, sh.split, nullptr, 0, s));
+            SDC_HIP(launch_secular(a, sh.split, s));
         }
     }
     return SUPERDC_OK;
@@ -1036,15 +1015,14 @@ int superdc_secular_backward(superdc_ctx *ctx, const superdc_batch *b, const dou
         a.tiles = L->lpt;
         a.ntiles = L->count;
         const int S = b->bwd.split;
-        SDC_HIP(launch_backward(a, S, 0, b->nprob, ctx->queues + Q_BWD1, ctx->queues + Q_BWD2,
-                                persistent_grid(ctx, L->count, std::max(1, 32 / S)), s));
+        SDC_HIP(launch_backward(a, S, 0, b->nprob, s));
     } else {
         for (int p = 0; p < b->nprob; ++p) {
             const int64_t np = b->off_h[p + 1] - b->off_h[p];
             const int S = shape_for(ctx, &np, 1, TILE).split;
             a.tiles = L->nat + L->begin[p];
             a.ntiles = L->begin[p + 1] - L->begin[p];
-            SDC_HIP(launch_backward(a, S, p, 1, nullptr, nullptr, 0, s));
+            SDC_HIP(launch_backward(a, S, p, 1, s));
         }
     }
     return SUPERDC_OK;

@@ -122,7 +122,6 @@ __device__ void apply_tile_mfma(const ApplyArgs &a, Tile t, int c0, double *Xs, 
     // VALU beside the multiply (one column does not need the MFMA)
     double bsum = 0.0;
     ApplyStage<NCT> st;
-    __syncthreads();  // the previous item's reads of the buffers are done
     apply_fetch<TRANS, NCT>(a, base, n, 0, c0, ncols, st);
     asm volatile("" : "+v"(ra), "+v"(rb));  // loaded here, not inside the loop
     // one barrier per chunk: a buffer is stored again two chunks later, behind the barrier
@@ -186,14 +185,11 @@ __device__ void apply_tile_mfma(const ApplyArgs &a, Tile t, int c0, double *Xs, 
 }
 
 template <int TRANS, int NCT, bool FB>
-__global__ __launch_bounds__(256) void k_apply_mfma(ApplyArgs a, Queue *q) {
+__global__ __launch_bounds__(256) void k_apply_mfma(ApplyArgs a) {
     __shared__ double Xs[2 * 16 * NCT * AP_LD];
     __shared__ double2 Sd[2 * AP_K];
-    __shared__ int slot;
     const int np = (a.m + 16 * NCT - 1) / (16 * NCT);  // passes of a tile: neighbouring items
-    for_each_item(q, a.ntiles * np, &slot, [&](int item) {
-        apply_tile_mfma<TRANS, NCT, FB>(a, a.tiles[item / np], item % np * (16 * NCT), Xs, Sd);
-    });
+    apply_tile_mfma<TRANS, NCT, FB>(a, a.tiles[blockIdx.x / np], blockIdx.x % np * (16 * NCT), Xs, Sd);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -285,20 +281,17 @@ __device__ void apply_tile_valu(const ApplyArgs &a, Tile t, double *Xs, double2 
 }
 
 template <int TRANS>
-__global__ __launch_bounds__(WAVE * AV_W) void k_apply_valu(ApplyArgs a, Queue *q) {
+__global__ __launch_bounds__(WAVE * AV_W) void k_apply_valu(ApplyArgs a) {
     // the partial-sum exchange reuses the staging area (it follows a barrier that ends
     // every read of it)
     static_assert((AV_W - 1) * AV_C * WAVE <= AV_W * WAVE * AV_C, "reduction area");
     __shared__ double Xs[AV_W * WAVE * AV_C];
     __shared__ double2 Sd[AV_W * WAVE];
-    __shared__ int slot;
     double *red = Xs;
-    for_each_item(q, a.ntiles, &slot, [&](int item) {
-        apply_tile_valu<TRANS>(a, a.tiles[item], Xs, Sd, red);
-    });
+    apply_tile_valu<TRANS>(a, a.tiles[blockIdx.x], Xs, Sd, red);
 }
 
-hipError_t launch_apply(const ApplyArgs &a0, int use_mfma, Queue *q, int num_cu, hipStream_t s) {
+hipError_t launch_apply(const ApplyArgs &a0, int use_mfma, int num_cu, hipStream_t s) {
     if (a0.ntiles <= 0) return hipSuccess;
     ApplyArgs a = a0;
     a.work = trace_work(use_mfma ? KID_APPLY_MFMA : KID_APPLY_VALU);
@@ -308,9 +301,9 @@ hipError_t launch_apply(const ApplyArgs &a0, int use_mfma, Queue *q, int num_cu,
         int nct = a.m <= 16 ? 1 : (a.m <= 32 ? 2 : 4);
         auto items = [&] { return a.ntiles * ((a.m + 16 * nct - 1) / (16 * nct)); };
         while (nct > 1 && items() < 2 * num_cu) nct /= 2;
-        const dim3 g(q ? min(items(), num_cu * 4) : items());
+        const dim3 g(items());
 #define SDC_APPLY_MFMA(T, C, FB) \
-    SDC_LAUNCH(KID_APPLY_MFMA, (k_apply_mfma<T, C, FB>), g, dim3(256), 0, s, a, q)
+    SDC_LAUNCH(KID_APPLY_MFMA, (k_apply_mfma<T, C, FB>), g, dim3(256), 0, s, a)
         if (a.trans) {
             if (a.fuse_b) SDC_APPLY_MFMA(1, 1, true);
             else if (nct == 1) SDC_APPLY_MFMA(1, 1, false);
@@ -323,11 +316,11 @@ hipError_t launch_apply(const ApplyArgs &a0, int use_mfma, Queue *q, int num_cu,
         }
 #undef SDC_APPLY_MFMA
     } else {
-        const dim3 g(q ? min(a.ntiles, num_cu * 8) : a.ntiles);
+        const dim3 g(a.ntiles);
         if (a.trans)
-            SDC_LAUNCH(KID_APPLY_VALU, k_apply_valu<1>, g, dim3(WAVE * AV_W), 0, s, a, q);
+            SDC_LAUNCH(KID_APPLY_VALU, k_apply_valu<1>, g, dim3(WAVE * AV_W), 0, s, a);
         else
-            SDC_LAUNCH(KID_APPLY_VALU, k_apply_valu<0>, g, dim3(WAVE * AV_W), 0, s, a, q);
+            SDC_LAUNCH(KID_APPLY_VALU, k_apply_valu<0>, g, dim3(WAVE * AV_W), 0, s, a);
     }
     return hipGetLastError();
 }

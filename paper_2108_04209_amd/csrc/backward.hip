@@ -151,13 +151,10 @@ __device__ void bwd_poles_tile(const BwdArgs &a, Tile t, double4 *red) {
 
 // blockDim.x = 64 S; dynamic LDS: two double4 per thread when S > 1
 template <bool PROJ, int PASS>
-__global__ __launch_bounds__(1024) void k_bwd(BwdArgs a, Queue *q) {
+__global__ __launch_bounds__(1024) void k_bwd(BwdArgs a) {
     extern __shared__ double4 red4[];
-    __shared__ int slot;
-    for_each_item(q, a.ntiles, &slot, [&](int item) {
-        if (PASS == 1) bwd_roots_tile<PROJ>(a, a.tiles[item], red4);
-        else bwd_poles_tile<PROJ>(a, a.tiles[item], red4);
-    });
+    if (PASS == 1) bwd_roots_tile<PROJ>(a, a.tiles[blockIdx.x], red4);
+    else bwd_poles_tile<PROJ>(a, a.tiles[blockIdx.x], red4);
 }
 
 // g_rho[p] = sum_k alpha_k / rho_p^2, fixed-order block reduction
@@ -179,18 +176,17 @@ __global__ __launch_bounds__(256) void k_bwd_rho(BwdArgs a, int prob_first) {
     }
 }
 
-hipError_t launch_backward(const BwdArgs &a, int split, int prob_first, int nprob, Queue *q1,
-                           Queue *q2, int grid, hipStream_t s) {
+hipError_t launch_backward(const BwdArgs &a, int split, int prob_first, int nprob, hipStream_t s) {
     if (a.ntiles <= 0) return hipSuccess;
     const bool proj = a.g_proj != nullptr;
-    const dim3 g1(q1 ? grid : a.ntiles), g2(q2 ? grid : a.ntiles), blk(WAVE * split);
+    const dim3 g(a.ntiles), blk(WAVE * split);
     const size_t lds = split > 1 ? 2 * sizeof(double4) * WAVE * split : 0;
     if (proj) {
-        SDC_LAUNCH(KID_BWD, (k_bwd<true, 1>), g1, blk, lds, s, a, q1);
-        SDC_LAUNCH(KID_BWD, (k_bwd<true, 2>), g2, blk, lds, s, a, q2);
+        SDC_LAUNCH(KID_BWD, (k_bwd<true, 1>), g, blk, lds, s, a);
+        SDC_LAUNCH(KID_BWD, (k_bwd<true, 2>), g, blk, lds, s, a);
     } else {
-        SDC_LAUNCH(KID_BWD, (k_bwd<false, 1>), g1, blk, lds, s, a, q1);
-        SDC_LAUNCH(KID_BWD, (k_bwd<false, 2>), g2, blk, lds, s, a, q2);
+        SDC_LAUNCH(KID_BWD, (k_bwd<false, 1>), g, blk, lds, s, a);
+        SDC_LAUNCH(KID_BWD, (k_bwd<false, 2>), g, blk, lds, s, a);
     }
     SDC_LAUNCH(KID_BWD_RHO, k_bwd_rho, dim3(nprob), dim3(256), 0, s, a, prob_first);
     return hipGetLastError();

@@ -23,12 +23,6 @@ struct Tile {
     int32_t row0;  // first local row of the tile
 };
 
-// self-resetting work queue of a persistent launch (two counters, zero between launches)
-struct Queue {
-    unsigned int next;
-    unsigned int done;
-};
-
 // ----------------------------------------------------------------------------------
 // device helpers
 // ----------------------------------------------------------------------------------
@@ -116,43 +110,12 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// Pull the next work item from a persistent queue (called by whole wavefront-0 of a WG
-// and broadcast through LDS).  Returns -1 when the queue is drained.
-__device__ __forceinline__ int queue_pull(Queue *q, int nitems, int *slot) {
-    if (threadIdx.x == 0) *slot = (int)atomicAdd(&q->next, 1u);
-    __syncthreads();
-    int it = __builtin_amdgcn_readfirstlane(*slot);
-    __syncthreads();
-    return it < nitems ? it : -1;
-}
-
-// The last workgroup to leave resets the counters, so the next launch (or graph replay)
-// starts from zero without a memset.
-__device__ __forceinline__ void queue_leave(Queue *q) {
-    if (threadIdx.x == 0) {
-        __threadfence();
-        unsigned prev = atomicAdd(&q->done, 1u);
-        if (prev == gridDim.x - 1) {
-            atomicExch(&q->next, 0u);
-            atomicExch(&q->done, 0u);
-            __threadfence();
-        }
-    }
-}
-
-// The work items of a launch with one call site of the body: persistent (q != nullptr)
-// workgroups pull items until the queue runs dry and then leave it; otherwise workgroup b
-// takes item b.  One inlined copy of a large body (rather than one per branch) keeps a
-// kernel's code within the instruction cache.
-template <class Body>
-__device__ __forceinline__ void for_each_item(Queue *q, int nitems, int *slot, Body &&body) {
-    int item = q ? queue_pull(q, nitems, slot) : ((int)blockIdx.x < nitems ? (int)blockIdx.x : -1);
-    while (item >= 0) {
-        body(item);
-        item = q ? queue_pull(q, nitems, slot) : -1;
-    }
-    if (q) queue_leave(q);
-}
+// Work items: a launch has one workgroup per item, item blockIdx.x of a list that holds the
+// longest problems first.  The hardware starts workgroups in that order as others end, which
+// balances the load; a grid of resident workgroups pulling items from an atomic counter did the
+// same at the price of the counter (two atomics and a device-scope fence a workgroup on one
+// address: a launch of 1024 items spent 18 to 27 us on it -- FMM evaluation of the HSS
+// conquer 79 -> 51 us, its Loewner products 56 -> 30 us, 512 small problems 187 -> 103 us a pass).
 
 // ----------------------------------------------------------------------------------
 // optional per-kernel timing (trace.cpp): a scope records HIP events around one launch
@@ -211,20 +174,14 @@ struct superdc_ctx {
     // grow-only workspace buffers
     void *ws[kNumWs] = {nullptr};
     size_t ws_cap[kNumWs] = {0};
-    sdc::Queue *queues = nullptr;  // kNumQueues counters, zeroed at creation
     int fmm_crossover = 1024;      // automatic method: FMM for problems at least this large (measured)
-};
-
-enum QueueSlot {
-    Q_SECULAR = 0, Q_LOEWNER, Q_BNORM, Q_APPLY, Q_BWD1, Q_BWD2, Q_VALIDATE, Q_SECULAR_FMM,
-    Q_FMMV, kNumQueues
 };
 
 namespace sdc {
 struct FmmPlan;
 }
 
-// Work items of one cut length: longest problems first (persistent launches) and in
+// Work items of one cut length: longest problems first (batched launches) and in
 // problem order (plain launches; problem p owns nat[begin[p] .. begin[p+1])).
 struct TileList {
     sdc::Tile *lpt = nullptr;
@@ -248,7 +205,7 @@ struct superdc_batch {
     int64_t *off_d = nullptr;
     std::vector<int> order;             // problems, longest first
     TileList lists[4];                  // cut lengths 64, 128, 256, 512
-    // chosen launch shapes (heuristic, or set by the autotuner): persistent launches
+    // chosen launch shapes (heuristic, or set by the autotuner): batched launches
     LaunchShape sec, vec, app, bwd;
     int fmm_ssplit = 0;                 // FMM solver: wavefronts per work item (0: heuristic)
     bool tuned = false;
@@ -265,8 +222,6 @@ namespace sdc {
 const TileList *tile_list(superdc_batch *b, int chunk);
 // SUPERDC_OK or SUPERDC_EINVAL for an options struct
 int opts_check(const superdc_opts *o);
-// grid of a persistent launch: per_cu workgroups per CU, at most one per work item
-int persistent_grid(const superdc_ctx *ctx, int ntiles, int per_cu);
 // problems of at least this many roots use the triangular FMM under these options
 int fmm_crossover_of(const superdc_ctx *ctx, const superdc_opts &o);
 // launch shape of the plain (one launch per problem) direct solve of an n-root problem
@@ -319,7 +274,7 @@ struct SolveArgs {
 // ([nprob][vsplit], indexed by problem) and are added in slice order by a second launch
 hipError_t launch_validate(const SolveArgs &a, int prob_first, int nprob, int max_n, hipStream_t s,
                            int vsplit = 1, double *vsum = nullptr, int32_t *vst = nullptr);
-hipError_t launch_secular(const SolveArgs &a, int split, Queue *q, int grid, hipStream_t s);
+hipError_t launch_secular(const SolveArgs &a, int split, hipStream_t s);
 
 struct VecArgs {
     const int64_t *off;
@@ -332,10 +287,10 @@ struct VecArgs {
     double *zhat, *bnorm;
 };
 // pack = false: the (d_K, eta) pairs were packed already (launch_pack_ke)
-hipError_t launch_loewner(const VecArgs &a, int split, Queue *q, int grid, hipStream_t s,
+hipError_t launch_loewner(const VecArgs &a, int split, hipStream_t s,
                           bool pack = true);
 hipError_t launch_pack_ke(const VecArgs &a, hipStream_t s);
-hipError_t launch_bnorm(const VecArgs &a, int split, Queue *q, int grid, hipStream_t s);
+hipError_t launch_bnorm(const VecArgs &a, int split, hipStream_t s);
 
 struct ApplyArgs {
     const int64_t *off;
@@ -354,8 +309,7 @@ struct ApplyArgs {
     unsigned long long *work;  // kernel timing on: algorithmic flops of the launch, (2m + 3)
                                // per Cauchy entry plus 2m per output row (set by launch_apply)
 };
-// persistent (q != nullptr) launches size themselves from num_cu
-hipError_t launch_apply(const ApplyArgs &a, int use_mfma, Queue *q, int num_cu, hipStream_t s);
+hipError_t launch_apply(const ApplyArgs &a, int use_mfma, int num_cu, hipStream_t s);
 
 struct BwdArgs {
     const int64_t *off;
@@ -370,8 +324,7 @@ struct BwdArgs {
     double4 *rk;    // workspace (d_K, eta, alpha, beta) per root
     double *gk;     // workspace gamma per root
 };
-hipError_t launch_backward(const BwdArgs &a, int split, int prob_first, int nprob, Queue *q1,
-                           Queue *q2, int grid, hipStream_t s);
+hipError_t launch_backward(const BwdArgs &a, int split, int prob_first, int nprob, hipStream_t s);
 
 // deflation (deflate.hip)
 hipError_t launch_deflate(const int64_t *off, int nprob, const double *d, const double *z,

@@ -216,17 +216,16 @@ hipError_t launch_fmmv_pos(const FmmvPackArgs &a, hipStream_t s);
 // Loewner far field: (d_j, delta_j) pairs and the last roots' offsets, then the products
 hipError_t launch_fmml_pack(const FmmvPackArgs &a, hipStream_t s);
 hipError_t launch_loewner_fmm(const VecArgs &a, const FmmArgs &f, const FmmlArgs &l, int split,
-                              Queue *q, int grid, hipStream_t s);
+                              hipStream_t s);
 
 
 hipError_t launch_fmm_build(const FmmArgs &f, hipStream_t s);
 // interaction lists only (no secular equivalent sources)
 hipError_t launch_fmm_lists(const FmmArgs &f, hipStream_t s);
 hipError_t launch_fmmv_sources(const FmmArgs &f, const FmmVec &v, hipStream_t s);
-// grid: persistent (q != nullptr) launches size themselves from num_cu
 hipError_t launch_fmmv_eval(const SolveArgs &items, const FmmArgs &f, const FmmVec &v, int split,
-                            Queue *q, int num_cu, hipStream_t s);
-hipError_t launch_secular_fmm(const SolveArgs &a, const FmmArgs &f, int split, Queue *q,
-                              int grid, hipStream_t s);
+                            int num_cu, hipStream_t s);
+hipError_t launch_secular_fmm(const SolveArgs &a, const FmmArgs &f, int split,
+                              hipStream_t s);
 
 }  // namespace sdc

@@ -408,7 +408,6 @@ __device__ void fmmv_item(const SolveArgs &it, const FmmArgs &f, const FmmVec &v
         }
         // far boxes of both sides, lambda-form, one Newton step
         const double2 iv = fv_interval(v, base, n, t.row0, min(t.row0 + WAVE, n) - 1);
-        __syncthreads();  // the previous item's reads of the lists are done
         if (wv == 0) {
             const int k = fv_split_far(f, v, L, nl, nr, iv, v.expand != 0, sh.fbox);
             if (lane == 0) sh.nexp = k;
@@ -514,13 +513,10 @@ __device__ void fmmv_item(const SolveArgs &it, const FmmArgs &f, const FmmVec &v
 
 // blockDim.x = 64 S; dynamic LDS: (S - 1) NC doubles per lane
 template <int KERN, int NC>
-__global__ __launch_bounds__(512) void k_fmmv_eval(SolveArgs it, FmmArgs f, FmmVec v, Queue *q) {
+__global__ __launch_bounds__(512) void k_fmmv_eval(SolveArgs it, FmmArgs f, FmmVec v) {
     extern __shared__ double red[];
     __shared__ FvEvalShared<NC> sh;
-    __shared__ int slot;
-    for_each_item(q, it.ntiles, &slot, [&](int item) {
-        fmmv_item<KERN, NC>(it, f, v, it.tiles[item], sh, red);
-    });
+    fmmv_item<KERN, NC>(it, f, v, it.tiles[blockIdx.x], sh, red);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -672,7 +668,6 @@ __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmV
     const int nn = wave_uniform(f.cnt[3 * (int64_t)L]);
     const bool direct = nn < 0;  // overflowed lists: every source, 64 at a time
     double2 iv = fv_interval(v, base, n, o0, min(o0 + FV_K, n) - 1);
-    __syncthreads();  // the previous item's reads of the tables and buffers are done
     if (!direct) {
         if (wave == 0) {  // a lane per near range, its chunks after those of the lanes below
             const int nl = wave_uniform(f.cnt[3 * (int64_t)L + 1]);
@@ -898,18 +893,15 @@ __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmV
 
 template <int TRANS, bool FB, int TEAMS>
 __global__ __launch_bounds__(256 * TEAMS, 4) void k_fmmv_eval_mfma(SolveArgs it, FmmArgs f,
-                                                                   FmmVec v, Queue *q) {
+                                                                   FmmVec v) {
     __shared__ FvShared<TEAMS> sh;
-    __shared__ int slot;
     if (TEAMS == 1 && threadIdx.x < FMM_P) {
         sh.node[threadIdx.x] = FV_NODE[threadIdx.x];
         sh.bary[threadIdx.x] = FV_BARY[threadIdx.x];
     }
     // the column groups of a tile are neighbouring items: they read the same lists and poles
     const int ng = (v.m + FMMV_MAX_M - 1) / FMMV_MAX_M;
-    for_each_item(q, it.ntiles * ng, &slot, [&](int item) {
-        fmmv_item_mfma<TRANS, FB, TEAMS>(it, f, v, it.tiles[item / ng], item % ng, sh);
-    });
+    fmmv_item_mfma<TRANS, FB, TEAMS>(it, f, v, it.tiles[blockIdx.x / ng], blockIdx.x % ng, sh);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1101,7 +1093,7 @@ hipError_t launch_fmmv_sources(const FmmArgs &f, const FmmVec &v, hipStream_t s)
 }
 
 hipError_t launch_fmmv_eval(const SolveArgs &it, const FmmArgs &f, const FmmVec &v0, int split,
-                            Queue *q, int num_cu, hipStream_t s) {
+                            int num_cu, hipStream_t s) {
     if (it.ntiles <= 0) return hipSuccess;
     FmmVec v = v0;
     // the MFMA for a dense enough block of columns, and for every sum over the roots
@@ -1110,9 +1102,9 @@ hipError_t launch_fmmv_eval(const SolveArgs &it, const FmmArgs &f, const FmmVec 
     if (mfma) {
         const int items = it.ntiles * ((v.m + FMMV_MAX_M - 1) / FMMV_MAX_M);
         const int teams = items >= FV_EXPAND_PER_CU * num_cu ? 1 : items >= num_cu ? 2 : 4;
-        const dim3 g(q ? min(items, num_cu * 4 / teams) : items);
+        const dim3 g(items);
 #define SDC_FV(T, FB, K) \
-    SDC_LAUNCH(KID_FMMV_EVAL_MFMA, (k_fmmv_eval_mfma<T, FB, K>), g, dim3(256 * K), 0, s, it, f, v, q)
+    SDC_LAUNCH(KID_FMMV_EVAL_MFMA, (k_fmmv_eval_mfma<T, FB, K>), g, dim3(256 * K), 0, s, it, f, v)
 #define SDC_FV_TEAMS(T, FB)              \
     {                                    \
         if (teams == 1) SDC_FV(T, FB, 1);     \
@@ -1128,13 +1120,13 @@ hipError_t launch_fmmv_eval(const SolveArgs &it, const FmmArgs &f, const FmmVec 
     }
     if (v.trans == 0 || v.m >= 4) return hipErrorInvalidValue;
     v.expand = it.ntiles >= FV_EXPAND_PER_CU * num_cu;
-    const dim3 g(q ? min(it.ntiles, num_cu * max(1, 32 / split)) : it.ntiles), blk(WAVE * split);
+    const dim3 g(it.ntiles), blk(WAVE * split);
     if (v.kern == 2) {
         const size_t lds = sizeof(double) * WAVE * (split - 1) * 1;
-        SDC_LAUNCH(KID_FMMV_EVAL, (k_fmmv_eval<2, 1>), g, blk, lds, s, it, f, v, q);
+        SDC_LAUNCH(KID_FMMV_EVAL, (k_fmmv_eval<2, 1>), g, blk, lds, s, it, f, v);
     } else {
         const size_t lds = sizeof(double) * WAVE * (split - 1) * 3;
-        SDC_LAUNCH(KID_FMMV_EVAL, (k_fmmv_eval<1, 3>), g, blk, lds, s, it, f, v, q);
+        SDC_LAUNCH(KID_FMMV_EVAL, (k_fmmv_eval<1, 3>), g, blk, lds, s, it, f, v);
     }
     return hipGetLastError();
 }

@@ -88,7 +88,7 @@ extern "C" int superdc_secular_solve_noalloc(superdc_ctx *ctx, const superdc_bat
     a.hybrid = o.interp;
     a.work = nullptr;
     // every buffer above is written before it is read within the call, so nothing needs
-    // clearing; the work queues in the context reset themselves at the end of each launch
+    // clearing
     hipError_t e = hipSuccess;
     if (o.persistent) {
         const LaunchShape sh = b->sec;
@@ -100,8 +100,7 @@ extern "C" int superdc_secular_solve_noalloc(superdc_ctx *ctx, const superdc_bat
         a.chunk = sh.chunk;
         e = launch_validate(a, 0, b->nprob, b->max_n, s);
         if (e == hipSuccess)
-            e = launch_secular(a, sh.split, ctx->queues + Q_SECULAR,
-                               persistent_grid(ctx, a.ntiles, std::max(1, 32 / sh.split)), s);
+            e = launch_secular(a, sh.split, s);
     } else {
         // one launch per problem on 64-root chunks, as superdc_secular_solve's plain mode
         const TileList &L = b->lists[0];
@@ -118,7 +117,7 @@ extern "C" int superdc_secular_solve_noalloc(superdc_ctx *ctx, const superdc_bat
                 const LaunchShape sh = plain_shape(ctx, np);
                 S = sh.split;
             }
-            e = launch_secular(a, S, nullptr, 0, s);
+            e = launch_secular(a, S, s);
         }
     }
     if (e != hipSuccess) return e == hipErrorOutOfMemory ? SUPERDC_ENOMEM : SUPERDC_EHIP;

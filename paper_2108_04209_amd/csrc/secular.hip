@@ -844,36 +844,29 @@ __device__ void secular_chunk(const SolveArgs &a, Tile t, double *red, const Fmm
 // blockDim.x = 64 S (S = 1, 2, 4, 8, 16); dynamic LDS: 32 S bytes per lane (S > 1).
 // UNSH: the unshifted ablation, a kernel of its own so that its code stays out of the other
 template <bool UNSH>
-__global__ __launch_bounds__(1024) void k_secular(SolveArgs a, Queue *q) {
+__global__ __launch_bounds__(1024) void k_secular(SolveArgs a) {
     extern __shared__ double red[];
-    __shared__ int slot;
-    for_each_item(q, a.ntiles, &slot, [&](int item) {
-        secular_chunk<false, UNSH>(a, a.tiles[item], red, nullptr);
-    });
+    secular_chunk<false, UNSH>(a, a.tiles[blockIdx.x], red, nullptr);
 }
 
 // FMM problems: one work item per 64-root piece of a target leaf; blockDim.x = 64 S with
 // the same dynamic LDS as k_secular
 template <bool UNSH>
-__global__ __launch_bounds__(512) void k_secular_fmm(SolveArgs a, FmmArgs f, Queue *q) {
+__global__ __launch_bounds__(512) void k_secular_fmm(SolveArgs a, FmmArgs f) {
     extern __shared__ double red[];
-    __shared__ int slot;
-    for_each_item(q, a.ntiles, &slot, [&](int item) {
-        secular_chunk<true, UNSH>(a, a.tiles[item], red, &f);
-    });
+    secular_chunk<true, UNSH>(a, a.tiles[blockIdx.x], red, &f);
 }
 
-hipError_t launch_secular_fmm(const SolveArgs &a, const FmmArgs &f, int split, Queue *q,
-                              int grid, hipStream_t s) {
+hipError_t launch_secular_fmm(const SolveArgs &a, const FmmArgs &f, int split, hipStream_t s) {
     if (a.ntiles <= 0) return hipSuccess;
     if (split < 1 || split > 8 || (split & (split - 1))) return hipErrorInvalidValue;
     const size_t lds = split > 1 ? sizeof(double4) * WAVE * split : 0;
     if (a.unshifted)
-        SDC_LAUNCH(KID_SECULAR_FMM, k_secular_fmm<true>, dim3(q ? grid : a.ntiles),
-                   dim3(WAVE * split), lds, s, a, f, q);
+        SDC_LAUNCH(KID_SECULAR_FMM, k_secular_fmm<true>, dim3(a.ntiles),
+                   dim3(WAVE * split), lds, s, a, f);
     else
-        SDC_LAUNCH(KID_SECULAR_FMM, k_secular_fmm<false>, dim3(q ? grid : a.ntiles),
-                   dim3(WAVE * split), lds, s, a, f, q);
+        SDC_LAUNCH(KID_SECULAR_FMM, k_secular_fmm<false>, dim3(a.ntiles),
+                   dim3(WAVE * split), lds, s, a, f);
     return hipGetLastError();
 }
 
@@ -891,15 +884,15 @@ hipError_t launch_validate(const SolveArgs &a, int prob_first, int nprob, int ma
     return hipGetLastError();
 }
 
-hipError_t launch_secular(const SolveArgs &a, int split, Queue *q, int grid, hipStream_t s) {
+hipError_t launch_secular(const SolveArgs &a, int split, hipStream_t s) {
     if (a.ntiles <= 0) return hipSuccess;
     const size_t lds = split > 1 ? sizeof(double4) * WAVE * split : 0;
     if (a.unshifted)
-        SDC_LAUNCH(KID_SECULAR, k_secular<true>, dim3(q ? grid : a.ntiles), dim3(WAVE * split),
-                   lds, s, a, q);
+        SDC_LAUNCH(KID_SECULAR, k_secular<true>, dim3(a.ntiles), dim3(WAVE * split),
+                   lds, s, a);
     else
-        SDC_LAUNCH(KID_SECULAR, k_secular<false>, dim3(q ? grid : a.ntiles), dim3(WAVE * split),
-                   lds, s, a, q);
+        SDC_LAUNCH(KID_SECULAR, k_secular<false>, dim3(a.ntiles), dim3(WAVE * split),
+                   lds, s, a);
     return hipGetLastError();
 }
 

@@ -271,7 +271,6 @@ __device__ void loewner_fmm_tile(const VecArgs &a, const FmmArgs &f, const FmmlA
             loewner_range<false, true>(ke, dd, max(lo, t1), hi, ii, di, num, den, E, sg);
         }
     } else {
-        __syncthreads();  // the previous item's reads of the staging are done
         // the near ranges' starts in their concatenation (a scan by the first wavefront)
         if (wv == 0) {
             int lo = 0, len = 0;
@@ -468,29 +467,20 @@ __device__ void bnorm_tile(const VecArgs &a, Tile t, double4 *red) {
 }
 
 // blockDim.x = 64 S; dynamic LDS: one double4 per thread when S > 1
-__global__ __launch_bounds__(1024) void k_loewner(VecArgs a, Queue *q) {
+__global__ __launch_bounds__(1024) void k_loewner(VecArgs a) {
     extern __shared__ double4 red4[];
-    __shared__ int slot;
-    for_each_item(q, a.ntiles, &slot, [&](int item) {
-        loewner_tile(a, a.tiles[item], red4);
-    });
+    loewner_tile(a, a.tiles[blockIdx.x], red4);
 }
 
-__global__ __launch_bounds__(1024) void k_bnorm(VecArgs a, Queue *q) {
+__global__ __launch_bounds__(1024) void k_bnorm(VecArgs a) {
     extern __shared__ double4 red4[];
-    __shared__ int slot;
-    for_each_item(q, a.ntiles, &slot, [&](int item) {
-        bnorm_tile(a, a.tiles[item], red4);
-    });
+    bnorm_tile(a, a.tiles[blockIdx.x], red4);
 }
 
-__global__ __launch_bounds__(1024) void k_loewner_fmm(VecArgs a, FmmArgs f, FmmlArgs l, Queue *q) {
+__global__ __launch_bounds__(1024) void k_loewner_fmm(VecArgs a, FmmArgs f, FmmlArgs l) {
     extern __shared__ double4 red4[];
     __shared__ LwShared sh;
-    __shared__ int slot;
-    for_each_item(q, a.ntiles, &slot, [&](int item) {
-        loewner_fmm_tile(a, f, l, a.tiles[item], red4, sh);
-    });
+    loewner_fmm_tile(a, f, l, a.tiles[blockIdx.x], red4, sh);
 }
 
 hipError_t launch_pack_ke(const VecArgs &a, hipStream_t s) {
@@ -500,27 +490,27 @@ hipError_t launch_pack_ke(const VecArgs &a, hipStream_t s) {
 }
 
 hipError_t launch_loewner_fmm(const VecArgs &a, const FmmArgs &f, const FmmlArgs &l, int split,
-                              Queue *q, int grid, hipStream_t s) {
+                              hipStream_t s) {
     if (a.ntiles <= 0) return hipSuccess;
     const size_t lds = split > 1 ? sizeof(double4) * WAVE * split : 0;
-    SDC_LAUNCH(KID_LOEWNER_FMM, k_loewner_fmm, dim3(q ? grid : a.ntiles), dim3(WAVE * split), lds,
-               s, a, f, l, q);
+    SDC_LAUNCH(KID_LOEWNER_FMM, k_loewner_fmm, dim3(a.ntiles), dim3(WAVE * split), lds,
+               s, a, f, l);
     return hipGetLastError();
 }
 
-hipError_t launch_loewner(const VecArgs &a, int split, Queue *q, int grid, hipStream_t s,
+hipError_t launch_loewner(const VecArgs &a, int split, hipStream_t s,
                           bool pack) {
     if (a.ntiles <= 0) return hipSuccess;
     const size_t lds = split > 1 ? sizeof(double4) * WAVE * split : 0;
     if (pack) SDC_LAUNCH(KID_PACK, k_pack_ke, dim3(a.ntiles), dim3(64), 0, s, a);
-    SDC_LAUNCH(KID_LOEWNER, k_loewner, dim3(q ? grid : a.ntiles), dim3(WAVE * split), lds, s, a, q);
+    SDC_LAUNCH(KID_LOEWNER, k_loewner, dim3(a.ntiles), dim3(WAVE * split), lds, s, a);
     return hipGetLastError();
 }
 
-hipError_t launch_bnorm(const VecArgs &a, int split, Queue *q, int grid, hipStream_t s) {
+hipError_t launch_bnorm(const VecArgs &a, int split, hipStream_t s) {
     if (a.ntiles <= 0) return hipSuccess;
     const size_t lds = split > 1 ? sizeof(double4) * WAVE * split : 0;
-    SDC_LAUNCH(KID_BNORM, k_bnorm, dim3(q ? grid : a.ntiles), dim3(WAVE * split), lds, s, a, q);
+    SDC_LAUNCH(KID_BNORM, k_bnorm, dim3(a.ntiles), dim3(WAVE * split), lds, s, a);
     return hipGetLastError();
 }
 
