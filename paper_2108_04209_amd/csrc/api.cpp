@@ -61,8 +61,14 @@ int fmm_crossover_of(const superdc_ctx *ctx, const superdc_opts &o) {
                                 : ctx->fmm_crossover;
 }
 
+int chunk_slot(int chunk) {
+    for (int i = 0; i < kNumChunks; ++i)
+        if (chunk == MIN_CHUNK << i) return i;
+    return -1;
+}
+
 const TileList *tile_list(superdc_batch *b, int chunk) {
-    int slot = chunk == 64 ? 0 : chunk == 128 ? 1 : chunk == 256 ? 2 : chunk == 512 ? 3 : -1;
+    const int slot = chunk_slot(chunk);
     if (slot < 0) return nullptr;
     TileList &l = b->lists[slot];
     if (l.nat) return &l;
@@ -97,20 +103,23 @@ const TileList *tile_list(superdc_batch *b, int chunk) {
 }  // namespace sdc
 
 namespace {
+// fewest poles each wavefront of a split sums: in the scalar-fetch solver, whose wavefronts all
+// repeat the step, and in the Loewner, b and adjoint kernels, which only add up (16 against 128
+// poles: 512 problems of 1 to 300 roots 37 -> 19 us for both, a conquer step of 1024 roots
+// 14.6 -> 8.0 us, the adjoint of 16 small problems 25 -> 9 us)
+constexpr int MIN_SPLIT_POLES = 128;
+constexpr int MIN_VEC_POLES = 16;
+
 // Launch shape for problems of the given sizes: the fewest wavefronts per work item
 // (split S, a power of two <= 16) and the longest chunk (<= max_chunk) whose work items
-// still give every CU 16 wavefronts, keeping >= 256 summed entries per wavefront.
-// fewest poles each wavefront of a split sums
-#ifndef SDC_MIN_SPLIT_POLES
-#define SDC_MIN_SPLIT_POLES 128
-#endif
-
-LaunchShape shape_for(const superdc_ctx *ctx, const int64_t *sizes, int count, int max_chunk) {
+// still give every CU 16 wavefronts, keeping >= min_poles summed entries per wavefront.
+LaunchShape shape_for(const superdc_ctx *ctx, const int64_t *sizes, int count, int max_chunk,
+                      int min_poles) {
     const long target = (long)ctx->num_cu * 16;
     int64_t nmax = 0;
     for (int i = 0; i < count; ++i) nmax = std::max(nmax, sizes[i]);
     for (int S = 1; S <= 16; S *= 2) {
-        if (S > 1 && nmax / S < SDC_MIN_SPLIT_POLES) break;
+        if (S > 1 && nmax / S < min_poles) break;
         for (int C = max_chunk; C >= TILE; C /= 2) {
             long wg = 0;
             for (int i = 0; i < count; ++i) wg += (sizes[i] + C - 1) / C;
@@ -118,21 +127,55 @@ LaunchShape shape_for(const superdc_ctx *ctx, const int64_t *sizes, int count, i
         }
     }
     int S = 1;
-    while (S < 16 && nmax / (2 * S) >= SDC_MIN_SPLIT_POLES) S *= 2;
+    while (S < 16 && nmax / (2 * S) >= min_poles) S *= 2;
     return LaunchShape{TILE, S};
 }
 
 }  // namespace
 
 namespace sdc {
-LaunchShape plain_shape(const superdc_ctx *ctx, int64_t n) { return shape_for(ctx, &n, 1, TILE); }
+LaunchShape plain_shape(const superdc_ctx *ctx, int64_t n) {
+    return shape_for(ctx, &n, 1, TILE, MIN_SPLIT_POLES);
+}
 }  // namespace sdc
 
 namespace {
-LaunchShape choose_shape(const superdc_ctx *ctx, const superdc_batch *b, int max_chunk) {
+LaunchShape choose_shape(const superdc_ctx *ctx, const superdc_batch *b, int max_chunk,
+                         int min_poles) {
     std::vector<int64_t> sizes(b->nprob);
     for (int p = 0; p < b->nprob; ++p) sizes[p] = b->off_h[p + 1] - b->off_h[p];
-    return shape_for(ctx, sizes.data(), b->nprob, max_chunk);
+    return shape_for(ctx, sizes.data(), b->nprob, max_chunk, min_poles);
+}
+
+// Roots per work item of the direct solver in LDS for the problems of fewer than `below` roots,
+// from the lanes g that hold a root at first.  Measured over batches of 1 to 4096 problems and
+// 64 to 4096 roots (g = 1 .. 64), a launch takes about the batch's work on all SIMDs,
+// 4.8 passes a root of (52 n + 1100 g) / 64 cycles (its pairs, and the step that every lane of
+// its team repeats; 10 % more at g = 1, where a wavefront waits for the slowest of 64 roots), and
+// 0.6 of the longest root, 9 passes of 30 n / g + 4400 cycles.  The g of the smallest sum is
+// taken: few large problems spread a root over many lanes (one of 1000 roots: 140 us at g = 1, 20
+// at g = 64), many small ones keep it to two (512 of 128 roots: 34 us at g = 2, 183 at 64).
+int lds_chunk(const superdc_batch *b, int64_t below) {
+    double roots = 0.0, pairs = 0.0, nmax = 0.0;
+    for (int p = 0; p < b->nprob; ++p) {
+        const double n = (double)(b->off_h[p + 1] - b->off_h[p]);
+        if (n >= (double)below) continue;
+        roots += n;
+        pairs += n * n;
+        nmax = std::max(nmax, n);
+    }
+    const double simds = 4.0 * b->ctx->num_cu;
+    int best = 1;
+    double cost = 1e300;
+    for (int g = 1; g <= WAVE; g *= 2) {
+        const double t = 4.8 * (52.0 * pairs + 1100.0 * g * roots) / 64.0 / simds * (1.0 + 0.1 / g) +
+                         0.6 * 9.0 * (30.0 * nmax / g + 4400.0);
+        if (t < cost) {
+            cost = t;
+            best = g;
+        }
+    }
+    return secl_waves((int)std::min(nmax, (double)SECL_MAX_N)) * WAVE / best;
 }
 
 // far-field separation: a box is far from a target leaf when the gap is >= FMM_SEP times
@@ -143,8 +186,6 @@ LaunchShape choose_shape(const superdc_ctx *ctx, const superdc_batch *b, int max
 // test's tolerance is n eps (1 + |psi| + |phi|) >= 1.1e-13 relative for the FMM's n >= 1024)
 constexpr double FMM_SEP = 1.5;
 constexpr double FMM_SEP_LOC = 0.75;
-
-int fmm_dir_slot(int chunk) { return chunk == 64 ? 0 : chunk == 128 ? 1 : chunk == 256 ? 2 : 3; }
 
 void fmm_free(FmmPlan *fp) {
     if (!fp) return;
@@ -180,7 +221,10 @@ FmmPlan *fmm_plan(superdc_batch *b, int leaf, int crossover) {
     fp->leaf_off_h.push_back(0);
     for (int p = 0; p < b->nprob; ++p) {
         const int64_t n = b->off_h[p + 1] - b->off_h[p];
-        if (n < crossover || n < 2 * leaf) continue;
+        if (n < crossover || n < 2 * leaf) {
+            fp->max_dir = std::max(fp->max_dir, (int)n);
+            continue;
+        }
         const int q = fp->nfmm++;
         fp->fmm_prob_h.push_back(p);
         fp->fmm_of_h[p] = q;
@@ -194,6 +238,7 @@ FmmPlan *fmm_plan(superdc_batch *b, int leaf, int crossover) {
         box_fmm.insert(box_fmm.end(), nb, q);
         leaf_fmm.insert(leaf_fmm.end(), nl, q);
     }
+    fp->lds_chunk = lds_chunk(b, (int64_t)fp->max_dir + 1);
     fp->nboxes = fp->box_off_h.back();
     fp->nleaves = fp->leaf_off_h.back();
     // the boxes the source kernels visit, so that their grids hold no workgroup without a
@@ -313,10 +358,10 @@ FmmPlan *fmm_plan(superdc_batch *b, int leaf, int crossover) {
               fmm_upload(fp, &fp->t_used, std::vector<int32_t>(), fp->nboxes) &&
               fmm_upload(fp, &fp->t_loc_ab, std::vector<double2>(), (size_t)fp->nleaves);
     // direct chunks of the other problems, for each cut length
-    fp->dir_lpt.assign(4, nullptr);
-    fp->dir_count.assign(4, 0);
-    for (int slot = 0; slot < 4 && ok; ++slot) {
-        const int C = TILE << slot;
+    fp->dir_lpt.assign(kNumChunks, nullptr);
+    fp->dir_count.assign(kNumChunks, 0);
+    for (int slot = 0; slot < kNumChunks && ok; ++slot) {
+        const int C = MIN_CHUNK << slot;
         std::vector<Tile> v;
         for (int p : b->order) {
             if (fp->fmm_of_h[p] >= 0) continue;
@@ -590,8 +635,8 @@ int loewner_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const
     if (o.persistent) {
         const int S = b->vec.split;
         if (fp) {
-            a.tiles = fp->dir_lpt[0];
-            a.ntiles = fp->dir_count[0];
+            a.tiles = fp->dir_lpt[chunk_slot(TILE)];
+            a.ntiles = fp->dir_count[chunk_slot(TILE)];
         }
         SDC_HIP(launch_loewner(a, S, s, false));
         if (fp) {
@@ -606,7 +651,7 @@ int loewner_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const
     } else {
         for (int p = 0; p < b->nprob; ++p) {
             const int64_t np = b->off_h[p + 1] - b->off_h[p];
-            const int S = shape_for(ctx, &np, 1, TILE).split;
+            const int S = shape_for(ctx, &np, 1, TILE, MIN_VEC_POLES).split;
             if (fp && fp->fmm_of_h[p] >= 0) {
                 const int q = fp->fmm_of_h[p];
                 VecArgs af = a;
@@ -671,8 +716,8 @@ int apply_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const d
     FmmPlan *fp = fmm_for(ctx, bm, o, rc);
     if (rc) return rc;
     if (o.persistent) {
-        a.tiles = fp ? fp->dir_lpt[0] : L->lpt;
-        a.ntiles = fp ? fp->dir_count[0] : L->count;
+        a.tiles = fp ? fp->dir_lpt[chunk_slot(TILE)] : L->lpt;
+        a.ntiles = fp ? fp->dir_count[chunk_slot(TILE)] : L->count;
         SDC_HIP(launch_apply(a, use_mfma, ctx->num_cu, s));
     } else {
         for (int p = 0; p < b->nprob; ++p) {
@@ -831,14 +876,15 @@ int superdc_batch_create(superdc_ctx *ctx, int32_t nprob, const int64_t *off_hos
         return hip_fail(e);
     }
     // launch shapes for the batched launches (the autotuner may replace them)
-    b->sec = choose_shape(ctx, b, SEC_CHUNK);
+    b->sec = choose_shape(ctx, b, SEC_CHUNK, MIN_SPLIT_POLES);
+    b->lds_chunk = lds_chunk(b, (int64_t)1 << 31);
     // the solver's tile list for that shape is built now, so that a later solve (the
     // allocation-free entry point in particular) finds it ready
-    if (!tile_list(b, b->sec.chunk)) {
+    if (!tile_list(b, b->sec.chunk) || !tile_list(b, b->lds_chunk)) {
         superdc_batch_destroy(b);
         return hip_fail(hipErrorOutOfMemory);
     }
-    b->vec = choose_shape(ctx, b, TILE);
+    b->vec = choose_shape(ctx, b, TILE, MIN_VEC_POLES);
     b->bwd = b->vec;
     b->app = LaunchShape{TILE, 1};
     *out = b;
@@ -906,20 +952,24 @@ int superdc_secular_solve(superdc_ctx *ctx, const superdc_batch *b, const double
         // one launch over the chunks of the direct problems, longest first,
         // and one over the target leaves of the FMM problems
         const LaunchShape sh = b->sec;
-        const TileList *L = tile_list(bm, sh.chunk);
-        if (!L) return SUPERDC_ENOMEM;
-        a.tiles = L->lpt;
-        a.ntiles = L->count;
-        a.chunk = sh.chunk;
+        const int max_dir = fp ? fp->max_dir : b->max_n;  // largest direct problem
+        const bool lds = max_dir <= SECL_MAX_N && !o.unshifted && !o.interp;
+        a.chunk = !lds ? sh.chunk : fp ? fp->lds_chunk : b->lds_chunk;
         if (fp) {
-            const int slot = fmm_dir_slot(sh.chunk);
+            const int slot = chunk_slot(a.chunk);
             a.tiles = fp->dir_lpt[slot];
             a.ntiles = fp->dir_count[slot];
+        } else {
+            const TileList *L = tile_list(bm, a.chunk);
+            if (!L) return SUPERDC_ENOMEM;
+            a.tiles = L->lpt;
+            a.ntiles = L->count;
         }
         SDC_HIP(launch_validate(a, 0, b->nprob, b->max_n, s, b->vsplit, b->vsum, b->vst));
         if (fp) SDC_HIP(launch_fmm_build(f, s));
         a.work = trace_work(KID_SECULAR);
-        SDC_HIP(launch_secular(a, sh.split, s));
+        if (lds) SDC_HIP(launch_secular_lds(a, max_dir, s));
+        else SDC_HIP(launch_secular(a, sh.split, s));
         if (fp) {
             SolveArgs af = a;
             af.tiles = fp->sitem_lpt;
@@ -949,7 +999,7 @@ int superdc_secular_solve(superdc_ctx *ctx, const superdc_batch *b, const double
                 SDC_HIP(launch_secular_fmm(af, f, fp->ssplit, s));
                 continue;
             }
-            const LaunchShape sh = shape_for(ctx, &np, 1, TILE);
+            const LaunchShape sh = plain_shape(ctx, np);
             const TileList *L = tile_list(bm, sh.chunk);
             if (!L) return SUPERDC_ENOMEM;
             a.tiles = L->nat + L->begin[p];
@@ -1019,7 +1069,7 @@ int superdc_secular_backward(superdc_ctx *ctx, const superdc_batch *b, const dou
     } else {
         for (int p = 0; p < b->nprob; ++p) {
             const int64_t np = b->off_h[p + 1] - b->off_h[p];
-            const int S = shape_for(ctx, &np, 1, TILE).split;
+            const int S = shape_for(ctx, &np, 1, TILE, MIN_VEC_POLES).split;
             a.tiles = L->nat + L->begin[p];
             a.ntiles = L->begin[p + 1] - L->begin[p];
             SDC_HIP(launch_backward(a, S, p, 1, s));

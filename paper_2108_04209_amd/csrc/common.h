@@ -16,7 +16,9 @@ namespace sdc {
 
 constexpr int WAVE = 64;       // CDNA wavefront width
 constexpr int TILE = 64;       // entries per work tile
-constexpr int SEC_CHUNK = 512; // roots per work item of the secular solver
+constexpr int SEC_CHUNK = 512; // most roots per work item of the secular solver
+constexpr int MIN_CHUNK = 2;   // fewest; cut lengths are MIN_CHUNK 2^i
+constexpr int kNumChunks = 9;
 
 struct Tile {
     int32_t prob;  // problem index
@@ -204,9 +206,10 @@ struct superdc_batch {
     std::vector<int64_t> off_h;
     int64_t *off_d = nullptr;
     std::vector<int> order;             // problems, longest first
-    TileList lists[4];                  // cut lengths 64, 128, 256, 512
+    TileList lists[sdc::kNumChunks];    // by cut length
     // chosen launch shapes (heuristic, or set by the autotuner): batched launches
     LaunchShape sec, vec, app, bwd;
+    int lds_chunk = 64;                 // roots per work item of the direct solver in LDS
     int fmm_ssplit = 0;                 // FMM solver: wavefronts per work item (0: heuristic)
     bool tuned = false;
     // triangular-FMM layout (built on the first FMM solve; see fmm.h)
@@ -218,7 +221,9 @@ struct superdc_batch {
 };
 
 namespace sdc {
-// the tile list of a given cut length (64, 128, 256 or 512), built on first use
+// index of a cut length (MIN_CHUNK 2^i), -1 for others
+int chunk_slot(int chunk);
+// the tile list of a given cut length, built on first use
 const TileList *tile_list(superdc_batch *b, int chunk);
 // SUPERDC_OK or SUPERDC_EINVAL for an options struct
 int opts_check(const superdc_opts *o);
@@ -275,6 +280,12 @@ struct SolveArgs {
 hipError_t launch_validate(const SolveArgs &a, int prob_first, int nprob, int max_n, hipStream_t s,
                            int vsplit = 1, double *vsum = nullptr, int32_t *vst = nullptr);
 hipError_t launch_secular(const SolveArgs &a, int split, hipStream_t s);
+// the direct solver with the poles in LDS: problems of at most SECL_MAX_N poles (the launch's
+// largest has max_n), default iteration (no ablation, no hybrid)
+constexpr int SECL_MAX_N = 4096;
+// its wavefronts per workgroup (work item), so that LDS holds 20 wavefronts a CU
+inline int secl_waves(int max_n) { return max_n <= 1024 ? 2 : max_n <= 2048 ? 4 : 8; }
+hipError_t launch_secular_lds(const SolveArgs &a, int max_n, hipStream_t s);
 
 struct VecArgs {
     const int64_t *off;

@@ -88,6 +88,8 @@ struct FmmPlan {
     int leaf = 0;
     int crossover = 0;               // problems with n >= crossover use the FMM
     int nfmm = 0, nboxes = 0, nleaves = 0;
+    int max_dir = 0;                 // most poles of a problem that does not use the FMM
+    int lds_chunk = 64;              // roots per work item of the direct solver in LDS
     std::vector<int32_t> fmm_prob_h, fmm_of_h, box_off_h, leaf_off_h;
     int32_t *fmm_prob = nullptr, *fmm_of = nullptr, *box_off = nullptr, *leaf_off = nullptr;
     int32_t *height = nullptr, *box_fmm = nullptr, *leaf_fmm = nullptr;

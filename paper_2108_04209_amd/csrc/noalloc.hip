@@ -92,18 +92,20 @@ extern "C" int superdc_secular_solve_noalloc(superdc_ctx *ctx, const superdc_bat
     hipError_t e = hipSuccess;
     if (o.persistent) {
         const LaunchShape sh = b->sec;
-        const int slot = sh.chunk == 64 ? 0 : sh.chunk == 128 ? 1 : sh.chunk == 256 ? 2 : 3;
-        const TileList &L = b->lists[slot];
+        const bool lds = b->max_n <= SECL_MAX_N && !o.unshifted && !o.interp;
+        a.chunk = lds ? b->lds_chunk : sh.chunk;
+        const TileList &L = b->lists[chunk_slot(a.chunk)];
         if (!L.lpt) return SUPERDC_EINVAL;  // built with the batch (or by the autotuner)
         a.tiles = L.lpt;
         a.ntiles = L.count;
-        a.chunk = sh.chunk;
         e = launch_validate(a, 0, b->nprob, b->max_n, s);
-        if (e == hipSuccess)
+        if (e == hipSuccess && lds)
+            e = launch_secular_lds(a, b->max_n, s);
+        else if (e == hipSuccess)
             e = launch_secular(a, sh.split, s);
     } else {
         // one launch per problem on 64-root chunks, as superdc_secular_solve's plain mode
-        const TileList &L = b->lists[0];
+        const TileList &L = b->lists[chunk_slot(TILE)];
         if (!L.nat) return SUPERDC_EINVAL;
         for (int p = 0; p < b->nprob && e == hipSuccess; ++p) {
             const int64_t np = b->off_h[p + 1] - b->off_h[p];

@@ -849,6 +849,286 @@ __global__ __launch_bounds__(1024) void k_secular(SolveArgs a) {
     secular_chunk<false, UNSH>(a, a.tiles[blockIdx.x], red, nullptr);
 }
 
+// ---------------------------------------------------------------------------------------
+// The direct solver with the poles in LDS (the middle way with local shifting; problems of at
+// most SECL_MAX_N poles).  A workgroup stages a problem's (d_j, w_j) once; each of its
+// wavefronts then iterates its own few roots, with no barrier between wavefronts.  A root
+// is held by a team of g lanes (a power of two, 64 / g roots a wavefront), which share its
+// poles two at a time and add their sums by a butterfly, so every lane of a team takes the
+// same step; when half the lanes are idle the live roots are regrouped into larger teams.
+//
+// What bounded the solver on small problems was not the pairs (52 cycles of the FP64 pipe
+// each, about a third of its time) but what surrounds them: a scalar fetch from L2 per 4
+// poles in every pass, wavefronts that split a root's poles and then all repeated its step
+// between two barriers, and one wavefront of 64 roots per SIMD where a batch has few.
+// Measured, that one -> this one (us a launch): one problem of 100 roots 32 -> 13, of 1024
+// 78 -> 20; 512 problems of 1 to 300 roots 70 -> 29, 512 of 128 68 -> 34, 128 of 512 145 -> 81;
+// the direct problems of a level of 4096 1830 -> 750 (786,000 roots), of 1024 graded ones
+// 1140 -> 150.
+// ---------------------------------------------------------------------------------------
+
+// v + (v of the lane that CTRL selects), both halves moved by DPP
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+    const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+    return v + __hiloint2double(hi, lo);
+}
+
+// the sums of each team of g lanes, in every lane of the team (the partner of a step holds the
+// other half's total: within quads by permutation, then mirrored halves and rows)
+__device__ __forceinline__ void team_total(int g, double &a, double &b, double &c, double &d) {
+#define SDC_TEAM_STEP(F) \
+    {                    \
+        a = F(a);        \
+        b = F(b);        \
+        c = F(c);        \
+        d = F(d);        \
+    }
+    if (g >= 2) SDC_TEAM_STEP(dpp_add<0xB1>)   // quad_perm 1 0 3 2
+    if (g >= 4) SDC_TEAM_STEP(dpp_add<0x4E>)   // quad_perm 2 3 0 1
+    if (g >= 8) SDC_TEAM_STEP(dpp_add<0x141>)  // row_half_mirror
+    if (g >= 16) SDC_TEAM_STEP(dpp_add<0x140>) // row_mirror
+#undef SDC_TEAM_STEP
+    for (int o = 16; o < g; o <<= 1) {
+        a += __shfl_xor(a, o);
+        b += __shfl_xor(b, o);
+        c += __shfl_xor(c, o);
+        d += __shfl_xor(d, o);
+    }
+}
+
+// poles [j0, j1) on one side of every live root, two with one reciprocal (as secular_range,
+// under the same condition on |t|; false, with nothing done, outside it).  Every lane takes
+// the same number of rounds, 2^lg pairs each, so that the loop is one scalar-counted run of
+// independent loads; the last, partial round is masked.
+// da, db: the range's end poles.
+__device__ __forceinline__ bool lds_side(const double2 *P, int j0, int j1, double da, double db,
+                                         int sub, int lg, double dK, double y, double &s0,
+                                         double &s1) {
+    if (j0 >= j1) return true;
+    const double ta = fabs((da - dK) - y), tb = fabs((db - dK) - y);
+    if (__ballot(!(fmin(ta, tb) >= 0x1p-300 && fmax(ta, tb) <= 0x1p300)) != 0ull) return false;
+    auto pair = [&](double2 pa, double2 pb) {
+        const double t0 = (pa.x - dK) - y, t1 = (pb.x - dK) - y;
+        const double R = rcp_nr1(t0 * t1);
+        const double u0 = pa.y * t1, u1 = pb.y * t0;
+        s0 = __builtin_fma(u0 + u1, R, s0);
+        s1 = __builtin_fma(__builtin_fma(u0, t1, u1 * t0) * R, R, s1);
+    };
+    const int np = (j1 - j0) >> 1, full = np >> lg, st = 2 << lg;
+    const double2 *q = P + j0 + 2 * sub;
+    int i = 0;
+    for (; i + 4 <= full; i += 4, q += 4 * st) {
+        const double2 a0 = q[0], a1 = q[1], b0 = q[st], b1 = q[st + 1];
+        const double2 c0 = q[2 * st], c1 = q[2 * st + 1], d0 = q[3 * st], d1 = q[3 * st + 1];
+        pair(a0, a1);
+        pair(b0, b1);
+        pair(c0, c1);
+        pair(d0, d1);
+    }
+    for (; i < full; ++i, q += st) pair(q[0], q[1]);
+    // the pairs left over, and the odd pole after them (in the lane that follows)
+    const int left = np - (full << lg);
+    if (sub < left) {
+        pair(q[0], q[1]);
+    } else if (sub == left && ((j1 - j0) & 1)) {
+        const double2 pw = P[j1 - 1];
+        const double r = rcp_nr1((pw.x - dK) - y);
+        const double wr = pw.y * r;
+        s0 += wr;
+        s1 = __builtin_fma(wr, r, s1);
+    }
+    return true;
+}
+
+// poles [j0, j1) by the sign of their terms: negative ones (left of the iterate) to psi
+__device__ __forceinline__ void lds_window(const double2 *P, int j0, int j1, int sub, int lg,
+                                           double dK, double y, double &psi, double &dpsi,
+                                           double &phi, double &dphi) {
+    auto term = [&](double2 pw) {
+        const double rr = rcp_nr1((pw.x - dK) - y);
+        const double wr = pw.y * rr;
+        const double wl = __builtin_fmin(wr, 0.0), wg = __builtin_fmax(wr, 0.0);
+        psi += wl;
+        dpsi = __builtin_fma(wl, rr, dpsi);
+        phi += wg;
+        dphi = __builtin_fma(wg, rr, dphi);
+    };
+    const int full = (j1 - j0) >> lg, st = 1 << lg;
+    const double2 *q = P + j0 + sub;
+    int i = 0;
+    for (; i + 4 <= full; i += 4, q += 4 * st) {
+        const double2 a = q[0], b = q[st], c = q[2 * st], d = q[3 * st];
+        term(a);
+        term(b);
+        term(c);
+        term(d);
+    }
+    for (; i < full; ++i, q += st) term(q[0]);
+    if (sub < (j1 - j0) - (full << lg)) term(q[0]);
+}
+
+__device__ void secular_lds_item(const SolveArgs &a, Tile t, double2 *P) {
+    const int p = t.prob;
+    const int64_t base = a.off[p];
+    const int n = (int)(a.off[p + 1] - base);
+    const int lane = lane_id();
+    const int wv = wave_uniform((int)(threadIdx.x / WAVE));
+    const int i0 = t.row0, i1 = min(n, t.row0 + a.chunk);
+    if (a.status[p] & ~SUPERDC_ST_NOCONV) {  // invalid input: outputs are NaN
+        const double nan = __builtin_nan("");
+        for (int k = i0 + (int)threadIdx.x; k < i1; k += blockDim.x) {
+            a.lam[base + k] = nan;
+            a.eta[base + k] = nan;
+            a.origin[base + k] = k;
+            if (a.iters) a.iters[base + k] = SUPERDC_ITER_SKIPPED;
+            a.ke[base + k] = make_double2(nan, nan);
+        }
+        return;
+    }
+    for (int j = threadIdx.x; j < n; j += blockDim.x) P[j] = a.dw[base + j];
+    __syncthreads();
+    // this wavefront's roots [c0, c1), at most one to a lane
+    const int nw = blockDim.x / WAVE, share = (i1 - i0 + nw - 1) / nw;
+    const int c0 = min(i1, i0 + wv * share), c1 = min(i1, c0 + share);
+    const double z2 = a.z2[p];
+    const double eps = 2.220446049250313e-16;
+    const double tol = a.stop_c * (double)n * eps;
+    int lg = 0;  // log2 of g, the lanes per live root
+    while (lg < 6 && (2 << lg) * (c1 - c0) <= WAVE) ++lg;
+    int k = c0 + (lane >> lg), K = k, nev = -1;  // evaluations after the midpoint pass
+    bool act = k < c1, last = k == n - 1, hi_closed = false, noconv = false;
+    if (!act) k = K = c0;
+    double dk = P[k].x, dk1 = P[min(k + 1, n - 1)].x, dK = dk, lo = 0.0, hi = 0.0;
+    double y = last ? 0.5 * z2 : 0.5 * (dk1 - dk);  // midpoint pass
+    unsigned long long work = 0, live = 0, slots = 0;
+    // the window, this wavefront's own poles: those left of it feed psi, right of it phi, its
+    // own by sign
+    const int w0 = c0, w1 = c1;
+    const double d0 = P[0].x, dn = P[n - 1].x;
+    const double dl = P[max(w0 - 1, 0)].x, dr = P[min(w1, n - 1)].x;  // poles beside the window
+    for (;;) {
+        const unsigned long long actm = __ballot(act);
+        if (actm == 0ull) break;
+        lg = wave_uniform(lg);
+        int g = 1 << lg;
+        if (g < WAVE && 2 * __popcll(actm) <= WAVE) {  // half the lanes are idle: larger teams
+            const unsigned long long rep = __ballot(act && (lane & (g - 1)) == 0);
+            const int nlive = __popcll(rep);
+            while (lg < 6 && (nlive * 2 << lg) <= WAVE) ++lg;
+            lg = wave_uniform(lg);
+            g = 1 << lg;
+            const int slot = lane >> lg;
+            const bool keep = slot < nlive;
+            const int src = keep ? nth_set_bit(rep, slot) : lane;
+            const int flags = __shfl((last ? 1 : 0) | (hi_closed ? 2 : 0), src);
+            act = keep;
+            last = (flags & 1) != 0;
+            hi_closed = (flags & 2) != 0;
+            k = __shfl(k, src);
+            K = __shfl(K, src);
+            nev = __shfl(nev, src);
+            dk = __shfl(dk, src);
+            dk1 = __shfl(dk1, src);
+            dK = __shfl(dK, src);
+            y = __shfl(y, src);
+            lo = __shfl(lo, src);
+            hi = __shfl(hi, src);
+        }
+        const int sub = lane & (g - 1);
+        double psi = 0.0, dpsi = 0.0, phi = 0.0, dphi = 0.0;
+        int r0 = w0, r1 = w1;
+        if (!lds_side(P, 0, w0, d0, dl, sub, lg, dK, y, psi, dpsi)) r0 = 0;
+        if (!lds_side(P, w1, n, dr, dn, sub, lg, dK, y, phi, dphi)) r1 = n;
+        lds_window(P, r0, r1, sub, lg, dK, y, psi, dpsi, phi, dphi);
+        team_total(g, psi, dpsi, phi, dphi);
+        if (a.work) {
+            const unsigned long long nroot = (unsigned long long)__popcll(__ballot(act && sub == 0));
+            work += (unsigned long long)n * nroot;
+            live += (unsigned long long)__popcll(__ballot(act));
+            slots += WAVE;
+        }
+        if (!act) continue;
+        const double f = 1.0 + psi + phi;
+        ++nev;
+        if (nev == 0) {
+            // the sign of f at the midpoint fixes the origin and the bracket (Sec. 4.2.1)
+            if (f >= 0.0) {  // root in (d_k, mid]: origin d_k
+                lo = 0.0;
+                hi = y;
+            } else if (last) {
+                lo = y;
+                hi = z2;
+                hi_closed = true;  // unevaluated bound where f >= 0 is known
+            } else {  // root in (mid, d_{k+1}): origin d_{k+1}
+                K = k + 1;
+                dK = dk1;
+                y = -y;
+                lo = y;
+                hi = 0.0;
+            }
+        } else if (f < 0.0) {
+            lo = y;
+        } else {
+            hi = y;
+            hi_closed = false;
+        }
+        bool done = fabs(f) <= tol * (1.0 + fabs(psi) + fabs(phi));  // eq. stopcrit
+        int why = 0;
+        if (!done && nev >= a.max_iter) {
+            done = true;
+            noconv = true;
+            why = SUPERDC_ITER_CAP;
+        }
+        if (!done) {
+            // the middle way's quadratic in the step (Sec. 4.1.1; the last root: one pole,
+            // psi ~ a + b/(d_n - x)), each branch as one quotient
+            const double A = (dk - dK) - y, B = (dk1 - dK) - y;  // < 0 < B
+            const double C = f - dpsi * A - dphi * B;
+            const double qa = C * (A + B) + dpsi * A * A + dphi * B * B;
+            const double qb = A * B * f;
+            const double disc = sqrt(fabs(qa * qa - 4.0 * qb * C));
+            const double nu = last ? dpsi * y * y : (qa > 0.0 ? 2.0 * qb : qa - disc);
+            const double de = last ? 1.0 + psi + dpsi * y : (qa > 0.0 ? qa + disc : 2.0 * C);
+            double yn = nu / de;
+            if (!last) yn += y;
+            const bool inside = (yn > lo) && (yn < hi || (hi_closed && yn == hi));
+            if (!inside || !isfinite(yn)) yn = 0.5 * (lo + hi);
+            // a step below rounding, or a collapsed bracket: accept without re-evaluation
+            if (fabs(yn - y) <= 2.0 * eps * fabs(yn) ||
+                hi - lo <= 2.0 * eps * fmax(fabs(lo), fabs(hi))) {
+                done = true;
+                why = SUPERDC_ITER_UNMET;
+            }
+            y = yn;
+        }
+        if (done) {
+            if (sub == 0) {
+                a.eta[base + k] = y;
+                a.lam[base + k] = dK + y;
+                a.origin[base + k] = K;
+                if (a.iters) a.iters[base + k] = nev | why;
+                a.ke[base + k] = make_double2(dK, y);
+            }
+            act = false;
+        }
+    }
+    // (a lane that met the cap keeps its flag: regrouping moves roots, not flags)
+    if (__ballot(noconv) != 0ull && lane == 0) atomicOr(&a.status[p], SUPERDC_ST_NOCONV);
+    if (a.work && lane == 0) {
+        atomicAdd(a.work, work);
+        atomicAdd(a.work + 1, live);
+        atomicAdd(a.work + 2, slots);
+    }
+}
+
+// dynamic LDS: 16 bytes per pole of the launch's largest problem
+__global__ __launch_bounds__(512, 4) void k_secular_lds(SolveArgs a) {
+    extern __shared__ double2 poles[];
+    secular_lds_item(a, a.tiles[blockIdx.x], poles);
+}
+
 // FMM problems: one work item per 64-root piece of a target leaf; blockDim.x = 64 S with
 // the same dynamic LDS as k_secular
 template <bool UNSH>
@@ -881,6 +1161,14 @@ hipError_t launch_validate(const SolveArgs &a, int prob_first, int nprob, int ma
     if (S > 1)
         SDC_LAUNCH(KID_VALIDATE, k_validate_sum, dim3((nprob + 63) / 64), dim3(64), 0, s, a,
                    prob_first, nprob, S, (const double *)vsum, (const int32_t *)vst);
+    return hipGetLastError();
+}
+
+hipError_t launch_secular_lds(const SolveArgs &a, int max_n, hipStream_t s) {
+    if (a.ntiles <= 0) return hipSuccess;
+    if (max_n > SECL_MAX_N || a.unshifted || a.hybrid) return hipErrorInvalidValue;
+    SDC_LAUNCH(KID_SECULAR, k_secular_lds, dim3(a.ntiles), dim3(WAVE * secl_waves(max_n)),
+               sizeof(double2) * max_n, s, a);
     return hipGetLastError();
 }
 

@@ -176,7 +176,7 @@ int superdc_autotune(superdc_ctx *ctx, superdc_batch *b, const double *d, const 
         float best = 1e30f;
         int bsplit = b->vec.split;
         for (int S = 1; S <= 16; S *= 2) {
-            if (S > 1 && b->max_n / S < 128) break;
+            if (S > 1 && b->max_n / S < 16) break;
             b->vec.split = S;
             bool ok = true;
             const float t = time_best([&] {
@@ -191,7 +191,7 @@ int superdc_autotune(superdc_ctx *ctx, superdc_batch *b, const double *d, const 
         best = 1e30f;
         bsplit = b->bwd.split;
         for (int S = 1; S <= 16; S *= 2) {
-            if (S > 1 && b->max_n / S < 128) break;
+            if (S > 1 && b->max_n / S < 16) break;
             b->bwd.split = S;
             bool ok = true;
             const float t = time_best([&] {

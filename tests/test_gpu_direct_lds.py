@@ -1,0 +1,64 @@
+"""The direct solver with the poles in LDS against the oracle at the shapes where it can go
+wrong: one to three roots, wavefronts whose teams hold a root each (single problems), pairs and
+odd numbers of roots and poles per lane, the largest problem that fits and the first that does
+not, and batches large enough that a lane holds a root alone.
+
+Bars: eigenvalues within 1e-12 ||A||_2 and equal origins, as for every other solver test; no
+root may end its iteration before the stopping test holds or at the cap."""
+import numpy as np
+import pytest
+
+from paper_2108_04209_amd import gen
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+SHAPES = {
+    "one": [1], "two": [2], "three": [3], "tiny": [1, 2, 3, 4, 5, 7, 8, 9], "65": [65],
+    "127": [127, 128, 129], "1023": [1023, 1025], "2049": [2048, 2049], "4096": [4096],
+    "4097": [4097, 100], "wave": [33] * 40, "teams": [150, 301] * 60, "lanes": [64] * 3000,
+}
+
+
+@pytest.mark.parametrize("kind", ["uniform", "clustered"])
+@pytest.mark.parametrize("shape", list(SHAPES))
+def test_direct_solver(orc, shape, kind):
+    from paper_2108_04209_amd import native
+    from tests import gpu_pipeline as gp
+    sizes = SHAPES[shape]
+    batch = gen.small_batch(sizes, seed=81, kind=kind)
+    res = gp.run(batch, opts=native.default_opts(method=1), vectors=False)
+    assert np.all(res["status"] == 0)
+    assert np.all(res["iters"] & (native.ITER_UNMET | native.ITER_CAP | native.ITER_SKIPPED) == 0)
+    for p in list(range(min(8, batch.nprob))) + [batch.nprob - 1]:
+        a, e = int(batch.off[p]), int(batch.off[p + 1])
+        pr = batch.problem(p)
+        roots = None if e - a <= 1500 else np.unique(np.r_[0, 1, e - a - 1, np.arange(5, e - a, 37)])
+        lam, eta, org, its, st = orc.secular(pr.d, pr.z, pr.rho, roots=roots)
+        got = slice(a, e) if roots is None else a + roots
+        nA = np.abs(lam).max()
+        assert np.abs(res["lam"][got] - lam).max() <= 1e-12 * nA
+        np.testing.assert_array_equal(res["origin"][got], org)
+
+
+def test_direct_solver_cap_and_invalid(orc):
+    """A cap of one iteration flags the problem and keeps bracketed iterates; an invalid problem
+    between valid ones gives NaN and its bits, and leaves the others alone."""
+    from paper_2108_04209_amd import native
+    from tests import gpu_pipeline as gp
+    batch = gen.small_batch([200, 90, 300], seed=82)
+    res = gp.run(batch, opts=native.default_opts(method=1, max_iter=1), vectors=False)
+    assert np.all(res["status"] == native.ST_NOCONV)
+    for p in range(3):
+        a, e = int(batch.off[p]), int(batch.off[p + 1])
+        d = batch.d[a:e]
+        assert np.all(res["lam"][a:e - 1] <= d[1:]) and np.all(res["lam"][a:e] >= d)
+    ref = gp.run(batch, opts=native.default_opts(method=1), vectors=False)
+    batch.z[int(batch.off[1]) + 7] = 0.0
+    bad = gp.run(batch, opts=native.default_opts(method=1), vectors=False)
+    a, e = int(batch.off[1]), int(batch.off[2])
+    assert list(bad["status"]) == [0, native.ST_ZERO, 0]
+    assert np.all(np.isnan(bad["lam"][a:e])) and np.all(bad["iters"][a:e] == native.ITER_SKIPPED)
+    keep = np.r_[0:a, e:batch.total_n]
+    np.testing.assert_array_equal(bad["lam"][keep], ref["lam"][keep])
