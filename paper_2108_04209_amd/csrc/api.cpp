@@ -67,11 +67,49 @@ int chunk_slot(int chunk) {
     return -1;
 }
 
-const TileList *tile_list(superdc_batch *b, int chunk) {
-    const int slot = chunk_slot(chunk);
-    if (slot < 0) return nullptr;
-    TileList &l = b->lists[slot];
-    if (l.nat) return &l;
+namespace {
+// Host arrays gathered into one device allocation with one copy: a batch and its FMM layout
+// hold some thirty small arrays, and a deflated pass makes new ones for its reduced
+// problems (an allocation and a synchronous copy each: 2.6 ms of a pass over 1024
+// problems, 0.6 ms now).
+class Upload {
+  public:
+    template <typename T>
+    void add(T **dst, const std::vector<T> &v) {
+        const size_t at = space(dst, v.size());
+        if (!v.empty()) std::memcpy(buf_.data() + at, v.data(), sizeof(T) * v.size());
+    }
+    // room for count entries, not initialised
+    template <typename T>
+    size_t space(T **dst, size_t count) {
+        const size_t at = (buf_.size() + 255) & ~(size_t)255;
+        buf_.resize(at + std::max<size_t>(1, sizeof(T) * count));
+        fix_.push_back({(void **)dst, at});
+        return at;
+    }
+    // the device memory that holds them all (nullptr on failure; *err: why)
+    void *commit(hipError_t *err) {
+        void *mem = nullptr;
+        *err = hipMalloc(&mem, buf_.size());
+        if (*err != hipSuccess) return nullptr;
+        *err = hipMemcpy(mem, buf_.data(), buf_.size(), hipMemcpyHostToDevice);
+        if (*err != hipSuccess) {
+            (void)hipFree(mem);
+            return nullptr;
+        }
+        for (const auto &f : fix_) *f.first = (char *)mem + f.second;
+        return mem;
+    }
+
+  private:
+    std::vector<char> buf_;
+    std::vector<std::pair<void **, size_t>> fix_;
+};
+
+// the items of a cut length added to an upload
+void list_add(superdc_batch *b, int chunk, Upload &up) {
+    TileList &l = b->lists[chunk_slot(chunk)];
+    if (l.count) return;
     std::vector<Tile> nat, lpt;
     l.begin.resize(b->nprob + 1);
     for (int p = 0; p < b->nprob; ++p) {
@@ -83,21 +121,26 @@ const TileList *tile_list(superdc_batch *b, int chunk) {
     lpt.reserve(nat.size());
     for (int p : b->order)
         for (int32_t t = l.begin[p]; t < l.begin[p + 1]; ++t) lpt.push_back(nat[t]);
-    Tile *dn = nullptr, *dl = nullptr;
-    if (hipMalloc(&dn, sizeof(Tile) * nat.size()) != hipSuccess) return nullptr;
-    if (hipMalloc(&dl, sizeof(Tile) * lpt.size()) != hipSuccess) {
-        (void)hipFree(dn);
-        return nullptr;
-    }
-    if (hipMemcpy(dn, nat.data(), sizeof(Tile) * nat.size(), hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(dl, lpt.data(), sizeof(Tile) * lpt.size(), hipMemcpyHostToDevice) != hipSuccess) {
-        (void)hipFree(dn);
-        (void)hipFree(dl);
-        return nullptr;
-    }
-    l.nat = dn;
-    l.lpt = dl;
     l.count = (int32_t)nat.size();
+    up.add(&l.nat, nat);
+    up.add(&l.lpt, lpt);
+}
+}  // namespace
+
+const TileList *tile_list(superdc_batch *b, int chunk) {
+    const int slot = chunk_slot(chunk);
+    if (slot < 0) return nullptr;
+    TileList &l = b->lists[slot];
+    if (l.nat) return &l;
+    Upload up;
+    list_add(b, chunk, up);
+    hipError_t e;
+    void *mem = up.commit(&e);
+    if (!mem) {
+        l.count = 0;
+        return nullptr;
+    }
+    b->mem.push_back(mem);
     return &l;
 }
 }  // namespace sdc
@@ -189,25 +232,95 @@ constexpr double FMM_SEP_LOC = 0.75;
 
 void fmm_free(FmmPlan *fp) {
     if (!fp) return;
+    if (fp->mem) (void)hipFree(fp->mem);
     for (void *p : fp->allocs) (void)hipFree(p);
     delete fp;
 }
 
-template <typename T>
-bool fmm_upload(FmmPlan *fp, T **dst, const std::vector<T> &v, size_t count = 0) {
-    const size_t n = std::max<size_t>(1, count ? count : v.size());
-    if (hipMalloc((void **)dst, sizeof(T) * n) != hipSuccess) return false;
-    fp->allocs.push_back(*dst);
-    if (!v.empty() &&
-        hipMemcpy(*dst, v.data(), sizeof(T) * v.size(), hipMemcpyHostToDevice) != hipSuccess)
-        return false;
+// direct chunks of length C of the problems that don't use the FMM, added to an upload
+void dir_add(const superdc_batch *b, FmmPlan *fp, int C, Upload &up) {
+    const int slot = chunk_slot(C);
+    if (fp->dir_built[slot]) return;
+    std::vector<Tile> v;
+    for (int p : b->order) {
+        if (fp->fmm_of_h[p] >= 0) continue;
+        const int64_t n = b->off_h[p + 1] - b->off_h[p];
+        for (int64_t r = 0; r < n; r += C) v.push_back(Tile{p, (int32_t)r});
+    }
+    fp->dir_count[slot] = (int32_t)v.size();
+    fp->dir_built[slot] = true;
+    up.add(&fp->dir_lpt[slot], v);
+}
+
+// the tiles and count of the direct chunks of length C (a length that the autotuner chose after
+// the layout was made is added on its first use); false: out of memory
+bool dir_list(const superdc_batch *b, FmmPlan *fp, int C, SolveArgs &a) {
+    const int slot = chunk_slot(C);
+    if (!fp->dir_built[slot]) {
+        Upload up;
+        dir_add(b, fp, C, up);
+        hipError_t e;
+        void *mem = up.commit(&e);
+        if (!mem) {
+            fp->dir_built[slot] = false;
+            return false;
+        }
+        fp->allocs.push_back(mem);
+    }
+    a.tiles = fp->dir_lpt[slot];
+    a.ntiles = fp->dir_count[slot];
     return true;
 }
 
-// The FMM layout of a batch: which problems use it, their leaf trees, list buffers and
-// work lists.  Rebuilt only when the leaf size or the crossover changes.
+// The per-call arrays of a layout (equivalent sources, lists, moments) in the context's
+// workspace: every call writes what it reads, but for the lists that a solve leaves to the
+// Loewner and apply calls that follow it inside the library on the same batch.  The use flags
+// have a buffer of their own, whose every entry is the number of some lists build (numbers
+// rise through the context's life), zero at first: a stale flag never equals a new number.
+bool fmm_scratch(FmmPlan *fp, superdc_ctx *ctx) {
+    const size_t nb = std::max(1, fp->nboxes), nl = std::max(1, fp->nleaves);
+    size_t at = 0;
+    std::vector<std::pair<void **, size_t>> fix;
+    auto room = [&](auto **dst, size_t count) {
+        fix.push_back({(void **)dst, at});
+        at += (sizeof(**dst) * count + 255) & ~(size_t)255;
+    };
+    room(&fp->eq, nb * FMM_P);
+    room(&fp->vnode, nb * FMM_P);
+    room(&fp->lgeo, nb);
+    room(&fp->lmom, nb * FMML_K);
+    room(&fp->loc, nl * FMM_LOC);
+    for (FmmLists *l : {&fp->own, &fp->roots}) {
+        room(&l->near_lo, nl * FMM_NEAR_MAX);
+        room(&l->near_hi, nl * FMM_NEAR_MAX);
+        room(&l->near_lf, nl * FMM_NEAR_MAX);
+        room(&l->far_l, nl * FMM_FAR_MAX);
+        room(&l->far_r, nl * FMM_FAR_MAX);
+        room(&l->far_ld, nl * FMM_FAR_MAX);
+        room(&l->far_rd, nl * FMM_FAR_MAX);
+        room(&l->cnt, nl * 3);
+        room(&l->cntd, nl * 2);
+        room(&l->loc_ab, nl);
+    }
+    char *mem = (char *)ws_get(ctx, WS_FMM, at);
+    const size_t flags = sizeof(int32_t) * 2 * nb;
+    const bool grow = ctx->ws_cap[WS_FMM_USED] < flags;
+    int32_t *used = (int32_t *)ws_get(ctx, WS_FMM_USED, flags);
+    if (!mem || !used) return false;
+    if (grow && (hipMemset(used, 0, ctx->ws_cap[WS_FMM_USED]) != hipSuccess ||
+                 hipDeviceSynchronize() != hipSuccess))
+        return false;
+    for (const auto &f : fix) *f.first = mem + f.second;
+    fp->own.used = used;
+    fp->roots.used = used + nb;
+    return true;
+}
+
+// The FMM layout of a batch: which problems use it, their leaf trees and work lists.
+// Rebuilt only when the leaf size or the crossover changes.
 FmmPlan *fmm_plan(superdc_batch *b, int leaf, int crossover) {
-    if (b->fmm && b->fmm->leaf == leaf && b->fmm->crossover == crossover) return b->fmm;
+    if (b->fmm && b->fmm->leaf == leaf && b->fmm->crossover == crossover)
+        return fmm_scratch(b->fmm, b->ctx) ? b->fmm : nullptr;
     (void)hipDeviceSynchronize();
     fmm_free(b->fmm);
     b->fmm = nullptr;
@@ -321,66 +434,46 @@ FmmPlan *fmm_plan(superdc_batch *b, int leaf, int crossover) {
     while (fp->ssplit < 8 &&
            (long)fp->snitems * fp->ssplit * 2 <= (long)b->ctx->num_cu * SDC_FMM_WAVES_PER_CU)
         fp->ssplit *= 2;
-    bool ok = fmm_upload(fp, &fp->fmm_prob, fp->fmm_prob_h) &&
-              fmm_upload(fp, &fp->fmm_of, fp->fmm_of_h) &&
-              fmm_upload(fp, &fp->box_off, fp->box_off_h) &&
-              fmm_upload(fp, &fp->leaf_off, fp->leaf_off_h) && fmm_upload(fp, &fp->height, height) &&
-              fmm_upload(fp, &fp->box_fmm, box_fmm) && fmm_upload(fp, &fp->leaf_fmm, leaf_fmm) &&
-              fmm_upload(fp, &fp->leaf_box, leaf_box) && fmm_upload(fp, &fp->upper_box, upper_box) &&
-              fmm_upload(fp, &fp->upper_item, upper_item) && fmm_upload(fp, &fp->split_box, split_box) &&
-              fmm_upload(fp, &fp->leaf_nat, lnat) && fmm_upload(fp, &fp->leaf_lpt, llpt) &&
-              fmm_upload(fp, &fp->sitem_nat, snat) && fmm_upload(fp, &fp->sitem_lpt, slpt) &&
-              fmm_upload(fp, &fp->eq, std::vector<double2>(), (size_t)fp->nboxes * FMM_P) &&
-              fmm_upload(fp, &fp->near_lo, std::vector<int32_t>(), (size_t)fp->nleaves * FMM_NEAR_MAX) &&
-              fmm_upload(fp, &fp->near_hi, std::vector<int32_t>(), (size_t)fp->nleaves * FMM_NEAR_MAX) &&
-              fmm_upload(fp, &fp->far_l, std::vector<int32_t>(), (size_t)fp->nleaves * FMM_FAR_MAX) &&
-              fmm_upload(fp, &fp->far_r, std::vector<int32_t>(), (size_t)fp->nleaves * FMM_FAR_MAX) &&
-              fmm_upload(fp, &fp->cnt, std::vector<int32_t>(), (size_t)fp->nleaves * 3) &&
-              fmm_upload(fp, &fp->near_lf, std::vector<int32_t>(), (size_t)fp->nleaves * FMM_NEAR_MAX) &&
-              fmm_upload(fp, &fp->t_near_lf, std::vector<int32_t>(), (size_t)fp->nleaves * FMM_NEAR_MAX) &&
-              fmm_upload(fp, &fp->loc_ab, std::vector<double2>(), (size_t)fp->nleaves) &&
-              fmm_upload(fp, &fp->far_ld, std::vector<int32_t>(), (size_t)fp->nleaves * FMM_FAR_MAX) &&
-              fmm_upload(fp, &fp->far_rd, std::vector<int32_t>(), (size_t)fp->nleaves * FMM_FAR_MAX) &&
-              fmm_upload(fp, &fp->cntd, std::vector<int32_t>(), (size_t)fp->nleaves * 2) &&
-              fmm_upload(fp, &fp->loc, std::vector<double>(), (size_t)fp->nleaves * FMM_LOC) &&
-              fmm_upload(fp, &fp->used, std::vector<int32_t>(), fp->nboxes) &&
-              fmm_upload(fp, &fp->vnode, std::vector<double>(), (size_t)fp->nboxes * FMM_P) &&
-              fmm_upload(fp, &fp->lgeo, std::vector<double2>(), fp->nboxes) &&
-              fmm_upload(fp, &fp->lmom, std::vector<double>(), (size_t)fp->nboxes * FMML_K) &&
-              fmm_upload(fp, &fp->t_near_lo, std::vector<int32_t>(), (size_t)fp->nleaves * FMM_NEAR_MAX) &&
-              fmm_upload(fp, &fp->t_near_hi, std::vector<int32_t>(), (size_t)fp->nleaves * FMM_NEAR_MAX) &&
-              fmm_upload(fp, &fp->t_far_l, std::vector<int32_t>(), (size_t)fp->nleaves * FMM_FAR_MAX) &&
-              fmm_upload(fp, &fp->t_far_r, std::vector<int32_t>(), (size_t)fp->nleaves * FMM_FAR_MAX) &&
-              fmm_upload(fp, &fp->t_cnt, std::vector<int32_t>(), (size_t)fp->nleaves * 3) &&
-              fmm_upload(fp, &fp->t_far_ld, std::vector<int32_t>(), (size_t)fp->nleaves * FMM_FAR_MAX) &&
-              fmm_upload(fp, &fp->t_far_rd, std::vector<int32_t>(), (size_t)fp->nleaves * FMM_FAR_MAX) &&
-              fmm_upload(fp, &fp->t_cntd, std::vector<int32_t>(), (size_t)fp->nleaves * 2) &&
-              fmm_upload(fp, &fp->t_used, std::vector<int32_t>(), fp->nboxes) &&
-              fmm_upload(fp, &fp->t_loc_ab, std::vector<double2>(), (size_t)fp->nleaves);
-    // direct chunks of the other problems, for each cut length
-    fp->dir_lpt.assign(kNumChunks, nullptr);
-    fp->dir_count.assign(kNumChunks, 0);
-    for (int slot = 0; slot < kNumChunks && ok; ++slot) {
-        const int C = MIN_CHUNK << slot;
-        std::vector<Tile> v;
-        for (int p : b->order) {
-            if (fp->fmm_of_h[p] >= 0) continue;
-            const int64_t n = b->off_h[p + 1] - b->off_h[p];
-            for (int64_t r = 0; r < n; r += C) v.push_back(Tile{p, (int32_t)r});
-        }
-        fp->dir_count[slot] = (int32_t)v.size();
-        ok = fmm_upload(fp, &fp->dir_lpt[slot], v);
-    }
-    // the use flags start below every lists number (the first build is number 1)
-    ok = ok && hipMemset(fp->used, 0, sizeof(int32_t) * std::max(1, fp->nboxes)) == hipSuccess &&
-         hipMemset(fp->t_used, 0, sizeof(int32_t) * std::max(1, fp->nboxes)) == hipSuccess &&
-         hipDeviceSynchronize() == hipSuccess;
-    if (!ok) {
+    Upload up;
+    up.add(&fp->fmm_prob, fp->fmm_prob_h);
+    up.add(&fp->fmm_of, fp->fmm_of_h);
+    up.add(&fp->box_off, fp->box_off_h);
+    up.add(&fp->leaf_off, fp->leaf_off_h);
+    up.add(&fp->height, height);
+    up.add(&fp->box_fmm, box_fmm);
+    up.add(&fp->leaf_fmm, leaf_fmm);
+    up.add(&fp->leaf_box, leaf_box);
+    up.add(&fp->upper_box, upper_box);
+    up.add(&fp->upper_item, upper_item);
+    up.add(&fp->split_box, split_box);
+    up.add(&fp->leaf_nat, lnat);
+    up.add(&fp->leaf_lpt, llpt);
+    up.add(&fp->sitem_nat, snat);
+    up.add(&fp->sitem_lpt, slpt);
+    // direct chunks of the other problems: the cut lengths in use now
+    for (int C : {(int)TILE, fp->lds_chunk, b->sec.chunk}) dir_add(b, fp, C, up);
+    hipError_t e;
+    if (!(fp->mem = up.commit(&e)) || !fmm_scratch(fp, b->ctx)) {
         fmm_free(fp);
         return nullptr;
     }
     b->fmm = fp;
     return fp;
+}
+
+void set_lists(FmmArgs &f, const FmmLists &l) {
+    f.near_lo = l.near_lo;
+    f.near_hi = l.near_hi;
+    f.near_lf = l.near_lf;
+    f.far_l = l.far_l;
+    f.far_r = l.far_r;
+    f.cnt = l.cnt;
+    f.far_ld = l.far_ld;
+    f.far_rd = l.far_rd;
+    f.cntd = l.cntd;
+    f.loc_ab = l.loc_ab;
+    f.used = l.used;
+    f.gen = l.gen;
 }
 
 FmmArgs fmm_args(const FmmPlan *fp, const superdc_batch *b, const SolveArgs &a,
@@ -398,19 +491,8 @@ FmmArgs fmm_args(const FmmPlan *fp, const superdc_batch *b, const SolveArgs &a,
     f.dw = a.dw;
     f.tail = a.z2;  // the last root lies below d_{n-1} + sum_j w_j
     f.status = a.status;
-    f.used = fp->used;
-    f.gen = fp->gen;
+    set_lists(f, fp->own);
     f.eq = fp->eq;
-    f.near_lo = fp->near_lo;
-    f.near_hi = fp->near_hi;
-    f.near_lf = fp->near_lf;
-    f.far_l = fp->far_l;
-    f.far_r = fp->far_r;
-    f.cnt = fp->cnt;
-    f.far_ld = fp->far_ld;
-    f.far_rd = fp->far_rd;
-    f.cntd = fp->cntd;
-    f.loc_ab = fp->loc_ab;
     f.loc = fp->loc;
     f.nboxes = fp->nboxes;
     f.nleaves = fp->nleaves;
@@ -448,18 +530,7 @@ FmmArgs fmm_roots_args(const FmmPlan *fp, const superdc_batch *b, const double *
                        const int32_t *status, const double *d) {
     FmmArgs f = fmm_vec_args(fp, b, pos, nullptr, nullptr, status);
     f.tpos = d;
-    f.near_lo = fp->t_near_lo;
-    f.near_hi = fp->t_near_hi;
-    f.near_lf = fp->t_near_lf;
-    f.far_l = fp->t_far_l;
-    f.far_r = fp->t_far_r;
-    f.cnt = fp->t_cnt;
-    f.far_ld = fp->t_far_ld;
-    f.far_rd = fp->t_far_rd;
-    f.cntd = fp->t_cntd;
-    f.used = fp->t_used;
-    f.gen = fp->t_gen;
-    f.loc_ab = fp->t_loc_ab;
+    set_lists(f, fp->roots);
     return f;
 }
 
@@ -618,7 +689,7 @@ int loewner_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const
         // leaves' launch packs the pairs itself
         if (!reuse_lists) {
             SDC_HIP(launch_fmml_pack(pk, s));
-            f.gen = ++fp->gen;
+            f.gen = fp->own.gen = ++ctx->lists_gen;
             SDC_HIP(launch_fmm_lists(f, s));
         } else {
             lf.pack = 1;
@@ -759,11 +830,11 @@ int apply_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const d
         v.ke = ke;
         SDC_HIP(launch_fmmv_pos(pk, s));
         f = fmm_roots_args(fp, b, pos, status, d);
-        f.gen = ++fp->t_gen;  // built with the first columns below
+        f.gen = fp->roots.gen = ++ctx->lists_gen;  // built with the first columns below
         lists = true;
     } else {
         f = fmm_vec_args(fp, b, d, eta, origin, status);
-        if (lists) f.gen = ++fp->gen;  // built with the first columns below
+        if (lists) f.gen = fp->own.gen = ++ctx->lists_gen;  // built with the first columns below
     }
     const int pass = fmmv_pass(fp, m + v.fuse_b);  // one pass when fused
     if (!fmmv_space(ctx, fp, pass, f, v)) return SUPERDC_ENOMEM;
@@ -861,31 +932,29 @@ int superdc_batch_create(superdc_ctx *ctx, int32_t nprob, const int64_t *off_hos
     std::stable_sort(b->order.begin(), b->order.end(), [&](int x, int y) {
         return off_host[x + 1] - off_host[x] > off_host[y + 1] - off_host[y];
     });
-    hipError_t e = hipMalloc(&b->off_d, sizeof(int64_t) * (nprob + 1));
-    if (e == hipSuccess)
-        e = hipMemcpy(b->off_d, off_host, sizeof(int64_t) * (nprob + 1), hipMemcpyHostToDevice);
     // problems of 16384 entries and more are validated in slices of about 4096
     b->vsplit = max_n >= 16384 ? std::min(16, max_n / 4096) : 1;
-    if (e == hipSuccess && b->vsplit > 1) {
-        e = hipMalloc(&b->vsum, sizeof(double) * nprob * b->vsplit);
-        if (e == hipSuccess) e = hipMalloc(&b->vst, sizeof(int32_t) * nprob * b->vsplit);
+    // launch shapes for the batched launches (the autotuner may replace them); the solver's
+    // tile lists for them are built now, so that a later solve (the allocation-free entry
+    // point in particular) finds them ready
+    b->sec = choose_shape(ctx, b, SEC_CHUNK, MIN_SPLIT_POLES);
+    b->lds_chunk = lds_chunk(b, (int64_t)1 << 31);
+    b->vec = choose_shape(ctx, b, TILE, MIN_VEC_POLES);
+    b->bwd = b->vec;
+    Upload up;
+    up.add(&b->off_d, b->off_h);
+    for (int C : {(int)TILE, b->sec.chunk, b->lds_chunk}) list_add(b, C, up);
+    if (b->vsplit > 1) {
+        up.space(&b->vsum, (size_t)nprob * b->vsplit);
+        up.space(&b->vst, (size_t)nprob * b->vsplit);
     }
-    if (e == hipSuccess && !tile_list(b, TILE)) e = hipErrorOutOfMemory;
-    if (e != hipSuccess) {
+    hipError_t e;
+    void *mem = up.commit(&e);
+    if (!mem) {
         superdc_batch_destroy(b);
         return hip_fail(e);
     }
-    // launch shapes for the batched launches (the autotuner may replace them)
-    b->sec = choose_shape(ctx, b, SEC_CHUNK, MIN_SPLIT_POLES);
-    b->lds_chunk = lds_chunk(b, (int64_t)1 << 31);
-    // the solver's tile list for that shape is built now, so that a later solve (the
-    // allocation-free entry point in particular) finds it ready
-    if (!tile_list(b, b->sec.chunk) || !tile_list(b, b->lds_chunk)) {
-        superdc_batch_destroy(b);
-        return hip_fail(hipErrorOutOfMemory);
-    }
-    b->vec = choose_shape(ctx, b, TILE, MIN_VEC_POLES);
-    b->bwd = b->vec;
+    b->mem.push_back(mem);
     b->app = LaunchShape{TILE, 1};
     *out = b;
     return SUPERDC_OK;
@@ -894,14 +963,8 @@ int superdc_batch_create(superdc_ctx *ctx, int32_t nprob, const int64_t *off_hos
 void superdc_batch_destroy(superdc_batch *b) {
     if (!b) return;
     (void)hipDeviceSynchronize();
-    if (b->off_d) (void)hipFree(b->off_d);
-    if (b->vsum) (void)hipFree(b->vsum);
-    if (b->vst) (void)hipFree(b->vst);
     fmm_free(b->fmm);
-    for (auto &l : b->lists) {
-        if (l.nat) (void)hipFree(l.nat);
-        if (l.lpt) (void)hipFree(l.lpt);
-    }
+    for (void *p : b->mem) (void)hipFree(p);
     delete b;
 }
 
@@ -946,7 +1009,7 @@ int superdc_secular_solve(superdc_ctx *ctx, const superdc_batch *b, const double
     FmmArgs f{};
     if (fp) {
         f = fmm_args(fp, b, a, o);
-        f.gen = ++fp->gen;  // the lists this solve builds
+        f.gen = fp->own.gen = ++ctx->lists_gen;  // the lists this solve builds
     }
     if (o.persistent) {
         // one launch over the chunks of the direct problems, longest first,
@@ -956,9 +1019,7 @@ int superdc_secular_solve(superdc_ctx *ctx, const superdc_batch *b, const double
         const bool lds = max_dir <= SECL_MAX_N && !o.unshifted && !o.interp;
         a.chunk = !lds ? sh.chunk : fp ? fp->lds_chunk : b->lds_chunk;
         if (fp) {
-            const int slot = chunk_slot(a.chunk);
-            a.tiles = fp->dir_lpt[slot];
-            a.ntiles = fp->dir_count[slot];
+            if (!dir_list(b, fp, a.chunk, a)) return SUPERDC_ENOMEM;
         } else {
             const TileList *L = tile_list(bm, a.chunk);
             if (!L) return SUPERDC_ENOMEM;

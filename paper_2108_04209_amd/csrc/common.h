@@ -167,7 +167,8 @@ class TraceScope {
 enum WsSlot {
     WS_DW = 0, WS_KE = 1, WS_DZ = 2, WS_Z2 = 3, WS_BK = 4, WS_BP = 5, WS_TMP = 6, WS_VPAIR = 7,
     WS_VW = 8, WS_DEFL_VAL = 9, WS_DEFL_FLAG = 10, WS_DEFL_T = 11, WS_DEFL_SEGI = 12,
-    WS_DEFL_SEGD = 13, WS_VPART = 14, kNumWs
+    WS_DEFL_SEGD = 13, WS_VPART = 14, WS_FMM = 15,
+    WS_FMM_USED = 16, kNumWs
 };
 
 struct superdc_ctx {
@@ -176,6 +177,7 @@ struct superdc_ctx {
     // grow-only workspace buffers
     void *ws[kNumWs] = {nullptr};
     size_t ws_cap[kNumWs] = {0};
+    int lists_gen = 0;             // number of the last FMM lists build
     int fmm_crossover = 1024;      // automatic method: FMM for problems at least this large (measured)
 };
 
@@ -205,6 +207,7 @@ struct superdc_batch {
     int32_t max_n = 0;
     std::vector<int64_t> off_h;
     int64_t *off_d = nullptr;
+    std::vector<void *> mem;            // the device memory of every array below
     std::vector<int> order;             // problems, longest first
     TileList lists[sdc::kNumChunks];    // by cut length
     // chosen launch shapes (heuristic, or set by the autotuner): batched launches

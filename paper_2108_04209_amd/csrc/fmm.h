@@ -83,7 +83,17 @@ struct FmmArgs {
     const double *tpos;
 };
 
-// Host side: the FMM layout of one batch for one leaf size (device buffers owned here).
+// interaction lists of one set of targets (see FmmArgs) and the number of their last build
+struct FmmLists {
+    int32_t *near_lo = nullptr, *near_hi = nullptr, *near_lf = nullptr;
+    int32_t *far_l = nullptr, *far_r = nullptr, *far_ld = nullptr, *far_rd = nullptr;
+    int32_t *cnt = nullptr, *cntd = nullptr, *used = nullptr;
+    double2 *loc_ab = nullptr;
+    int gen = 0;
+};
+
+// Host side: the FMM layout of one batch for one leaf size.  The index arrays are device
+// buffers owned here; the per-call arrays are the context's workspace, set on every use.
 struct FmmPlan {
     int leaf = 0;
     int crossover = 0;               // problems with n >= crossover use the FMM
@@ -98,12 +108,13 @@ struct FmmPlan {
     int4 *upper_item = nullptr;
     int2 *split_box = nullptr;
     int nupper_item = 0, nsplit = 0, nslot = 0;
-    double2 *eq = nullptr;
-    int32_t *near_lo = nullptr, *near_hi = nullptr, *far_l = nullptr, *far_r = nullptr;
-    int32_t *cnt = nullptr, *near_lf = nullptr;
-    int32_t *far_ld = nullptr, *far_rd = nullptr, *cntd = nullptr;
-    double2 *loc_ab = nullptr;
-    double *loc = nullptr;
+    double2 *eq = nullptr;           // per-call arrays (fmm_scratch)
+    double *loc = nullptr, *vnode = nullptr;
+    double2 *lgeo = nullptr;
+    double *lmom = nullptr;
+    FmmLists own;                    // lists of the poles' targets
+    FmmLists roots;                  // of the sums over the roots (Y = Qhat X), kept apart from
+                                     // the solver's, which later calls on the same poles reuse
     // work items: 64-root pieces of the target leaves (a piece never crosses a leaf)
     int sub = TILE;                    // roots per work item
     int nitems = 0;
@@ -119,21 +130,12 @@ struct FmmPlan {
     std::vector<int32_t> sitem_off_h;
     Tile *sitem_lpt = nullptr;
     Tile *sitem_nat = nullptr;
-    std::vector<Tile *> dir_lpt;       // direct chunks of the other problems, per cut length
-    std::vector<int32_t> dir_count;
-    int32_t *used = nullptr;           // [nboxes], zeroed at creation
-    int gen = 0, t_gen = 0;            // numbers of the last lists built (solver's, roots')
-    double *vnode = nullptr;           // eigenvector-side equivalent sources' positions
-    double2 *lgeo = nullptr;           // Loewner far field: box geometry and moments
-    double *lmom = nullptr;
-    // the lists of the sums over the roots (Y = Qhat X: sources at the roots, targets at the
-    // poles), kept apart from the solver's, which later calls on the same poles reuse
-    int32_t *t_near_lo = nullptr, *t_near_hi = nullptr, *t_far_l = nullptr, *t_far_r = nullptr;
-    int32_t *t_cnt = nullptr, *t_far_ld = nullptr, *t_far_rd = nullptr, *t_cntd = nullptr;
-    int32_t *t_near_lf = nullptr;
-    int32_t *t_used = nullptr;
-    double2 *t_loc_ab = nullptr;
-    std::vector<void *> allocs;
+    // direct chunks of the other problems, by cut length (those in use)
+    Tile *dir_lpt[kNumChunks] = {nullptr};
+    int32_t dir_count[kNumChunks] = {0};
+    bool dir_built[kNumChunks] = {false};
+    void *mem = nullptr;               // the arrays above that hold the layout
+    std::vector<void *> allocs;        // direct chunks added later
 };
 
 // Eigenvector-side FMM (Sec. 4.3-4.4 with local shifting): sums over the poles i of a
