@@ -91,7 +91,10 @@ typedef struct {
                             0: one launch per problem per phase (the "plain" baseline)    */
     int32_t apply_kernel;/* Cauchy apply: 0 auto (MFMA for m >= 4), 1 VALU, 2 FP64 MFMA    */
     int32_t fmm_crossover;/* method 0: problems with at least this many roots use the FMM
-                            (solver, b, Qhat^T X); 0 = the context's default (1024)       */
+                            (solver, b, Qhat^T X); 0 = the context's default: 1024, and
+                            direct sums for every problem of a batch too small to gain
+                            from it (none above 4096 roots, sum of n^2 up to 4e7; applies
+                            9e6)                                                          */
     int32_t unshifted;   /* 1: ablation of the local shifting (Sec. 4.2.2): the iterate is
                             kept as lambda itself and every pole difference is formed as
                             d_j - lambda (f evaluated at lambda with no shift); the

@@ -54,11 +54,23 @@ int opts_check(const superdc_opts *o) {
     return SUPERDC_OK;
 }
 
-int fmm_crossover_of(const superdc_ctx *ctx, const superdc_opts &o) {
-    return o.method == 1 ? 0x7fffffff
-           : o.method == 2 ? 2 * o.fmm_leaf
-           : o.fmm_crossover > 0 ? o.fmm_crossover
-                                : ctx->fmm_crossover;
+// Small batches by direct sums: the FMM's chain of set-up launches takes as long as
+// DIRECT_PAIRS pole-root pairs (n = 1024 .. 4096, whole pipelines with 16 columns, direct
+// against FMM: 1 problem of 1024 roots 75 and 175 us, 1 of 4096 205 and 275, 8 of 2048
+// 168 and 218, 32 of 1024 164 and 223, 64 of 1024 270 and 268, 128 of 1024 493 and 391).  An
+// apply alone crosses earlier, for its FMM has fewer launches and the direct product all
+// columns' pairs (8 problems of 1024 roots, 64 columns: 39 and 41 us; 4 of 2048: 70 and 42).
+constexpr double DIRECT_PAIRS = 4e7;
+constexpr double DIRECT_APPLY_PAIRS = 9e6;
+
+int fmm_crossover_of(const superdc_batch *b, const superdc_opts &o, bool apply) {
+    if (o.method == 1) return 0x7fffffff;
+    if (o.method == 2) return 2 * o.fmm_leaf;
+    if (o.fmm_crossover > 0) return o.fmm_crossover;
+    const bool direct = b->max_n <= SECL_MAX_N &&
+                        b->big_pairs <= (apply ? DIRECT_APPLY_PAIRS : DIRECT_PAIRS) &&
+                        !o.unshifted && !o.interp && o.persistent;
+    return direct ? 0x7fffffff : b->ctx->fmm_crossover;
 }
 
 int chunk_slot(int chunk) {
@@ -535,9 +547,9 @@ FmmArgs fmm_roots_args(const FmmPlan *fp, const superdc_batch *b, const double *
 }
 
 // the FMM plan that applies to this call, or nullptr (rc = ENOMEM on allocation failure)
-FmmPlan *fmm_for(superdc_ctx *ctx, superdc_batch *b, const superdc_opts &o, int &rc) {
+FmmPlan *fmm_for(superdc_batch *b, const superdc_opts &o, int &rc, bool apply = false) {
     rc = SUPERDC_OK;
-    const int crossover = fmm_crossover_of(ctx, o);
+    const int crossover = fmm_crossover_of(b, o, apply);
     if (b->max_n < crossover) return nullptr;
     FmmPlan *fp = fmm_plan(b, o.fmm_leaf, crossover);
     if (!fp) {
@@ -652,7 +664,7 @@ int loewner_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const
     // large problems: zhat and b through the FMM (far boxes by moment expansions of the
     // Loewner log-sums and by equivalent sources for b), the others by direct products/sums
     int rc;
-    FmmPlan *fp = fmm_for(ctx, bm, o, rc);
+    FmmPlan *fp = fmm_for(bm, o, rc);
     if (rc) return rc;
     FmmvPackArgs pk{};
     FmmVec v{};
@@ -774,28 +786,33 @@ int apply_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const d
     a.ldy = ldy;
     a.fuse_b = fuse_b ? 1 : 0;
     a.bout = const_cast<double *>(bnorm);  // written only with fuse_b
-    const int use_mfma =
-        fuse_b ? 1 : (o.apply_kernel == 2 ? 1 : (o.apply_kernel == 1 ? 0 : (m >= 4)));
     superdc_batch *bm = const_cast<superdc_batch *>(b);
     const TileList *L = tile_list(bm, TILE);
     if (!L) return SUPERDC_ENOMEM;
+    // few columns: the VALU kernel does less work, the MFMA kernel is the faster alone (one
+    // problem of 100 roots and one column: 3 against 9 us)
+    const int use_mfma = fuse_b || o.apply_kernel == 2 ||
+                         (o.apply_kernel == 0 && (m >= 4 || L->count < 2 * ctx->num_cu));
     // Y = Qhat^T X of the large problems by the eigenvector-side FMM (the sums run over the
     // poles for every root, the layout of the solver's lists), Y = Qhat X by the FMM of the
     // sums over the roots (sources at the roots, targets at the poles, lists of their own);
     // the other problems by the direct kernels
     int rc;
-    FmmPlan *fp = fmm_for(ctx, bm, o, rc);
+    FmmPlan *fp = fmm_for(bm, o, rc, true);
     if (rc) return rc;
+    // the solve left lists only if it used the FMM as well
+    if (fmm_crossover_of(b, o) == 0x7fffffff) reuse_lists = false;
     if (o.persistent) {
         a.tiles = fp ? fp->dir_lpt[chunk_slot(TILE)] : L->lpt;
         a.ntiles = fp ? fp->dir_count[chunk_slot(TILE)] : L->count;
-        SDC_HIP(launch_apply(a, use_mfma, ctx->num_cu, s));
+        SDC_HIP(launch_apply(a, use_mfma, fp ? fp->max_dir : b->max_n, ctx->num_cu, s));
     } else {
         for (int p = 0; p < b->nprob; ++p) {
             if (fp && fp->fmm_of_h[p] >= 0) continue;
             a.tiles = L->nat + L->begin[p];
             a.ntiles = L->begin[p + 1] - L->begin[p];
-            SDC_HIP(launch_apply(a, use_mfma, ctx->num_cu, s));
+            const int np = (int)(b->off_h[p + 1] - b->off_h[p]);
+            SDC_HIP(launch_apply(a, use_mfma, np, ctx->num_cu, s));
         }
     }
     if (!fp) return SUPERDC_OK;
@@ -926,6 +943,10 @@ int superdc_batch_create(superdc_ctx *ctx, int32_t nprob, const int64_t *off_hos
     b->nprob = nprob;
     b->total = off_host[nprob];
     b->max_n = max_n;
+    for (int p = 0; p < nprob; ++p) {
+        const double n = (double)(off_host[p + 1] - off_host[p]);
+        if (n >= ctx->fmm_crossover) b->big_pairs += n * n;
+    }
     b->off_h.assign(off_host, off_host + nprob + 1);
     b->order.resize(nprob);
     std::iota(b->order.begin(), b->order.end(), 0);
@@ -999,7 +1020,7 @@ int superdc_secular_solve(superdc_ctx *ctx, const superdc_batch *b, const double
     superdc_batch *bm = const_cast<superdc_batch *>(b);
     // problems at or above the crossover size use the triangular FMM (method 2: every
     // problem large enough to have two leaves; method 1: none)
-    const int crossover = fmm_crossover_of(ctx, o);
+    const int crossover = fmm_crossover_of(b, o);
     FmmPlan *fp = nullptr;
     if (b->max_n >= crossover) {
         fp = fmm_plan(bm, o.fmm_leaf, crossover);

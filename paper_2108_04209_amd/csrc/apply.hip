@@ -56,8 +56,7 @@ struct ApplyStage {
 
 template <int TRANS, int NCT>
 __device__ __forceinline__ void apply_fetch(const ApplyArgs &a, int64_t base, int n, int s0,
-                                            int c0, int ncols, ApplyStage<NCT> &st) {
-    const int tid = threadIdx.x;
+                                            int c0, int ncols, int tid, ApplyStage<NCT> &st) {
     const int64_t s = base + min(s0 + tid % AP_K, n - 1);
     const double *x = a.X + s + (int64_t)c0 * a.ldx;
     st.sc = (TRANS == 0 ? a.bnorm : a.zhat)[s];
@@ -73,9 +72,8 @@ __device__ __forceinline__ void apply_fetch(const ApplyArgs &a, int64_t base, in
 }
 
 template <int TRANS, int NCT>
-__device__ __forceinline__ void apply_store(int n, int s0, int ncols, const ApplyStage<NCT> &st,
-                                            double *Xs, double2 *Sd) {
-    const int tid = threadIdx.x;
+__device__ __forceinline__ void apply_store(int n, int s0, int ncols, int tid,
+                                            const ApplyStage<NCT> &st, double *Xs, double2 *Sd) {
     const bool in = s0 + tid % AP_K < n;
     if (wave_uniform(tid / WAVE) == 0)
         Sd[tid] = make_double2(st.sd.x, TRANS && !in ? 0.0 : st.sd.y);
@@ -88,14 +86,24 @@ __device__ __forceinline__ void apply_store(int n, int s0, int ncols, const Appl
 }
 
 // NCT: 16-column blocks per pass (the pass width is 16 NCT columns); this item's pass starts
-// at column c0.  FB: form b beside the columns
-template <int TRANS, int NCT, bool FB>
-__device__ void apply_tile_mfma(const ApplyArgs &a, Tile t, int c0, double *Xs, double2 *Sd) {
+// at column c0.  FB: form b beside the columns.  TEAMS teams of four wavefronts take the
+// reduction's chunks in turn and add their sums in team order, for launches with too few items
+// to fill the chip (the levels of a 1024-row HSS conquer: 6.2 -> 5.3 us a launch on average)
+template <int NCT>
+struct ApplyTeam {
+    double Xs[2][16 * NCT * AP_LD];
+    double2 Sd[2][AP_K];
+};
+
+template <int TRANS, int NCT, bool FB, int TEAMS>
+__device__ void apply_tile_mfma(const ApplyArgs &a, Tile t, int c0, ApplyTeam<NCT> *sh) {
     const int p = t.prob;
     const int64_t base = a.off[p];
     const int n = (int)(a.off[p + 1] - base);
     const int lane = lane_id();
-    const int wv = threadIdx.x / WAVE;
+    const int wave = wave_uniform((int)(threadIdx.x / WAVE));
+    const int tm = wave >> 2, wv = wave & 3;  // team, wavefront of the team
+    const int tid = threadIdx.x & 255;        // thread of the team
     const int o0 = t.row0;
     const int ncols = min(16 * NCT, a.m - c0);
     if (a.status[p] & ~SUPERDC_ST_NOCONV) {
@@ -122,17 +130,22 @@ __device__ void apply_tile_mfma(const ApplyArgs &a, Tile t, int c0, double *Xs, 
     // VALU beside the multiply (one column does not need the MFMA)
     double bsum = 0.0;
     ApplyStage<NCT> st;
-    apply_fetch<TRANS, NCT>(a, base, n, 0, c0, ncols, st);
+    const int nch = (n + AP_K - 1) / AP_K, rounds = (nch + TEAMS - 1) / TEAMS;
+    if (tm < nch) apply_fetch<TRANS, NCT>(a, base, n, tm * AP_K, c0, ncols, tid, st);
     asm volatile("" : "+v"(ra), "+v"(rb));  // loaded here, not inside the loop
     // one barrier per chunk: a buffer is stored again two chunks later, behind the barrier
     // that every wavefront reaches after its last read of it
-    for (int s0 = 0, buf = 0; s0 < n; s0 += AP_K, buf ^= 1) {
-        double *Xb = Xs + buf * (16 * NCT * AP_LD);
-        double2 *Sb = Sd + buf * AP_K;
-        apply_store<TRANS, NCT>(n, s0, ncols, st, Xb, Sb);
+    for (int rd = 0; rd < rounds; ++rd) {
+        double *Xb = sh[tm].Xs[rd & 1];
+        double2 *Sb = sh[tm].Sd[rd & 1];
+        const int ci = rd * TEAMS + tm;
+        const bool live = ci < nch;
+        if (live) apply_store<TRANS, NCT>(n, ci * AP_K, ncols, tid, st, Xb, Sb);
         __syncthreads();
         // the next chunk's loads are in flight while this one is multiplied
-        if (s0 + AP_K < n) apply_fetch<TRANS, NCT>(a, base, n, s0 + AP_K, c0, ncols, st);
+        if (ci + TEAMS < nch)
+            apply_fetch<TRANS, NCT>(a, base, n, (ci + TEAMS) * AP_K, c0, ncols, tid, st);
+        if (!live) continue;
         // one step of 4 sources: this lane's Cauchy entry (one reciprocal with a Newton
         // step) into the MFMA of every column tile; padding entries have weight zero at the
         // position of the problem's last source
@@ -163,6 +176,25 @@ __device__ void apply_tile_mfma(const ApplyArgs &a, Tile t, int c0, double *Xs, 
         atomicAdd(a.work, rows * (unsigned long long)n * (2 * me + 3) + 2 * rows * me);
     }
     mfma_drain();
+    if (TEAMS > 1) {  // the teams' sums through their own buffers, added in team order
+        static_assert(NCT == 1 || TEAMS == 1, "one column tile per team");
+        double *mine = &sh[tm].Xs[0][0] + wv * 5 * WAVE;
+        static_assert(4 * 5 * WAVE <= 2 * 16 * AP_LD, "a team's sums fit its buffers");
+        __syncthreads();
+        if (tm > 0) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) mine[v * WAVE + lane] = acc[0][v];
+            if (FB) mine[4 * WAVE + lane] = bsum;
+        }
+        __syncthreads();
+        if (tm > 0) return;
+        for (int u = 1; u < TEAMS; ++u) {
+            const double *o = &sh[u].Xs[0][0] + wv * 5 * WAVE;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) acc[0][v] += o[v * WAVE + lane];
+            if (FB) bsum += o[4 * WAVE + lane];
+        }
+    }
     // v_mfma_f64_16x16x4f64 returns D[4 v + lane/16][lane % 16] in accumulator v
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
@@ -184,12 +216,12 @@ __device__ void apply_tile_mfma(const ApplyArgs &a, Tile t, int c0, double *Xs, 
     }
 }
 
-template <int TRANS, int NCT, bool FB>
-__global__ __launch_bounds__(256) void k_apply_mfma(ApplyArgs a) {
-    __shared__ double Xs[2 * 16 * NCT * AP_LD];
-    __shared__ double2 Sd[2 * AP_K];
+template <int TRANS, int NCT, bool FB, int TEAMS>
+__global__ __launch_bounds__(256 * TEAMS) void k_apply_mfma(ApplyArgs a) {
+    __shared__ ApplyTeam<NCT> sh[TEAMS];
     const int np = (a.m + 16 * NCT - 1) / (16 * NCT);  // passes of a tile: neighbouring items
-    apply_tile_mfma<TRANS, NCT, FB>(a, a.tiles[blockIdx.x / np], blockIdx.x % np * (16 * NCT), Xs, Sd);
+    apply_tile_mfma<TRANS, NCT, FB, TEAMS>(a, a.tiles[blockIdx.x / np],
+                                           blockIdx.x % np * (16 * NCT), sh);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -291,7 +323,7 @@ __global__ __launch_bounds__(WAVE * AV_W) void k_apply_valu(ApplyArgs a) {
     apply_tile_valu<TRANS>(a, a.tiles[blockIdx.x], Xs, Sd, red);
 }
 
-hipError_t launch_apply(const ApplyArgs &a0, int use_mfma, int num_cu, hipStream_t s) {
+hipError_t launch_apply(const ApplyArgs &a0, int use_mfma, int max_n, int num_cu, hipStream_t s) {
     if (a0.ntiles <= 0) return hipSuccess;
     ApplyArgs a = a0;
     a.work = trace_work(use_mfma ? KID_APPLY_MFMA : KID_APPLY_VALU);
@@ -302,17 +334,21 @@ hipError_t launch_apply(const ApplyArgs &a0, int use_mfma, int num_cu, hipStream
         auto items = [&] { return a.ntiles * ((a.m + 16 * nct - 1) / (16 * nct)); };
         while (nct > 1 && items() < 2 * num_cu) nct /= 2;
         const dim3 g(items());
-#define SDC_APPLY_MFMA(T, C, FB) \
-    SDC_LAUNCH(KID_APPLY_MFMA, (k_apply_mfma<T, C, FB>), g, dim3(256), 0, s, a)
+        const bool teams = nct == 1 && items() < 2 * num_cu && max_n > 2 * AP_K;
+#define SDC_APPLY_MFMA(T, C, FB, K)                                                         \
+    SDC_LAUNCH(KID_APPLY_MFMA, (k_apply_mfma<T, C, FB, K>), g, dim3(256 * K), 0, s, a)
         if (a.trans) {
-            if (a.fuse_b) SDC_APPLY_MFMA(1, 1, true);
-            else if (nct == 1) SDC_APPLY_MFMA(1, 1, false);
-            else if (nct == 2) SDC_APPLY_MFMA(1, 2, false);
-            else SDC_APPLY_MFMA(1, 4, false);
+            if (a.fuse_b && teams) SDC_APPLY_MFMA(1, 1, true, 4);
+            else if (a.fuse_b) SDC_APPLY_MFMA(1, 1, true, 1);
+            else if (teams) SDC_APPLY_MFMA(1, 1, false, 4);
+            else if (nct == 1) SDC_APPLY_MFMA(1, 1, false, 1);
+            else if (nct == 2) SDC_APPLY_MFMA(1, 2, false, 1);
+            else SDC_APPLY_MFMA(1, 4, false, 1);
         } else {
-            if (nct == 1) SDC_APPLY_MFMA(0, 1, false);
-            else if (nct == 2) SDC_APPLY_MFMA(0, 2, false);
-            else SDC_APPLY_MFMA(0, 4, false);
+            if (teams) SDC_APPLY_MFMA(0, 1, false, 4);
+            else if (nct == 1) SDC_APPLY_MFMA(0, 1, false, 1);
+            else if (nct == 2) SDC_APPLY_MFMA(0, 2, false, 1);
+            else SDC_APPLY_MFMA(0, 4, false, 1);
         }
 #undef SDC_APPLY_MFMA
     } else {

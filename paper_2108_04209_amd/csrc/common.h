@@ -209,6 +209,7 @@ struct superdc_batch {
     int64_t *off_d = nullptr;
     std::vector<void *> mem;            // the device memory of every array below
     std::vector<int> order;             // problems, longest first
+    double big_pairs = 0.0;             // sum of n^2 over the problems of the FMM's sizes
     TileList lists[sdc::kNumChunks];    // by cut length
     // chosen launch shapes (heuristic, or set by the autotuner): batched launches
     LaunchShape sec, vec, app, bwd;
@@ -230,8 +231,9 @@ int chunk_slot(int chunk);
 const TileList *tile_list(superdc_batch *b, int chunk);
 // SUPERDC_OK or SUPERDC_EINVAL for an options struct
 int opts_check(const superdc_opts *o);
-// problems of at least this many roots use the triangular FMM under these options
-int fmm_crossover_of(const superdc_ctx *ctx, const superdc_opts &o);
+// problems of at least this many roots use the triangular FMM under these options: in the solver,
+// Loewner and b calls, and (apply) in the Cauchy applies
+int fmm_crossover_of(const superdc_batch *b, const superdc_opts &o, bool apply = false);
 // launch shape of the plain (one launch per problem) direct solve of an n-root problem
 ::LaunchShape plain_shape(const superdc_ctx *ctx, int64_t n);
 // the allocation-free solve's scratch array: its address on `device` is looked up once
@@ -323,7 +325,8 @@ struct ApplyArgs {
     unsigned long long *work;  // kernel timing on: algorithmic flops of the launch, (2m + 3)
                                // per Cauchy entry plus 2m per output row (set by launch_apply)
 };
-hipError_t launch_apply(const ApplyArgs &a, int use_mfma, int num_cu, hipStream_t s);
+// max_n: the launch's largest problem
+hipError_t launch_apply(const ApplyArgs &a, int use_mfma, int max_n, int num_cu, hipStream_t s);
 
 struct BwdArgs {
     const int64_t *off;

@@ -152,7 +152,7 @@ int superdc_autotune(superdc_ctx *ctx, superdc_batch *b, const double *d, const 
         }
         b->sec = bs;
         // the FMM solver's split, when some problem of the batch uses the FMM
-        if (b->max_n >= fmm_crossover_of(ctx, o)) {
+        if (b->max_n >= fmm_crossover_of(b, o)) {
             float bestf = 1e30f;
             int bf = 0;
             for (int S = 1; S <= 8; S *= 2) {

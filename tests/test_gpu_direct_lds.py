@@ -62,3 +62,20 @@ def test_direct_solver_cap_and_invalid(orc):
     assert np.all(np.isnan(bad["lam"][a:e])) and np.all(bad["iters"][a:e] == native.ITER_SKIPPED)
     keep = np.r_[0:a, e:batch.total_n]
     np.testing.assert_array_equal(bad["lam"][keep], ref["lam"][keep])
+
+
+@pytest.mark.parametrize("sizes,direct", [([1024], True), ([4096, 300], True), ([1024] * 38, True),
+                                          ([1024] * 39, False), ([4097], False),
+                                          ([2048] * 10, False)])
+def test_small_batches_by_direct_sums(sizes, direct):
+    """The automatic method takes direct sums for a batch of few pole-root pairs (4e7 over the
+    problems of 1024 roots and more, none above 4096) and the FMM from there: bit for bit
+    what method 1, or a crossover of 1024 given, computes."""
+    from paper_2108_04209_amd import native
+    from tests import gpu_pipeline as gp
+    batch = gen.small_batch(sizes, seed=83)
+    auto = gp.run(batch)
+    same = gp.run(batch, opts=native.default_opts(method=1) if direct
+                  else native.default_opts(fmm_crossover=1024))
+    for k in ("lam", "eta", "origin", "zhat", "b"):
+        assert np.array_equal(auto[k], same[k]), k
