@@ -428,7 +428,7 @@ FmmPlan *fmm_plan(superdc_batch *b, int leaf, int crossover) {
         fp->split *= 2;
     // the solver's items (pieces of ssub roots that never cross a leaf)
     std::vector<Tile> snat, slpt;
-    fp->ssub = leaf % (2 * TILE) == 0 ? 2 * TILE : TILE;  // divides the leaf
+    fp->ssub = TILE;
     fp->sitem_off_h.push_back(0);
     for (int q = 0; q < fp->nfmm; ++q) {
         const int p = fp->fmm_prob_h[q];
@@ -442,10 +442,16 @@ FmmPlan *fmm_plan(superdc_batch *b, int leaf, int crossover) {
         if (q < 0) continue;
         for (int t = fp->sitem_off_h[q]; t < fp->sitem_off_h[q + 1]; ++t) slpt.push_back(snat[t]);
     }
-    fp->ssplit = 1;
-    while (fp->ssplit < 8 &&
-           (long)fp->snitems * fp->ssplit * 2 <= (long)b->ctx->num_cu * SDC_FMM_WAVES_PER_CU)
-        fp->ssplit *= 2;
+    // wavefronts per item of the solver: fewer repeat less of a root's step and window, more
+    // fill the chip (batches of 4096 to 65536 roots a problem, us a solve with 1, 2, 4, 8:
+    // 128 items 104 77 66 64, 1024 items 134 117 110 127, 4096 items 289 248 256 329, 32768
+    // items 1556 1583 1745 2328); a larger leaf takes more, for the LDS it is staged in
+    const long cu = b->ctx->num_cu;
+    fp->ssplit = fp->snitems <= cu        ? 8
+                 : fp->snitems <= 12 * cu ? 4
+                 : fp->snitems <= 64 * cu ? 2
+                                          : 1;
+    while (fp->ssplit < 8 && fp->ssplit * 64 < leaf) fp->ssplit *= 2;
     Upload up;
     up.add(&fp->fmm_prob, fp->fmm_prob_h);
     up.add(&fp->fmm_of, fp->fmm_of_h);

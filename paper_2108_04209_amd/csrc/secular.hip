@@ -899,16 +899,25 @@ __device__ __forceinline__ void team_total(int g, double &a, double &b, double &
 }
 
 // poles [j0, j1) on one side of every live root, two with one reciprocal (as secular_range,
-// under the same condition on |t|; false, with nothing done, outside it).  Every lane takes
-// the same number of rounds, 2^lg pairs each, so that the loop is one scalar-counted run of
-// independent loads; the last, partial round is masked.
-// da, db: the range's end poles.
-__device__ __forceinline__ bool lds_side(const double2 *P, int j0, int j1, double da, double db,
+// under the same condition on |t|; one by one outside it).  Every lane takes the same number
+// of rounds, 2^lg pairs each, so that the loop is one scalar-counted run of independent
+// loads; the last, partial round is masked.
+// da, db: poles at or beyond the range's ends.
+__device__ __forceinline__ void lds_side(const double2 *P, int j0, int j1, double da, double db,
                                          int sub, int lg, double dK, double y, double &s0,
                                          double &s1) {
-    if (j0 >= j1) return true;
+    if (j0 >= j1) return;
+    auto single = [&](double2 pw) {
+        const double r = rcp_nr1((pw.x - dK) - y);
+        const double wr = pw.y * r;
+        s0 += wr;
+        s1 = __builtin_fma(wr, r, s1);
+    };
     const double ta = fabs((da - dK) - y), tb = fabs((db - dK) - y);
-    if (__ballot(!(fmin(ta, tb) >= 0x1p-300 && fmax(ta, tb) <= 0x1p300)) != 0ull) return false;
+    if (__ballot(!(fmin(ta, tb) >= 0x1p-300 && fmax(ta, tb) <= 0x1p300)) != 0ull) {
+        for (int j = j0 + sub; j < j1; j += 1 << lg) single(P[j]);
+        return;
+    }
     auto pair = [&](double2 pa, double2 pb) {
         const double t0 = (pa.x - dK) - y, t1 = (pb.x - dK) - y;
         const double R = rcp_nr1(t0 * t1);
@@ -933,13 +942,8 @@ __device__ __forceinline__ bool lds_side(const double2 *P, int j0, int j1, doubl
     if (sub < left) {
         pair(q[0], q[1]);
     } else if (sub == left && ((j1 - j0) & 1)) {
-        const double2 pw = P[j1 - 1];
-        const double r = rcp_nr1((pw.x - dK) - y);
-        const double wr = pw.y * r;
-        s0 += wr;
-        s1 = __builtin_fma(wr, r, s1);
+        single(P[j1 - 1]);
     }
-    return true;
 }
 
 // poles [j0, j1) by the sign of their terms: negative ones (left of the iterate) to psi
@@ -969,29 +973,26 @@ __device__ __forceinline__ void lds_window(const double2 *P, int j0, int j1, int
     if (sub < (j1 - j0) - (full << lg)) term(q[0]);
 }
 
-__device__ void secular_lds_item(const SolveArgs &a, Tile t, double2 *P) {
-    const int p = t.prob;
-    const int64_t base = a.off[p];
-    const int n = (int)(a.off[p + 1] - base);
-    const int lane = lane_id();
-    const int wv = wave_uniform((int)(threadIdx.x / WAVE));
-    const int i0 = t.row0, i1 = min(n, t.row0 + a.chunk);
-    if (a.status[p] & ~SUPERDC_ST_NOCONV) {  // invalid input: outputs are NaN
-        const double nan = __builtin_nan("");
-        for (int k = i0 + (int)threadIdx.x; k < i1; k += blockDim.x) {
-            a.lam[base + k] = nan;
-            a.eta[base + k] = nan;
-            a.origin[base + k] = k;
-            if (a.iters) a.iters[base + k] = SUPERDC_ITER_SKIPPED;
-            a.ke[base + k] = make_double2(nan, nan);
-        }
-        return;
+// invalid input: the outputs of an item's roots [i0, i1) are NaN
+__device__ __forceinline__ void invalid_roots(const SolveArgs &a, int64_t base, int i0, int i1) {
+    const double nan = __builtin_nan("");
+    for (int k = i0 + (int)threadIdx.x; k < i1; k += blockDim.x) {
+        a.lam[base + k] = nan;
+        a.eta[base + k] = nan;
+        a.origin[base + k] = k;
+        if (a.iters) a.iters[base + k] = SUPERDC_ITER_SKIPPED;
+        a.ke[base + k] = make_double2(nan, nan);
     }
-    for (int j = threadIdx.x; j < n; j += blockDim.x) P[j] = a.dw[base + j];
-    __syncthreads();
-    // this wavefront's roots [c0, c1), at most one to a lane
-    const int nw = blockDim.x / WAVE, share = (i1 - i0 + nw - 1) / nw;
-    const int c0 = min(i1, i0 + wv * share), c1 = min(i1, c0 + share);
+}
+
+// A wavefront's roots [c0, c1) of problem p, at most one to a lane.  pole(j): d_j;
+// sums(sub, lg, dK, y, psi, dpsi, phi, dphi): adds the terms of lane `sub` of a team of 2^lg
+// lanes at the iterate y from origin dK (pairs of them over the team, kernel timing only).
+template <class POLE, class SUMS>
+__device__ __forceinline__ void secular_teams(const SolveArgs &a, int p, int64_t base, int n,
+                                              int c0, int c1, unsigned long long pairs,
+                                              POLE pole, SUMS sums) {
+    const int lane = lane_id();
     const double z2 = a.z2[p];
     const double eps = 2.220446049250313e-16;
     const double tol = a.stop_c * (double)n * eps;
@@ -1000,14 +1001,9 @@ __device__ void secular_lds_item(const SolveArgs &a, Tile t, double2 *P) {
     int k = c0 + (lane >> lg), K = k, nev = -1;  // evaluations after the midpoint pass
     bool act = k < c1, last = k == n - 1, hi_closed = false, noconv = false;
     if (!act) k = K = c0;
-    double dk = P[k].x, dk1 = P[min(k + 1, n - 1)].x, dK = dk, lo = 0.0, hi = 0.0;
+    double dk = pole(k), dk1 = pole(min(k + 1, n - 1)), dK = dk, lo = 0.0, hi = 0.0;
     double y = last ? 0.5 * z2 : 0.5 * (dk1 - dk);  // midpoint pass
     unsigned long long work = 0, live = 0, slots = 0;
-    // the window, this wavefront's own poles: those left of it feed psi, right of it phi, its
-    // own by sign
-    const int w0 = c0, w1 = c1;
-    const double d0 = P[0].x, dn = P[n - 1].x;
-    const double dl = P[max(w0 - 1, 0)].x, dr = P[min(w1, n - 1)].x;  // poles beside the window
     for (;;) {
         const unsigned long long actm = __ballot(act);
         if (actm == 0ull) break;
@@ -1038,14 +1034,11 @@ __device__ void secular_lds_item(const SolveArgs &a, Tile t, double2 *P) {
         }
         const int sub = lane & (g - 1);
         double psi = 0.0, dpsi = 0.0, phi = 0.0, dphi = 0.0;
-        int r0 = w0, r1 = w1;
-        if (!lds_side(P, 0, w0, d0, dl, sub, lg, dK, y, psi, dpsi)) r0 = 0;
-        if (!lds_side(P, w1, n, dr, dn, sub, lg, dK, y, phi, dphi)) r1 = n;
-        lds_window(P, r0, r1, sub, lg, dK, y, psi, dpsi, phi, dphi);
+        sums(sub, lg, dK, y, psi, dpsi, phi, dphi);
         team_total(g, psi, dpsi, phi, dphi);
         if (a.work) {
             const unsigned long long nroot = (unsigned long long)__popcll(__ballot(act && sub == 0));
-            work += (unsigned long long)n * nroot;
+            work += pairs * nroot;
             live += (unsigned long long)__popcll(__ballot(act));
             slots += WAVE;
         }
@@ -1123,14 +1116,160 @@ __device__ void secular_lds_item(const SolveArgs &a, Tile t, double2 *P) {
     }
 }
 
+__device__ void secular_lds_item(const SolveArgs &a, Tile t, double2 *P) {
+    const int p = t.prob;
+    const int64_t base = a.off[p];
+    const int n = (int)(a.off[p + 1] - base);
+    const int wv = wave_uniform((int)(threadIdx.x / WAVE));
+    const int i0 = t.row0, i1 = min(n, t.row0 + a.chunk);
+    if (a.status[p] & ~SUPERDC_ST_NOCONV) {
+        invalid_roots(a, base, i0, i1);
+        return;
+    }
+    for (int j = threadIdx.x; j < n; j += blockDim.x) P[j] = a.dw[base + j];
+    __syncthreads();
+    // this wavefront's roots are the window: the poles left of it feed psi, those right of it
+    // phi, its own by sign
+    const int nw = blockDim.x / WAVE, share = (i1 - i0 + nw - 1) / nw;
+    const int c0 = min(i1, i0 + wv * share), c1 = min(i1, c0 + share);
+    const double d0 = P[0].x, dn = P[n - 1].x;
+    const double dl = P[max(c0 - 1, 0)].x, dr = P[min(c1, n - 1)].x;  // beside the window
+    secular_teams(a, p, base, n, c0, c1, (unsigned long long)n, [&](int j) { return P[j].x; },
+                  [&](int sub, int lg, double dK, double y, double &psi, double &dpsi,
+                      double &phi, double &dphi) {
+                      lds_side(P, 0, c0, d0, dl, sub, lg, dK, y, psi, dpsi);
+                      lds_side(P, c1, n, dr, dn, sub, lg, dK, y, phi, dphi);
+                      lds_window(P, c0, c1, sub, lg, dK, y, psi, dpsi, phi, dphi);
+                  });
+}
+
+// ---------------------------------------------------------------------------------------
+// The FMM solver in LDS: the same teams, over what a target leaf sums instead of all poles.
+// A workgroup takes 64 roots of one leaf and stages, in this order, the equivalent sources of
+// the far boxes left of it that are summed one by one, its near poles (ascending; the
+// item's own among them) and the far boxes right of it; the leaf's local expansion lies
+// behind them.  A leaf of more than `cap` entries, or whose lists overflowed, takes the
+// same iteration over loads from memory (team_sums).
+// Bound by the FP64 pipe (a level of 4096 problems, 98,000 leaves: the vector units are
+// busy all of the time, 79 % of it with pairs).  Measured against one to eight wavefronts
+// that split every root's sums and fetch the poles through the scalar cache, us a launch:
+// HSS levels of 65536 roots 71 -> 58, clustered poles 76 -> 60, the level 3118 -> 2730.
+// ---------------------------------------------------------------------------------------
+__device__ void secular_fmm_item(const SolveArgs &a, Tile t, const FmmArgs &f, double2 *P,
+                                 int cap) {
+    const int p = t.prob;
+    const int64_t base = a.off[p];
+    const int n = (int)(a.off[p + 1] - base);
+    const int lane = lane_id();
+    const int wv = wave_uniform((int)(threadIdx.x / WAVE));
+    const int i0 = t.row0, i1 = min(n, t.row0 + a.chunk);
+    if (a.status[p] & ~SUPERDC_ST_NOCONV) {
+        invalid_roots(a, base, i0, i1);
+        return;
+    }
+    const double2 *__restrict__ dw = a.dw + base;
+    const int nw = blockDim.x / WAVE, share = (i1 - i0 + nw - 1) / nw;
+    const int c0 = min(i1, i0 + wv * share), c1 = min(i1, c0 + share);
+    const int L = wave_uniform(f.leaf_off[f.fmm_of[p]] + t.row0 / f.leaf);
+    const int nn = wave_uniform(f.cnt[3 * (int64_t)L]);
+    const int nl = wave_uniform(f.cntd[2 * (int64_t)L]);
+    const int nr = wave_uniform(f.cntd[2 * (int64_t)L + 1]);
+    // lane e holds the e-th near range (empty: in the expansion) and where it is staged
+    int lo = 0, len = 0;
+    if (lane < nn && !f.near_lf[(int64_t)L * FMM_NEAR_MAX + lane]) {
+        lo = f.near_lo[(int64_t)L * FMM_NEAR_MAX + lane];
+        len = f.near_hi[(int64_t)L * FMM_NEAR_MAX + lane] - lo;
+    }
+    int end = len;
+    static_assert(FMM_NEAR_MAX <= 32, "the scan below covers 32 lanes");
+    for (int o = 1; o < 32; o <<= 1) {
+        const int v = __shfl_up(end, o);
+        if (lane >= o) end += v;
+    }
+    const int nnear = __builtin_amdgcn_readlane(end, FMM_NEAR_MAX - 1);
+    const int total = nl * FMM_P + nnear + nr * FMM_P;
+    const int at = nl * FMM_P + end - len;  // staged place of the range's first pole
+    const unsigned long long own = __ballot(len > 0 && lo <= i0 && i0 < lo + len);
+    const bool staged = nn >= 0 && total <= cap && own != 0ull;
+    double *C = reinterpret_cast<double *>(P + cap);
+    int w0 = 0;  // staged place of this wavefront's first pole
+    if (staged) {
+        const int tid = threadIdx.x, nt = blockDim.x;
+        const int e = __builtin_ctzll(own);
+        w0 = c0 - __builtin_amdgcn_readlane(lo, e) + __builtin_amdgcn_readlane(at, e);
+        for (int j = 0; j < nn; ++j) {
+            const int l = __builtin_amdgcn_readlane(lo, j), m = __builtin_amdgcn_readlane(len, j);
+            double2 *q = P + __builtin_amdgcn_readlane(at, j);
+            for (int i = tid; i < m; i += nt) q[i] = dw[l + i];
+        }
+        for (int i = tid; i < nl * FMM_P; i += nt) {
+            const int g = f.far_ld[(int64_t)L * FMM_FAR_MAX + i / FMM_P];
+            P[i] = f.eq[(int64_t)g * FMM_P + i % FMM_P];
+        }
+        for (int i = tid; i < nr * FMM_P; i += nt) {
+            const int g = f.far_rd[(int64_t)L * FMM_FAR_MAX + i / FMM_P];
+            P[nl * FMM_P + nnear + i] = f.eq[(int64_t)g * FMM_P + i % FMM_P];
+        }
+        for (int i = tid; i < FMM_LOC; i += nt) C[i] = f.loc[(int64_t)L * FMM_LOC + i];
+    }
+    __syncthreads();
+    if (c0 >= c1) return;
+    const int w1 = w0 + c1 - c0;
+    const double2 cw = f.loc_ab[L];
+    const double iw = cw.y > 0x1p-1000 ? 1.0 / cw.y : 0.0;
+    // bounds of the staged positions: the problem's end poles, those beside the window
+    const double d0 = dw[0].x, dn = dw[n - 1].x;
+    const double dl = dw[max(c0 - 1, 0)].x, dr = dw[min(c1, n - 1)].x;
+    // pair evaluations per root and pass: the local expansion (four 20-term Clenshaw series,
+    // each 19 steps of a subtraction and an FMA and a last FMA: 240 flops) counts as 34
+    static_assert(FMM_PL == 20, "the local expansion's pair count");
+    secular_teams(a, p, base, n, c0, c1, (unsigned long long)(nn >= 0 ? total + 34 : n),
+                  [&](int j) { return dw[j].x; },
+                  [&](int sub, int lg, double dK, double y, double &psi, double &dpsi,
+                      double &phi, double &dphi) {
+                      if (!staged) {
+                          team_sums(&f, L, nn, nl, nr, dw, 0, n, dK, y, 0, 1, sub, 1 << lg, false,
+                                    psi, dpsi, phi, dphi);
+                          return;
+                      }
+                      lds_side(P, 0, w0, d0, dl, sub, lg, dK, y, psi, dpsi);
+                      lds_side(P, w1, total, dr, dn, sub, lg, dK, y, phi, dphi);
+                      lds_window(P, w0, w1, sub, lg, dK, y, psi, dpsi, phi, dphi);
+                      // the local expansion's four series, spread over the team
+                      const double x = dK + y;
+                      const double tc = fmin(1.0, fmax(-1.0, (x - cw.x) * iw));
+                      for (int fn = sub; fn < 4; fn += 1 << lg) {
+                          const double *c = C + fn * FMM_PL;
+                          double b1 = 0.0, b2 = 0.0;
+#pragma unroll
+                          for (int j = FMM_PL - 1; j >= 1; --j) {
+                              const double b0 = __builtin_fma(2.0 * tc, b1, c[j] - b2);
+                              b2 = b1;
+                              b1 = b0;
+                          }
+                          const double r = __builtin_fma(tc, b1, c[0] - b2);
+                          psi += fn == 0 ? r : 0.0;
+                          dpsi += fn == 1 ? r : 0.0;
+                          phi += fn == 2 ? r : 0.0;
+                          dphi += fn == 3 ? r : 0.0;
+                      }
+                  });
+}
+
 // dynamic LDS: 16 bytes per pole of the launch's largest problem
 __global__ __launch_bounds__(512, 4) void k_secular_lds(SolveArgs a) {
     extern __shared__ double2 poles[];
     secular_lds_item(a, a.tiles[blockIdx.x], poles);
 }
 
-// FMM problems: one work item per 64-root piece of a target leaf; blockDim.x = 64 S with
-// the same dynamic LDS as k_secular
+// dynamic LDS: 16 bytes per staged entry (cap of them) and the local expansion
+__global__ __launch_bounds__(512, 4) void k_secular_fmm_lds(SolveArgs a, FmmArgs f, int cap) {
+    extern __shared__ double2 poles[];
+    secular_fmm_item(a, a.tiles[blockIdx.x], f, poles, cap);
+}
+
+// the same problems' unshifted and hybrid ablations; blockDim.x = 64 S with the same dynamic
+// LDS as k_secular
 template <bool UNSH>
 __global__ __launch_bounds__(512) void k_secular_fmm(SolveArgs a, FmmArgs f) {
     extern __shared__ double red[];
@@ -1140,6 +1279,16 @@ __global__ __launch_bounds__(512) void k_secular_fmm(SolveArgs a, FmmArgs f) {
 hipError_t launch_secular_fmm(const SolveArgs &a, const FmmArgs &f, int split, hipStream_t s) {
     if (a.ntiles <= 0) return hipSuccess;
     if (split < 1 || split > 8 || (split & (split - 1))) return hipErrorInvalidValue;
+    if (!a.unshifted && !a.hybrid) {
+        // four wavefronts a SIMD fit the registers: each takes its part of the LDS, 10 KB (a
+        // leaf of 64 stages 130 to 330 entries on uniform poles, 600 fit)
+        const size_t loc = sizeof(double) * FMM_LOC;
+        const int cap = (int)((std::min(10240 * split, 65536) - loc) / sizeof(double2));
+        if (a.chunk > WAVE * split) return hipErrorInvalidValue;
+        SDC_LAUNCH(KID_SECULAR_FMM, k_secular_fmm_lds, dim3(a.ntiles), dim3(WAVE * split),
+                   sizeof(double2) * cap + loc, s, a, f, cap);
+        return hipGetLastError();
+    }
     const size_t lds = split > 1 ? sizeof(double4) * WAVE * split : 0;
     if (a.unshifted)
         SDC_LAUNCH(KID_SECULAR_FMM, k_secular_fmm<true>, dim3(a.ntiles),

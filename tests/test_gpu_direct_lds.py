@@ -79,3 +79,32 @@ def test_small_batches_by_direct_sums(sizes, direct):
                   else native.default_opts(fmm_crossover=1024))
     for k in ("lam", "eta", "origin", "zhat", "b"):
         assert np.array_equal(auto[k], same[k]), k
+
+
+@pytest.mark.parametrize("leaf", [64, 256, 1024])
+@pytest.mark.parametrize("kind,n", [("uniform", 2049), ("uniform", 20000), ("graded", 5000),
+                                    ("stairs", 9000)])
+def test_fmm_solver_in_lds(kind, n, leaf):
+    """FMM roots against direct sums: items staged in LDS, and leaves that do not fit (large
+    leaves, graded poles whose lists are long or overflow) by the same iteration over loads.
+    The stopping test |f| <= c n eps (1 + |psi| + |phi|) bounds each solution's error by
+    2 c n eps (lambda - d_0), as |psi| <= psi' (lambda - d_0)."""
+    from paper_2108_04209_amd import native
+    from tests import gpu_pipeline as gp
+    batch = gen.small_batch([n, n // 2 + 7], seed=89)
+    g = np.random.default_rng(89)
+    for p in range(2):
+        s, e = int(batch.off[p]), int(batch.off[p + 1])
+        m = e - s
+        if kind == "graded":
+            batch.d[s:e] = np.sort(np.exp(g.uniform(-20.0, 0.0, m))) + 1e-9 * np.arange(m)
+        elif kind == "stairs":
+            batch.d[s:e] = np.arange(m) // 64 + 1e-7 * (1.0 + np.arange(m) % 64)
+    fmm = gp.run(batch, opts=native.default_opts(method=2, fmm_leaf=leaf))
+    direct = gp.run(batch, opts=native.default_opts(method=1))
+    assert not fmm["status"].any() and not direct["status"].any()
+    for p in range(2):
+        s, e = int(batch.off[p]), int(batch.off[p + 1])
+        span = batch.d[e - 1] - batch.d[s] + batch.rho[p] * np.sum(batch.z[s:e] ** 2)
+        tol = 4.0 * native.default_opts().stop_c * (e - s) * 2.0 ** -52 * span
+        assert np.max(np.abs(fmm["lam"][s:e] - direct["lam"][s:e])) <= tol
