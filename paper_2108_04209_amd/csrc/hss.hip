@@ -8,6 +8,8 @@
 // [q n_l, (q+1) n_l), n_l = leaf 2^(depth-l).  Per-level column blocks (update columns Z,
 // basis columns W) are column-major with leading dimension n.  Small generators are
 // row-major r x r, stored per node in level order (heap index 2^l - 1 + q).
+#include <type_traits>
+
 #include "common.h"
 #include "hss.h"
 
@@ -15,8 +17,8 @@ namespace sdc {
 
 // ---------------------------------------------------------------------------------------
 // leaf eigendecomposition: cyclic Jacobi in three kernels:
-//   k_leaf_jacobi  rotates A -- kept by position, its upper triangle packed by rows
-//                  (66 KB for a leaf of 128) -- in LDS, two leaves to a CU (the rounds are
+//   k_leaf_jacobi  rotates A -- kept by position, its upper triangle in lines of two rows
+//                  (66 KB for a leaf of 128) -- in LDS, two such leaves to a CU (the rounds are
 //                  short and end in a barrier: a second leaf's waves fill the first one's
 //                  waits), and logs every round's rotations to HBM as (cos, signed sin) by
 //                  position;
@@ -29,12 +31,18 @@ namespace sdc {
 // the reversed order, so a sweep reverses the positions), and a pair's rotation only ever
 // touches two neighbouring positions.
 // ---------------------------------------------------------------------------------------
-constexpr int LJ_THREADS = 1024;
-constexpr int LJ_PACKED = LEAF_MAX * (LEAF_MAX + 1) / 2;
-// slots of the folded block triangle per thread: (h/2)(h+1) blocks, h = LEAF_MAX/2 rounded
-// up to even, over the threads past the first wavefront
-constexpr int LJ_BLK =
-    ((LEAF_MAX / 4) * (LEAF_MAX / 2 + 1) + LJ_THREADS - WAVE - 1) / (LJ_THREADS - WAVE);
+constexpr int LJ_TILE = 4;  // rows and columns of a thread's tile: two pairs of each
+// Tile rows a and T-1-a together have T-1 tiles right of the diagonal: they go to one group of
+// lanes.  Threads: the first wavefront and one tile a lane, but at most 8 wavefronts, so that
+// two leaves of 128 share a CU at 128 registers; the last wavefront then takes the groups
+// left over as well (nine had left one leaf to a CU)
+constexpr int lj_rows(int L) { return (L + LJ_TILE - 1) / LJ_TILE; }
+constexpr int lj_group(int L) { return lj_rows(L) > 16 ? 32 : lj_rows(L) > 8 ? 16 : 8; }
+constexpr int lj_waves(int L) {
+    return ((lj_rows(L) + 1) / 2 * lj_group(L) + WAVE - 1) / WAVE;
+}
+constexpr int lj_threads(int L) { return WAVE * (1 + (lj_waves(L) < 7 ? lj_waves(L) : 7)); }
+static_assert(lj_waves(LEAF_MAX) <= 8, "the last wavefront takes one more group of 64 lanes");
 constexpr int LV_SEG = 16;                          // positions a lane holds
 constexpr int LV_NSEG = LEAF_MAX / LV_SEG;          // segments of a row (8)
 constexpr int LV_RPL = 4;                           // rows a lane holds
@@ -45,29 +53,46 @@ constexpr int LV_CLD = LV_PAIRS + LV_NSEG;          // staged entry k sits at k 
                                                     // so the segments' reads hit distinct banks
 constexpr int LV_RB = 4;                            // rounds per staged block
 static_assert(LEAF_MAX / 2 <= WAVE, "a round's pairs must fit one wavefront");
-static_assert(LJ_PACKED < (1 << 15), "addresses in the packed triangle fit 15 bits");
+static_assert(LEAF_MAX <= 128, "columns in four planes of 32");
 static_assert(LV_PAIRS == WAVE, "one staged log entry per lane");
 static_assert(LV_NSEG * LV_SEG == LEAF_MAX && LV_NSEG <= 16 && 16 % LV_NSEG == 0,
               "a row's segments are neighbouring lanes of one 16-lane DPP row");
 static_assert(LV_RB == 4, "a staged block starts on a round A, and two padding rounds negate\n"
               "every position but the first");
 
-// entry (i, j), i <= j, of the upper triangle of an m x m matrix (m even) packed by rows,
-// each row holding its even columns first and then its odd ones: a round's blocks take a
-// column of one parity from every pair, so lanes with neighbouring column pairs read
-// neighbouring words of a row instead of every other one (which halved the LDS bank
-// throughput)
-__device__ __forceinline__ int ut(int i, int j, int m) {
-    const int start = (i * (2 * m - i + 1)) >> 1;  // where row i starts
-    const int odd = i & 1;
-    const int neven = (m - i - odd) >> 1;           // even columns in [i, m)
-    return start + ((j & 1) ? neven + ((j - i - 1 + odd) >> 1) : ((j - i - odd) >> 1));
+// Entry (i, j), i <= j, of an m x m matrix.  Rows i and m-1-i share a line above the diagonal,
+// row i < m/2 from its column on and the other from the front; the diagonal lies behind the
+// lines, at diag.  A line is four planes of PW words by column mod 4, one word per bank (PW =
+// 32; 16 for leaves up to 64): the lanes of a group read one column of tile row a (banks from
+// a + 1 on) and of tile row T-1-a (banks up to a) without conflicts.  With planes of 16, the
+// next group's lines have theirs swapped, so that two groups share the banks; the lines
+// are skewed by a bank every few, which spreads the entries near the diagonal.
+template <int PW>
+__device__ __forceinline__ int ut(int i, int j, int m, int diag) {
+    if (i == j) return diag + i;
+    const int line = min(i, m - 1 - i);
+    const int x = i == line ? j : j - i - 1;
+    const int plane = PW == 32 ? x & 3 : (x & 3) ^ ((line >> 2) & 1);
+    return (line * 4 + plane) * PW + (((x >> 2) + (line >> (PW == 32 ? 2 : 3))) & (PW - 1));
 }
 
 // cos and sin of the rotation with tangent t
 __device__ __forceinline__ double2 rot_cs(double t) {
     const double c = rcp_nr(sqrt(t * t + 1.0));
     return make_double2(c, t * c);
+}
+
+// 1 / sqrt(t) for t well inside the exponent range, to about an ulp
+__device__ __forceinline__ double rsqrt_nr(double t) {
+    double r = __builtin_amdgcn_rsq(t);
+    double g = t * r, h = 0.5 * r;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const double e = __builtin_fma(-h, g, 0.5);
+        g = __builtin_fma(g, e, g);
+        h = __builtin_fma(h, e, h);
+    }
+    return 2.0 * h;
 }
 
 // The matrix is kept by position: entry (i, j) of the packed upper triangle is the entry
@@ -87,12 +112,29 @@ __device__ __forceinline__ double2 rot_cs(double t) {
 // position that sits the round out), so its three entries all lie in those blocks.  That
 // wavefront therefore computes the next round's rotations right after its own blocks,
 // while the other wavefronts still update theirs, and a round ends in a single barrier;
-// the rotation data is double-buffered by round parity.
-__global__ __launch_bounds__(LJ_THREADS, 2 * LJ_THREADS / WAVE / 4) void k_leaf_jacobi(LeafArgs a) {
-    __shared__ double A[LJ_PACKED];         // upper triangle by position, packed by rows
-    __shared__ double2 cs[2][LEAF_MAX / 2];  // (c, sigma) of each pair
-    __shared__ double tt[2][LEAF_MAX / 2];   // tangent of each pair's rotation (0: none)
-    __shared__ double red[LJ_THREADS / WAVE];
+// the rotation data is double-buffered by round parity.  The other blocks are cut into
+// tiles of two pairs by two, one to a thread, with the addresses of a tile's 16 entries per
+// round type in registers; entries that are not the thread's (the first wavefront's blocks,
+// pairs past the last) go to a spare word of the bank that is free.
+//
+// What bounded a round of two leaves of 128 on a CU was the issue of instructions (75 to a
+// 2 x 2 block, 16 of them in FP64, with the blocks dealt one by one over 16 wavefronts) and,
+// for small leaves, the first wavefront's chain of three square roots and three reciprocals.
+// With tiles and two reciprocal square roots it is the LDS, 66 KB each way per leaf, busy two
+// thirds of the time.  Measured: 512 leaves of 128 2580 -> 1900 us, 32 leaves of 32 330 ->
+// 132 us.
+template <int LP>
+__global__ __launch_bounds__(lj_threads(LP), 4) void k_leaf_jacobi(LeafArgs a) {
+    // upper triangle by position, its diagonal, and PW spare words, one per bank
+    constexpr int PW = LP > 64 ? 32 : 16, DIAG = LP / 2 * 4 * PW, SPARE = DIAG + LP;
+    __shared__ double A[SPARE + PW];
+    // (c, sigma) of each pair, by round type; even pairs, then odd ones (a tile takes one of
+    // each, so neighbouring lanes read neighbouring entries)
+    __shared__ double2 cs[2][2][LP / 4];
+    __shared__ double tt[2][LP / 2];   // tangent of each pair's rotation (0: none)
+    __shared__ double red[lj_threads(LP) / WAVE];
+    // the last wavefront's second tiles (LDS: the registers hold the first ones)
+    __shared__ int4 more_ad[2][2][LP > 64 ? WAVE : 1], more_p[LP > 64 ? WAVE : 1];
     __shared__ int swept[2];       // per sweep parity: the sweep rotated something
     __shared__ int swbig[2];       // per sweep parity: some tangent was at least 1e-6
 
@@ -105,122 +147,182 @@ __global__ __launch_bounds__(LJ_THREADS, 2 * LJ_THREADS / WAVE / 4) void k_leaf_
     for (int e = tid; e < L * L; e += nt) {
         const int i = e / L, j = e - i * L;
         const double v = D[e];
-        if (i <= j) A[ut(i, j, L)] = v;
+        if (i <= j) A[ut<PW>(i, j, L, DIAG)] = v;
         fro += v * v;
     }
     for (int o = WAVE / 2; o > 0; o >>= 1) fro += __shfl_xor(fro, o);
     if (lane_id() == 0) red[tid / WAVE] = fro;
+    const int m = L;  // even
+    const int half = m / 2;
+    constexpr int spare = SPARE;
+    if (tid < PW) A[spare + tid] = 0.0;
     __syncthreads();
     double tot = 0.0;
     for (int w = 0; w < nt / WAVE; ++w) tot += red[w];
     const double absfloor = 1e-18 * sqrt(tot);
-    const int m = L;  // even
-    const int half = m / 2;
-    const int hh = (half + 1) & ~1;          // half rounded up to even, for the folding
-    const int nfold = (hh / 2) * (hh + 1);  // blocks of the folded triangle
+    // squares of the entries stay in range (see rotations)
+    const bool plain = __builtin_amdgcn_readfirstlane(tot >= 0x1p-800 && tot <= 0x1p800);
     const int total = a.max_sweeps * m;     // rounds the log has room for
     double2 *log = reinterpret_cast<double2 *>(a.rot) + (size_t)leafid * total * half;
     const bool first = tid < WAVE;
-    // addresses of the block of row pair (r0, r1) and column pair (c0, c1), r1 < c0: a
-    // column pair (m-1, 0) is the pair that sits round B out, whose entries (r, 0) are kept
-    // at (0, r)
-    auto block_addr = [&](int r0, int r1, int c0, int c1, int4 &ad) {
-        if (c1 != 0) ad = make_int4(ut(r0, c0, m), ut(r0, c1, m), ut(r1, c0, m), ut(r1, c1, m));
-        else ad = make_int4(ut(r0, m - 1, m), ut(0, r0, m), ut(r1, m - 1, m), ut(0, r1, m));
-    };
-    // the other wavefronts' blocks, the same in every round: the folded triangle dealt out
-    // over their threads, without the first wavefront's blocks.  A slot keeps P1 | P2 << 8
-    // and, per round type, the addresses of the two rows' entries in the column pair's
-    // first column (16 bits each); the second column's follow from the row's parity, so
-    // that the kernel keeps to 64 registers and two leaves share a CU
-    int bP[LJ_BLK];  // < 0: no block
-    int adA[LJ_BLK], adB[LJ_BLK];
-#pragma unroll
-    for (int u = 0; u < LJ_BLK; ++u) {
-        bP[u] = -1;
-        adA[u] = adB[u] = 0;
-        const int blk = (tid - WAVE) + u * (nt - WAVE);
-        if (first || blk >= nfold) continue;
-        const int r = blk / (hh + 1), e = blk - r * (hh + 1);
-        int P1, P2;
-        if (e < hh - r) {
-            P1 = r;
-            P2 = r + e;
-        } else {
-            P1 = hh - 1 - r;
-            P2 = e - 1;
-        }
-        if (P2 >= half) continue;  // padding of an odd half
-        if (P2 - P1 <= 1 || (P1 == 0 && P2 == half - 1)) continue;  // the first wavefront's
-        bP[u] = P1 | P2 << 8;
-        int4 ad;
-        block_addr(2 * P1, 2 * P1 + 1, 2 * P2, 2 * P2 + 1, ad);
-        adA[u] = ad.x | ad.z << 16;
-        if (P2 < half - 1) block_addr(2 * P1 + 1, 2 * P1 + 2, 2 * P2 + 1, 2 * P2 + 2, ad);
-        else block_addr(2 * P1 + 1, 2 * P1 + 2, m - 1, 0, ad);
-        adB[u] = ad.x | ad.z << 16;
-    }
-    // the four addresses of slot block (P1, P2) in a round of type b from the packed pair:
-    // in row r the column pair's second column lies neven(r) + odd(r) words after its first
-    // in round A (even, odd), and 1 - odd(r) - neven(r) words in round B (odd, even); when
-    // the column pair (m-1, 0) sits out, rows r0 = 2 P1 + 1 and r1 = r0 + 1 keep column 0
-    // at (0, r), which is m/2 + P1 and P1 + 1
-    auto slot_addr = [&](int pk, int P1, int b, bool cols_idle) {
-        const int ax = pk & 0xffff, az = pk >> 16;
-        if (cols_idle) return make_int4(ax, half + P1, az, P1 + 1);
-        auto step = [&](int r) {
-            const int odd = r & 1, neven = (m - r - odd) >> 1;
-            return b ? 1 - odd - neven : neven + odd;
-        };
-        const int r0 = 2 * P1 + b;
-        return make_int4(ax, ax + step(r0), az, az + step(r0 + 1));
+    // pair P's v-th position in a round of type p; in round B the last pair is (m - 1, 0), which
+    // sits the round out
+    auto position = [&](int P, int v, int p) { return 2 * P + v + p == m ? 0 : 2 * P + v + p; };
+    auto entry = [&](int i, int j) { return i <= j ? ut<PW>(i, j, m, DIAG) : ut<PW>(j, i, m, DIAG); };
+    // the blocks of a round that are not the first wavefront's
+    auto tiled = [&](int P1, int P2) {
+        return P2 < half && P2 - P1 > 1 && !(P1 == 0 && P2 == half - 1);
     };
 
-    // off-diagonal block of pairs P1 < P2 at addresses ad, with the reflections of buffer b
-    // (cols_idle: the column pair sits the round out)
-    auto update_block = [&](int P1, int P2, const int4 &ad, int b, bool cols_idle) {
-        const double2 r1 = cs[b][P1];
-        const double x00 = A[ad.x], x01 = A[ad.y], x10 = A[ad.z], x11 = A[ad.w];
-        // rows: R1 X
-        const double y00 = fma(r1.x, x10, r1.y * x00), y10 = fma(r1.x, x00, -(r1.y * x10));
-        const double y01 = fma(r1.x, x11, r1.y * x01), y11 = fma(r1.x, x01, -(r1.y * x11));
-        if (cols_idle) {
-            A[ad.x] = y00;
-            A[ad.y] = y01;
-            A[ad.z] = y10;
-            A[ad.w] = y11;
-            return;
-        }
-        // columns: (R1 X) R2
-        const double2 r2 = cs[b][P2];
-        A[ad.x] = fma(r2.x, y01, r2.y * y00);
-        A[ad.y] = fma(r2.x, y00, -(r2.y * y01));
-        A[ad.z] = fma(r2.x, y11, r2.y * y10);
-        A[ad.w] = fma(r2.x, y10, -(r2.y * y11));
+    // Addresses in this thread's registers, two to a word, per round type.  First wavefront,
+    // lane k: words 0 and 1 the diagonal block of pair k (left, right, between them), words
+    // 2 and 3 a block of neighbours, (k, k+1) in round A and (k-1, k) in round B, or, in the
+    // lane left over, the block (0, m/2 - 1).  Others: entries (v, 2h), (v, 2h+1) of the tile in
+    // word 2v + h.
+    struct Tile4 {
+        int ad[2][8];
+        int P1, P2;        // first row and column pair (first wavefront: of its block, round A)
+        int out;           // bit h: column pair P2 + h sits round B out
     };
-
-    // rotations of round g (first wavefront, lane k: pair k) into buffer g & 1, with the
-    // log entry; returns the lane's tangent (0: no rotation)
-    auto rotations = [&](int g) -> double {
+    Tile4 t0;
+    int Q1 = 0, Q2 = 0;  // first wavefront: the pairs of its block in round B
+    bool sits = false;   // whose column pair sits the round out
+    int(&ad)[2][8] = t0.ad;
+    int &P1 = t0.P1, &P2 = t0.P2;
+    P1 = P2 = 0;
+    const bool more = LP > 64 && tid >= 7 * WAVE && lj_waves(m) > 7;
+    if (first) {
         const int k = tid;
-        const int B = g & 1;  // m is even: round A pairs positions (2k, 2k+1), B (2k+1, 2k+2)
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            const bool diag = k < half && !(p && k == half - 1);
+            const int l = 2 * k + p;
+            ad[p][0] = diag ? ut<PW>(l, l, m, DIAG) | ut<PW>(l + 1, l + 1, m, DIAG) << 16 : spare | spare << 16;
+            ad[p][1] = diag ? ut<PW>(l, l + 1, m, DIAG) : spare;
+            const int left = p ? 0 : half - 1;  // the lane left over
+            int R = p ? k - 1 : k, S = R + 1;
+            bool has = k < half && k != left;
+            if (k == left && half >= 3) {
+                R = 0;
+                S = half - 1;
+                has = true;
+            }
+            if (!has) R = S = 0;
+            if (p) {
+                Q1 = R;
+                Q2 = S;
+            } else {
+                P1 = R;
+                P2 = S;
+            }
+#pragma unroll
+            for (int v = 0; v < 2; ++v) {
+                const int r = position(R, v, p);
+                ad[p][2 + v] = has ? entry(r, position(S, 0, p)) | entry(r, position(S, 1, p)) << 16
+                                   : spare | spare << 16;
+            }
+            if (p) sits = has && S == half - 1;
+        }
+    } else {
+        const int T = (half + 1) / 2, G = lj_group(m);
+        auto take = [&](int e, Tile4 &t) {
+            int ta = e / G, tb = ta + 1 + e % G;
+            const int row = min(ta, T - 1);  // the group's first tile row
+            if (2 * ta >= T) {
+                tb = half;  // past the tiles: nothing valid
+            } else if (tb >= T) {  // the group's second tile row
+                const int other = T - 1 - ta;
+                tb = other > ta && tb - T < ta ? tb - T + other + 1 : half;
+                ta = other;
+            }
+            ta = max(min(ta, T - 2), 0);
+            t.P1 = 2 * ta;
+            t.P2 = min(2 * tb, (half - 1) & ~1);
+            t.out = 2 * tb == half - 1 ? 1 : 2 * tb == half - 2 ? 2 : 0;  // the last pair
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const int R = 2 * ta + (v >> 1), S = 2 * tb + h;
+                        int w[2];
+                        for (int u = 0; u < 2; ++u) {
+                            if (tb < T && S < half) {
+                                w[u] = entry(position(R, v & 1, p), position(S, u, p));
+                                if (!tiled(R, S)) w[u] = spare + w[u] % PW;  // the same bank
+                            } else {  // a lane without a tile: the bank that its group leaves free
+                                const int line = 4 * row + v + p;
+                                const int free = 2 * h + u <= v ? row : 0;
+                                w[u] = spare + (free + (line >> (PW == 32 ? 2 : 3))) % PW;
+                            }
+                        }
+                        t.ad[p][2 * v + h] = w[0] | w[1] << 16;
+                    }
+        };
+        take(tid - WAVE, t0);
+        if (more) {  // past the 7 wavefronts' first tiles
+            Tile4 t1;
+            take(tid, t1);
+            more_p[lane_id()] = make_int4(t1.P1, t1.P2, t1.out, 0);
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int h = 0; h < 2; ++h)
+                    more_ad[p][h][lane_id()] = make_int4(t1.ad[p][4 * h], t1.ad[p][4 * h + 1],
+                                                         t1.ad[p][4 * h + 2], t1.ad[p][4 * h + 3]);
+        }
+    }
+    auto lo = [](int w) { return w & 0xffff; };
+    auto hi = [](int w) { return (int)((unsigned)w >> 16); };
+    // rows of a 2 x 2 block by the reflection (c, s) of their pair, and columns; a column pair
+    // that sits the round out has (0, 1) and keeps its second column too
+    auto rows = [](double2 r, double &x0, double &x1) {
+        const double y = fma(r.x, x1, r.y * x0);
+        x1 = fma(r.x, x0, -(r.y * x1));
+        x0 = y;
+    };
+    auto cols = [](double2 r, double n, double &x0, double &x1) {
+        const double y = fma(r.x, x1, r.y * x0);
+        x1 = fma(r.x, x0, n * x1);
+        x0 = y;
+    };
+
+    // rotations of round g of type p (first wavefront, lane k: pair k) into buffer p, with the
+    // log entry; returns the lane's tangent (0: no rotation)
+    auto rotations = [&](int g, auto par) -> double {
+        constexpr int p = decltype(par)::value;
+        const int k = tid;
         double t = 0.0;
+        const double x = A[lo(ad[p][0])], y = A[hi(ad[p][0])], w = A[ad[p][1]];
         if (k < half) {
-            // in round B, positions m-1 and 0 sit out
-            const bool idle = B && k == half - 1;
-            const int lp = idle ? 0 : 2 * k + B, rp = lp + 1;
-            const double w = A[ut(lp, rp, m)];
-            const double x = A[ut(lp, lp, m)], y = A[ut(rp, rp, m)];
-            if (!idle && fabs(w) > 2.220446049250313e-16 * sqrt(fabs(x) * fabs(y)) + absfloor) {
+            const bool idle = p && k == half - 1;
+            double2 r = make_double2(1.0, 0.0);
+            if (plain) {
+                // |w| > eps sqrt(|x y|) + absfloor by squares; with d = y - x, r = 1 / sqrt(d^2 +
+                // 4 w^2): cos 2 phi = |d| r and c = sqrt((1 + cos 2 phi) / 2), so that two
+                // reciprocal square roots give the whole rotation
+                const double over = fabs(w) - absfloor;
+                const double d = y - x;
+                const double ri = rsqrt_nr(fma(d, d, 4.0 * (w * w)));
+                const double c2 = fma(0.5 * fabs(d), ri, 0.5);
+                const double rc = rsqrt_nr(c2);
+                const double ws = d > 0.0 ? w : d < 0.0 ? -w : fabs(w);
+                if (!idle && over > 0.0 && over * over > 0x1p-104 * fabs(x * y)) {
+                    const double s = ws * ri * rc;
+                    r = make_double2(c2 * rc, s);
+                    t = s * rc;
+                }
+            } else if (!idle && fabs(w) > 2.220446049250313e-16 * sqrt(fabs(x) * fabs(y)) + absfloor) {
                 // the rotation only has to annihilate w to rounding, so reciprocals by
                 // Newton-refined estimates stand in for the divisions
                 const double theta = (y - x) * (0.5 * rcp_nr(w));
                 if (fabs(theta) > 1e150) t = 0.5 * rcp_nr(theta);
                 else t = (theta >= 0.0 ? 1.0 : -1.0) * rcp_nr(fabs(theta) + sqrt(theta * theta + 1.0));
+                if (t != 0.0) r = rot_cs(t);
             }
-            const double2 r = t != 0.0 ? rot_cs(t) : make_double2(1.0, 0.0);
-            cs[B][k] = r;
-            tt[B][k] = t;
+            cs[p][k & 1][k >> 1] = idle ? make_double2(0.0, 1.0) : r;
+            tt[p][k] = t;
             // the left position's new column is c y + sigma x and the right one's
             // c x - sigma y, for the columns x, y at the two positions before the round
             if (!idle) {
@@ -245,9 +347,9 @@ __global__ __launch_bounds__(LJ_THREADS, 2 * LJ_THREADS / WAVE / 4) void k_leaf_
         const int i = t / tpr;
         bool any = false;
         if (i < m) {
-            const double x = fabs(A[ut(i, i, m)]);
+            const double x = fabs(A[ut<PW>(i, i, m, DIAG)]);
             for (int j = i + 1 + t % tpr; j < m; j += tpr)
-                any |= fabs(A[ut(i, j, m)]) > 2.220446049250313e-16 * sqrt(x * fabs(A[ut(j, j, m)])) + absfloor;
+                any |= fabs(A[ut<PW>(i, j, m, DIAG)]) > 2.220446049250313e-16 * sqrt(x * fabs(A[ut<PW>(j, j, m, DIAG)])) + absfloor;
         }
         return __syncthreads_or(any);
     };
@@ -255,75 +357,118 @@ __global__ __launch_bounds__(LJ_THREADS, 2 * LJ_THREADS / WAVE / 4) void k_leaf_
     // first wavefront: whether the current sweep has rotated anything so far, and anything
     // by a tangent of at least 1e-6
     bool rot_acc = false, big_acc = false;
+    auto note = [&](double t) {
+        rot_acc |= __any(t != 0.0);
+        big_acc |= __any(fabs(t) >= 1e-6);
+    };
+    auto update = [&](const Tile4 &t, auto par) {
+        constexpr int p = decltype(par)::value;
+        const double2 r0 = cs[p][0][t.P1 >> 1], r1 = cs[p][1][t.P1 >> 1];
+        const double2 q0 = cs[p][0][t.P2 >> 1], q1 = cs[p][1][t.P2 >> 1];
+        double x[4][4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                x[v][2 * h] = A[lo(t.ad[p][2 * v + h])];
+                x[v][2 * h + 1] = A[hi(t.ad[p][2 * v + h])];
+            }
+        const double n0 = p && (t.out & 1) ? q0.y : -q0.y, n1 = p && (t.out & 2) ? q1.y : -q1.y;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            rows(r0, x[0][u], x[1][u]);
+            rows(r1, x[2][u], x[3][u]);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            cols(q0, n0, x[v][0], x[v][1]);
+            cols(q1, n1, x[v][2], x[v][3]);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                A[lo(t.ad[p][2 * v + h])] = x[v][2 * h];
+                A[hi(t.ad[p][2 * v + h])] = x[v][2 * h + 1];
+            }
+        }
+    };
+    // round g of type p up to its barrier; next: the first wavefront goes on to the rotations
+    // of round g + 1
+    auto round = [&](int g, auto par, bool next) {
+        constexpr int p = decltype(par)::value;
+        if (first) {
+            // all loads first: lane k's diagonal block and its block of neighbours
+            const double t = tt[p][min(tid, half - 1)];
+            const int R = p ? Q1 : P1, S = p ? Q2 : P2;
+            const double2 r1 = cs[p][R & 1][R >> 1], r2 = cs[p][S & 1][S >> 1];
+            const double x = A[lo(ad[p][0])], y = A[hi(ad[p][0])], w = A[ad[p][1]];
+            double x00 = A[lo(ad[p][2])], x01 = A[hi(ad[p][2])];
+            double x10 = A[lo(ad[p][3])], x11 = A[hi(ad[p][3])];
+            A[lo(ad[p][0])] = fma(t, w, y);
+            A[hi(ad[p][0])] = fma(-t, w, x);
+            A[ad[p][1]] = t != 0.0 ? 0.0 : w;
+            rows(r1, x00, x10);
+            rows(r1, x01, x11);
+            const double n = p && sits ? r2.y : -r2.y;
+            cols(r2, n, x00, x01);
+            cols(r2, n, x10, x11);
+            A[lo(ad[p][2])] = x00;
+            A[hi(ad[p][2])] = x01;
+            A[lo(ad[p][3])] = x10;
+            A[hi(ad[p][3])] = x11;
+            if (next) {
+                wave_sync();
+                note(rotations(g + 1, std::integral_constant<int, 1 - p>{}));
+            }
+        } else {
+            update(t0, par);
+            if (more) {
+                Tile4 t1;
+                const int4 q = more_p[lane_id()];
+                t1.P1 = q.x;
+                t1.P2 = q.y;
+                t1.out = q.z;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int4 w = more_ad[p][h][lane_id()];
+                    t1.ad[p][4 * h] = w.x;
+                    t1.ad[p][4 * h + 1] = w.y;
+                    t1.ad[p][4 * h + 2] = w.z;
+                    t1.ad[p][4 * h + 3] = w.w;
+                }
+                update(t1, par);
+            }
+        }
+        __syncthreads();
+    };
+    const std::integral_constant<int, 0> roundA{};
+    const std::integral_constant<int, 1> roundB{};
     if (first) {
-        const double t = rotations(0);
-        rot_acc = __any(t != 0.0);
-        big_acc = __any(fabs(t) >= 1e-6);
+        wave_priority(3);  // the other wavefronts wait for its chain at every barrier
+        note(rotations(0, roundA));
     }
     __syncthreads();
     int sweep = 0;
     bool converged = false, reversed = false;  // reversed: an empty sweep ran
-    for (int g = 0;; ++g) {
-        const int b = g & 1;  // rotation buffer, and round B when set
-        if (first) {
-            const int k = tid;
-            if (k < half && !(b && k == half - 1)) {
-                // diagonal block of pair k at positions (l, l+1)
-                const int l = 2 * k + b;
-                const int ixx = ut(l, l, m), ixw = ut(l, l + 1, m), iyy = ut(l + 1, l + 1, m);
-                const double t = tt[b][k];
-                const double x = A[ixx], w = A[ixw], y = A[iyy];
-                A[ixx] = fma(t, w, y);
-                A[iyy] = fma(-t, w, x);
-                A[ixw] = t != 0.0 ? 0.0 : w;
+    for (int g = 0, left = half;; g += 2) {  // left: round pairs of the sweep
+        round(g, roundA, true);
+        if (--left == 0 && first) {  // the sweep's last round is decided
+            if (tid == 0) {
+                swept[sweep & 1] = rot_acc;
+                swbig[sweep & 1] = big_acc;
             }
-            int4 ad;
-            if (!b && k + 1 < half) {  // round A: block (k, k+1)
-                block_addr(2 * k, 2 * k + 1, 2 * k + 2, 2 * k + 3, ad);
-                update_block(k, k + 1, ad, b, false);
-            }
-            if (b && k >= 1 && k < half) {  // round B: block (k-1, k)
-                const bool idle = k == half - 1;
-                block_addr(2 * k - 1, 2 * k, idle ? m - 1 : 2 * k + 1, idle ? 0 : 2 * k + 2, ad);
-                update_block(k - 1, k, ad, b, idle);
-            }
-            if (k == 0 && half >= 3) {  // block (0, m/2 - 1)
-                if (!b) block_addr(0, 1, m - 2, m - 1, ad);
-                else block_addr(1, 2, m - 1, 0, ad);
-                update_block(0, half - 1, ad, b, b);
-            }
-            if (g + 1 < total) {
-                wave_sync();
-                const double t = rotations(g + 1);
-                rot_acc |= __any(t != 0.0);
-                big_acc |= __any(fabs(t) >= 1e-6);
-                if ((g + 1) % m == m - 1) {  // the sweep's last round is decided
-                    if (tid == 0) {
-                        swept[((g + 1) / m) & 1] = rot_acc;
-                        swbig[((g + 1) / m) & 1] = big_acc;
-                    }
-                    rot_acc = big_acc = false;
-                }
-            }
-        } else {
-#pragma unroll
-            for (int u = 0; u < LJ_BLK; ++u) {
-                if (bP[u] < 0) continue;
-                const int P1 = bP[u] & 0xff, P2 = bP[u] >> 8;
-                const bool idle = b && P2 == half - 1;
-                update_block(P1, P2, slot_addr(b ? adB[u] : adA[u], P1, b, idle), b, idle);
-            }
+            rot_acc = big_acc = false;
         }
-        __syncthreads();
-        if (g % m == m - 1) {  // the end of sweep g / m
-            if (!swept[(g / m) & 1]) {  // a sweep without rotations: nothing of it needs replaying
+        round(g + 1, roundB, g + 2 < total);
+        if (left == 0) {  // the end of a sweep
+            left = half;
+            if (!swept[sweep & 1]) {  // a sweep without rotations: nothing of it needs replaying
                 converged = reversed = true;
                 break;
             }
+            const bool big = swbig[sweep & 1];
             ++sweep;
             // once the sweep's rotations are all tiny, the next one may well be empty: test
             // every pair now instead of running it to find out (the same decision)
-            if (!swbig[(g / m) & 1] && !any_pair_rotates()) {
+            if (!big && !any_pair_rotates()) {
                 converged = true;
                 break;
             }
@@ -334,10 +479,10 @@ __global__ __launch_bounds__(LJ_THREADS, 2 * LJ_THREADS / WAVE / 4) void k_leaf_
     // positions, and the replay stops short of a last sweep without rotations, so position j
     // here is position m-1-j of the replayed vectors when that sweep ran
     if (tid < L) {
-        const double v = A[ut(tid, tid, L)];
+        const double v = A[ut<PW>(tid, tid, L, DIAG)];
         int r = 0;
         for (int j = 0; j < L; ++j) {
-            const double w = A[ut(j, j, L)];
+            const double w = A[ut<PW>(j, j, L, DIAG)];
             r += (w < v) || (w == v && j < tid);
         }
         a.rank[(size_t)leafid * L + (reversed ? L - 1 - tid : tid)] = r;
@@ -669,7 +814,11 @@ __global__ void k_fill(double *x, int64_t n, double v) {
 static inline dim3 grid_for(int64_t n, int b = 256) { return dim3((unsigned)((n + b - 1) / b)); }
 
 hipError_t launch_leaf_jacobi(const LeafArgs &a, hipStream_t s) {
-    SDC_LAUNCH(KID_LEAF, k_leaf_jacobi, dim3(a.nleaf), dim3(LJ_THREADS), 0, s, a);
+    // the smallest LDS that holds the leaf, so that small leaves share a CU
+    const dim3 nt(lj_threads(a.leaf));
+    if (a.leaf <= 32) SDC_LAUNCH(KID_LEAF, k_leaf_jacobi<32>, dim3(a.nleaf), nt, 0, s, a);
+    else if (a.leaf <= 64) SDC_LAUNCH(KID_LEAF, k_leaf_jacobi<64>, dim3(a.nleaf), nt, 0, s, a);
+    else SDC_LAUNCH(KID_LEAF, k_leaf_jacobi<LEAF_MAX>, dim3(a.nleaf), nt, 0, s, a);
     SDC_LAUNCH(KID_LEAF_VECTORS, k_leaf_vectors, dim3(a.nleaf * ((a.leaf + LV_WROWS - 1) / LV_WROWS)),
                dim3(WAVE), 0, s, a);
     SDC_LAUNCH(KID_LEAF_VECTORS, k_leaf_w, dim3(a.nleaf), dim3(256), 0, s, a);
