@@ -112,6 +112,20 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// columns [c0, c1) of one row, up to eight loads in flight
+__device__ __forceinline__ void copy_cols(const double *x, int64_t ldx, double *y, int64_t ldy,
+                                          int c0, int c1) {
+    int c = c0;
+    for (; c + 8 <= c1; c += 8) {
+        double v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = x[(c + u) * ldx];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) y[(c + u) * ldy] = v[u];
+    }
+    for (; c < c1; ++c) y[c * ldy] = x[c * ldx];
+}
+
 // Work items: a launch has one workgroup per item, item blockIdx.x of a list that holds the
 // longest problems first.  The hardware starts workgroups in that order as others end, which
 // balances the load; a grid of resident workgroups pulling items from an atomic counter did the
@@ -343,6 +357,19 @@ struct BwdArgs {
 };
 hipError_t launch_backward(const BwdArgs &a, int split, int prob_first, int nprob, hipStream_t s);
 
+// columns per thread of the row kernels: as many as leave the chip enough threads, and no
+// more blocks of columns than a grid holds
+inline int cols_per_thread(int64_t rows, int m) {
+    int cpt = 16;
+    while (cpt > 1 && rows * ((m + cpt - 1) / cpt) < (1 << 18) && (m + cpt / 2 - 1) / (cpt / 2) <= 65535)
+        cpt /= 2;
+    while ((m + cpt - 1) / cpt > 65535) cpt *= 2;
+    return cpt;
+}
+inline dim3 row_grid(int64_t rows, int m, int cpt) {
+    return dim3((unsigned)((rows + 255) / 256), (unsigned)((m + cpt - 1) / cpt));
+}
+
 // deflation (deflate.hip)
 hipError_t launch_deflate(const int64_t *off, int nprob, const double *d, const double *z,
                           const double *rho, double tau, double *dout, double *zout,
@@ -350,7 +377,7 @@ hipError_t launch_deflate(const int64_t *off, int nprob, const double *d, const 
                           int32_t *kept, int32_t *status, double2 *val, int8_t *flag,
                           int max_n, int4 *seg_i, double2 *seg_d, hipStream_t s);
 // segments per problem of the deflation scan (records seg_i, seg_d: nprob times this)
-int deflate_segments(int max_n);
+int deflate_segments(int nprob, int max_n);
 hipError_t launch_deflate_expand(const int64_t *off, int nprob, int64_t total, int m,
                                  const int32_t *perm, const int32_t *rright,
                                  const int32_t *rleft, const double *rc, const double *rs,

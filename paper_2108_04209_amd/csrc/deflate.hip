@@ -23,11 +23,27 @@
 // Decisions are taken with the same expressions in the same order as a plain sequential
 // implementation, without contraction into fused multiply-adds, so they do not depend on
 // how the lanes split the work.
+#include <algorithm>
+
 #include "common.h"
 
 namespace sdc {
 
-constexpr int DEFL_SEG = 2048;  // poles per segment of the parallel scan (a multiple of 64)
+// Poles per segment of the parallel scan (a multiple of 64): short enough to spread a problem over
+// wavefronts, but a boundary that rotates costs a second scan of its segment (18 rank-one
+// steps of a tridiagonal matrix of 65536 rows, which rotate at most boundaries, us a step for
+// 64, 128, 256, 512, 1024 poles: 59 46 36 28 31).  Problems of up to 8 segments (DEFL_WG) take
+// one launch with the joins and the placement.  Longer segments where the records (problems
+// x segments of the largest) would grow past 64 MB, or past 256 to a problem.
+constexpr int DEFL_SEG = 512, DEFL_SEG_MAX = 2048;
+constexpr int DEFL_WAVES = 8, DEFL_WG = DEFL_WAVES * DEFL_SEG;
+
+static int defl_seg(int nprob, int max_n) {
+    int seg = DEFL_SEG;
+    while (seg < DEFL_SEG_MAX && (max_n > 256 * seg || (int64_t)nprob * ((max_n + seg - 1) / seg) > (1 << 21)))
+        seg *= 2;
+    return seg;
+}
 
 struct DeflArgs {
     const int64_t *off;
@@ -41,7 +57,7 @@ struct DeflArgs {
     int8_t *flag;    // workspace: 1 kept, 0 deflated
     int4 *seg_i;     // workspace [nprob][maxseg]: current pole, first survivor, status, kept
     double2 *seg_d;  // workspace [nprob][maxseg]: the current pole's (d, z)
-    int maxseg;
+    int seg, maxseg; // poles per segment, segments of the largest problem
 };
 
 // the rule-2 test and the rotation (evaluated exactly as written)
@@ -85,7 +101,7 @@ __device__ __forceinline__ int lane_get(int v, int l) { return __builtin_amdgcn_
 // the number of poles decided kept.
 __device__ int defl_scan(const DeflArgs &a, int64_t base, int lo, int hi, double sv, int &ca,
                          double &cd, double &cz, int &first, double *sd, double *sz, int *si) {
-    const int lane = threadIdx.x;
+    const int lane = lane_id();
     const double tau = a.tau;
     const double *d = a.d + base, *z = a.z + base;
     double2 *val = a.val + base;
@@ -125,11 +141,11 @@ __device__ int defl_scan(const DeflArgs &a, int64_t base, int lo, int hi, double
             sz[rank] = zi;
             si[rank] = i;
         }
-        __syncthreads();
+        wave_sync();
         const bool live = lane < cnt;
         const double bd = live ? sd[lane] : 0.0, bz = live ? sz[lane] : 0.0;
         const int bi = live ? si[lane] : -1;
-        __syncthreads();
+        wave_sync();
         if (cnt == 0) continue;
         if (first < 0) first = lane_get(bi, 0);
         // left neighbour of every lane's pair: the previous lane's pole, the current pole
@@ -194,7 +210,7 @@ __device__ int defl_scan(const DeflArgs &a, int64_t base, int lo, int hi, double
 // validation of poles [lo, hi) of problem p: finite, non-decreasing (across the range's
 // end as well), rho > 0
 __device__ int defl_check(const DeflArgs &a, int p, int64_t base, int lo, int hi, int n) {
-    const int lane = threadIdx.x;
+    const int lane = lane_id();
     const double *d = a.d + base, *z = a.z + base;
     int st = 0;
     for (int i = lo + lane; i < hi; i += WAVE) {
@@ -209,124 +225,92 @@ __device__ int defl_check(const DeflArgs &a, int p, int64_t base, int lo, int hi
     return st;
 }
 
-// Segments of DEFL_SEG poles are scanned in parallel (blockIdx.y), each as if no pole came
-// before it; their records keep the undecided current pole at the end, the first pole that
-// survives rule 1, the status bits and the number of poles decided kept.
-__global__ __launch_bounds__(WAVE) void k_deflate(DeflArgs a) {
-    __shared__ double sd[WAVE], sz[WAVE];
-    __shared__ int si[WAVE];
-    const int p = blockIdx.x, sg = blockIdx.y;
-    const int64_t base = a.off[p];
-    const int n = (int)(a.off[p + 1] - base);
-    const int lo = sg * DEFL_SEG;
+// Segments are scanned in parallel, one wavefront each, as if no pole came before them; their
+// records keep the undecided current pole at the end, the first pole that survives rule 1,
+// the status bits and the number of poles decided kept.
+__device__ void defl_segment(const DeflArgs &a, int p, int64_t base, int n, int sg, int4 *rec_i,
+                             double2 *rec_d, double *sd, double *sz, int *si) {
+    const int lo = sg * a.seg;
     if (lo >= n) return;
-    const int hi = min(n, lo + DEFL_SEG);
-    const int64_t r = (int64_t)p * a.maxseg + sg;
+    const int hi = min(n, lo + a.seg);
     const int st = defl_check(a, p, base, lo, hi, n);
-    if (st) {
-        if (threadIdx.x == 0) {
-            a.seg_i[r] = make_int4(-1, -1, st, 0);
-            a.seg_d[r] = make_double2(0.0, 0.0);
-        }
-        return;
-    }
-    int ca = -1, first = -1;
+    int ca = -1, first = -1, nk = 0;
     double cd = 0.0, cz = 0.0;
-    const int nk = defl_scan(a, base, lo, hi, sqrt(a.rho[p]), ca, cd, cz, first, sd, sz, si);
-    if (threadIdx.x == 0) {
-        a.seg_i[r] = make_int4(ca, first, 0, nk);
-        a.seg_d[r] = make_double2(cd, cz);
+    if (!st) nk = defl_scan(a, base, lo, hi, sqrt(a.rho[p]), ca, cd, cz, first, sd, sz, si);
+    if (lane_id() == 0) {
+        rec_i[sg] = make_int4(ca, first, st, nk);
+        rec_d[sg] = make_double2(cd, cz);
     }
 }
 
-// The joins, in order, one wavefront per problem.  The scan entering segment s holds the
+// The joins of a problem, in order, by one wavefront.  The scan entering segment s holds the
 // current pole of everything before it.  If that pole and the segment's first survivor do
 // not rotate, the pole is kept and the segment's own scan stands exactly (it started from
-// that survivor); if they do, the segment is scanned again from the incoming pole.
-__global__ __launch_bounds__(WAVE) void k_deflate_join(DeflArgs a) {
-    __shared__ double sd[WAVE], sz[WAVE];
-    __shared__ int si[WAVE];
-    const int p = blockIdx.x;
-    const int64_t base = a.off[p];
-    const int n = (int)(a.off[p + 1] - base);
-    const int nseg = (n + DEFL_SEG - 1) / DEFL_SEG;
-    const int64_t r0 = (int64_t)p * a.maxseg;
+// that survivor); if they do, the segment is scanned again from the incoming pole (which
+// deflates).  The records of 64 segments and their first survivors are loaded at once, so
+// that the chain runs in registers.  Returns the status; on 0 the records' counts are final
+// and kept is the problem's.
+__device__ int defl_join(const DeflArgs &a, int p, int64_t base, int n, int4 *rec_i,
+                         const double2 *rec_d, int &kept, double *sd, double *sz, int *si) {
+    const int lane = lane_id();
+    const int nseg = (n + a.seg - 1) / a.seg;
     int st = 0;
-    for (int sg = 0; sg < nseg; ++sg) st |= a.seg_i[r0 + sg].z;
-    if (st) {
-        if (threadIdx.x == 0) {
-            a.status[p] = st;
-            a.kept[p] = 0;
-        }
-        return;
-    }
+    for (int sg = lane; sg < nseg; sg += WAVE) st |= rec_i[sg].z;
+    for (int o = WAVE / 2; o > 0; o >>= 1) st |= __shfl_xor(st, o);
+    kept = 0;
+    if (st) return st;
     const double sv = sqrt(a.rho[p]);
-    int4 ri = a.seg_i[r0];
-    double2 rd = a.seg_d[r0];
-    int ca = ri.x, nk = ri.w;
-    double cd = rd.x, cz = rd.y;
-    for (int sg = 1; sg < nseg; ++sg) {
-        ri = a.seg_i[r0 + sg];
-        rd = a.seg_d[r0 + sg];
-        const int f = ri.y;
-        if (f < 0) continue;  // nothing survives rule 1 here: the current pole passes on
-        if (ca >= 0 && defl_test(cd, cz, a.d[base + f], a.z[base + f], a.tau)) {
-            int first;
-            const int lo = sg * DEFL_SEG;
-            nk += defl_scan(a, base, lo, min(n, lo + DEFL_SEG), sv, ca, cd, cz, first, sd, sz, si);
-            continue;
-        }
-        if (ca >= 0) {  // the incoming pole is kept; the segment's scan stands
-            if (threadIdx.x == 0) {
-                a.val[base + ca] = make_double2(cd, cz);
-                a.flag[base + ca] = 1;
-            }
-            ++nk;
-        }
-        ca = ri.x;
-        cd = rd.x;
-        cz = rd.y;
-        nk += ri.w;
-    }
-    if (ca >= 0) {
-        if (threadIdx.x == 0) {
+    int ca = -1, nk = 0;
+    double cd = 0.0, cz = 0.0;
+    auto keep = [&]() {  // the current pole is kept
+        if (lane == 0) {
             a.val[base + ca] = make_double2(cd, cz);
             a.flag[base + ca] = 1;
+            atomicAdd(&rec_i[ca / a.seg].w, 1);
         }
         ++nk;
+    };
+    for (int s0 = 0; s0 < nseg; s0 += WAVE) {
+        const int mine = min(s0 + lane, nseg - 1);
+        const int4 ri = rec_i[mine];
+        const double2 rd = rec_d[mine];
+        const int fi = max(ri.y, 0);
+        const double fd = a.d[base + fi], fz = a.z[base + fi];
+        for (int u = 0; u < min(WAVE, nseg - s0); ++u) {
+            const int f = lane_get(ri.y, u);
+            if (f < 0) continue;  // nothing survives rule 1 here: the current pole passes on
+            if (ca >= 0 && defl_test(cd, cz, lane_get(fd, u), lane_get(fz, u), a.tau)) {
+                int first;
+                const int lo = (s0 + u) * a.seg;
+                const int k = defl_scan(a, base, lo, min(n, lo + a.seg), sv, ca, cd, cz, first, sd,
+                                        sz, si);
+                if (lane == 0) rec_i[s0 + u].w = k;
+                nk += k;
+                continue;
+            }
+            if (ca >= 0) keep();  // and the segment's scan stands
+            ca = lane_get(ri.x, u);
+            cd = lane_get(rd.x, u);
+            cz = lane_get(rd.y, u);
+            nk += lane_get(ri.w, u);
+        }
     }
-    if (threadIdx.x == 0) {
-        a.kept[p] = nk;
-        a.status[p] = 0;
-    }
+    if (ca >= 0) keep();
+    kept = nk;
+    return 0;
 }
 
-// kept poles per segment, for the placement
-__global__ __launch_bounds__(WAVE) void k_deflate_count(DeflArgs a) {
-    const int p = blockIdx.x, sg = blockIdx.y;
-    const int64_t base = a.off[p];
-    const int n = (int)(a.off[p + 1] - base);
-    const int lo = sg * DEFL_SEG;
-    if (lo >= n || a.status[p]) return;
-    const int hi = min(n, lo + DEFL_SEG);
-    int c = 0;
-    for (int i = lo + (int)threadIdx.x; i < hi; i += WAVE) c += a.flag[base + i] != 0;
-    for (int o = WAVE / 2; o > 0; o >>= 1) c += __shfl_xor(c, o);
-    if (threadIdx.x == 0) a.seg_i[(int64_t)p * a.maxseg + sg].w = c;
-}
-
-// placement: kept poles first, deflated ones after, each in pole order
-__global__ __launch_bounds__(WAVE) void k_deflate_place(DeflArgs a) {
-    const int p = blockIdx.x, sg = blockIdx.y;
-    const int64_t base = a.off[p];
-    const int n = (int)(a.off[p + 1] - base);
-    const int lo = sg * DEFL_SEG;
-    if (lo >= n || a.status[p]) return;
-    const int hi = min(n, lo + DEFL_SEG);
-    const int lane = threadIdx.x;
+// placement of a segment: kept poles first, deflated ones after, each in pole order
+__device__ void defl_place(const DeflArgs &a, int64_t base, int n, int sg, const int4 *rec_i,
+                           int kept) {
+    const int lo = sg * a.seg;
+    if (lo >= n) return;
+    const int hi = min(n, lo + a.seg);
+    const int lane = lane_id();
     int pk = 0;  // kept poles before this segment
-    for (int u = 0; u < sg; ++u) pk += a.seg_i[(int64_t)p * a.maxseg + u].w;
-    int pd = a.kept[p] + (lo - pk);
+    for (int u = lane; u < sg; u += WAVE) pk += rec_i[u].w;
+    for (int o = WAVE / 2; o > 0; o >>= 1) pk += __shfl_xor(pk, o);
+    int pd = kept + (lo - pk);
     const double2 *val = a.val + base;
     const int8_t *flag = a.flag + base;
     int8_t nfl = lo + lane < hi ? flag[lo + lane] : 0;
@@ -356,6 +340,63 @@ __global__ __launch_bounds__(WAVE) void k_deflate_place(DeflArgs a) {
     }
 }
 
+// problems of up to DEFL_WG poles: one workgroup scans, joins and places
+__global__ __launch_bounds__(DEFL_WAVES * WAVE) void k_deflate(DeflArgs a) {
+    __shared__ double sd[DEFL_WAVES][WAVE], sz[DEFL_WAVES][WAVE];
+    __shared__ int si[DEFL_WAVES][WAVE];
+    __shared__ int4 rec_i[DEFL_WAVES];
+    __shared__ double2 rec_d[DEFL_WAVES];
+    __shared__ int res[2];
+    const int p = blockIdx.x, wv = wave_uniform((int)(threadIdx.x / WAVE));
+    const int64_t base = a.off[p];
+    const int n = (int)(a.off[p + 1] - base);
+    defl_segment(a, p, base, n, wv, rec_i, rec_d, sd[wv], sz[wv], si[wv]);
+    __syncthreads();
+    if (wv == 0) {
+        int kept;
+        const int st = defl_join(a, p, base, n, rec_i, rec_d, kept, sd[0], sz[0], si[0]);
+        if (lane_id() == 0) {
+            a.kept[p] = res[0] = kept;
+            a.status[p] = res[1] = st;
+        }
+    }
+    __threadfence_block();
+    __syncthreads();
+    if (!res[1]) defl_place(a, base, n, wv, rec_i, res[0]);
+}
+
+// larger ones: the segments, the joins and the placement in launches of their own
+__global__ __launch_bounds__(WAVE) void k_deflate_scan(DeflArgs a) {
+    __shared__ double sd[WAVE], sz[WAVE];
+    __shared__ int si[WAVE];
+    const int p = blockIdx.x;
+    const int64_t base = a.off[p], r0 = (int64_t)p * a.maxseg;
+    defl_segment(a, p, base, (int)(a.off[p + 1] - base), blockIdx.y, a.seg_i + r0, a.seg_d + r0, sd,
+                 sz, si);
+}
+
+__global__ __launch_bounds__(WAVE) void k_deflate_join(DeflArgs a) {
+    __shared__ double sd[WAVE], sz[WAVE];
+    __shared__ int si[WAVE];
+    const int p = blockIdx.x;
+    const int64_t base = a.off[p], r0 = (int64_t)p * a.maxseg;
+    int kept;
+    const int st = defl_join(a, p, base, (int)(a.off[p + 1] - base), a.seg_i + r0, a.seg_d + r0,
+                             kept, sd, sz, si);
+    if (lane_id() == 0) {
+        a.kept[p] = kept;
+        a.status[p] = st;
+    }
+}
+
+__global__ __launch_bounds__(WAVE) void k_deflate_place(DeflArgs a) {
+    const int p = blockIdx.x;
+    if (a.status[p]) return;
+    const int64_t base = a.off[p];
+    defl_place(a, base, (int)(a.off[p + 1] - base), blockIdx.y, a.seg_i + (int64_t)p * a.maxseg,
+               a.kept[p]);
+}
+
 // ---------------------------------------------------------------------------------------
 // the orthogonal factor: Y = G^T P U (trans 0) or Y = P^T G X (trans 1) on total x m
 // column-major blocks (leading dimensions ldx, ldy), each problem on its own rows
@@ -372,6 +413,17 @@ struct ExpandArgs {
     double *T;  // workspace for trans 1 (total x m, leading dimension total)
 };
 
+// whether pole i (of the problem at base) has a rotation partner on its right / left: links that
+// run through increasing poles and that both ends hold
+__device__ __forceinline__ bool defl_right(const ExpandArgs &a, int64_t base, int n, int i) {
+    const int r = a.rright[base + i];
+    return r > i && r < n && a.rleft[base + r] == i;
+}
+__device__ __forceinline__ bool defl_left(const ExpandArgs &a, int64_t base, int i) {
+    const int l = a.rleft[base + i];
+    return l >= 0 && l < i && a.rright[base + l] == i;
+}
+
 __device__ __forceinline__ int find_prob(const int64_t *off, int nprob, int64_t e) {
     int lo = 0, hi = nprob;  // off[lo] <= e < off[hi]
     while (hi - lo > 1) {
@@ -382,69 +434,113 @@ __device__ __forceinline__ int find_prob(const int64_t *off, int nprob, int64_t 
     return lo;
 }
 
-// trans 0: Y[perm[j]] = X[j]; trans 1: Y[j] = T[perm[j]]  (one thread per row and column)
-__global__ __launch_bounds__(256) void k_defl_place(ExpandArgs a, int trans, int64_t total) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= total * a.m) return;
-    const int64_t row = e % total;
-    const int c = (int)(e / total);
-    const int p = find_prob(a.off, a.nprob, row);
-    const int64_t base = a.off[p];
-    const int pj = a.perm[row];
-    if (pj < 0 || pj >= a.off[p + 1] - base) return;  // not a placement of this problem
-    const int64_t prow = base + pj;
-    if (trans == 0) a.Y[c * a.ldy + prow] = a.X[c * a.ldx + row];
-    else a.Y[c * a.ldy + row] = a.T[c * total + prow];
+// The kernels below are bound by memory: one thread takes a row through `cpt` columns, so that
+// the search for its problem, the permutation and the links are read once for all of them
+// (one thread per row and column, with the search and a 64-bit division each, took 3 to 6 times
+// as long; 1024 problems, 1.7 million rows: row copies 585 -> 196 us
+// in all, 16 columns through the factor 764 -> 318 us).  The problem of the
+// wavefront's first row is found with wave-uniform loads; most lanes share it.
+__device__ __forceinline__ int row_prob(const int64_t *off, int nprob, int64_t row, int64_t total) {
+    const int64_t first = (int64_t)blockIdx.x * blockDim.x + wave_uniform((int)threadIdx.x & -WAVE);
+    const int lo = wave_uniform(find_prob(off, nprob, first < total ? first : total - 1));
+    if (row < off[lo + 1]) return lo;
+    return lo + find_prob(off + lo, nprob - lo, row);
 }
 
-// rotations along their chains (one thread per chain and column) on V (leading dimension
-// ldv): trans 0 applies G^T = G_1^T ... G_R^T, walking each chain back from its last pole;
-// trans 1 applies G = G_R ... G_1, walking forward from its first pole.  Chains are
-// disjoint.
-__global__ __launch_bounds__(256) void k_defl_rotate(ExpandArgs a, int trans, int64_t total,
-                                                     double *V, int64_t ldv) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= total * a.m) return;
-    const int64_t row = e % total;
-    const int c = (int)(e / total);
-    const bool end = a.rleft[row] >= 0 && a.rright[row] < 0;
-    const bool beg = a.rright[row] >= 0 && a.rleft[row] < 0;
-    if (!(trans == 0 ? end : beg)) return;
-    const int p = find_prob(a.off, a.nprob, row);
+// trans 0: Y[perm[j]] = X[j]; trans 1: Y[j] = (G X)[perm[j]], taken from T for the rows of
+// rotation chains and from X for the others
+__global__ __launch_bounds__(256) void k_defl_place(ExpandArgs a, int trans, int64_t total, int cpt) {
+    const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int p = row_prob(a.off, a.nprob, row, total);
+    if (row >= total) return;
     const int64_t base = a.off[p];
-    double *v = V + c * ldv + base;
-    const int32_t *rr = a.rright + base, *rl = a.rleft + base;
-    const double *rc = a.rc + base, *rs = a.rs + base;
-    const int i = (int)(row - base);
-    // a chain runs through strictly increasing poles; a link that does not is not
-    // followed, so every walk ends within n_p steps
+    const int n = (int)(a.off[p + 1] - base);
+    const int pj = a.perm[row];
+    if (pj < 0 || pj >= n) return;  // not a placement of this problem
+    const int64_t prow = base + pj;
+    const int c0 = blockIdx.y * cpt, c1 = min(a.m, c0 + cpt);
     if (trans == 0) {
-        int bb = i;
-        for (int aa = rl[bb]; aa >= 0 && aa < bb; bb = aa, aa = rl[aa]) {
-            const double cc = rc[aa], ss = rs[aa];
-            const double ya = v[aa], yb = v[bb];
-            v[aa] = cc * ya + ss * yb;
-            v[bb] = -ss * ya + cc * yb;
-        }
+        copy_cols(a.X + row, a.ldx, a.Y + prow, a.ldy, c0, c1);
     } else {
-        const int n = (int)(a.off[p + 1] - base);
-        int aa = i;
-        for (int bb = rr[aa]; bb > aa && bb < n; aa = bb, bb = rr[bb]) {
-            const double cc = rc[aa], ss = rs[aa];
-            const double ya = v[aa], yb = v[bb];
-            v[aa] = cc * ya - ss * yb;
-            v[bb] = ss * ya + cc * yb;
-        }
+        const bool chain = defl_left(a, base, pj) || defl_right(a, base, n, pj);
+        copy_cols((chain ? a.T : a.X) + prow, chain ? total : a.ldx, a.Y + row, a.ldy, c0, c1);
     }
 }
 
+// rotations along their chains (one thread per chain and column group): trans 0 applies
+// G^T = G_1^T ... G_R^T to V = Y in place, walking each chain back from its last pole; trans 1
+// takes X to T = G X, G = G_R ... G_1, on the chains' rows alone, walking forward from their
+// first pole.  Chains are disjoint.  The value that a chain carries on stays in a register.
+template <int NC>
+__device__ void defl_walk(const ExpandArgs &a, int trans, int64_t total, int64_t base, int n, int i,
+                          int c0) {
+    const double *rc = a.rc + base, *rs = a.rs + base;
+    const int32_t *rr = a.rright + base, *rl = a.rleft + base;
+    double y[NC];
+    // a chain runs through strictly increasing poles; a link that does not is not
+    // followed, so every walk ends within n_p steps
+    if (trans == 0) {
+        double *v = a.Y + c0 * a.ldy + base;
+        int bb = i;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) y[c] = v[bb + c * a.ldy];
+        for (int aa = rl[bb]; aa >= 0 && aa < bb; bb = aa, aa = rl[aa]) {
+            const double cc = rc[aa], ss = rs[aa];
+            double x[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) x[c] = v[aa + c * a.ldy];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                v[bb + c * a.ldy] = -ss * x[c] + cc * y[c];
+                y[c] = cc * x[c] + ss * y[c];
+            }
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) v[bb + c * a.ldy] = y[c];
+    } else {
+        const double *v = a.X + c0 * a.ldx + base;
+        double *t = a.T + c0 * total + base;
+        int aa = i;
+#pragma unroll
+        for (int c = 0; c < NC; ++c) y[c] = v[aa + c * a.ldx];
+        while (defl_right(a, base, n, aa)) {
+            const int bb = rr[aa];
+            const double cc = rc[aa], ss = rs[aa];
+            double x[NC];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) x[c] = v[bb + c * a.ldx];
+#pragma unroll
+            for (int c = 0; c < NC; ++c) {
+                t[aa + c * total] = cc * y[c] - ss * x[c];
+                y[c] = ss * y[c] + cc * x[c];
+            }
+            aa = bb;
+        }
+#pragma unroll
+        for (int c = 0; c < NC; ++c) t[aa + c * total] = y[c];
+    }
+}
+
+__global__ __launch_bounds__(256) void k_defl_rotate(ExpandArgs a, int trans, int64_t total, int cpt) {
+    const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int p = row_prob(a.off, a.nprob, row, total);
+    if (row >= total) return;
+    const int64_t base = a.off[p];
+    const int n = (int)(a.off[p + 1] - base), i = (int)(row - base);
+    const bool start = trans == 0 ? a.rleft[row] >= 0 && a.rright[row] < 0
+                                  : defl_right(a, base, n, i) && !defl_left(a, base, i);
+    if (!start) return;
+    const int c1 = min(a.m, ((int)blockIdx.y + 1) * cpt);
+    int c = blockIdx.y * cpt;
+    for (; c + 4 <= c1; c += 4) defl_walk<4>(a, trans, total, base, n, i, c);
+    for (; c < c1; ++c) defl_walk<1>(a, trans, total, base, n, i, c);
+}
+
+// X into T as it stands (trans 1 with X and Y overlapping)
 __global__ __launch_bounds__(256) void k_defl_copy(const double *X, int64_t ldx, double *T,
                                                    int64_t total, int m) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= total * m) return;
-    const int64_t row = e % total;
-    const int c = (int)(e / total);
-    T[c * total + row] = X[c * ldx + row];
+    const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (row < total) copy_cols(X + row, ldx, T + row, total, 0, m);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -464,12 +560,10 @@ struct CopyRowsArgs {
     double fill;
 };
 
-__global__ __launch_bounds__(256) void k_copy_rows(CopyRowsArgs a, int64_t dtotal) {
-    const int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (e >= dtotal * a.m) return;
-    const int64_t row = e % dtotal;
-    const int c = (int)(e / dtotal);
-    const int p = find_prob(a.doff, a.nprob, row);
+__global__ __launch_bounds__(256) void k_copy_rows(CopyRowsArgs a, int64_t dtotal, int cpt) {
+    const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int p = row_prob(a.doff, a.nprob, row, dtotal);
+    if (row >= dtotal) return;
     const int64_t db = a.doff[p], nd = a.doff[p + 1] - db;
     const int64_t sb = a.soff[p], ns = a.soff[p + 1] - sb;
     int64_t cnt = ns < nd ? ns : nd;
@@ -478,15 +572,16 @@ __global__ __launch_bounds__(256) void k_copy_rows(CopyRowsArgs a, int64_t dtota
         if (r < cnt) cnt = r;
     }
     const int64_t j = row - db;
-    double *out = a.dst + c * a.ldd + row;
-    if (j < cnt) *out = a.src[c * a.lds + sb + j];
-    else if (a.has_fill) *out = a.fill;
+    const int c0 = blockIdx.y * cpt, c1 = min(a.m, c0 + cpt);
+    if (j < cnt) copy_cols(a.src + sb + j, a.lds, a.dst + row, a.ldd, c0, c1);
+    else if (a.has_fill)
+        for (int c = c0; c < c1; ++c) a.dst[c * a.ldd + row] = a.fill;
 }
 
 // ---------------------------------------------------------------------------------------
-int deflate_segments(int max_n) {
-    const int s = (max_n + DEFL_SEG - 1) / DEFL_SEG;
-    return s > 1 ? s : 1;
+int deflate_segments(int nprob, int max_n) {
+    const int seg = defl_seg(nprob, max_n);
+    return max_n > seg ? (max_n + seg - 1) / seg : 1;
 }
 
 hipError_t launch_deflate(const int64_t *off, int nprob, const double *d, const double *z,
@@ -494,17 +589,21 @@ hipError_t launch_deflate(const int64_t *off, int nprob, const double *d, const 
                           int32_t *perm, int32_t *rright, int32_t *rleft, double *rc, double *rs,
                           int32_t *kept, int32_t *status, double2 *val, int8_t *flag,
                           int max_n, int4 *seg_i, double2 *seg_d, hipStream_t s) {
-    DeflArgs a{off,  d,      z,      rho,  tau,  dout,  zout,  perm,   rright,
-               rleft, rc,    rs,     kept, status, val, flag, seg_i, seg_d, deflate_segments(max_n)};
+    DeflArgs a{off,  d,  z,    rho,    tau, dout, zout,  perm,  rright, rleft,
+               rc,   rs, kept, status, val, flag, seg_i, seg_d, DEFL_SEG, 0};
+    if (max_n <= DEFL_WG) {
+        SDC_LAUNCH(KID_DEFLATE, k_deflate, dim3(nprob),
+                   dim3(WAVE * std::max(1, (max_n + DEFL_SEG - 1) / DEFL_SEG)), 0, s, a);
+        return hipGetLastError();
+    }
+    a.seg = defl_seg(nprob, max_n);
+    a.maxseg = deflate_segments(nprob, max_n);
     const dim3 g2(nprob, a.maxseg);
-    SDC_LAUNCH(KID_DEFLATE, k_deflate, g2, dim3(WAVE), 0, s, a);
+    SDC_LAUNCH(KID_DEFLATE, k_deflate_scan, g2, dim3(WAVE), 0, s, a);
     SDC_LAUNCH(KID_DEFLATE, k_deflate_join, dim3(nprob), dim3(WAVE), 0, s, a);
-    SDC_LAUNCH(KID_DEFLATE, k_deflate_count, g2, dim3(WAVE), 0, s, a);
     SDC_LAUNCH(KID_DEFLATE, k_deflate_place, g2, dim3(WAVE), 0, s, a);
     return hipGetLastError();
 }
-
-static dim3 grid_of(int64_t cnt) { return dim3((unsigned)((cnt + 255) / 256)); }
 
 hipError_t launch_deflate_expand(const int64_t *off, int nprob, int64_t total, int m,
                                  const int32_t *perm, const int32_t *rright,
@@ -512,17 +611,20 @@ hipError_t launch_deflate_expand(const int64_t *off, int nprob, int64_t total, i
                                  int trans, const double *X, int64_t ldx, double *Y,
                                  int64_t ldy, double *T, hipStream_t s) {
     ExpandArgs a{off, nprob, m, perm, rright, rleft, rc, rs, X, ldx, Y, ldy, T};
-    const int64_t cnt = total * m;
-    if (cnt == 0) return hipSuccess;
+    if (total * m == 0) return hipSuccess;
+    const int cpt = cols_per_thread(total, m);
+    const dim3 g = row_grid(total, m, cpt);
     if (trans == 0) {
-        SDC_LAUNCH(KID_DEFL_PLACE, k_defl_place, grid_of(cnt), dim3(256), 0, s, a, 0, total);
-        SDC_LAUNCH(KID_DEFL_ROTATE, k_defl_rotate, grid_of(cnt), dim3(256), 0, s, a, 0, total, Y,
-                   ldy);
+        SDC_LAUNCH(KID_DEFL_PLACE, k_defl_place, g, dim3(256), 0, s, a, 0, total, cpt);
+        SDC_LAUNCH(KID_DEFL_ROTATE, k_defl_rotate, g, dim3(256), 0, s, a, 0, total, cpt);
     } else {
-        SDC_LAUNCH(KID_DEFL_PLACE, k_defl_copy, grid_of(cnt), dim3(256), 0, s, X, ldx, T, total, m);
-        SDC_LAUNCH(KID_DEFL_ROTATE, k_defl_rotate, grid_of(cnt), dim3(256), 0, s, a, 1, total, T,
-                   total);
-        SDC_LAUNCH(KID_DEFL_PLACE, k_defl_place, grid_of(cnt), dim3(256), 0, s, a, 1, total);
+        if (X < Y + (m - 1) * ldy + total && Y < X + (m - 1) * ldx + total) {
+            SDC_LAUNCH(KID_DEFL_PLACE, k_defl_copy, dim3(g.x), dim3(256), 0, s, X, ldx, T, total, m);
+            a.X = T;
+            a.ldx = total;
+        }
+        SDC_LAUNCH(KID_DEFL_ROTATE, k_defl_rotate, g, dim3(256), 0, s, a, 1, total, cpt);
+        SDC_LAUNCH(KID_DEFL_PLACE, k_defl_place, g, dim3(256), 0, s, a, 1, total, cpt);
     }
     return hipGetLastError();
 }
@@ -532,9 +634,9 @@ hipError_t launch_copy_rows(const int64_t *soff, const int64_t *doff, int nprob,
                             int64_t lds, double *dst, int64_t ldd, const double *fill,
                             hipStream_t s) {
     CopyRowsArgs a{soff, doff, nprob, m, rows, src, lds, dst, ldd, fill ? 1 : 0, fill ? *fill : 0.0};
-    const int64_t cnt = dtotal * m;
-    if (cnt == 0) return hipSuccess;
-    SDC_LAUNCH(KID_COPY_ROWS, k_copy_rows, grid_of(cnt), dim3(256), 0, s, a, dtotal);
+    if (dtotal * m == 0) return hipSuccess;
+    const int cpt = cols_per_thread(dtotal, m);
+    SDC_LAUNCH(KID_COPY_ROWS, k_copy_rows, row_grid(dtotal, m, cpt), dim3(256), 0, s, a, dtotal, cpt);
     return hipGetLastError();
 }
 

@@ -25,7 +25,7 @@ int superdc_deflate(superdc_ctx *ctx, const superdc_batch *b, const double *d, c
     hipStream_t s = (hipStream_t)stream;
     double2 *val = (double2 *)ws_get(ctx, WS_DEFL_VAL, sizeof(double2) * b->total);
     int8_t *flag = (int8_t *)ws_get(ctx, WS_DEFL_FLAG, sizeof(int8_t) * b->total);
-    const size_t nrec = (size_t)b->nprob * deflate_segments(b->max_n);
+    const size_t nrec = (size_t)b->nprob * deflate_segments(b->nprob, b->max_n);
     int4 *seg_i = (int4 *)ws_get(ctx, WS_DEFL_SEGI, sizeof(int4) * nrec);
     double2 *seg_d = (double2 *)ws_get(ctx, WS_DEFL_SEGD, sizeof(double2) * nrec);
     if (!val || !flag || !seg_i || !seg_d) return SUPERDC_ENOMEM;

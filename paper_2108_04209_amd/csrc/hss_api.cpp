@@ -129,7 +129,9 @@ hipError_t defl_alloc(superdc_hss *h) {
     if (e == hipSuccess) e = alloc(h, &h->xv, n);
     if (e == hipSuccess) e = alloc(h, &h->xval, n);
     if (e == hipSuccess) e = alloc(h, &h->xflag, n);
-    const size_t nrec = ((size_t)1 << (h->depth - 1)) * deflate_segments((int)n);
+    size_t nrec = 0;  // of the level that needs most
+    for (int l = 0; l < h->depth; ++l)
+        nrec = std::max(nrec, ((size_t)1 << l) * deflate_segments(1 << l, (int)(n >> l)));
     if (e == hipSuccess) e = alloc(h, &h->xsegi, nrec);
     if (e == hipSuccess) e = alloc(h, &h->xsegd, nrec);
     for (double **p : {&h->xY, &h->xR0, &h->xR1, &h->xT})
