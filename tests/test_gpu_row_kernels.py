@@ -107,3 +107,20 @@ def test_copy_rows_columns(m):
     got = native.batch_copy_rows(ctx, native.Batch(ctx, soff), native.Batch(ctx, doff), gp.to_dev(src),
                                  rows=gp.to_dev(rows, torch.int32), fill=-2.0)
     assert np.array_equal(got.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("n,leaf", [(60, 30), (2048, 64), (2240, 70), (3200, 100), (4160, 130 // 2),
+                                    (6144, 96)])
+def test_sort_runs(n, leaf):
+    """Node sizes around the runs sorted in LDS (2048 keys; ragged last runs), through the
+    deflated HSS pass: eigenvalues within 5e-9 of the closed form and whole eigenvectors'
+    residual, as for the larger trees (tau = 1e-10)."""
+    from tests.test_gpu_hss_deflate import columns, run, tmatvec
+    plan, lam, st = run(gen.tridiag_hss(n, leaf), 1e-10)
+    assert st == 0 and (np.diff(lam) >= 0).all()
+    exact = np.sort(3.0 - 2.0 * np.cos(np.arange(1, n + 1) * np.pi / (n + 1)))
+    assert np.abs(lam - exact).max() <= 5e-9
+    ks = np.unique(np.linspace(0, n - 1, 25).astype(int))
+    Qs = columns(plan, ks, n)
+    res = np.linalg.norm(tmatvec(np.full(n, 3.0), np.full(n - 1, -1.0), Qs) - Qs * lam[ks], axis=0)
+    assert res.max() <= 5e-9
