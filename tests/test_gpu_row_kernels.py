@@ -109,7 +109,7 @@ def test_copy_rows_columns(m):
     assert np.array_equal(got.cpu().numpy(), want)
 
 
-@pytest.mark.parametrize("n,leaf", [(60, 30), (2048, 64), (2240, 70), (3200, 100), (4160, 130 // 2),
+@pytest.mark.parametrize("n,leaf", [(60, 30), (2048, 64), (2240, 70), (3200, 100), (4224, 66),
                                     (6144, 96)])
 def test_sort_runs(n, leaf):
     """Node sizes around the runs sorted in LDS (2048 keys; ragged last runs), through the
