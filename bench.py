@@ -78,7 +78,7 @@ MFMA_MIN_M = 4           # the library's automatic VALU/MFMA apply switch (colum
 
 
 MFMA_KERNELS = ("k_apply_mfma", "k_fmmv_eval_mfma")  # FP64 matrix-core kernels
-APPLY_KERNELS = ("k_apply_mfma", "k_apply_valu", "k_fmmv_eval_mfma", "k_fmmv_eval")
+APPLY_KERNELS = ("k_apply_mfma", "k_apply_valu", "k_fmmv_eval_mfma", "k_fmmv_eval", "k_bwd_fmm")
 SOLVER_KERNELS = ("k_secular", "k_secular_fmm")
 
 
@@ -883,9 +883,8 @@ def bench_grad(args):
 
     kt, kw, lanes = kernel_pass(native, fwd_bwd, args.steps)
     sizes = full.sizes().astype(np.float64)
-    n2 = float(np.sum(sizes ** 2))
     small = sizes[sizes < FMM_CROSSOVER]
-    kflops = {"k_bwd": FLOPS_BWD_PAIR * n2, "k_loewner": FLOPS_LOEWNER * float(np.sum(small ** 2)),
+    kflops = {"k_bwd": FLOPS_BWD_PAIR * float(np.sum(small ** 2)), "k_loewner": FLOPS_LOEWNER * float(np.sum(small ** 2)),
               "k_bnorm": FLOPS_BNORM * float(np.sum(small ** 2))}
     kflops.update(counted_flops(kw, args.steps))
     kernels, roofline = kernel_roofline(kt, kflops, args.steps)

@@ -62,13 +62,18 @@ int opts_check(const superdc_opts *o) {
 // columns' pairs (8 problems of 1024 roots, 64 columns: 39 and 41 us; 4 of 2048: 70 and 42).
 constexpr double DIRECT_PAIRS = 4e7;
 constexpr double DIRECT_APPLY_PAIRS = 9e6;
+// The adjoint's direct sums take longer the longer the largest problem is (few tiles, each
+// through all its poles): direct against FMM, 16 problems of 1024 roots 40 and 72 us, 4 of
+// 2048 62 and 77, 1 of 4096 108 and 84, 64 of 1024 172 and 113.
+constexpr double DIRECT_BWD_PAIRS = 2e7;
+constexpr int DIRECT_BWD_N = 2048;
 
-int fmm_crossover_of(const superdc_batch *b, const superdc_opts &o, bool apply) {
+int fmm_crossover_of(const superdc_batch *b, const superdc_opts &o, double pairs) {
     if (o.method == 1) return 0x7fffffff;
     if (o.method == 2) return 2 * o.fmm_leaf;
     if (o.fmm_crossover > 0) return o.fmm_crossover;
     const bool direct = b->max_n <= SECL_MAX_N &&
-                        b->big_pairs <= (apply ? DIRECT_APPLY_PAIRS : DIRECT_PAIRS) &&
+                        b->big_pairs <= (pairs > 0.0 ? pairs : DIRECT_PAIRS) &&
                         !o.unshifted && !o.interp && o.persistent;
     return direct ? 0x7fffffff : b->ctx->fmm_crossover;
 }
@@ -553,9 +558,9 @@ FmmArgs fmm_roots_args(const FmmPlan *fp, const superdc_batch *b, const double *
 }
 
 // the FMM plan that applies to this call, or nullptr (rc = ENOMEM on allocation failure)
-FmmPlan *fmm_for(superdc_batch *b, const superdc_opts &o, int &rc, bool apply = false) {
+FmmPlan *fmm_for(superdc_batch *b, const superdc_opts &o, int &rc, double pairs = 0.0) {
     rc = SUPERDC_OK;
-    const int crossover = fmm_crossover_of(b, o, apply);
+    const int crossover = fmm_crossover_of(b, o, pairs);
     if (b->max_n < crossover) return nullptr;
     FmmPlan *fp = fmm_plan(b, o.fmm_leaf, crossover);
     if (!fp) {
@@ -804,7 +809,7 @@ int apply_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const d
     // sums over the roots (sources at the roots, targets at the poles, lists of their own);
     // the other problems by the direct kernels
     int rc;
-    FmmPlan *fp = fmm_for(bm, o, rc, true);
+    FmmPlan *fp = fmm_for(bm, o, rc, DIRECT_APPLY_PAIRS);
     if (rc) return rc;
     // the solve left lists only if it used the FMM as well
     if (fmm_crossover_of(b, o) == 0x7fffffff) reuse_lists = false;
@@ -1150,17 +1155,75 @@ int superdc_secular_backward(superdc_ctx *ctx, const superdc_batch *b, const dou
     const TileList *L = tile_list(bm, TILE);
     if (!L) return SUPERDC_ENOMEM;
     if (o.persistent) {
-        a.tiles = L->lpt;
-        a.ntiles = L->count;
-        const int S = b->bwd.split;
-        SDC_HIP(launch_backward(a, S, 0, b->nprob, s));
+        // the large problems through the FMM; all of them directly where its workspace does
+        // not fit
+        int rc;
+        FmmPlan *fp = fmm_for(bm, o, rc, b->max_n <= DIRECT_BWD_N ? DIRECT_BWD_PAIRS : 1.0);
+        if (rc) return rc;
+        const int nw = g_proj ? 2 : 1;  // weights of a pole; of a root one more with projections
+        double *pos = nullptr;
+        double2 *ke = nullptr;
+        FmmArgs f{};
+        FmmVec v{};
+        if (fp) {
+            pos = (double *)ws_get(ctx, WS_VPAIR, sizeof(double) * b->total);
+            ke = (double2 *)ws_get(ctx, WS_KE, sizeof(double2) * b->total);
+            if (!pos || !ke || !fmmv_space(ctx, fp, g_proj ? 3 : 1, f, v)) fp = nullptr;
+        }
+        a.tiles = fp ? fp->dir_lpt[chunk_slot(TILE)] : L->lpt;
+        a.ntiles = fp ? fp->dir_count[chunk_slot(TILE)] : L->count;
+        SDC_HIP(launch_backward(a, b->bwd.split, s));
+        if (fp) {
+            a.tiles = fp->leaf_lpt;
+            a.ntiles = fp->nitems;
+            v.d = d;
+            v.origin = origin;
+            v.eta = eta;
+            v.scale = z;
+            v.u = u;
+            v.rk = a.rk;
+            v.gk = a.gk;
+            double *const part = f.vpart;
+            // the roots' sums over the poles
+            v.kern = 3;
+            v.m = nw;
+            v.trans = 1;
+            f = fmm_vec_args(fp, b, d, eta, origin, status);
+            f.vpart = part;
+            f.gen = fp->own.gen = ++ctx->lists_gen;
+            SDC_HIP(launch_fmm_lists(f, s));
+            SDC_HIP(launch_fmmv_sources(f, v, s));
+            SDC_HIP(launch_backward_fmm(a, f, v, fp->split, ctx->num_cu, s));
+            // the poles' sums over the roots
+            FmmvPackArgs pk{};
+            pk.off = b->off_d;
+            pk.tiles = fp->leaf_nat;
+            pk.ntiles = fp->nitems;
+            pk.d = d;
+            pk.eta = eta;
+            pk.origin = origin;
+            pk.pos = pos;
+            pk.ke = ke;
+            SDC_HIP(launch_fmmv_pos(pk, s));
+            v.kern = 4;
+            v.m = g_proj ? 3 : 1;
+            v.trans = 0;
+            f = fmm_roots_args(fp, b, pos, status, d);
+            f.vpart = part;
+            f.gen = fp->roots.gen = ++ctx->lists_gen;
+            SDC_HIP(launch_fmm_lists(f, s));
+            SDC_HIP(launch_fmmv_sources(f, v, s));
+            SDC_HIP(launch_backward_fmm(a, f, v, fp->split, ctx->num_cu, s));
+        }
+        SDC_HIP(launch_backward_rho(a, 0, b->nprob, s));
     } else {
         for (int p = 0; p < b->nprob; ++p) {
             const int64_t np = b->off_h[p + 1] - b->off_h[p];
             const int S = shape_for(ctx, &np, 1, TILE, MIN_VEC_POLES).split;
             a.tiles = L->nat + L->begin[p];
             a.ntiles = L->begin[p + 1] - L->begin[p];
-            SDC_HIP(launch_backward(a, S, p, 1, s));
+            SDC_HIP(launch_backward(a, S, s));
+            SDC_HIP(launch_backward_rho(a, p, 1, s));
         }
     }
     return SUPERDC_OK;

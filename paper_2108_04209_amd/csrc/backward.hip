@@ -13,9 +13,43 @@
 //   g_rho   = sum_k alpha_k / rho^2
 // Pass 1 (one lane per root) forms the root sums over poles; pass 2 (one lane per pole)
 // forms the six Cauchy-like sums over roots; pass 3 reduces g_rho per problem.
-#include "common.h"
+#include "fmm_far.h"
 
 namespace sdc {
+
+// a root's cotangents from its sums
+template <bool PROJ>
+__device__ __forceinline__ void bwd_root_out(const BwdArgs &a, int64_t k, double dK, double eta,
+                                             double S, double S3, double h, double H2) {
+    const double b = 1.0 / sqrt(S);
+    const double b2 = b * b;
+    double lbar = a.g_lam ? a.g_lam[k] : 0.0;
+    double beta = 0.0, gamma = 0.0;
+    if (PROJ) {
+        const double gp = a.g_proj[k];
+        lbar += gp * (b * H2 - h * b2 * b * S3);
+        beta = gp * b;
+        gamma = gp * h * b2 * b;
+    }
+    a.rk[k] = make_double4(dK, eta, lbar * b2, beta);
+    a.gk[k] = gamma;
+}
+
+// a pole's gradients from its sums
+template <bool PROJ>
+__device__ __forceinline__ void bwd_pole_out(const BwdArgs &a, int64_t i, double A1, double A2,
+                                             double A3, double B1, double B2, double B3) {
+    const double zi = a.z[i];
+    double gd = zi * zi * (A1 + A3);
+    double gz = -2.0 * zi * B1 - zi * B3;
+    if (PROJ) {
+        const double ui = a.u[i];
+        gd -= ui * zi * A2;
+        gz += ui * B2;
+    }
+    a.g_d[i] = gd;
+    a.g_z[i] = gz;
+}
 
 template <bool PROJ>
 __device__ void bwd_roots_tile(const BwdArgs &a, Tile t, double4 *red) {
@@ -69,18 +103,7 @@ __device__ void bwd_roots_tile(const BwdArgs &a, Tile t, double4 *red) {
         a.gk[base + k] = nan;
         return;
     }
-    const double b = 1.0 / sqrt(S);
-    const double b2 = b * b;
-    double lbar = a.g_lam ? a.g_lam[base + k] : 0.0;
-    double beta = 0.0, gamma = 0.0;
-    if (PROJ) {
-        const double gp = a.g_proj[base + k];
-        lbar += gp * (b * H2 - h * b2 * b * S3);
-        beta = gp * b;
-        gamma = gp * h * b2 * b;
-    }
-    a.rk[base + k] = make_double4(dK, eta, lbar * b2, beta);
-    a.gk[base + k] = gamma;
+    bwd_root_out<PROJ>(a, base + k, dK, eta, S, S3, h, H2);
 }
 
 template <bool PROJ>
@@ -137,16 +160,7 @@ __device__ void bwd_poles_tile(const BwdArgs &a, Tile t, double4 *red) {
         __syncthreads();
     }
     if (!active || wv != 0) return;
-    const double zi = a.z[base + i];
-    double gd = zi * zi * (A1 + A3);
-    double gz = -2.0 * zi * B1 - zi * B3;
-    if (PROJ) {
-        const double ui = a.u[base + i];
-        gd -= ui * zi * A2;
-        gz += ui * B2;
-    }
-    a.g_d[base + i] = gd;
-    a.g_z[base + i] = gz;
+    bwd_pole_out<PROJ>(a, base + i, A1, A2, A3, B1, B2, B3);
 }
 
 // blockDim.x = 64 S; dynamic LDS: two double4 per thread when S > 1
@@ -155,6 +169,246 @@ __global__ __launch_bounds__(1024) void k_bwd(BwdArgs a) {
     extern __shared__ double4 red4[];
     if (PASS == 1) bwd_roots_tile<PROJ>(a, a.tiles[blockIdx.x], red4);
     else bwd_poles_tile<PROJ>(a, a.tiles[blockIdx.x], red4);
+}
+
+// ---------------------------------------------------------------------------------------
+// The same sums through the FMM, for the large problems: near sources directly in the shifted
+// form, far boxes through equivalent sources.  The equivalent weights of a box don't depend on
+// the kernel, so those of (z^2, u z) serve the roots' four sums and those of (alpha, beta,
+// gamma) the poles' six.  One lane per target, S wavefronts per item of 64 targets; the far
+// field of the boxes away from the targets' interval goes through its nodes (fmm_far.h).
+// Bound by the FP64 pipe, as the direct sums: 1024 problems of 256 to 4096 roots with
+// projections took those 7.7 ms at 93 % of it; here 1.2 ms, 0.5 ms for the weights of the boxes
+// and 0.3 ms for the problems below the crossover.
+// ---------------------------------------------------------------------------------------
+template <bool PROJ, int PASS>
+struct BwdFar {
+    static constexpr int NF = PASS == 1 ? (PROJ ? 4 : 1) : (PROJ ? 6 : 2);  // sums
+    static constexpr int NW = PASS == 1 ? (PROJ ? 2 : 1) : (PROJ ? 3 : 1);  // weights
+    // a source's terms with reciprocal difference r and weights w
+    static __device__ __forceinline__ void add(double r, const double (&w)[NW], double (&acc)[NF]) {
+        const double r2 = r * r;
+        if constexpr (PASS == 1) {  // S, S3, h, H2
+            const double t2 = w[0] * r2;
+            acc[0] += t2;
+            if constexpr (PROJ) {
+                acc[1] = __builtin_fma(t2, r, acc[1]);
+                const double t1 = w[1] * r;
+                acc[2] += t1;
+                acc[3] = __builtin_fma(t1, r, acc[3]);
+            }
+        } else {  // A1, B1, A2, B2, A3, B3
+            acc[0] = __builtin_fma(w[0], r2, acc[0]);
+            acc[1] = __builtin_fma(w[0], r, acc[1]);
+            if constexpr (PROJ) {
+                acc[2] = __builtin_fma(w[1], r2, acc[2]);
+                acc[3] = __builtin_fma(w[1], r, acc[3]);
+                const double g2 = w[2] * r2;
+                acc[4] = __builtin_fma(g2, r, acc[4]);
+                acc[5] += g2;
+            }
+        }
+    }
+    int fbox[2 * FMM_FAR_MAX];
+    int nexp;
+    double gsum[8][NF][FMM_P];  // far field at the nodes, per wavefront (at most 8)
+};
+
+template <bool PROJ, int PASS>
+__device__ void bwd_fmm_item(const BwdArgs &a, const FmmArgs &f, const FmmVec &v, Tile t,
+                             BwdFar<PROJ, PASS> &sh, double *red) {
+    using Far = BwdFar<PROJ, PASS>;
+    constexpr int NF = Far::NF, NW = Far::NW;
+    const int p = t.prob;
+    const int64_t base = a.off[p];
+    const int n = (int)(a.off[p + 1] - base);
+    const int lane = lane_id();
+    const int S = blockDim.x / WAVE, wv = wave_uniform((int)(threadIdx.x / WAVE));
+    const int j = t.row0 + lane;
+    const bool active = j < n;
+    const int jj = active ? j : n - 1;
+    const bool bad = (a.status[p] & ~SUPERDC_ST_NOCONV) != 0;
+    // the target x = x0 + x1 (a root's d_K + eta, or a pole)
+    const double x0 = PASS == 1 ? a.d[base + clamp_idx(a.origin[base + jj], n)] : a.d[base + jj];
+    const double x1 = PASS == 1 ? a.eta[base + jj] : 0.0;
+    if (bad) {
+        const double nan = __builtin_nan("");
+        if (active && wv == 0) {
+            if (PASS == 1) {
+                a.rk[base + j] = make_double4(x0, x1, nan, nan);
+                a.gk[base + j] = nan;
+            } else {
+                a.g_d[base + j] = nan;
+                a.g_z[base + j] = nan;
+            }
+        }
+        return;
+    }
+    const int L = wave_uniform(f.leaf_off[f.fmm_of[p]] + t.row0 / f.leaf);
+    const int nn = wave_uniform(f.cnt[3 * (int64_t)L]);
+    const int nl = wave_uniform(f.cnt[3 * (int64_t)L + 1]);
+    const int nr = wave_uniform(f.cnt[3 * (int64_t)L + 2]);
+    const const_double_ptr d = as_const(a.d + base), z = as_const(a.z + base);
+    const const_double_ptr u = as_const(PROJ ? a.u + base : a.z + base);
+    const const_double4_ptr rk = as_const(a.rk + base);  // PASS 2: written by the roots' pass
+    const const_double_ptr gk = as_const(a.gk + base);
+    double acc[NF];
+#pragma unroll
+    for (int c = 0; c < NF; ++c) acc[c] = 0.0;
+    int64_t ent = 0;  // sources this wavefront sums per target (kernel timing)
+    // roots: two poles with one reciprocal while every |t| lies inside [2^-300, 2^300] (the
+    // smallest is |eta|, the largest at an end of the problem)
+    const bool pair = PASS == 1 &&
+                      __ballot(fabs(x1) < 0x1p-300 ||
+                               fmax(fabs((d[0] - x0) - x1), fabs((d[n - 1] - x0) - x1)) > 0x1p300) == 0ull;
+    auto near = [&](int lo, int hi) {
+        lo = wave_uniform(lo);
+        hi = wave_uniform(hi);
+        ent += hi > lo ? hi - lo : 0;
+        if constexpr (PASS == 1) {
+            // squared after the division (z^2 r^2 can leave the range)
+            auto pole = [&](int i, double r) {
+                const double zr = z[i] * r;
+                const double t2 = zr * zr;
+                acc[0] += t2;
+                if constexpr (PROJ) {
+                    acc[1] = __builtin_fma(t2, r, acc[1]);
+                    const double t1 = u[i] * zr;
+                    acc[2] += t1;
+                    acc[3] = __builtin_fma(t1, r, acc[3]);
+                }
+            };
+            int i = lo;
+            if (pair) {
+#pragma unroll 2
+                for (; i + 2 <= hi; i += 2) {
+                    const double t0 = (d[i] - x0) - x1, t1 = (d[i + 1] - x0) - x1;
+                    const double R = rcp_nr(t0 * t1);
+                    pole(i, t1 * R);
+                    pole(i + 1, t0 * R);
+                }
+            }
+            for (; i < hi; ++i) pole(i, rcp_nr((d[i] - x0) - x1));
+        } else {
+#pragma unroll 2
+            for (int k = lo; k < hi; ++k) {
+                const double4 q = rk[k];
+                double w[NW];
+                w[0] = q.z;
+                if constexpr (PROJ) {
+                    w[1] = q.w;
+                    w[2] = gk[k];
+                }
+                Far::add(rcp_nr((x0 - q.x) - q.y), w, acc);
+            }
+        }
+    };
+    if (nn < 0) {  // lists overflowed: every source directly, split over the wavefronts
+        near((int)(((int64_t)n * wv) / S), (int)(((int64_t)n * (wv + 1)) / S));
+    } else {
+        for (int e = 0; e < nn; ++e) {
+            const int lo0 = wave_uniform(f.near_lo[(int64_t)L * FMM_NEAR_MAX + e]);
+            const int hi0 = wave_uniform(f.near_hi[(int64_t)L * FMM_NEAR_MAX + e]);
+            near(lo0 + (int)(((int64_t)(hi0 - lo0) * wv) / S),
+                 lo0 + (int)(((int64_t)(hi0 - lo0) * (wv + 1)) / S));
+        }
+        constexpr double sg = PASS == 1 ? 1.0 : -1.0;  // t: source - root, pole - source
+        const double2 iv = fv_interval(v, base, n, t.row0, min(t.row0 + WAVE, n) - 1);
+        if (wv == 0) {
+            const int k = fv_split_far(f, v, L, nl, nr, iv, v.expand != 0, sh.fbox);
+            if (lane == 0) sh.nexp = k;
+        }
+        __syncthreads();
+        const int ne = wave_uniform(sh.nexp);
+        if (ne > 0) {
+            // lane: node lane % 16, every fourth source of a box
+            const double off = iv.y * FV_NODE[lane & 15];
+            double gs[NF];
+#pragma unroll
+            for (int c = 0; c < NF; ++c) gs[c] = 0.0;
+            for (int e = wv; e < ne; e += S) {
+                const int64_t g = sh.fbox[2 * FMM_FAR_MAX - 1 - e];
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int64_t sq = g * FMM_P + 4 * k + (lane >> 4);
+                    double w[NW];
+#pragma unroll
+                    for (int c = 0; c < NW; ++c) w[c] = v.vw[sq * NW + c];
+                    Far::add(sg * rcp_nr((v.vnode[sq] - iv.x) - off), w, gs);
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < NF; ++c) {
+                gs[c] += __shfl_xor(gs[c], 16);
+                gs[c] += __shfl_xor(gs[c], 32);
+                if (lane < FMM_P) sh.gsum[wv][c][lane] = gs[c];
+            }
+            wave_sync();
+            // this wavefront's share of the far field at the targets
+            const double tau = ((x0 - iv.x) + x1) / iv.y;
+            double num[NF], den = 0.0;
+#pragma unroll
+            for (int c = 0; c < NF; ++c) num[c] = 0.0;
+            for (int q = 0; q < FMM_P; ++q) {
+                const double dl = tau - FV_NODE[q];
+                // a target on a node: that node's term outweighs the others
+                const double b = FV_BARY[q] * rcp_nr(dl == 0.0 ? 0x1p-200 : dl);
+                den += b;
+#pragma unroll
+                for (int c = 0; c < NF; ++c) num[c] = __builtin_fma(b, sh.gsum[wv][c][q], num[c]);
+            }
+            const double iden = 1.0 / den;
+#pragma unroll
+            for (int c = 0; c < NF; ++c) acc[c] = __builtin_fma(num[c], iden, acc[c]);
+            if (v.work && lane == 0)
+                atomicAdd(v.work, (unsigned long long)((ne - wv + S - 1) / S) * FMM_P * FMM_P * (3 * NF) +
+                                      (unsigned long long)(WAVE * FMM_P * 2 * NF));
+        }
+        for (int e = wv; e < nl + nr - ne; e += S) {
+            const int g = wave_uniform(sh.fbox[e]);
+            const const_double_ptr nd = as_const(v.vnode + (int64_t)g * FMM_P);
+            const const_double_ptr ww = as_const(v.vw + (int64_t)g * FMM_P * NW);
+            ent += FMM_P;
+#pragma unroll 4
+            for (int q = 0; q < FMM_P; ++q) {
+                double w[NW];
+#pragma unroll
+                for (int c = 0; c < NW; ++c) w[c] = ww[q * NW + c];
+                Far::add(sg * rcp_nr((nd[q] - x0) - x1), w, acc);
+            }
+        }
+    }
+    if (v.work && lane == 0)  // kernel timing: algorithmic flops of this wavefront's share
+        atomicAdd(v.work, (unsigned long long)__popcll(__ballot(active)) * (unsigned long long)ent *
+                              (3 * NF));
+    if (S > 1) {
+        if (wv > 0)
+#pragma unroll
+            for (int c = 0; c < NF; ++c) red[((wv - 1) * NF + c) * WAVE + lane] = acc[c];
+        __syncthreads();
+        if (wv == 0)
+            for (int w = 1; w < S; ++w)
+#pragma unroll
+                for (int c = 0; c < NF; ++c) acc[c] += red[((w - 1) * NF + c) * WAVE + lane];
+    }
+    if (!active || wv != 0) return;
+    if constexpr (PASS == 1) {
+        if constexpr (PROJ) bwd_root_out<true>(a, base + j, x0, x1, acc[0], acc[1], acc[2], acc[3]);
+        else bwd_root_out<false>(a, base + j, x0, x1, acc[0], 0.0, 0.0, 0.0);
+    } else {
+        if constexpr (PROJ)
+            bwd_pole_out<true>(a, base + j, acc[0], acc[2], acc[4], acc[1], acc[3], acc[5]);
+        else
+            bwd_pole_out<false>(a, base + j, acc[0], 0.0, 0.0, acc[1], 0.0, 0.0);
+    }
+}
+
+// blockDim.x = 64 S; dynamic LDS: S - 1 wavefronts' sums
+template <bool PROJ, int PASS>
+__global__ __launch_bounds__(512) void k_bwd_fmm(BwdArgs a, FmmArgs f, FmmVec v) {
+    extern __shared__ double red[];
+    __shared__ BwdFar<PROJ, PASS> sh;
+    bwd_fmm_item<PROJ, PASS>(a, f, v, a.tiles[blockIdx.x], sh, red);
 }
 
 // g_rho[p] = sum_k alpha_k / rho_p^2, fixed-order block reduction
@@ -176,7 +430,7 @@ __global__ __launch_bounds__(256) void k_bwd_rho(BwdArgs a, int prob_first) {
     }
 }
 
-hipError_t launch_backward(const BwdArgs &a, int split, int prob_first, int nprob, hipStream_t s) {
+hipError_t launch_backward(const BwdArgs &a, int split, hipStream_t s) {
     if (a.ntiles <= 0) return hipSuccess;
     const bool proj = a.g_proj != nullptr;
     const dim3 g(a.ntiles), blk(WAVE * split);
@@ -188,6 +442,37 @@ hipError_t launch_backward(const BwdArgs &a, int split, int prob_first, int npro
         SDC_LAUNCH(KID_BWD, (k_bwd<false, 1>), g, blk, lds, s, a);
         SDC_LAUNCH(KID_BWD, (k_bwd<false, 2>), g, blk, lds, s, a);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_backward_fmm(const BwdArgs &a, const FmmArgs &f, const FmmVec &v0, int split,
+                               int num_cu, hipStream_t s) {
+    if (a.ntiles <= 0) return hipSuccess;
+    const bool proj = a.g_proj != nullptr;
+    FmmVec v = v0;
+    if (v.m != (v.kern == 3 ? (proj ? 2 : 1) : (proj ? 3 : 1)) || split > 8) return hipErrorInvalidValue;
+    v.work = trace_work(KID_BWD_FMM);
+    v.expand = a.ntiles >= FV_EXPAND_PER_CU * num_cu;
+    const dim3 g(a.ntiles), blk(WAVE * split);
+#define SDC_BWD(P, K)                                                                   \
+    {                                                                                   \
+        constexpr int nf = (BwdFar<P, K>::NF);                                          \
+        SDC_LAUNCH(KID_BWD_FMM, (k_bwd_fmm<P, K>), g, blk,                              \
+                   sizeof(double) * WAVE * (split - 1) * nf, s, a, f, v);               \
+    }
+    if (v.kern == 3) {
+        if (proj) SDC_BWD(true, 1)
+        else SDC_BWD(false, 1)
+    } else {
+        if (proj) SDC_BWD(true, 2)
+        else SDC_BWD(false, 2)
+    }
+#undef SDC_BWD
+    return hipGetLastError();
+}
+
+hipError_t launch_backward_rho(const BwdArgs &a, int prob_first, int nprob, hipStream_t s) {
+    if (nprob <= 0) return hipSuccess;
     SDC_LAUNCH(KID_BWD_RHO, k_bwd_rho, dim3(nprob), dim3(256), 0, s, a, prob_first);
     return hipGetLastError();
 }

@@ -142,7 +142,8 @@ enum KernelId : int {
     KID_MERGE, KID_ASSEMBLE, KID_PERMUTE, KID_LEAF_APPLY, KID_STATUS_OR, KID_FILL,
     KID_LEAF_VECTORS, KID_FMMV_PACK, KID_FMMV_SOURCES, KID_FMMV_EVAL,
     KID_FMMV_EVAL_MFMA, KID_FMML_PACK, KID_FMML_MOMENTS, KID_LOEWNER_FMM, KID_DEFLATE,
-    KID_DEFL_PLACE, KID_DEFL_ROTATE, KID_COPY_ROWS, KID_FMM_LOCAL, KID_DIVIDE, KID_SORT, KID_COUNT
+    KID_DEFL_PLACE, KID_DEFL_ROTATE, KID_COPY_ROWS, KID_FMM_LOCAL, KID_DIVIDE, KID_SORT,
+    KID_BWD_FMM, KID_COUNT
 };
 
 // device counters of kernel `kid` while kernel timing is on (the current device), else
@@ -247,7 +248,7 @@ const TileList *tile_list(superdc_batch *b, int chunk);
 int opts_check(const superdc_opts *o);
 // problems of at least this many roots use the triangular FMM under these options: in the solver,
 // Loewner and b calls, and (apply) in the Cauchy applies
-int fmm_crossover_of(const superdc_batch *b, const superdc_opts &o, bool apply = false);
+int fmm_crossover_of(const superdc_batch *b, const superdc_opts &o, double pairs = 0.0);
 // launch shape of the plain (one launch per problem) direct solve of an n-root problem
 ::LaunchShape plain_shape(const superdc_ctx *ctx, int64_t n);
 // the allocation-free solve's scratch array: its address on `device` is looked up once
@@ -355,7 +356,9 @@ struct BwdArgs {
     double4 *rk;    // workspace (d_K, eta, alpha, beta) per root
     double *gk;     // workspace gamma per root
 };
-hipError_t launch_backward(const BwdArgs &a, int split, int prob_first, int nprob, hipStream_t s);
+// both passes over a.tiles, and the problems' g_rho from their roots' alpha
+hipError_t launch_backward(const BwdArgs &a, int split, hipStream_t s);
+hipError_t launch_backward_rho(const BwdArgs &a, int prob_first, int nprob, hipStream_t s);
 
 // columns per thread of the row kernels: as many as leave the chip enough threads, and no
 // more blocks of columns than a grid holds

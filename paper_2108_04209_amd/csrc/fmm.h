@@ -145,7 +145,8 @@ struct FmmPlan {
 // (the apply Y = Qhat X: src = b_j X_j,c, scaled by zhat_i), sources at the roots.
 struct FmmVec {
     int m;                    // weight columns (<= FMMV_MAX_PASS), in groups of FMMV_MAX_M
-    int kern;                 // 1: 1/t, 2: 1/t^2
+    int kern;                 // 1: 1/t, 2: 1/t^2; 3 and 4: the adjoint's sums over the poles and
+                              // over the roots (several kernels of two and three columns)
     int trans;                // 1: sums over the poles (targets the roots); 0: over the roots
                               // (source positions lambda_j = d_{K_j} + eta_j, written by
                               // launch_fmmv_pos)
@@ -171,6 +172,9 @@ struct FmmVec {
     int expand;               // VALU evaluation: far boxes through the targets' interval (set
                               // by launch_fmmv_eval)
     const double *zh;         // fuse_b: zhat, for b's near terms (zhat / t)^2
+    const double *u;          // kern 3: u (scale: z)
+    const double4 *rk;        // kern 4: (d_K, eta, alpha, beta) per root
+    const double *gk;         // ... and gamma
     unsigned long long *work; // kernel timing on: algorithmic flops of the launch (set by
                               // launch_fmmv_eval): (2m + 3) per near pole or far source of a
                               // root for kern 1, 6 for kern 2, plus the output scaling
@@ -231,5 +235,9 @@ hipError_t launch_fmmv_eval(const SolveArgs &items, const FmmArgs &f, const FmmV
                             int num_cu, hipStream_t s);
 hipError_t launch_secular_fmm(const SolveArgs &a, const FmmArgs &f, int split,
                               hipStream_t s);
+// one pass of the adjoint (kern 3: the roots' sums over the poles, kern 4: the poles' over the
+// roots) for the FMM problems
+hipError_t launch_backward_fmm(const BwdArgs &a, const FmmArgs &f, const FmmVec &v, int split,
+                               int num_cu, hipStream_t s);
 
 }  // namespace sdc

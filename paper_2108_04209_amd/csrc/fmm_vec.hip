@@ -11,7 +11,7 @@
 // W_q,c = sum_{i in box} src_i,c L_q(d_i), one column per right-hand side.  Plain sums
 // need no psi/phi split, but the lists are the directional ones of the solver and the
 // near field keeps the local shifting, as the paper prescribes for these products.
-#include "fmm.h"
+#include "fmm_far.h"
 
 namespace sdc {
 
@@ -45,8 +45,16 @@ __global__ __launch_bounds__(64) void k_fmmv_pos(FmmvPackArgs a) {
 // operands loaded straight from memory before the Lagrange values are formed: a leaf's from
 // the columns of X (each lane the 16 consecutive points of one column that it feeds), an
 // upper box's from the leaves' weights (point-major: the 4 points x 16 columns of one step
-// are 128-byte runs).  blockIdx.y is the group of FMMV_MAX_M columns.
-template <bool LEAVES>
+// are 128-byte runs).  blockIdx.y is the group of FMMV_MAX_M columns.  Up to four columns (b,
+// the adjoint) are added on the VALU instead: lane (node, quarter of the points), the weights
+// from the lanes that loaded them; a 16-column step costs as much as 16 columns of that
+// (boxes and leaves of a level of 4096 problems, b: 780 -> 690 us).
+template <int C>
+__device__ __forceinline__ double row_lane(double v) {  // lane C of each row of 16
+    return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), 0x150 + C, 0xf, 0xf, true),
+                            __builtin_amdgcn_mov_dpp(__double2loint(v), 0x150 + C, 0xf, 0xf, true));
+}
+template <bool LEAVES, bool FEW>
 __global__ __launch_bounds__(LEAVES ? 64 : 256, LEAVES ? 1 : 4) void k_fmmv_sources(FmmArgs f, FmmVec v) {
     // leaves: one wavefront, 64 points per chunk; upper boxes (up to 16 sources per leaf
     // below): four wavefronts, 256 points per chunk
@@ -75,13 +83,18 @@ __global__ __launch_bounds__(LEAVES ? 64 : 256, LEAVES ? 1 : 4) void k_fmmv_sour
     const int m = v.m;
     const int g0 = blockIdx.y * FMMV_MAX_M;       // this group's columns [g0, g0 + mg)
     const int mg = min(FMMV_MAX_M, m - g0);
-    const int mx = v.kern == 2 ? 0 : min(mg, m - v.fuse_b - g0);  // those that are X's
+    const int mx = v.kern >= 2 ? 0 : min(mg, m - v.fuse_b - g0);  // those that are X's
     const double *d = f.pos + base;               // the points' positions (poles, or roots)
     const double *sc = v.scale + base;
-    const double *X = v.kern == 2 ? nullptr : v.X + base + (int64_t)g0 * v.ldx;
-    // weight of point i in column c of the group: scale X, or scale^2 for the b sum's column
-    auto weight = [&](int i, int c) {
-        return c < mx ? sc[i] * X[i + (int64_t)c * v.ldx] : (c < mg ? sc[i] * sc[i] : 0.0);
+    const double *X = v.kern >= 2 ? nullptr : v.X + base + (int64_t)g0 * v.ldx;
+    // column c of the group: scale X, or scale^2 for the b sum's; the adjoint's z^2 and u z of a
+    // pole (kern 3), alpha, beta and gamma of a root (kern 4, no scale)
+    auto column = [&](int c, int &stride) -> const double * {
+        stride = v.kern == 4 && c < 2 ? 4 : 1;
+        if (v.kern == 4)
+            return c < 2 ? reinterpret_cast<const double *>(v.rk + base) + 2 + c : v.gk + base;
+        if (c < mx) return X + (int64_t)c * v.ldx;
+        return v.kern == 3 && c == 1 ? v.u + base : sc;
     };
     const double a = d[lo], b = d[hi - 1];
     const double cc = 0.5 * (a + b), hw = 0.5 * (b - a);
@@ -91,7 +104,11 @@ __global__ __launch_bounds__(LEAVES ? 64 : 256, LEAVES ? 1 : 4) void k_fmmv_sour
         if (tid < FMM_P) {
             const bool in = lo + tid < hi;
             if (blockIdx.y == 0) node[tid] = in ? d[lo + tid] : cc;
-            for (int c = 0; c < mg; ++c) w[tid * m + c] = in ? weight(lo + tid, c) : 0.0;
+            for (int c = 0; c < mg; ++c) {
+                int st;
+                const double *wc = column(c, st);
+                w[tid * m + c] = !in ? 0.0 : v.kern == 4 ? wc[(lo + tid) * st] : sc[lo + tid] * wc[lo + tid];
+            }
         }
         return;
     }
@@ -110,7 +127,7 @@ __global__ __launch_bounds__(LEAVES ? 64 : 256, LEAVES ? 1 : 4) void k_fmmv_sour
         lam[r] = cheb_bary(r);
     }
     const double ihw = 1.0 / hw;
-    v4d_f acc = v4d_f{0.0, 0.0, 0.0, 0.0};
+    v4d_f acc = v4d_f{0.0, 0.0, 0.0, 0.0};  // FEW: columns 0 .. 3 of node lane % 16
     // an upper box's points' weights, m per point: the sources of the box's leaves
     const double *wsrc = v.vw + (int64_t)(f.box_off[qf] + leaf0) * FMM_P * m + g0;
     for (int k0 = pk0; k0 < pk1; k0 += FV_CHUNK) {
@@ -122,14 +139,22 @@ __global__ __launch_bounds__(LEAVES ? 64 : 256, LEAVES ? 1 : 4) void k_fmmv_sour
         const int c = lane & 15;
         if (LEAVES) {
             const int p0 = k0 + 16 * (lane >> 4);
-            if (c < mx && p0 + 16 <= pk1) {
-                const double *xc = X + lo + p0 + (int64_t)c * v.ldx, *sp = sc + lo + p0;
+            int stride;
+            const double *xc = column(min(c, mg - 1), stride) + (int64_t)(lo + p0) * stride;
+            const double *sp = sc + lo + p0;
+            if (c < mg && p0 + 16 <= pk1) {
+                if (v.kern == 4) {
 #pragma unroll
-                for (int st = 0; st < 16; ++st) bs[st] = sp[st] * xc[st];
+                    for (int st = 0; st < 16; ++st) bs[st] = xc[st * stride];
+                } else {
+#pragma unroll
+                    for (int st = 0; st < 16; ++st) bs[st] = sp[st] * xc[st];
+                }
             } else {
 #pragma unroll
                 for (int st = 0; st < 16; ++st)
-                    bs[st] = p0 + st < pk1 ? weight(lo + p0 + st, c) : 0.0;
+                    bs[st] = p0 + st < pk1 && c < mg
+                                 ? (v.kern == 4 ? 1.0 : sp[st]) * xc[st * stride] : 0.0;
             }
         } else {
 #pragma unroll
@@ -164,14 +189,45 @@ __global__ __launch_bounds__(LEAVES ? 64 : 256, LEAVES ? 1 : 4) void k_fmmv_sour
 #pragma unroll
         for (int st = 0; st < 16; ++st) {
             const int kk = LEAVES ? 16 * (lane >> 4) + st : wv * 64 + 4 * st + (lane >> 4);
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(Lq[kk][lane & 15], bs[st], acc, 0, 0, 0);
+            const double l = Lq[kk][lane & 15];
+            if (FEW) {
+                acc[0] = __builtin_fma(l, row_lane<0>(bs[st]), acc[0]);
+                if (mg > 1) acc[1] = __builtin_fma(l, row_lane<1>(bs[st]), acc[1]);
+                if (mg > 2) acc[2] = __builtin_fma(l, row_lane<2>(bs[st]), acc[2]);
+                if (mg > 3) acc[3] = __builtin_fma(l, row_lane<3>(bs[st]), acc[3]);
+            } else {
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(l, bs[st], acc, 0, 0, 0);
+            }
         }
         __syncthreads();
+    }
+    double *red = &Lq[0][0];
+    if (FEW) {
+        // the four quarters' sums, column c of node q to lane 16 c + q, then the wavefronts'
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            acc[c] += __shfl_xor(acc[c], 16);
+            acc[c] += __shfl_xor(acc[c], 32);
+        }
+        const int qn = lane & 15, cn = lane >> 4;
+        double s2 = cn < 2 ? (cn ? acc[1] : acc[0]) : (cn == 2 ? acc[2] : acc[3]);
+        if (NW > 1) {
+            if (wv > 0) red[(wv - 1) * WAVE + lane] = s2;
+            __syncthreads();
+        }
+        if (wv == 0) {
+            for (int u = 0; u < NW - 1; ++u) s2 += red[u * WAVE + lane];
+            if (it.w >= 0)
+                f.vpart[(((int64_t)it.w * gridDim.y + blockIdx.y) * FMM_P + qn) * FMMV_MAX_M + cn] = s2;
+            else if (cn < mg)
+                w[qn * m + cn] = s2;
+        }
+        if (it.y == 0 && blockIdx.y == 0 && tid < FMM_P) node[tid] = cc + hw * tq[tid];
+        return;
     }
     mfma_drain();
     // the four wavefronts' partial W added in wavefront order (through the staging LDS);
     // accumulator r of lane l holds W[4 r + l / 16][l % 16]
-    double *red = &Lq[0][0];
     if (NW > 1 && wv > 0) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) red[((wv - 1) * 4 + r) * WAVE + lane] = acc[r];
@@ -218,95 +274,6 @@ __global__ __launch_bounds__(FMM_P * FMMV_MAX_M) void k_fmmv_sources_sum(FmmArgs
     for (int u = 0; u < parts; ++u)
         s += f.vpart[(((int64_t)(sb.y + u) * gridDim.y + gy) * FMM_P + q) * FMMV_MAX_M + c];
     v.vw[((int64_t)g * FMM_P + q) * v.m + col] = s;
-}
-
-// ---------------------------------------------------------------------------------------
-// The far field of one work item (64 neighbouring targets) as a function on the targets'
-// interval.  Instead of meeting every target, a far box's 16 equivalent sources meet the 16
-// Chebyshev nodes of the interval, and each target interpolates the boxes' sum there: a
-// quarter of the Cauchy entries plus one 16-term series.  Only boxes at least FV_SEP_T interval
-// widths away take part -- interpolating 1/(s - x) at that distance converges like
-// (4 + sqrt 15)^-16 = 5e-15, the separation at which a box's own sources stand for its poles --
-// the others stay with the direct sums (entries per row, level of 4096 problems: 541 -> 387;
-// evaluation 3.25 -> 2.60 ms, b 1.75 -> 1.54 ms).  Node positions are kept as offsets from the
-// interval's centre, so a difference s - x_m = (s - centre) - offset_m is as accurate as the
-// shifted differences of the targets themselves.
-constexpr double FV_SEP_T = 1.5;
-constexpr int FV_MIN_EXP = 4;  // fewer boxes: the interpolation costs more than it saves
-// A launch uses the expansion once its items give every CU two workgroups: from there the
-// FP64 pipe is the bound (1024 items, one problem of 65536 with 64 columns: 232 -> 173 us with
-// the expansion), below the latency of one item, which it lengthens (16 items, n = 1024: 17
-// -> 20 us for 16 columns, 13 -> 18 us for b).
-constexpr int FV_EXPAND_PER_CU = 2;
-
-// cos((2q + 1) pi / 32) and (-1)^q sin((2q + 1) pi / 32): the nodes and barycentric weights
-__constant__ double FV_NODE[FMM_P] = {
-    0.99518472667219693, 0.95694033573220882, 0.88192126434835505, 0.77301045336273699,
-    0.63439328416364549, 0.47139673682599781, 0.29028467725446233, 0.09801714032956077,
-    -0.098017140329560645, -0.29028467725446216, -0.4713967368259977, -0.63439328416364538,
-    -0.77301045336273699, -0.88192126434835494, -0.95694033573220882, -0.99518472667219682
-};
-__constant__ double FV_BARY[FMM_P] = {
-    0.098017140329560604, -0.29028467725446233, 0.47139673682599764, -0.63439328416364549,
-    0.77301045336273699, -0.88192126434835494, 0.95694033573220894, -0.99518472667219682,
-    0.99518472667219693, -0.95694033573220894, 0.88192126434835505, -0.7730104533627371,
-    0.63439328416364549, -0.47139673682599786, 0.29028467725446239, -0.098017140329560826
-};
-
-// centre and half-width of an item's targets, rows r0 .. r1 of the problem's n (targets are
-// ascending: roots d_K + eta, or with trans 0 the poles); hw = 0: no expansion (one target, or
-// targets so close together that the centre's rounding would show)
-__device__ __forceinline__ double2 fv_interval(const FmmVec &v, int64_t base, int n, int r0, int r1) {
-    double da = v.d[base + r0], db = v.d[base + r1], ea = 0.0, eb = 0.0;
-    if (v.trans) {
-        da = v.d[base + clamp_idx(v.origin[base + r0], n)];
-        db = v.d[base + clamp_idx(v.origin[base + r1], n)];
-        ea = v.eta[base + r0];
-        eb = v.eta[base + r1];
-    }
-    const double c = 0.5 * ((da + ea) + (db + eb)), h = 0.5 * ((db - da) + (eb - ea));
-    return make_double2(c, h >= 0x1p-44 * fabs(c) ? h : 0.0);
-}
-
-// The far boxes of leaf L (nl left, nr right ones) into fbox: those summed directly from the
-// front, those of the expansion from the back; returns how many of the latter (none with
-// expand false).  One wavefront, all lanes.
-__device__ __forceinline__ int fv_split_far(const FmmArgs &f, const FmmVec &v, int L, int nl, int nr,
-                                            double2 iv, bool expand, int *fbox) {
-    const int lane = lane_id();
-    int nd = 0, ne = 0;
-    for (int e0 = 0; e0 < nl + nr; e0 += WAVE) {
-        const int e = e0 + lane;
-        const bool in = e < nl + nr;
-        int g = 0;
-        bool ex = false;
-        if (in) {
-            g = e < nl ? f.far_l[(int64_t)L * FMM_FAR_MAX + e]
-                       : f.far_r[(int64_t)L * FMM_FAR_MAX + e - nl];
-            // the box's end sources: its nodes descend (a leaf of few poles keeps them
-            // ascending instead, but that is a problem's last leaf, whose nearest is the first)
-            const double *nd2 = v.vnode + (int64_t)g * FMM_P;
-            const double dist = fmin(fabs(nd2[0] - iv.x), fabs(nd2[FMM_P - 1] - iv.x)) - iv.y;
-            ex = expand && iv.y > 0.0 && dist >= FV_SEP_T * 2.0 * iv.y;
-        }
-        const unsigned long long md = __ballot(in && !ex), me = __ballot(ex);
-        auto rank = [&](unsigned long long mk) {
-            return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(mk >> 32),
-                                                  __builtin_amdgcn_mbcnt_lo((unsigned)mk, 0u));
-        };
-        if (ex) fbox[2 * FMM_FAR_MAX - 1 - (ne + rank(me))] = g;
-        else if (in) fbox[nd + rank(md)] = g;
-        nd += __popcll(md);
-        ne += __popcll(me);
-    }
-    if (ne > 0 && ne < FV_MIN_EXP) {  // too few: back among the direct ones
-        if (lane < ne) {
-            const int g = fbox[2 * FMM_FAR_MAX - 1 - lane];
-            fbox[nd + lane] = g;
-        }
-        ne = 0;
-    }
-    return wave_uniform(ne);
 }
 
 // Evaluation at the roots: work items are 64-root pieces of the target leaves; S
@@ -1082,10 +1049,16 @@ hipError_t launch_fmmv_pos(const FmmvPackArgs &a, hipStream_t s) {
 hipError_t launch_fmmv_sources(const FmmArgs &f, const FmmVec &v, hipStream_t s) {
     if (f.nboxes <= 0) return hipSuccess;
     const int ng = (v.m + FMMV_MAX_M - 1) / FMMV_MAX_M;
-    SDC_LAUNCH(KID_FMMV_SOURCES, k_fmmv_sources<true>, dim3(f.nleaves, ng), dim3(64), 0, s, f, v);
-    if (f.nupper_item > 0)
-        SDC_LAUNCH(KID_FMMV_SOURCES, k_fmmv_sources<false>, dim3(f.nupper_item, ng), dim3(256), 0,
-                   s, f, v);
+    const dim3 gl(f.nleaves, ng), gu(f.nupper_item, ng);
+    if (v.m <= 4) {
+        SDC_LAUNCH(KID_FMMV_SOURCES, (k_fmmv_sources<true, true>), gl, dim3(64), 0, s, f, v);
+        if (f.nupper_item > 0)
+            SDC_LAUNCH(KID_FMMV_SOURCES, (k_fmmv_sources<false, true>), gu, dim3(256), 0, s, f, v);
+    } else {
+        SDC_LAUNCH(KID_FMMV_SOURCES, (k_fmmv_sources<true, false>), gl, dim3(64), 0, s, f, v);
+        if (f.nupper_item > 0)
+            SDC_LAUNCH(KID_FMMV_SOURCES, (k_fmmv_sources<false, false>), gu, dim3(256), 0, s, f, v);
+    }
     if (f.nsplit > 0)
         SDC_LAUNCH(KID_FMMV_SOURCES, k_fmmv_sources_sum, dim3(f.nsplit, ng),
                    dim3(FMM_P * FMMV_MAX_M), 0, s, f, v);
