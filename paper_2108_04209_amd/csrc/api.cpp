@@ -395,10 +395,15 @@ FmmPlan *fmm_plan(superdc_batch *b, int leaf, int crossover) {
                          [](const std::pair<int, int32_t> &x, const std::pair<int, int32_t> &y) {
                              return x.first > y.first;
                          });
-        for (const auto &e : up) upper_box.push_back(e.second);
+        for (const auto &e : up) {
+            upper_box.push_back(e.second);
+            for (int c = 0; c < 6; ++c) fp->upper_cls[c] += e.first > (64 >> c);
+        }
+        fp->upper_cls[6] = (int)up.size();
         for (const auto &e : up) {
             const int parts = (e.first * FMM_P + FMMV_PART_PTS - 1) / FMMV_PART_PTS;
             if (parts == 1) {
+                if (e.first > 4) fp->nitem_big = (int)upper_item.size() + 1;
                 upper_item.push_back(make_int4(e.second, 0, 1, -1));
                 continue;
             }
@@ -406,6 +411,7 @@ FmmPlan *fmm_plan(superdc_batch *b, int leaf, int crossover) {
             for (int u = 0; u < parts; ++u)
                 upper_item.push_back(make_int4(e.second, u, parts, nslot + u));
             nslot += parts;
+            fp->nitem_big = (int)upper_item.size();
         }
     }
     fp->nupper = (int)upper_box.size();
@@ -526,6 +532,8 @@ FmmArgs fmm_args(const FmmPlan *fp, const superdc_batch *b, const SolveArgs &a,
     f.nupper = fp->nupper;
     f.upper_item = fp->upper_item;
     f.nupper_item = fp->nupper_item;
+    f.nitem_big = fp->nitem_big;
+    std::copy(fp->upper_cls, fp->upper_cls + 7, f.upper_cls);
     f.split_box = fp->split_box;
     f.nsplit = fp->nsplit;
     (void)o;
@@ -1159,7 +1167,6 @@ int superdc_secular_backward(superdc_ctx *ctx, const superdc_batch *b, const dou
         // not fit
         int rc;
         FmmPlan *fp = fmm_for(bm, o, rc, b->max_n <= DIRECT_BWD_N ? DIRECT_BWD_PAIRS : 1.0);
-        if (rc) return rc;
         const int nw = g_proj ? 2 : 1;  // weights of a pole; of a root one more with projections
         double *pos = nullptr;
         double2 *ke = nullptr;

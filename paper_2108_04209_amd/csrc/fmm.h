@@ -69,11 +69,15 @@ struct FmmArgs {
     const int32_t *upper_box; // [nupper] global ids of the boxes above the leaves that hold
                               // poles, the largest (most leaves below) first
     int nupper;
+    // Small upper boxes share a wavefront or a workgroup: of the first upper_cls[c] boxes none has
+    // 2^(6-c) leaves or fewer (c = 0 .. 5; with c = 0 those of more than 64)
+    int upper_cls[7];         // ([6]: nupper)
     // the eigenvector-side sources of the upper boxes in parts of at most FMMV_PART_PTS
     // points: items (box, part, parts, partial slot or -1), largest boxes first; the boxes
     // cut into several parts (box, first slot) and their partial weights
     const int4 *upper_item;   // [nupper_item]
     int nupper_item;
+    int nitem_big;            // those of boxes with more than 4 leaves (the first ones)
     const int2 *split_box;    // [nsplit]
     int nsplit;
     double *vpart;            // [slots][column groups][FMM_P][FMMV_MAX_M]
@@ -107,7 +111,8 @@ struct FmmPlan {
     int nupper = 0;
     int4 *upper_item = nullptr;
     int2 *split_box = nullptr;
-    int nupper_item = 0, nsplit = 0, nslot = 0;
+    int nupper_item = 0, nitem_big = 0, nsplit = 0, nslot = 0;
+    int upper_cls[7] = {0};          // see FmmArgs
     double2 *eq = nullptr;           // per-call arrays (fmm_scratch)
     double *loc = nullptr, *vnode = nullptr;
     double2 *lgeo = nullptr;

@@ -47,9 +47,10 @@ __device__ __forceinline__ BoxRange box_range(const FmmArgs &f, int g) {
 // wavefronts, from the equivalent sources of its leaves (16 per leaf instead of every pole
 // below: the far field of a leaf's sources equals that of its poles to the interpolation
 // accuracy, and the box's nodes interpolate it again).  part holds 64 or 256 rows of
-// FMM_P + 1 doubles, red 16 of them (upper boxes); tid is the thread's index among the box's
-// nt threads (one wavefront for a leaf, which syncs only itself).
-template <bool LEAVES>
+// FMM_P + 1 doubles, red 16 of them (four wavefronts); tid is the thread's index among the box's
+// nt threads.  ONE: one wavefront, which syncs only itself (a leaf, or an upper box of at most
+// 4 leaves, whose 64 points leave three of four wavefronts idle).
+template <bool LEAVES, bool ONE>
 __device__ __forceinline__ void box_sources(const FmmArgs &f, int g, double *part, double *red,
                                             int tid, int nt) {
     static_assert(FMM_P == 16, "the upper boxes' sum maps 256 threads to 16 x 16");
@@ -109,11 +110,11 @@ __device__ __forceinline__ void box_sources(const FmmArgs &f, int g, double *par
     double wq = 0.0;
 #pragma unroll
     for (int r = 0; r < FMM_P; ++r) part[tid * (FMM_P + 1) + r] = W[r];
-    if (LEAVES)
+    if (ONE)
         wave_sync();
     else
         __syncthreads();
-    if (LEAVES) {
+    if (ONE) {
         if (tid < FMM_P)
             for (int u = 0; u < 64; ++u) wq += part[u * (FMM_P + 1) + tid];
     } else {
@@ -128,13 +129,24 @@ __device__ __forceinline__ void box_sources(const FmmArgs &f, int g, double *par
     if (tid < FMM_P) f.eq[(int64_t)g * FMM_P + tid] = make_double2(c + hw * tq[tid], wq);
 }
 
-// the used upper boxes (the leaves are compressed by the lists launch of the solver)
+// the used upper boxes (the leaves are compressed by the lists launch of the solver): a
+// workgroup to a box, or, of boxes with at most 4 leaves, to four of them
 __global__ __launch_bounds__(256) void k_fmm_boxes(FmmArgs f) {
     __shared__ double part[256 * (FMM_P + 1)];
     __shared__ double red[16 * (FMM_P + 1)];
-    const int g = f.upper_box[blockIdx.x];
+    const int nbig = f.upper_cls[4];
+    if ((int)blockIdx.x < nbig) {
+        const int g = f.upper_box[blockIdx.x];
+        if (f.used[g] != f.gen) return;
+        box_sources<false, false>(f, g, part, red, threadIdx.x, blockDim.x);
+        return;
+    }
+    const int wv = wave_uniform((int)(threadIdx.x / WAVE));
+    const int i = nbig + ((int)blockIdx.x - nbig) * 4 + wv;
+    if (i >= f.nupper) return;
+    const int g = f.upper_box[i];
     if (f.used[g] != f.gen) return;
-    box_sources<false>(f, g, part, red, threadIdx.x, blockDim.x);
+    box_sources<false, true>(f, g, part + wv * WAVE * (FMM_P + 1), nullptr, lane_id(), WAVE);
 }
 
 // interaction lists: one wavefront per target leaf walks its problem's tree level by level.
@@ -149,7 +161,7 @@ __global__ __launch_bounds__(EQ ? 2 * WAVE : WAVE) void k_fmm_lists(FmmArgs f) {
     const int L = blockIdx.x;
     // EQ (the solver's lists): a second wavefront compresses the leaf itself meanwhile
     if (EQ && threadIdx.x >= WAVE) {
-        box_sources<true>(f, f.leaf_box[L], part, nullptr, threadIdx.x - WAVE, WAVE);
+        box_sources<true, true>(f, f.leaf_box[L], part, nullptr, threadIdx.x - WAVE, WAVE);
         return;
     }
     const int lane = threadIdx.x;
@@ -424,7 +436,8 @@ hipError_t launch_fmm_build(const FmmArgs &f, hipStream_t s) {
     // the lists and every leaf's equivalent sources in one launch, then the used upper boxes
     SDC_LAUNCH(KID_FMM_LISTS, k_fmm_lists<true>, dim3(f.nleaves), dim3(2 * WAVE), 0, s, f);
     if (f.nupper > 0)
-        SDC_LAUNCH(KID_FMM_BOXES, k_fmm_boxes, dim3(f.nupper), dim3(256), 0, s, f);
+        SDC_LAUNCH(KID_FMM_BOXES, k_fmm_boxes,
+                   dim3(f.upper_cls[4] + (f.nupper - f.upper_cls[4] + 3) / 4), dim3(256), 0, s, f);
     SDC_LAUNCH(KID_FMM_LOCAL, k_fmm_local, dim3(f.nleaves), dim3(FMM_PL * LOC_PARTS), 0, s, f);
     return hipGetLastError();
 }

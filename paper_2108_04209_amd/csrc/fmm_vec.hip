@@ -48,7 +48,8 @@ __global__ __launch_bounds__(64) void k_fmmv_pos(FmmvPackArgs a) {
 // are 128-byte runs).  blockIdx.y is the group of FMMV_MAX_M columns.  Up to four columns (b,
 // the adjoint) are added on the VALU instead: lane (node, quarter of the points), the weights
 // from the lanes that loaded them; a 16-column step costs as much as 16 columns of that
-// (boxes and leaves of a level of 4096 problems, b: 780 -> 690 us).
+// (boxes and leaves of a level of 4096 problems, b: 780 -> 690 us; with boxes of at most four
+// leaves on a wavefront instead of a workgroup 450).
 template <int C>
 __device__ __forceinline__ double row_lane(double v) {  // lane C of each row of 16
     return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), 0x150 + C, 0xf, 0xf, true),
@@ -62,8 +63,14 @@ __global__ __launch_bounds__(LEAVES ? 64 : 256, LEAVES ? 1 : 4) void k_fmmv_sour
     constexpr int FV_CHUNK = 64 * NW;
     __shared__ double Lq[FV_CHUNK][FMM_P + 1];
     // leaves in the first launch; in the second the parts of the upper boxes with poles
-    // (used ones): (box, part, parts, partial slot)
-    const int4 it = LEAVES ? make_int4(f.leaf_box[blockIdx.x], 0, 1, -1) : f.upper_item[blockIdx.x];
+    // (used ones): (box, part, parts, partial slot); boxes of at most 4 leaves, 64 points, four to
+    // a workgroup, a wavefront each (`one`)
+    const bool one = LEAVES || (int)blockIdx.x >= f.nitem_big;
+    const int wv = LEAVES ? 0 : wave_uniform((int)(threadIdx.x / WAVE));
+    const int item = !LEAVES && one ? f.nitem_big + ((int)blockIdx.x - f.nitem_big) * 4 + wv
+                                    : (int)blockIdx.x;
+    if (!LEAVES && item >= f.nupper_item) return;
+    const int4 it = LEAVES ? make_int4(f.leaf_box[item], 0, 1, -1) : f.upper_item[item];
     const int g = it.x;
     if (!LEAVES && f.used[g] != f.gen) return;
     const int qf = f.box_fmm[g];
@@ -79,7 +86,14 @@ __global__ __launch_bounds__(LEAVES ? 64 : 256, LEAVES ? 1 : 4) void k_fmmv_sour
     const int64_t span = (int64_t)f.leaf << (H - h);
     const int lo = (int)min((int64_t)n, bi * span), hi = (int)min((int64_t)n, (bi + 1) * span);
     if (lo >= hi) return;  // empty box (never listed)
-    const int tid = threadIdx.x;
+    const int lane = lane_id();
+    const int row0 = wv * WAVE;                    // the wavefront's rows of Lq
+    const int tid = one ? lane : (int)threadIdx.x; // thread of the box
+    const int chunk = one ? WAVE : FV_CHUNK;
+    auto sync = [&]() {
+        if (one) wave_sync();
+        else __syncthreads();
+    };
     const int m = v.m;
     const int g0 = blockIdx.y * FMMV_MAX_M;       // this group's columns [g0, g0 + mg)
     const int mg = min(FMMV_MAX_M, m - g0);
@@ -119,7 +133,6 @@ __global__ __launch_bounds__(LEAVES ? 64 : 256, LEAVES ? 1 : 4) void k_fmmv_sour
     // this part's points [pk0, pk1)
     const int pk0 = LEAVES ? 0 : min(npts, it.y * FMMV_PART_PTS);
     const int pk1 = LEAVES ? npts : (it.z == 1 ? npts : min(npts, pk0 + FMMV_PART_PTS));
-    const int lane = tid & (WAVE - 1), wv = tid / WAVE;
     double tq[FMM_P], lam[FMM_P];
 #pragma unroll
     for (int r = 0; r < FMM_P; ++r) {
@@ -130,7 +143,7 @@ __global__ __launch_bounds__(LEAVES ? 64 : 256, LEAVES ? 1 : 4) void k_fmmv_sour
     v4d_f acc = v4d_f{0.0, 0.0, 0.0, 0.0};  // FEW: columns 0 .. 3 of node lane % 16
     // an upper box's points' weights, m per point: the sources of the box's leaves
     const double *wsrc = v.vw + (int64_t)(f.box_off[qf] + leaf0) * FMM_P * m + g0;
-    for (int k0 = pk0; k0 < pk1; k0 += FV_CHUNK) {
+    for (int k0 = pk0; k0 < pk1; k0 += chunk) {
         // W (16 nodes x 16 columns) += L (16 x chunk) S (chunk x 16) on the FP64 MFMA: each
         // wavefront takes 64 points of the chunk, 4 per step (A lane l = L[l % 16][point],
         // B lane l = S[point][l % 16]): step st of lane l takes point 16 (l / 16) + st for a
@@ -159,7 +172,7 @@ __global__ __launch_bounds__(LEAVES ? 64 : 256, LEAVES ? 1 : 4) void k_fmmv_sour
         } else {
 #pragma unroll
             for (int st = 0; st < 16; ++st) {
-                const int pt = k0 + wv * 64 + 4 * st + (lane >> 4);
+                const int pt = k0 + (one ? 0 : row0) + 4 * st + (lane >> 4);
                 bs[st] = pt < pk1 && c < mg ? wsrc[(int64_t)pt * m + c] : 0.0;
             }
         }
@@ -180,15 +193,15 @@ __global__ __launch_bounds__(LEAVES ? 64 : 256, LEAVES ? 1 : 4) void k_fmmv_sour
             const double iden = 1.0 / den;
 #pragma unroll
             for (int r = 0; r < FMM_P; ++r)
-                Lq[tid][r] = hit >= 0 ? (r == hit ? 1.0 : 0.0) : inv[r] * iden;
+                Lq[row0 + lane][r] = hit >= 0 ? (r == hit ? 1.0 : 0.0) : inv[r] * iden;
         } else {
 #pragma unroll
-            for (int r = 0; r < FMM_P; ++r) Lq[tid][r] = 0.0;
+            for (int r = 0; r < FMM_P; ++r) Lq[row0 + lane][r] = 0.0;
         }
-        __syncthreads();
+        sync();
 #pragma unroll
         for (int st = 0; st < 16; ++st) {
-            const int kk = LEAVES ? 16 * (lane >> 4) + st : wv * 64 + 4 * st + (lane >> 4);
+            const int kk = LEAVES ? 16 * (lane >> 4) + st : row0 + 4 * st + (lane >> 4);
             const double l = Lq[kk][lane & 15];
             if (FEW) {
                 acc[0] = __builtin_fma(l, row_lane<0>(bs[st]), acc[0]);
@@ -199,7 +212,7 @@ __global__ __launch_bounds__(LEAVES ? 64 : 256, LEAVES ? 1 : 4) void k_fmmv_sour
                 acc = __builtin_amdgcn_mfma_f64_16x16x4f64(l, bs[st], acc, 0, 0, 0);
             }
         }
-        __syncthreads();
+        sync();
     }
     double *red = &Lq[0][0];
     if (FEW) {
@@ -211,12 +224,13 @@ __global__ __launch_bounds__(LEAVES ? 64 : 256, LEAVES ? 1 : 4) void k_fmmv_sour
         }
         const int qn = lane & 15, cn = lane >> 4;
         double s2 = cn < 2 ? (cn ? acc[1] : acc[0]) : (cn == 2 ? acc[2] : acc[3]);
-        if (NW > 1) {
+        if (!one) {
             if (wv > 0) red[(wv - 1) * WAVE + lane] = s2;
             __syncthreads();
         }
-        if (wv == 0) {
-            for (int u = 0; u < NW - 1; ++u) s2 += red[u * WAVE + lane];
+        if (one || wv == 0) {
+            if (!one)
+                for (int u = 0; u < NW - 1; ++u) s2 += red[u * WAVE + lane];
             if (it.w >= 0)
                 f.vpart[(((int64_t)it.w * gridDim.y + blockIdx.y) * FMM_P + qn) * FMMV_MAX_M + cn] = s2;
             else if (cn < mg)
@@ -228,16 +242,16 @@ __global__ __launch_bounds__(LEAVES ? 64 : 256, LEAVES ? 1 : 4) void k_fmmv_sour
     mfma_drain();
     // the four wavefronts' partial W added in wavefront order (through the staging LDS);
     // accumulator r of lane l holds W[4 r + l / 16][l % 16]
-    if (NW > 1 && wv > 0) {
+    if (!one && wv > 0) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) red[((wv - 1) * 4 + r) * WAVE + lane] = acc[r];
     }
-    if (NW > 1) __syncthreads();
-    if (wv == 0) {
+    if (!one) __syncthreads();
+    if (one || wv == 0) {
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             double s2 = acc[r];
-            for (int u = 0; u < NW - 1; ++u) s2 += red[(u * 4 + r) * WAVE + lane];
+            for (int u = 0; u < (one ? 0 : NW - 1); ++u) s2 += red[(u * 4 + r) * WAVE + lane];
             const int qn = 4 * r + (lane >> 4), cn = lane & 15;
             if (it.w >= 0)  // one part of several: its partial weights, summed afterwards
                 f.vpart[(((int64_t)it.w * gridDim.y + blockIdx.y) * FMM_P + qn) * FMMV_MAX_M + cn] = s2;
@@ -887,135 +901,206 @@ __host__ __device__ constexpr double binom(int k, int m) {
     return c;
 }
 // ---------------------------------------------------------------------------------------
-template <bool LEAVES>
-__global__ __launch_bounds__(LEAVES ? 64 : 256, LEAVES ? 1 : 4) void k_fmml_moments(FmmArgs f, FmmlArgs l) {
-    __shared__ double part[64][FMML_K + 1];
-    __shared__ double part2[LEAVES ? 1 : 64][FMML_K + 1];
-    const int g = LEAVES ? f.leaf_box[blockIdx.x] : f.upper_box[blockIdx.x];
-    if (!LEAVES && f.used[g] != f.gen) return;
+// the range of box g; false: invalid problem, or an empty box
+struct MomBox {
+    int H, n, lo, hi, leaf0;  // leaf0: its first leaf's box
+    int64_t base;
+    double c, hw;
+};
+__device__ __forceinline__ bool mom_box(const FmmArgs &f, int g, MomBox &b) {
     const int qf = f.box_fmm[g];
     const int p = f.fmm_prob[qf];
-    const int64_t base = f.off[p];
-    const int n = (int)(f.off[p + 1] - base);
+    b.base = f.off[p];
+    b.n = (int)(f.off[p + 1] - b.base);
     const int hidx = g - f.box_off[qf];
-    const int H = f.height[qf];
+    b.H = f.height[qf];
     int h = 0;
     while ((2 << h) - 1 <= hidx) ++h;
-    if (f.status[p] & ~SUPERDC_ST_NOCONV) return;
     const int bi = hidx - ((1 << h) - 1);
-    const int64_t span = (int64_t)f.leaf << (H - h);
-    const int lo = (int)min((int64_t)n, bi * span), hi = (int)min((int64_t)n, (bi + 1) * span);
-    if (lo >= hi) return;
-    if (LEAVES && l.pack) {  // the leaf's poles packed here (the same arithmetic as k_fmml_pack)
-        for (int j = lo + (int)threadIdx.x; j < hi; j += blockDim.x) {
-            const double dj = l.d[base + j];
-            const double dK = l.d[base + clamp_idx(l.origin[base + j], n)];
-            const double ej = l.eta[base + j];
+    const int64_t span = (int64_t)f.leaf << (b.H - h);
+    b.lo = (int)min((int64_t)b.n, bi * span);
+    b.hi = (int)min((int64_t)b.n, (bi + 1) * span);
+    b.leaf0 = f.box_off[qf] + (1 << b.H) - 1 + bi * (1 << (b.H - h));
+    return !(f.status[p] & ~SUPERDC_ST_NOCONV) && b.lo < b.hi;
+}
+__device__ __forceinline__ void mom_span(const FmmlArgs &l, MomBox &b) {
+    const double2 *pd = l.pd + b.base;
+    const double x0 = pd[b.lo].x, x1 = pd[b.hi - 1].x + pd[b.hi - 1].y;  // its poles and roots
+    b.c = 0.5 * (x0 + x1);
+    b.hw = 0.5 * (x1 - x0);
+}
+// leaf gl's moments translated to the box's centre and half-width, added to M
+__device__ __forceinline__ void mom_translate(const FmmlArgs &l, int gl, double c, double ihw,
+                                              double (&M)[FMML_K]) {
+    const double2 gc = l.geo[gl];
+    const double al = (gc.x - c) * ihw, be = gc.y * ihw;
+    const double *Ml = l.mom + (int64_t)gl * FMML_K;
+    // moment m of the leaf spread over k >= m: C(k, m) alpha^(k-m) beta^m M_m, the
+    // power of alpha built up along k (no row of coefficients kept: few registers)
+    double bm = 1.0;
+#pragma unroll
+    for (int m = 1; m <= FMML_K; ++m) {
+        bm *= be;
+        double q = Ml[m - 1] * bm;  // alpha^(k-m) beta^m M_m
+#pragma unroll
+        for (int k = m; k <= FMML_K; ++k) {
+            M[k - 1] = __builtin_fma(binom(k, m), q, M[k - 1]);
+            q *= al;
+        }
+    }
+}
+
+// every leaf, one wavefront each
+__global__ __launch_bounds__(WAVE) void k_fmml_moments(FmmArgs f, FmmlArgs l) {
+    __shared__ double part[WAVE][FMML_K + 1];
+    const int g = f.leaf_box[blockIdx.x], tid = threadIdx.x;
+    MomBox b;
+    if (!mom_box(f, g, b)) return;
+    if (l.pack) {  // the leaf's poles packed here (the same arithmetic as k_fmml_pack)
+        for (int j = b.lo + tid; j < b.hi; j += WAVE) {
+            const double dj = l.d[b.base + j];
+            const double dK = l.d[b.base + clamp_idx(l.origin[b.base + j], b.n)];
+            const double ej = l.eta[b.base + j];
             const double delta = (dK - dj) + ej;
-            l.pd[base + j] = make_double2(dj, delta);
-            if (l.ke) l.ke[base + j] = make_double2(dK, ej);
+            l.pd[b.base + j] = make_double2(dj, delta);
+            if (l.ke) l.ke[b.base + j] = make_double2(dK, ej);
         }
         __syncthreads();
     }
-    const double2 *pd = l.pd + base;
-    const double a = pd[lo].x, b = pd[hi - 1].x + pd[hi - 1].y;  // poles and roots of the box
-    const double c = 0.5 * (a + b), hw = 0.5 * (b - a), ihw = 1.0 / hw;
-    const int tid = threadIdx.x;
+    mom_span(l, b);
+    const double2 *pd = l.pd + b.base;
+    const double ihw = 1.0 / b.hw;
     double M[FMML_K];
 #pragma unroll
     for (int k = 0; k < FMML_K; ++k) M[k] = 0.0;
-    if (LEAVES) {
-        for (int j = lo + tid; j < hi; j += blockDim.x) {
-            const double t = (pd[j].x - c) * ihw, D = pd[j].y * ihw, tD = t + D;
-            double P = D, tk = 1.0;
+    for (int j = b.lo + tid; j < b.hi; j += WAVE) {
+        const double t = (pd[j].x - b.c) * ihw, D = pd[j].y * ihw, tD = t + D;
+        double P = D, tk = 1.0;
 #pragma unroll
-            for (int k = 0; k < FMML_K; ++k) {
-                M[k] += P;  // P = (t + D)^(k+1) - t^(k+1)
-                tk *= t;
-                P = __builtin_fma(tD, P, D * tk);
-            }
-        }
-    } else {
-        const int leaf0 = (1 << H) - 1 + bi * (1 << (H - h));
-        const int nleaf = (int)((hi - lo + f.leaf - 1) / f.leaf);
-        for (int e = tid; e < nleaf; e += blockDim.x) {
-            const int gl = f.box_off[qf] + leaf0 + e;
-            const double2 gc = l.geo[gl];
-            const double al = (gc.x - c) * ihw, be = gc.y * ihw;
-            const double *Ml = l.mom + (int64_t)gl * FMML_K;
-            // moment m of the leaf spread over k >= m: C(k, m) alpha^(k-m) beta^m M_m, the
-            // power of alpha built up along k (no row of coefficients kept: few registers)
-            double bm = 1.0;
-#pragma unroll
-            for (int m = 1; m <= FMML_K; ++m) {
-                bm *= be;
-                double q = Ml[m - 1] * bm;  // alpha^(k-m) beta^m M_m
-#pragma unroll
-                for (int k = m; k <= FMML_K; ++k) {
-                    M[k - 1] = __builtin_fma(binom(k, m), q, M[k - 1]);
-                    q *= al;
-                }
-            }
+        for (int k = 0; k < FMML_K; ++k) {
+            M[k] += P;  // P = (t + D)^(k+1) - t^(k+1)
+            tk *= t;
+            P = __builtin_fma(tD, P, D * tk);
         }
     }
-    if (LEAVES) {  // one wavefront: lane k adds column k over the 64 lanes in order
+    // lane k adds column k over the 64 lanes in order
 #pragma unroll
-        for (int k = 0; k < FMML_K; ++k) part[tid][k] = M[k];
-        __syncthreads();
-        if (tid < FMML_K) {
-            double sk = 0.0;
-            for (int u = 0; u < 64; ++u) sk += part[u][tid];
-            l.mom[(int64_t)g * FMML_K + tid] = sk;
-        }
-    } else {
-        // only the first nleaf threads hold moments.  Beyond 64 leaves the four wavefronts
-        // are folded onto the first, (w0 + w2) + (w1 + w3), through two 64-row buffers; then
-        // lane k adds column k over the rows in use, in order (one pass, no barrier per level
-        // of a tree)
-        const int nleaf = (int)((hi - lo + f.leaf - 1) / f.leaf);
-        const int wv = tid / WAVE, ln = tid % WAVE;
-        if (nleaf > WAVE) {
-            if (wv >= 2) {
-#pragma unroll
-                for (int k = 0; k < FMML_K; ++k) (wv == 2 ? part : part2)[ln][k] = M[k];
-            }
-            __syncthreads();
-            if (wv < 2) {
-#pragma unroll
-                for (int k = 0; k < FMML_K; ++k) M[k] += (wv == 0 ? part : part2)[ln][k];
-            }
-            __syncthreads();
-            if (wv == 1) {
-#pragma unroll
-                for (int k = 0; k < FMML_K; ++k) part[ln][k] = M[k];
-            }
-            __syncthreads();
-            if (wv == 0) {
-#pragma unroll
-                for (int k = 0; k < FMML_K; ++k) M[k] += part[ln][k];
-            }
-            __syncthreads();
-        }
-        if (wv == 0) {
-#pragma unroll
-            for (int k = 0; k < FMML_K; ++k) part[ln][k] = M[k];
-        }
-        __syncthreads();
-        if (tid < FMML_K) {
-            double sk = 0.0;
-            for (int u = 0; u < min(nleaf, WAVE); ++u) sk += part[u][tid];
-            l.mom[(int64_t)g * FMML_K + tid] = sk;
-        }
+    for (int k = 0; k < FMML_K; ++k) part[tid][k] = M[k];
+    __syncthreads();
+    if (tid < FMML_K) {
+        double sk = 0.0;
+        for (int u = 0; u < WAVE; ++u) sk += part[u][tid];
+        l.mom[(int64_t)g * FMML_K + tid] = sk;
     }
-    if (tid == 0) l.geo[g] = make_double2(c, hw);
+    if (tid == 0) l.geo[g] = make_double2(b.c, b.hw);
+}
+
+// Used boxes above the leaves from their leaves' moments.  More than 64 leaves: a workgroup.
+// Others: 2^c lanes, one a leaf, 2^(6-c) boxes to a wavefront -- most upper boxes have two or
+// four leaves, and with a workgroup each they took 500 us of a level of 4096 problems (now 36).
+constexpr int MOM_HALF = FMML_K / 2;
+static_assert(2 * MOM_HALF == FMML_K, "moments go through LDS in two halves");
+__global__ __launch_bounds__(256, 4) void k_fmml_moments_up(FmmArgs f, FmmlArgs l) {
+    __shared__ double lds[4 * WAVE * (MOM_HALF + 1)];
+    static_assert(2 * WAVE * (FMML_K + 1) <= 4 * WAVE * (MOM_HALF + 1), "a large box's two buffers");
+    const int tid = threadIdx.x, wv = wave_uniform(tid / WAVE), ln = tid % WAVE;
+    double M[FMML_K];
+#pragma unroll
+    for (int k = 0; k < FMML_K; ++k) M[k] = 0.0;
+    MomBox b;
+    const int nbig = f.upper_cls[0];
+    if ((int)blockIdx.x >= nbig) {
+        // this wavefront's boxes: class c of at most 2^c leaves
+        int w = ((int)blockIdx.x - nbig) * 4 + wv, c = 6;
+        for (; c >= 1; --c) {
+            const int waves = (f.upper_cls[7 - c] - f.upper_cls[6 - c] + (64 >> c) - 1) / (64 >> c);
+            if (w < waves) break;
+            w -= waves;
+        }
+        if (c < 1) return;
+        const int first = f.upper_cls[6 - c] + w * (64 >> c);
+        const int i = first + (ln >> c);
+        const bool in = i < f.upper_cls[7 - c];
+        const int g = in ? f.upper_box[i] : 0;
+        const bool ok = in && f.used[g] == f.gen && mom_box(f, g, b);
+        if (ok) {
+            mom_span(l, b);
+            const int e = ln & ((1 << c) - 1), nleaf = (b.hi - b.lo + f.leaf - 1) / f.leaf;
+            if (e < nleaf) mom_translate(l, b.leaf0 + e, b.c, 1.0 / b.hw, M);
+            if (e == 0) l.geo[g] = make_double2(b.c, b.hw);
+        }
+        const unsigned long long live = __ballot(ok);
+        // sums over each box's lanes, in leaf order
+        double *part = lds + wv * WAVE * (MOM_HALF + 1);
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int k = 0; k < MOM_HALF; ++k)
+                part[ln * (MOM_HALF + 1) + k] = h ? M[MOM_HALF + k] : M[k];
+            wave_sync();
+            for (int e = ln; e < (64 >> c) * MOM_HALF; e += WAVE) {
+                const int u = e / MOM_HALF, k = e % MOM_HALF;
+                if (!(live >> (u << c) & 1)) continue;
+                double s = 0.0;
+                for (int r = 0; r < 1 << c; ++r) s += part[((u << c) + r) * (MOM_HALF + 1) + k];
+                l.mom[(int64_t)f.upper_box[first + u] * FMML_K + h * MOM_HALF + k] = s;
+            }
+            wave_sync();
+        }
+        return;
+    }
+    double(*part)[FMML_K + 1] = reinterpret_cast<double(*)[FMML_K + 1]>(lds);
+    double(*part2)[FMML_K + 1] = part + WAVE;
+    const int g = f.upper_box[blockIdx.x];
+    if (f.used[g] != f.gen || !mom_box(f, g, b)) return;
+    mom_span(l, b);
+    const int nleaf = (b.hi - b.lo + f.leaf - 1) / f.leaf;
+    const double ihw = 1.0 / b.hw;
+    for (int e = tid; e < nleaf; e += blockDim.x) mom_translate(l, b.leaf0 + e, b.c, ihw, M);
+    // the four wavefronts are folded onto the first, (w0 + w2) + (w1 + w3), through two 64-row
+    // buffers; then lane k adds column k over the rows, in order (one pass, no barrier per level
+    // of a tree)
+    if (wv >= 2) {
+#pragma unroll
+        for (int k = 0; k < FMML_K; ++k) (wv == 2 ? part : part2)[ln][k] = M[k];
+    }
+    __syncthreads();
+    if (wv < 2) {
+#pragma unroll
+        for (int k = 0; k < FMML_K; ++k) M[k] += (wv == 0 ? part : part2)[ln][k];
+    }
+    __syncthreads();
+    if (wv == 1) {
+#pragma unroll
+        for (int k = 0; k < FMML_K; ++k) part[ln][k] = M[k];
+    }
+    __syncthreads();
+    if (wv == 0) {
+#pragma unroll
+        for (int k = 0; k < FMML_K; ++k) M[k] += part[ln][k];
+    }
+    __syncthreads();
+    if (wv == 0) {
+#pragma unroll
+        for (int k = 0; k < FMML_K; ++k) part[ln][k] = M[k];
+    }
+    __syncthreads();
+    if (tid < FMML_K) {
+        double sk = 0.0;
+        for (int u = 0; u < WAVE; ++u) sk += part[u][tid];
+        l.mom[(int64_t)g * FMML_K + tid] = sk;
+    }
+    if (tid == 0) l.geo[g] = make_double2(b.c, b.hw);
 }
 
 hipError_t launch_fmml_moments(const FmmArgs &f, const FmmlArgs &l, hipStream_t s) {
     if (f.nboxes <= 0) return hipSuccess;
-    SDC_LAUNCH(KID_FMML_MOMENTS, k_fmml_moments<true>, dim3(f.nleaves), dim3(64), 0, s, f, l);
-    if (f.nupper > 0)
-        SDC_LAUNCH(KID_FMML_MOMENTS, k_fmml_moments<false>, dim3(f.nupper), dim3(256), 0, s, f,
-                   l);
+    SDC_LAUNCH(KID_FMML_MOMENTS, k_fmml_moments, dim3(f.nleaves), dim3(WAVE), 0, s, f, l);
+    int waves = 0;
+    for (int c = 1; c <= 6; ++c)
+        waves += (f.upper_cls[7 - c] - f.upper_cls[6 - c] + (64 >> c) - 1) / (64 >> c);
+    const int blocks = f.upper_cls[0] + (waves + 3) / 4;
+    if (blocks > 0)
+        SDC_LAUNCH(KID_FMML_MOMENTS, k_fmml_moments_up, dim3(blocks), dim3(256), 0, s, f, l);
     return hipGetLastError();
 }
 
@@ -1049,7 +1134,7 @@ hipError_t launch_fmmv_pos(const FmmvPackArgs &a, hipStream_t s) {
 hipError_t launch_fmmv_sources(const FmmArgs &f, const FmmVec &v, hipStream_t s) {
     if (f.nboxes <= 0) return hipSuccess;
     const int ng = (v.m + FMMV_MAX_M - 1) / FMMV_MAX_M;
-    const dim3 gl(f.nleaves, ng), gu(f.nupper_item, ng);
+    const dim3 gl(f.nleaves, ng), gu(f.nitem_big + (f.nupper_item - f.nitem_big + 3) / 4, ng);
     if (v.m <= 4) {
         SDC_LAUNCH(KID_FMMV_SOURCES, (k_fmmv_sources<true, true>), gl, dim3(64), 0, s, f, v);
         if (f.nupper_item > 0)
