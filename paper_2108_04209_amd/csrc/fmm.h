@@ -201,7 +201,7 @@ constexpr int FMML_K = 28;  // moments per box (|r| <= 1/4 at separation 1.5: 0.
 struct FmmlArgs {
     double2 *pd;              // (d_j, delta_j) per entry (pole and its root's offset)
     double2 *geo;             // [boxes] (c, hw)
-    double *mom;              // [boxes][FMML_K] moments M_1 .. M_K
+    double *mom;              // [boxes][FMML_K] coefficients (-1)^(k+1) M_k / k, k = 1 .. K
     // pack != 0: the leaves' launch packs its poles itself (when the lists already exist, as
     // the separate packing launch would): (d_j, delta_j) into pd, (d_{K_j}, eta_j) into ke
     // when ke is set

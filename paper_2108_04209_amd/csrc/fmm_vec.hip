@@ -901,11 +901,14 @@ __host__ __device__ constexpr double binom(int k, int m) {
     return c;
 }
 // ---------------------------------------------------------------------------------------
+// moments are stored as the series' coefficients (-1)^(k+1) M_k / k
+__host__ __device__ constexpr double mom_scale(int k) { return k & 1 ? (double)k : -(double)k; }
+
 // the range of box g; false: invalid problem, or an empty box
 struct MomBox {
     int H, n, lo, hi, leaf0;  // leaf0: its first leaf's box
     int64_t base;
-    double c, hw;
+    double c, hw, ihw;
 };
 __device__ __forceinline__ bool mom_box(const FmmArgs &f, int g, MomBox &b) {
     const int qf = f.box_fmm[g];
@@ -925,9 +928,13 @@ __device__ __forceinline__ bool mom_box(const FmmArgs &f, int g, MomBox &b) {
 }
 __device__ __forceinline__ void mom_span(const FmmlArgs &l, MomBox &b) {
     const double2 *pd = l.pd + b.base;
-    const double x0 = pd[b.lo].x, x1 = pd[b.hi - 1].x + pd[b.hi - 1].y;  // its poles and roots
+    // its poles and roots, without the problem's last root: that one lies rho |z|^2 above its
+    // pole, as far as the others spread, and would widen the box until most poles are too
+    // close for its expansion (they multiply the last pair's factor themselves)
+    const double x0 = pd[b.lo].x, x1 = pd[b.hi - 1].x + (b.hi < b.n ? pd[b.hi - 1].y : 0.0);
     b.c = 0.5 * (x0 + x1);
     b.hw = 0.5 * (x1 - x0);
+    b.ihw = b.hw > 0.0 ? 1.0 / b.hw : 0.0;
 }
 // leaf gl's moments translated to the box's centre and half-width, added to M
 __device__ __forceinline__ void mom_translate(const FmmlArgs &l, int gl, double c, double ihw,
@@ -941,7 +948,7 @@ __device__ __forceinline__ void mom_translate(const FmmlArgs &l, int gl, double 
 #pragma unroll
     for (int m = 1; m <= FMML_K; ++m) {
         bm *= be;
-        double q = Ml[m - 1] * bm;  // alpha^(k-m) beta^m M_m
+        double q = Ml[m - 1] * (bm * mom_scale(m));  // alpha^(k-m) beta^m M_m
 #pragma unroll
         for (int k = m; k <= FMML_K; ++k) {
             M[k - 1] = __builtin_fma(binom(k, m), q, M[k - 1]);
@@ -969,12 +976,11 @@ __global__ __launch_bounds__(WAVE) void k_fmml_moments(FmmArgs f, FmmlArgs l) {
     }
     mom_span(l, b);
     const double2 *pd = l.pd + b.base;
-    const double ihw = 1.0 / b.hw;
     double M[FMML_K];
 #pragma unroll
     for (int k = 0; k < FMML_K; ++k) M[k] = 0.0;
-    for (int j = b.lo + tid; j < b.hi; j += WAVE) {
-        const double t = (pd[j].x - b.c) * ihw, D = pd[j].y * ihw, tD = t + D;
+    for (int j = b.lo + tid; j < min(b.hi, b.n - 1); j += WAVE) {
+        const double t = (pd[j].x - b.c) * b.ihw, D = pd[j].y * b.ihw, tD = t + D;
         double P = D, tk = 1.0;
 #pragma unroll
         for (int k = 0; k < FMML_K; ++k) {
@@ -990,7 +996,7 @@ __global__ __launch_bounds__(WAVE) void k_fmml_moments(FmmArgs f, FmmlArgs l) {
     if (tid < FMML_K) {
         double sk = 0.0;
         for (int u = 0; u < WAVE; ++u) sk += part[u][tid];
-        l.mom[(int64_t)g * FMML_K + tid] = sk;
+        l.mom[(int64_t)g * FMML_K + tid] = sk / mom_scale(tid + 1);
     }
     if (tid == 0) l.geo[g] = make_double2(b.c, b.hw);
 }
@@ -1026,7 +1032,7 @@ __global__ __launch_bounds__(256, 4) void k_fmml_moments_up(FmmArgs f, FmmlArgs 
         if (ok) {
             mom_span(l, b);
             const int e = ln & ((1 << c) - 1), nleaf = (b.hi - b.lo + f.leaf - 1) / f.leaf;
-            if (e < nleaf) mom_translate(l, b.leaf0 + e, b.c, 1.0 / b.hw, M);
+            if (e < nleaf) mom_translate(l, b.leaf0 + e, b.c, b.ihw, M);
             if (e == 0) l.geo[g] = make_double2(b.c, b.hw);
         }
         const unsigned long long live = __ballot(ok);
@@ -1042,7 +1048,8 @@ __global__ __launch_bounds__(256, 4) void k_fmml_moments_up(FmmArgs f, FmmlArgs 
                 if (!(live >> (u << c) & 1)) continue;
                 double s = 0.0;
                 for (int r = 0; r < 1 << c; ++r) s += part[((u << c) + r) * (MOM_HALF + 1) + k];
-                l.mom[(int64_t)f.upper_box[first + u] * FMML_K + h * MOM_HALF + k] = s;
+                l.mom[(int64_t)f.upper_box[first + u] * FMML_K + h * MOM_HALF + k] =
+                    s / mom_scale(h * MOM_HALF + k + 1);
             }
             wave_sync();
         }
@@ -1054,8 +1061,7 @@ __global__ __launch_bounds__(256, 4) void k_fmml_moments_up(FmmArgs f, FmmlArgs 
     if (f.used[g] != f.gen || !mom_box(f, g, b)) return;
     mom_span(l, b);
     const int nleaf = (b.hi - b.lo + f.leaf - 1) / f.leaf;
-    const double ihw = 1.0 / b.hw;
-    for (int e = tid; e < nleaf; e += blockDim.x) mom_translate(l, b.leaf0 + e, b.c, ihw, M);
+    for (int e = tid; e < nleaf; e += blockDim.x) mom_translate(l, b.leaf0 + e, b.c, b.ihw, M);
     // the four wavefronts are folded onto the first, (w0 + w2) + (w1 + w3), through two 64-row
     // buffers; then lane k adds column k over the rows, in order (one pass, no barrier per level
     // of a tree)
@@ -1087,7 +1093,7 @@ __global__ __launch_bounds__(256, 4) void k_fmml_moments_up(FmmArgs f, FmmlArgs 
     if (tid < FMML_K) {
         double sk = 0.0;
         for (int u = 0; u < WAVE; ++u) sk += part[u][tid];
-        l.mom[(int64_t)g * FMML_K + tid] = sk;
+        l.mom[(int64_t)g * FMML_K + tid] = sk / mom_scale(tid + 1);
     }
     if (tid == 0) l.geo[g] = make_double2(b.c, b.hw);
 }

@@ -42,78 +42,81 @@ __device__ __forceinline__ void renorm(double &num, double &den, int &E) {
 
 // products over roots j in [j0, j1); SKIP drops the denominator factor j == i.
 // Two independent product chains (even and odd roots) keep the multiplies from waiting
-// on each other; roots are read in pointer-stepped blocks of 4 (one scalar address add per
-// block) into two register sets that alternate, so the next block's scalar loads are in
-// flight while this block is multiplied; each chain strips its exponents after every 8
-// factors.
+// on each other; each strips its exponents after every 8 factors.  Roots come in blocks of 4
+// through the scalar cache, into two register sets that alternate, so the next block's loads
+// are in flight while this block is multiplied: 16 roots to a turn of the loop without a
+// branch in it (a loop that tested for the end after each block spent more scalar
+// instructions on moving the sets about than vector instructions on the factors).
 // SC: every factor is multiplied by sg (a power of two) before it enters its product.
+struct LwSet {
+    double k[8], d[4];  // (d_K, eta) pairs and poles
+};
+__device__ __forceinline__ void lw_load(LwSet &s, const_double_ptr kp, const_double_ptr dp) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s.k[u] = kp[u];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) s.d[u] = dp[u];
+}
+
 template <bool SKIP, bool SC>
 __device__ __forceinline__ void loewner_range(const_double2_ptr ke, const_double_ptr dd,
                                               int j0, int j1,
                                               int i, double di, double &num, double &den,
                                               int &E, double sg) {
-#define SDC_SCL(F) (SC ? (F) * sg : (F))
-#define SDC_LW_LOAD(S, KP, DP)                                                            \
-    S##k0 = (KP)[0]; S##k1 = (KP)[1]; S##k2 = (KP)[2]; S##k3 = (KP)[3];                    \
-    S##k4 = (KP)[4]; S##k5 = (KP)[5]; S##k6 = (KP)[6]; S##k7 = (KP)[7];                    \
-    S##d0 = (DP)[0]; S##d1 = (DP)[1]; S##d2 = (DP)[2]; S##d3 = (DP)[3];
-#define SDC_LW_BLOCK(S, J)                                                                \
-    {                                                                                     \
-        na *= SDC_SCL((S##k0 - di) + S##k1);                                              \
-        nb *= SDC_SCL((S##k2 - di) + S##k3);                                              \
-        na *= SDC_SCL((S##k4 - di) + S##k5);                                              \
-        nb *= SDC_SCL((S##k6 - di) + S##k7);                                              \
-        const double f0 = SDC_SCL(S##d0 - di), f1 = SDC_SCL(S##d1 - di);                  \
-        const double f2 = SDC_SCL(S##d2 - di), f3 = SDC_SCL(S##d3 - di);                  \
-        da *= (SKIP && (J) == i) ? 1.0 : f0;                                              \
-        db *= (SKIP && (J) + 1 == i) ? 1.0 : f1;                                          \
-        da *= (SKIP && (J) + 2 == i) ? 1.0 : f2;                                          \
-        db *= (SKIP && (J) + 3 == i) ? 1.0 : f3;                                          \
-        if (++blk == 4) { /* 8 factors per chain */                                       \
-            renorm(na, da, E);                                                            \
-            renorm(nb, db, E);                                                            \
-            blk = 0;                                                                      \
-        }                                                                                 \
-    }
+    if (j0 >= j1) return;
     double na = 1.0, da = 1.0, nb = 1.0, db = 1.0;
-    int j = j0;
-    if (j + 4 <= j1) {
-        const_double_ptr kp = ke.p + 2 * (int64_t)j;  // (d_K, eta) pairs
-        const_double_ptr dp = dd + j;
-        double ak0, ak1, ak2, ak3, ak4, ak5, ak6, ak7, ad0, ad1, ad2, ad3;
-        double bk0, bk1, bk2, bk3, bk4, bk5, bk6, bk7, bd0, bd1, bd2, bd3;
-        int blk = 0;
-        SDC_LW_LOAD(a, kp, dp)
-        for (;;) {
-            const bool more = j + 8 <= j1;
-            if (more) { SDC_LW_LOAD(b, kp + 8, dp + 4) }
-            SDC_LW_BLOCK(a, j)
-            j += 4;
-            kp += 8;
-            dp += 4;
-            if (!more) break;
-            const bool more2 = j + 8 <= j1;
-            if (more2) { SDC_LW_LOAD(a, kp + 8, dp + 4) }
-            SDC_LW_BLOCK(b, j)
-            j += 4;
-            kp += 8;
-            dp += 4;
-            if (!more2) break;
+    auto scl = [&](double f) { return SC ? f * sg : f; };
+    auto block = [&](const LwSet &s, int j) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const double fn = scl((s.k[2 * u] - di) + s.k[2 * u + 1]), fd = scl(s.d[u] - di);
+            const double fk = SKIP && j + u == i ? 1.0 : fd;
+            if (u & 1) {
+                nb *= fn;
+                db *= fk;
+            } else {
+                na *= fn;
+                da *= fk;
+            }
         }
+    };
+    auto strip = [&]() {
+        renorm(na, da, E);
+        renorm(nb, db, E);
+    };
+    int j = j0;
+    if (j + 16 <= j1) {
+        LwSet s0, s1;
+        lw_load(s0, ke.p + 2 * (int64_t)j, dd + j);
+        do {
+            const const_double_ptr kp = ke.p + 2 * (int64_t)j, dp = dd + j;
+            lw_load(s1, kp + 8, dp + 4);
+            block(s0, j);
+            lw_load(s0, kp + 16, dp + 8);
+            block(s1, j + 4);
+            lw_load(s1, kp + 24, dp + 12);
+            block(s0, j + 8);
+            const int jn = min(j + 16, j1 - 4);  // past the last turn: within the range, not used
+            lw_load(s0, ke.p + 2 * (int64_t)jn, dd + jn);
+            block(s1, j + 12);
+            strip();
+            j += 16;
+        } while (j + 16 <= j1);
     }
-    renorm(na, da, E);  // at most 8 factors per chain since the last strip
-    renorm(nb, db, E);
+    for (; j + 4 <= j1; j += 4) {
+        LwSet s;
+        lw_load(s, ke.p + 2 * (int64_t)j, dd + j);
+        block(s, j);
+    }
+    strip();  // at most 6 factors per chain since the last one
     for (; j < j1; ++j) {  // at most 3 more factors per chain after the strip above
         const double2 kv = ke[j];
-        na *= SDC_SCL((kv.x - di) + kv.y);
-        da *= (SKIP && j == i) ? 1.0 : SDC_SCL(dd[j] - di);
+        na *= scl((kv.x - di) + kv.y);
+        da *= SKIP && j == i ? 1.0 : scl(dd[j] - di);
     }
     num *= na * nb;  // mantissas in [0.5, 1) times at most 3 factors: no over- or underflow
     den *= da * db;
     renorm(num, den, E);
-#undef SDC_LW_BLOCK
-#undef SDC_LW_LOAD
-#undef SDC_SCL
 }
 
 // The binary exponent e used to scale a problem's factors (0 when its span is in range):
@@ -200,35 +203,21 @@ __device__ void loewner_tile(const VecArgs &a, Tile t, double4 *red) {
 // with a direct product over the box for the rare pole where |r| > 0.35.  Work items are
 // 64-pole pieces of the target leaves; S wavefronts split the lists.
 // ---------------------------------------------------------------------------------------
-__device__ __forceinline__ double lw_series(const double *M, double r) {
-    // Horner from the top: sum_{k=1}^{K} (-1)^(k+1) M_k r^k / k
+// M: coefficients (-1)^(k+1) M_k / k, as the moments are stored
+__device__ __forceinline__ double lw_series(const_double_ptr M, double r) {
     double acc = 0.0;
 #pragma unroll
-    for (int k = FMML_K; k >= 1; --k) {
-        const double ck = ((k & 1) ? 1.0 : -1.0) / (double)k;
-        acc = __builtin_fma(acc, r, ck * M[k - 1]);
-    }
+    for (int k = FMML_K; k >= 1; --k) acc = __builtin_fma(acc, r, M[k - 1]);
     return acc * r;
 }
 
-// The poles and far boxes of an item are staged through LDS, a round of them at a time
-// (every thread loads its share of the round, so a round costs one memory round trip
-// instead of one per pole block or per box), and the wavefronts read them from there.
-constexpr int LW_CH = 256;  // near poles per round
-constexpr int LW_FB = 16;   // far boxes per round
-struct LwShared {
-    double2 kep[LW_CH];     // (d_K, eta) of the staged poles' roots
-    double dd[LW_CH];       // the staged poles
-    int jj[LW_CH];          // their indices in the problem
-    int rs[FMM_NEAR_MAX + 1];  // start of near range e in the concatenation of the ranges
-    int rl[FMM_NEAR_MAX];      // its first pole
-    double2 geo[LW_FB];        // (centre, half-width) of the staged far boxes
-    double mom[LW_FB][FMML_K];
-    int box[LW_FB];
-};
-
+// Poles and boxes are the same for the whole wavefront, so both come through the scalar cache
+// and cost the vector units nothing but their arithmetic.  (Staged in LDS they cost three LDS
+// reads a pole and 28 a box, which bound the launch, and an item ran in rounds of loads and
+// barriers; the coefficients were formed per lane.  Measured, LDS -> scalar loads, us: a
+// level of 4096 problems 2640 -> 2210; with the last root out of the boxes 1110.)
 __device__ void loewner_fmm_tile(const VecArgs &a, const FmmArgs &f, const FmmlArgs &l, Tile t,
-                                 double4 *red, LwShared &sh) {
+                                 double4 *red) {
     const int p = t.prob;
     const int64_t base = a.off[p];
     const int n = (int)(a.off[p + 1] - base);
@@ -253,14 +242,26 @@ __device__ void loewner_fmm_tile(const VecArgs &a, const FmmArgs &f, const FmmlA
     const int qf = f.fmm_of[p];
     const int L = wave_uniform(f.leaf_off[qf] + t.row0 / f.leaf);
     const int nn = wave_uniform(f.cnt[3 * (int64_t)L]);
+    const int nl = wave_uniform(f.cnt[3 * (int64_t)L + 1]);
+    const int nr = wave_uniform(f.cnt[3 * (int64_t)L + 2]);
     const int t0 = t.row0, t1 = wave_uniform(min(t.row0 + TILE, n));
-    // exact products over [lo, hi), the poles of this item dropping their own factor;
     // a problem out of range has every factor scaled by sg = 2^-es (added back below)
     const int es = wave_uniform(loewner_scale(ke, dd, n));
     const double sg = __builtin_ldexp(1.0, -es);
-    if (nn < 0) {  // overflowed lists (rare): every pole, from global memory
-        const int lo = wave_uniform((int)(((int64_t)n * wv) / S));
-        const int hi = wave_uniform((int)(((int64_t)n * (wv + 1)) / S));
+    // far boxes: lane e holds the e-th (two registers: up to 2 FMM_FAR_MAX of them)
+    static_assert(FMM_FAR_MAX == WAVE, "a lane per far box of a side");
+    int gl = 0, gr = 0;
+    if (lane < nl) gl = f.far_l[(int64_t)L * FMM_FAR_MAX + lane];
+    if (lane < nr) gr = f.far_r[(int64_t)L * FMM_FAR_MAX + lane];
+    // exact products over the near ranges (overflowed lists, rare: every pole), each split over
+    // the wavefronts, the poles of this item dropping their own factor
+    int top = 0;  // end of the near poles
+    for (int e = 0; e < (nn < 0 ? 1 : nn); ++e) {
+        const int lo0 = nn < 0 ? 0 : wave_uniform(f.near_lo[(int64_t)L * FMM_NEAR_MAX + e]);
+        const int hi0 = nn < 0 ? n : wave_uniform(f.near_hi[(int64_t)L * FMM_NEAR_MAX + e]);
+        top = hi0;
+        const int lo = wave_uniform(lo0 + (int)(((int64_t)(hi0 - lo0) * wv) / S));
+        const int hi = wave_uniform(lo0 + (int)(((int64_t)(hi0 - lo0) * (wv + 1)) / S));
         if (es == 0) {
             loewner_range<false, false>(ke, dd, lo, min(hi, t0), ii, di, num, den, E, 1.0);
             loewner_range<true, false>(ke, dd, max(lo, t0), min(hi, t1), ii, di, num, den, E, 1.0);
@@ -270,112 +271,37 @@ __device__ void loewner_fmm_tile(const VecArgs &a, const FmmArgs &f, const FmmlA
             loewner_range<true, true>(ke, dd, max(lo, t0), min(hi, t1), ii, di, num, den, E, sg);
             loewner_range<false, true>(ke, dd, max(lo, t1), hi, ii, di, num, den, E, sg);
         }
-    } else {
-        // the near ranges' starts in their concatenation (a scan by the first wavefront)
-        if (wv == 0) {
-            int lo = 0, len = 0;
-            if (lane < nn) {
-                lo = f.near_lo[(int64_t)L * FMM_NEAR_MAX + lane];
-                len = f.near_hi[(int64_t)L * FMM_NEAR_MAX + lane] - lo;
+    }
+    // the last pole and its root are in no box's moments
+    if (top < n && wv == 0) {
+        const double2 kv = ke[n - 1];
+        num *= ((kv.x - di) + kv.y) * sg;
+        den *= (dd[n - 1] - di) * sg;
+        renorm(num, den, E);
+    }
+    for (int e = wv; e < nl + nr && nn >= 0; e += S) {
+        const int g = e < nl ? __builtin_amdgcn_readlane(gl, e) : __builtin_amdgcn_readlane(gr, e - nl);
+        const const_double2_ptr geo = as_const(l.geo + g);
+        const double2 gc = geo[0];
+        const double r = gc.y * rcp_nr(gc.x - di);
+        if (fabs(r) <= 0.35) {
+            far += lw_series(as_const(l.mom + (int64_t)g * FMML_K), r);
+        } else {  // too close for the expansion: the box's exact products for this lane
+            const int hidx = g - f.box_off[qf];
+            const int H = f.height[qf];
+            int h = 0;
+            while ((2 << h) - 1 <= hidx) ++h;
+            const int bi = hidx - ((1 << h) - 1);
+            const int64_t span = (int64_t)f.leaf << (H - h);
+            const int lo = (int)min((int64_t)n, bi * span);
+            const int hi = (int)min((int64_t)n - 1, (bi + 1) * span);
+            for (int j = lo; j < hi; ++j) {  // j != i: a far box never holds pole i
+                const double2 kv = ke[j];
+                num *= ((kv.x - di) + kv.y) * sg;  // as many factors on both sides
+                den *= (dd[j] - di) * sg;
+                if ((j & 7) == 7) renorm(num, den, E);
             }
-            int incl = len;
-            for (int o = 1; o < WAVE; o <<= 1) {
-                const int v = __shfl_up(incl, o);
-                if (lane >= o) incl += v;
-            }
-            if (lane < nn) {
-                sh.rs[lane + 1] = incl;
-                sh.rl[lane] = lo;
-            }
-            if (lane == 0) sh.rs[0] = 0;
-        }
-        __syncthreads();
-        const int T = sh.rs[nn];
-        // near poles, a round of LW_CH at a time: staged by every thread, then wavefront wv
-        // multiplies the factors of its contiguous share of the round (two chains, exponents
-        // stripped every 8 factors per chain)
-        for (int c0 = 0; c0 < T; c0 += LW_CH) {
-            const int cnt = min(LW_CH, T - c0);
-            for (int u = threadIdx.x; u < cnt; u += blockDim.x) {
-                const int pos = c0 + u;
-                int e = 0;
-                while (sh.rs[e + 1] <= pos) ++e;
-                const int j = sh.rl[e] + (pos - sh.rs[e]);
-                sh.kep[u] = ke[j];
-                sh.dd[u] = dd[j];
-                sh.jj[u] = j;
-            }
-            __syncthreads();
-            const int u0 = (int)(((int64_t)cnt * wv) / S), u1 = (int)(((int64_t)cnt * (wv + 1)) / S);
-            double na = 1.0, da = 1.0, nb = 1.0, db = 1.0;
-            int u = u0, blk = 0;
-            for (; u + 2 <= u1; u += 2) {
-                const double2 k0 = sh.kep[u], k1 = sh.kep[u + 1];
-                const double f0 = (sh.dd[u] - di) * sg, f1 = (sh.dd[u + 1] - di) * sg;
-                na *= ((k0.x - di) + k0.y) * sg;
-                nb *= ((k1.x - di) + k1.y) * sg;
-                da *= sh.jj[u] == ii ? 1.0 : f0;
-                db *= sh.jj[u + 1] == ii ? 1.0 : f1;
-                if (++blk == 8) {  // 8 factors per chain
-                    renorm(na, da, E);
-                    renorm(nb, db, E);
-                    blk = 0;
-                }
-            }
-            if (u < u1) {
-                const double2 k0 = sh.kep[u];
-                na *= ((k0.x - di) + k0.y) * sg;
-                da *= sh.jj[u] == ii ? 1.0 : (sh.dd[u] - di) * sg;
-            }
-            renorm(na, da, E);
-            renorm(nb, db, E);
-            num *= na * nb;
-            den *= da * db;
             renorm(num, den, E);
-            __syncthreads();  // the round's reads are done before the next is staged
-        }
-        // far boxes, a round of LW_FB at a time: ids and geometry, then their moments, staged
-        // by every thread; wavefront wv takes the round's boxes wv, wv + S, ...
-        const int nl = wave_uniform(f.cnt[3 * (int64_t)L + 1]);
-        const int nr = wave_uniform(f.cnt[3 * (int64_t)L + 2]);
-        for (int c0 = 0; c0 < nl + nr; c0 += LW_FB) {
-            const int cnt = min(LW_FB, nl + nr - c0);
-            if (threadIdx.x < cnt) {
-                const int e = c0 + threadIdx.x;
-                const int g = e < nl ? f.far_l[(int64_t)L * FMM_FAR_MAX + e]
-                                     : f.far_r[(int64_t)L * FMM_FAR_MAX + e - nl];
-                sh.box[threadIdx.x] = g;
-                sh.geo[threadIdx.x] = l.geo[g];
-            }
-            __syncthreads();
-            for (int u = threadIdx.x; u < cnt * FMML_K; u += blockDim.x)
-                sh.mom[u / FMML_K][u % FMML_K] = l.mom[(int64_t)sh.box[u / FMML_K] * FMML_K + u % FMML_K];
-            __syncthreads();
-            for (int b = wv; b < cnt; b += S) {
-                const double2 gc = sh.geo[b];
-                const double r = gc.y / (gc.x - di);
-                if (fabs(r) <= 0.35) {
-                    far += lw_series(sh.mom[b], r);
-                } else {  // too close for the expansion: the box's exact products for this lane
-                    const int g = sh.box[b];
-                    const int hidx = g - f.box_off[qf];
-                    const int H = f.height[qf];
-                    int h = 0;
-                    while ((2 << h) - 1 <= hidx) ++h;
-                    const int bi = hidx - ((1 << h) - 1);
-                    const int64_t span = (int64_t)f.leaf << (H - h);
-                    const int lo = (int)min((int64_t)n, bi * span);
-                    const int hi = (int)min((int64_t)n, (bi + 1) * span);
-                    for (int j = lo; j < hi; ++j) {  // j != i: a far box never holds pole i
-                        const double2 kv = ke[j];
-                        num *= ((kv.x - di) + kv.y) * sg;  // as many factors on both sides
-                        den *= (dd[j] - di) * sg;
-                        if ((j & 7) == 7) renorm(num, den, E);
-                    }
-                    renorm(num, den, E);
-                }
-            }
-            __syncthreads();  // the round's reads are done before the next is staged
         }
     }
     if (es != 0 && wv == 0) E += es;
@@ -479,8 +405,7 @@ __global__ __launch_bounds__(1024) void k_bnorm(VecArgs a) {
 
 __global__ __launch_bounds__(1024) void k_loewner_fmm(VecArgs a, FmmArgs f, FmmlArgs l) {
     extern __shared__ double4 red4[];
-    __shared__ LwShared sh;
-    loewner_fmm_tile(a, f, l, a.tiles[blockIdx.x], red4, sh);
+    loewner_fmm_tile(a, f, l, a.tiles[blockIdx.x], red4);
 }
 
 hipError_t launch_pack_ke(const VecArgs &a, hipStream_t s) {

@@ -36,3 +36,23 @@ def test_box_classes(sizes, m):
         a, e = int(batch.off[p]), int(batch.off[p + 1])
         for f, g in zip(*res):
             assert np.abs(f[..., a:e] - g[..., a:e]).max() <= 1e-11 * np.abs(g[..., a:e]).max(), p
+
+
+@pytest.mark.parametrize("rho", [1e-6, 1.0, 1e6])
+@pytest.mark.parametrize("sizes", [[129, 193, 1025], [4097, 2050]])
+def test_last_root_far_out(sizes, rho):
+    """zhat where the last root lies just above its pole, a spectrum's width and a million widths
+    away (it is kept out of the boxes' moments), and where the last leaf is a single pole:
+    through the FMM against the direct products, 1e-12 relative per entry."""
+    from paper_2108_04209_amd import native
+    from tests import gpu_pipeline as gp
+    batch = gen.small_batch(sizes, seed=103)
+    batch.rho[:] = rho
+    ctx = gp.context()
+    b = native.Batch(ctx, batch.off)
+    d, z, r = gp.to_dev(batch.d), gp.to_dev(batch.z), gp.to_dev(batch.rho)
+    s = native.secular_solve(ctx, b, d, z, r, opts=native.default_opts(method=1))
+    zh = [native.loewner(ctx, b, d, z, r, s["eta"], s["origin"], s["status"],
+                         opts=native.default_opts(method=mt))[0].cpu().numpy() for mt in (2, 1)]
+    assert not s["status"].cpu().numpy().any()
+    assert np.max(np.abs(zh[0] - zh[1]) / np.abs(zh[1])) <= 1e-12
