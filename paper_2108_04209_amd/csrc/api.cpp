@@ -653,8 +653,8 @@ void *ws_get(superdc_ctx *ctx, int slot, size_t bytes) {
     }
 
 namespace sdc {
-// Loewner/b and the Cauchy apply.  reuse_lists: the batch's FMM interaction lists were
-// built by a solve on the same poles d and stay valid (internal callers only).
+// Loewner/b and the Cauchy apply.  reuse_lists: right before, a solve of the same problems
+// left their FMM interaction lists and (d_K, eta) pairs in the workspace (internal callers only).
 int loewner_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const double *z,
                 const double *rho, const double *eta, const int32_t *origin,
                 const int32_t *status, double *zhat, double *bnorm, const superdc_opts *opts,
@@ -727,13 +727,13 @@ int loewner_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const
             lf.d = d;
             lf.eta = eta;
             lf.origin = origin;
-            lf.ke = pk.ke;
         }
         SDC_HIP(launch_fmml_moments(f, lf, s));
     }
     a.tiles = L->lpt;
     a.ntiles = L->count;
-    if (!pk.ke) SDC_HIP(launch_pack_ke(a, s));
+    // a solve right before (reuse_lists) left ke as well
+    if (!pk.ke && !reuse_lists) SDC_HIP(launch_pack_ke(a, s));
     if (o.persistent) {
         const int S = b->vec.split;
         if (fp) {

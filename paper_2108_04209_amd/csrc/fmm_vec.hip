@@ -970,7 +970,6 @@ __global__ __launch_bounds__(WAVE) void k_fmml_moments(FmmArgs f, FmmlArgs l) {
             const double ej = l.eta[b.base + j];
             const double delta = (dK - dj) + ej;
             l.pd[b.base + j] = make_double2(dj, delta);
-            if (l.ke) l.ke[b.base + j] = make_double2(dK, ej);
         }
         __syncthreads();
     }
