@@ -35,15 +35,15 @@ namespace sdc {
 constexpr int LJ_TILE = 4;  // rows and columns of a thread's tile: two pairs of each
 // Tile rows a and T-1-a together have T-1 tiles right of the diagonal: they go to one group of
 // lanes.  Threads: the first wavefront and one tile a lane, but at most 8 wavefronts, so that
-// two leaves of 128 share a CU at 128 registers; the last wavefront then takes the groups
-// left over as well (nine had left one leaf to a CU)
+// two leaves of 128 share a CU at 128 registers (nine had left one leaf to a CU); the last four
+// then take the groups left over as well, a 2 x 2 block of each of their tiles per wavefront
 constexpr int lj_rows(int L) { return (L + LJ_TILE - 1) / LJ_TILE; }
 constexpr int lj_group(int L) { return lj_rows(L) > 16 ? 32 : lj_rows(L) > 8 ? 16 : 8; }
 constexpr int lj_waves(int L) {
     return ((lj_rows(L) + 1) / 2 * lj_group(L) + WAVE - 1) / WAVE;
 }
 constexpr int lj_threads(int L) { return WAVE * (1 + (lj_waves(L) < 7 ? lj_waves(L) : 7)); }
-static_assert(lj_waves(LEAF_MAX) <= 8, "the last wavefront takes one more group of 64 lanes");
+static_assert(lj_waves(LEAF_MAX) <= 8, "at most 64 tiles left over");
 constexpr int LV_SEG = 16;                          // positions a lane holds
 constexpr int LV_NSEG = LEAF_MAX / LV_SEG;          // segments of a row (8)
 constexpr int LV_RPL = 4;                           // rows a lane holds
@@ -96,7 +96,7 @@ __device__ __forceinline__ double rsqrt_nr(double t) {
     return 2.0 * h;
 }
 
-// The matrix is kept by position: entry (i, j) of the packed upper triangle is the entry
+// The matrix is kept by position: entry (i, j) of the stored upper triangle is the entry
 // of the two indices at positions i and j.  A round's rotation of pair k then acts on the
 // positions (l, r) of the pair by the reflection [[sigma, c], [c, -sigma]] -- the rotation
 // followed by the trade of positions -- with theta = (A(r,r) - A(l,l)) / (2 A(l,r)) taken
@@ -121,10 +121,18 @@ __device__ __forceinline__ double rsqrt_nr(double t) {
 // What bounded a round of two leaves of 128 on a CU was the issue of instructions (75 to a
 // 2 x 2 block, 16 of them in FP64, with the blocks dealt one by one over 16 wavefronts) and,
 // for small leaves, the first wavefront's chain of three square roots and three reciprocals.
-// With tiles and two reciprocal square roots it is the LDS, 66 KB each way per leaf, busy two
-// thirds of the time.  Measured: 512 leaves of 128 2580 -> 1900 us, 32 leaves of 32 330 ->
-// 132 us.
-template <int LP>
+// Measured: 512 leaves of 128 2580 -> 1900 us with tiles and two reciprocal square roots, the
+// LDS then busy two thirds of the time -> 1640 with the tiles in registers (RES) -> 1350 with the
+// tiles left over spread over four wavefronts instead of one; 32 leaves of 32 330 -> 132 us.
+// What is left is the chain of a round (32 leaves of 128, one to a CU, take 820 us).
+//
+// RES: a tile's entries off the rows and columns 0 mod 4 belong to the same thread in both round
+// types (a round B takes the tile one row and column further on), and stay in its registers
+// from round to round: 8 words each way through the LDS instead of 16.  Two of them change
+// hands all the same, where a tile touches the first wavefront's blocks: entry (3, 2) or, in
+// round B, (1, 0) beside the diagonal, (2, 3) and (0, 1) in the tile of the block (0, m/2 - 1).
+// Leaves of whole tiles only (a multiple of 4), with those two kinds of tile apart (12 and more).
+template <int LP, bool RES>
 __global__ __launch_bounds__(lj_threads(LP), 4) void k_leaf_jacobi(LeafArgs a) {
     // upper triangle by position, its diagonal, and PW spare words, one per bank
     constexpr int PW = LP > 64 ? 32 : 16, DIAG = LP / 2 * 4 * PW, SPARE = DIAG + LP;
@@ -134,8 +142,6 @@ __global__ __launch_bounds__(lj_threads(LP), 4) void k_leaf_jacobi(LeafArgs a) {
     __shared__ double2 cs[2][2][LP / 4];
     __shared__ double tt[2][LP / 2];   // tangent of each pair's rotation (0: none)
     __shared__ double red[lj_threads(LP) / WAVE];
-    // the last wavefront's second tiles (LDS: the registers hold the first ones)
-    __shared__ int4 more_ad[2][2][LP > 64 ? WAVE : 1], more_p[LP > 64 ? WAVE : 1];
     __shared__ int swept[2];       // per sweep parity: the sweep rotated something
     __shared__ int swbig[2];       // per sweep parity: some tangent was at least 1e-6
 
@@ -176,7 +182,7 @@ __global__ __launch_bounds__(lj_threads(LP), 4) void k_leaf_jacobi(LeafArgs a) {
     };
 
     // Addresses in this thread's registers, two to a word, per round type.  First wavefront,
-    // lane k: words 0 and 1 the diagonal block of pair k (left, right, between them), words
+    // lane k (in edge): words 0 and 1 the diagonal block of pair k (left, right, between them), words
     // 2 and 3 a block of neighbours, (k, k+1) in round A and (k-1, k) in round B, or, in the
     // lane left over, the block (0, m/2 - 1).  Others: entries (v, 2h), (v, 2h+1) of the tile in
     // word 2v + h.
@@ -186,20 +192,63 @@ __global__ __launch_bounds__(lj_threads(LP), 4) void k_leaf_jacobi(LeafArgs a) {
         int out;           // bit h: column pair P2 + h sits round B out
     };
     Tile4 t0;
+    double x[4][4];        // RES: the tile
+    int edge[2][4];        // RES: two addresses to a word: entries 0 .. 3 of the tile's row 0 (round
+                           // B: 3), the other three of its column 0 (3), the one that changes hands
+    bool beside = false, corner = false;  // beside the diagonal; with the block (0, m/2 - 1)
     int Q1 = 0, Q2 = 0;  // first wavefront: the pairs of its block in round B
     bool sits = false;   // whose column pair sits the round out
-    int(&ad)[2][8] = t0.ad;
     int &P1 = t0.P1, &P2 = t0.P2;
     P1 = P2 = 0;
-    const bool more = LP > 64 && tid >= 7 * WAVE && lj_waves(m) > 7;
+    const int T = (half + 1) / 2, G = lj_group(m);
+    auto take = [&](int e, Tile4 &t) {
+        int ta = e / G, tb = ta + 1 + e % G;
+        const int row = min(ta, T - 1);  // the group's first tile row
+        if (2 * ta >= T) {
+            tb = half;  // past the tiles: nothing valid
+        } else if (tb >= T) {  // the group's second tile row
+            const int other = T - 1 - ta;
+            tb = other > ta && tb - T < ta ? tb - T + other + 1 : half;
+            ta = other;
+        }
+        ta = max(min(ta, T - 2), 0);
+        t.P1 = 2 * ta;
+        t.P2 = min(2 * tb, (half - 1) & ~1);
+        t.out = 2 * tb == half - 1 ? 1 : 2 * tb == half - 2 ? 2 : 0;  // the last pair
+#pragma unroll
+        for (int p = 0; p < 2; ++p)
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int R = 2 * ta + (v >> 1), S = 2 * tb + h;
+                    int w[2];
+                    for (int u = 0; u < 2; ++u) {
+                        if (tb < T && S < half) {
+                            w[u] = entry(position(R, v & 1, p), position(S, u, p));
+                            if (!tiled(R, S)) w[u] = spare + w[u] % PW;  // the same bank
+                        } else {  // a lane without a tile: the bank that its group leaves free
+                            const int line = 4 * row + v + p;
+                            const int free = 2 * h + u <= v ? row : 0;
+                            w[u] = spare + (free + (line >> (PW == 32 ? 2 : 3))) % PW;
+                        }
+                    }
+                    t.ad[p][2 * v + h] = w[0] | w[1] << 16;
+                }
+    };
+    // block (mi, mh) of a tile left over: its addresses, pairs and whether its columns sit round B out
+    const bool more = LP > 64 && tid >= 4 * WAVE && lj_waves(m) > 7;
+    const int mi = (wave_uniform(tid / WAVE) >> 1) & 1, mh = wave_uniform(tid / WAVE) & 1;
+    int mad[2][2], mP = 0, mS = 0;
+    bool mout = false;
     if (first) {
         const int k = tid;
 #pragma unroll
         for (int p = 0; p < 2; ++p) {
             const bool diag = k < half && !(p && k == half - 1);
             const int l = 2 * k + p;
-            ad[p][0] = diag ? ut<PW>(l, l, m, DIAG) | ut<PW>(l + 1, l + 1, m, DIAG) << 16 : spare | spare << 16;
-            ad[p][1] = diag ? ut<PW>(l, l + 1, m, DIAG) : spare;
+            (RES ? edge[p] : t0.ad[p])[0] = diag ? ut<PW>(l, l, m, DIAG) | ut<PW>(l + 1, l + 1, m, DIAG) << 16 : spare | spare << 16;
+            (RES ? edge[p] : t0.ad[p])[1] = diag ? ut<PW>(l, l + 1, m, DIAG) : spare;
             const int left = p ? 0 : half - 1;  // the lane left over
             int R = p ? k - 1 : k, S = R + 1;
             bool has = k < half && k != left;
@@ -219,59 +268,48 @@ __global__ __launch_bounds__(lj_threads(LP), 4) void k_leaf_jacobi(LeafArgs a) {
 #pragma unroll
             for (int v = 0; v < 2; ++v) {
                 const int r = position(R, v, p);
-                ad[p][2 + v] = has ? entry(r, position(S, 0, p)) | entry(r, position(S, 1, p)) << 16
+                (RES ? edge[p] : t0.ad[p])[2 + v] = has ? entry(r, position(S, 0, p)) | entry(r, position(S, 1, p)) << 16
                                    : spare | spare << 16;
             }
             if (p) sits = has && S == half - 1;
         }
     } else {
-        const int T = (half + 1) / 2, G = lj_group(m);
-        auto take = [&](int e, Tile4 &t) {
-            int ta = e / G, tb = ta + 1 + e % G;
-            const int row = min(ta, T - 1);  // the group's first tile row
-            if (2 * ta >= T) {
-                tb = half;  // past the tiles: nothing valid
-            } else if (tb >= T) {  // the group's second tile row
-                const int other = T - 1 - ta;
-                tb = other > ta && tb - T < ta ? tb - T + other + 1 : half;
-                ta = other;
-            }
-            ta = max(min(ta, T - 2), 0);
-            t.P1 = 2 * ta;
-            t.P2 = min(2 * tb, (half - 1) & ~1);
-            t.out = 2 * tb == half - 1 ? 1 : 2 * tb == half - 2 ? 2 : 0;  // the last pair
-#pragma unroll
-            for (int p = 0; p < 2; ++p)
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const int R = 2 * ta + (v >> 1), S = 2 * tb + h;
-                        int w[2];
-                        for (int u = 0; u < 2; ++u) {
-                            if (tb < T && S < half) {
-                                w[u] = entry(position(R, v & 1, p), position(S, u, p));
-                                if (!tiled(R, S)) w[u] = spare + w[u] % PW;  // the same bank
-                            } else {  // a lane without a tile: the bank that its group leaves free
-                                const int line = 4 * row + v + p;
-                                const int free = 2 * h + u <= v ? row : 0;
-                                w[u] = spare + (free + (line >> (PW == 32 ? 2 : 3))) % PW;
-                            }
-                        }
-                        t.ad[p][2 * v + h] = w[0] | w[1] << 16;
-                    }
-        };
         take(tid - WAVE, t0);
+        if (RES) {
+            beside = P2 == P1 + 2;
+            corner = P1 == 0 && P2 == half - 2;
+            auto at = [&](int p, int v, int u) {
+                const int w = t0.ad[p][2 * v + (u >> 1)];
+                return u & 1 ? (int)((unsigned)w >> 16) : w & 0xffff;
+            };
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const int e = p ? 3 : 0, f = p ? 0 : 1;  // the edge, the first entry off it
+                const int hand = p ? (corner ? at(1, 0, 1) : at(1, 1, 0))
+                                   : (corner ? at(0, 2, 3) : at(0, 3, 2));
+                edge[p][0] = at(p, e, 0) | at(p, e, 1) << 16;
+                edge[p][1] = at(p, e, 2) | at(p, e, 3) << 16;
+                edge[p][2] = at(p, f, e) | at(p, f + 1, e) << 16;
+                edge[p][3] = at(p, f + 2, e) |
+                             (beside || corner ? hand : spare + hand % PW) << 16;
+            }
+#pragma unroll
+            for (int v = 1; v < 4; ++v)
+#pragma unroll
+                for (int u = 1; u < 4; ++u) x[v][u] = A[at(0, v, u)];
+        }
         if (more) {  // past the 7 wavefronts' first tiles
             Tile4 t1;
-            take(tid, t1);
-            more_p[lane_id()] = make_int4(t1.P1, t1.P2, t1.out, 0);
+            take(7 * WAVE + lane_id(), t1);
+            mP = t1.P1 >> 1;
+            mS = t1.P2 >> 1;
+            mout = (t1.out >> mh) & 1;
 #pragma unroll
             for (int p = 0; p < 2; ++p)
 #pragma unroll
-                for (int h = 0; h < 2; ++h)
-                    more_ad[p][h][lane_id()] = make_int4(t1.ad[p][4 * h], t1.ad[p][4 * h + 1],
-                                                         t1.ad[p][4 * h + 2], t1.ad[p][4 * h + 3]);
+                for (int v = 0; v < 2; ++v)
+                    mad[p][v] = mi ? (mh ? t1.ad[p][5 + 2 * v] : t1.ad[p][4 + 2 * v])
+                                   : (mh ? t1.ad[p][1 + 2 * v] : t1.ad[p][2 * v]);
         }
     }
     auto lo = [](int w) { return w & 0xffff; };
@@ -293,9 +331,10 @@ __global__ __launch_bounds__(lj_threads(LP), 4) void k_leaf_jacobi(LeafArgs a) {
     // log entry; returns the lane's tangent (0: no rotation)
     auto rotations = [&](int g, auto par) -> double {
         constexpr int p = decltype(par)::value;
+        const int *const ad = RES ? edge[p] : t0.ad[p];
         const int k = tid;
         double t = 0.0;
-        const double x = A[lo(ad[p][0])], y = A[hi(ad[p][0])], w = A[ad[p][1]];
+        const double x = A[lo(ad[0])], y = A[hi(ad[0])], w = A[ad[1]];
         if (k < half) {
             const bool idle = p && k == half - 1;
             double2 r = make_double2(1.0, 0.0);
@@ -391,51 +430,112 @@ __global__ __launch_bounds__(lj_threads(LP), 4) void k_leaf_jacobi(LeafArgs a) {
             }
         }
     };
+    // the same with the tile in registers
+    auto update_res = [&](auto par) {
+        constexpr int p = decltype(par)::value;
+        const double2 r0 = cs[p][0][P1 >> 1], r1 = cs[p][1][P1 >> 1];
+        const double2 q0 = cs[p][0][P2 >> 1], q1 = cs[p][1][P2 >> 1];
+        constexpr int e = p ? 3 : 0, f = p ? 0 : 1;
+        double y[4][4];
+#pragma unroll
+        for (int v = 0; v < 3; ++v)
+#pragma unroll
+            for (int u = 0; u < 3; ++u) y[f + v][f + u] = x[1 + v][1 + u];
+        y[e][0] = A[lo(edge[p][0])];
+        y[e][1] = A[hi(edge[p][0])];
+        y[e][2] = A[lo(edge[p][1])];
+        y[e][3] = A[hi(edge[p][1])];
+        y[f][e] = A[lo(edge[p][2])];
+        y[f + 1][e] = A[hi(edge[p][2])];
+        y[f + 2][e] = A[lo(edge[p][3])];
+        const double hand = A[hi(edge[p][3])];
+        double &b = y[p ? 1 : 3][p ? 0 : 2], &c = y[p ? 0 : 2][p ? 1 : 3];
+        b = beside ? hand : b;
+        c = corner ? hand : c;
+        const double n0 = -q0.y, n1 = p && (t0.out & 2) ? q1.y : -q1.y;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            rows(r0, y[0][u], y[1][u]);
+            rows(r1, y[2][u], y[3][u]);
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            cols(q0, n0, y[v][0], y[v][1]);
+            cols(q1, n1, y[v][2], y[v][3]);
+        }
+        A[lo(edge[p][0])] = y[e][0];
+        A[hi(edge[p][0])] = y[e][1];
+        A[lo(edge[p][1])] = y[e][2];
+        A[hi(edge[p][1])] = y[e][3];
+        A[lo(edge[p][2])] = y[f][e];
+        A[hi(edge[p][2])] = y[f + 1][e];
+        A[lo(edge[p][3])] = y[f + 2][e];
+        A[hi(edge[p][3])] = corner ? c : b;
+#pragma unroll
+        for (int v = 0; v < 3; ++v)
+#pragma unroll
+            for (int u = 0; u < 3; ++u) x[1 + v][1 + u] = y[f + v][f + u];
+    };
+    // the tiles' registers into the matrix, after a round B
+    auto flush = [&]() {
+        if (!RES || first) return;
+        int e = tid - WAVE;
+        asm volatile("" : "+v"(e));  // its addresses formed here, not held through the rounds
+        Tile4 t;
+        take(e, t);
+#pragma unroll
+        for (int v = 0; v < 3; ++v)
+#pragma unroll
+            for (int u = 0; u < 3; ++u) {
+                const int w = t.ad[1][2 * v + (u >> 1)];
+                A[u & 1 ? hi(w) : lo(w)] = x[1 + v][1 + u];
+            }
+    };
     // round g of type p up to its barrier; next: the first wavefront goes on to the rotations
     // of round g + 1
     auto round = [&](int g, auto par, bool next) {
         constexpr int p = decltype(par)::value;
+        const int *const ad = RES ? edge[p] : t0.ad[p];
         if (first) {
             // all loads first: lane k's diagonal block and its block of neighbours
             const double t = tt[p][min(tid, half - 1)];
             const int R = p ? Q1 : P1, S = p ? Q2 : P2;
             const double2 r1 = cs[p][R & 1][R >> 1], r2 = cs[p][S & 1][S >> 1];
-            const double x = A[lo(ad[p][0])], y = A[hi(ad[p][0])], w = A[ad[p][1]];
-            double x00 = A[lo(ad[p][2])], x01 = A[hi(ad[p][2])];
-            double x10 = A[lo(ad[p][3])], x11 = A[hi(ad[p][3])];
-            A[lo(ad[p][0])] = fma(t, w, y);
-            A[hi(ad[p][0])] = fma(-t, w, x);
-            A[ad[p][1]] = t != 0.0 ? 0.0 : w;
+            const double x = A[lo(ad[0])], y = A[hi(ad[0])], w = A[ad[1]];
+            double x00 = A[lo(ad[2])], x01 = A[hi(ad[2])];
+            double x10 = A[lo(ad[3])], x11 = A[hi(ad[3])];
+            A[lo(ad[0])] = fma(t, w, y);
+            A[hi(ad[0])] = fma(-t, w, x);
+            A[ad[1]] = t != 0.0 ? 0.0 : w;
             rows(r1, x00, x10);
             rows(r1, x01, x11);
             const double n = p && sits ? r2.y : -r2.y;
             cols(r2, n, x00, x01);
             cols(r2, n, x10, x11);
-            A[lo(ad[p][2])] = x00;
-            A[hi(ad[p][2])] = x01;
-            A[lo(ad[p][3])] = x10;
-            A[hi(ad[p][3])] = x11;
+            A[lo(ad[2])] = x00;
+            A[hi(ad[2])] = x01;
+            A[lo(ad[3])] = x10;
+            A[hi(ad[3])] = x11;
             if (next) {
                 wave_sync();
                 note(rotations(g + 1, std::integral_constant<int, 1 - p>{}));
             }
         } else {
-            update(t0, par);
+            if (RES) update_res(par);
+            else update(t0, par);
             if (more) {
-                Tile4 t1;
-                const int4 q = more_p[lane_id()];
-                t1.P1 = q.x;
-                t1.P2 = q.y;
-                t1.out = q.z;
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int4 w = more_ad[p][h][lane_id()];
-                    t1.ad[p][4 * h] = w.x;
-                    t1.ad[p][4 * h + 1] = w.y;
-                    t1.ad[p][4 * h + 2] = w.z;
-                    t1.ad[p][4 * h + 3] = w.w;
-                }
-                update(t1, par);
+                const double2 r = cs[p][mi][mP], q = cs[p][mh][mS];
+                const double n = p && mout ? q.y : -q.y;
+                double x00 = A[lo(mad[p][0])], x01 = A[hi(mad[p][0])];
+                double x10 = A[lo(mad[p][1])], x11 = A[hi(mad[p][1])];
+                rows(r, x00, x10);
+                rows(r, x01, x11);
+                cols(q, n, x00, x01);
+                cols(q, n, x10, x11);
+                A[lo(mad[p][0])] = x00;
+                A[hi(mad[p][0])] = x01;
+                A[lo(mad[p][1])] = x10;
+                A[hi(mad[p][1])] = x11;
             }
         }
         __syncthreads();
@@ -469,9 +569,13 @@ __global__ __launch_bounds__(lj_threads(LP), 4) void k_leaf_jacobi(LeafArgs a) {
             ++sweep;
             // once the sweep's rotations are all tiny, the next one may well be empty: test
             // every pair now instead of running it to find out (the same decision)
-            if (!big && !any_pair_rotates()) {
-                converged = true;
-                break;
+            if (!big) {
+                flush();
+                __syncthreads();
+                if (!any_pair_rotates()) {
+                    converged = true;
+                    break;
+                }
             }
             if (sweep == a.max_sweeps) break;
         }
@@ -853,9 +957,16 @@ static inline dim3 grid_for(int64_t n, int b = 256) { return dim3((unsigned)((n 
 hipError_t launch_leaf_jacobi(const LeafArgs &a, hipStream_t s) {
     // the smallest LDS that holds the leaf, so that small leaves share a CU
     const dim3 nt(lj_threads(a.leaf));
-    if (a.leaf <= 32) SDC_LAUNCH(KID_LEAF, k_leaf_jacobi<32>, dim3(a.nleaf), nt, 0, s, a);
-    else if (a.leaf <= 64) SDC_LAUNCH(KID_LEAF, k_leaf_jacobi<64>, dim3(a.nleaf), nt, 0, s, a);
-    else SDC_LAUNCH(KID_LEAF, k_leaf_jacobi<LEAF_MAX>, dim3(a.nleaf), nt, 0, s, a);
+    const bool res = a.leaf % LJ_TILE == 0 && a.leaf >= 3 * LJ_TILE;
+#define SDC_LJ(LP)                                                                               \
+    {                                                                                            \
+        if (res) SDC_LAUNCH(KID_LEAF, (k_leaf_jacobi<LP, true>), dim3(a.nleaf), nt, 0, s, a);    \
+        else SDC_LAUNCH(KID_LEAF, (k_leaf_jacobi<LP, false>), dim3(a.nleaf), nt, 0, s, a);       \
+    }
+    if (a.leaf <= 32) SDC_LJ(32)
+    else if (a.leaf <= 64) SDC_LJ(64)
+    else SDC_LJ(LEAF_MAX)
+#undef SDC_LJ
     SDC_LAUNCH(KID_LEAF_VECTORS, k_leaf_vectors, dim3(a.nleaf * ((a.leaf + LV_WROWS - 1) / LV_WROWS)),
                dim3(WAVE), 0, s, a);
     SDC_LAUNCH(KID_LEAF_VECTORS, k_leaf_w, dim3(a.nleaf), dim3(256), 0, s, a);
