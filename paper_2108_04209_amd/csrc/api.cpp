@@ -63,10 +63,12 @@ int opts_check(const superdc_opts *o) {
 constexpr double DIRECT_PAIRS = 4e7;
 constexpr double DIRECT_APPLY_PAIRS = 9e6;
 // The adjoint's direct sums take longer the longer the largest problem is (few tiles, each
-// through all its poles): direct against FMM, 16 problems of 1024 roots 40 and 72 us, 4 of
-// 2048 62 and 77, 1 of 4096 108 and 84, 64 of 1024 172 and 113.
-constexpr double DIRECT_BWD_PAIRS = 2e7;
-constexpr int DIRECT_BWD_N = 2048;
+// through all its poles), its FMM eleven launches more: direct against FMM, 16 problems of 1024
+// roots 40 and 72 us, 4 of 2048 62 and 77, 1 of 4096 108 and 84, 64 of 1024 172 and 113, 1 of
+// 8192 202 and 97, 128 of 1024 435 and 192.  The line lies where the FMM also gains on a
+// program that issues the calls itself (30 us of launches more).
+constexpr double DIRECT_BWD_PAIRS = 7e7;
+constexpr int DIRECT_BWD_N = 4096;
 
 int fmm_crossover_of(const superdc_batch *b, const superdc_opts &o, double pairs) {
     if (o.method == 1) return 0x7fffffff;

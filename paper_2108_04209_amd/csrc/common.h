@@ -386,6 +386,12 @@ hipError_t launch_deflate_expand(const int64_t *off, int nprob, int64_t total, i
                                  const int32_t *rleft, const double *rc, const double *rs,
                                  int trans, const double *X, int64_t ldx, double *Y,
                                  int64_t ldy, double *T, hipStream_t s);
+hipError_t launch_step_reduced(const int64_t *off, const int64_t *roff, int nprob,
+                               const int32_t *kept, const double *d, const double *z, double *dr,
+                               double *zr, int64_t rtotal, hipStream_t s);
+hipError_t launch_step_values(const int64_t *off, const int64_t *roff, int nprob,
+                              const int32_t *kept, const double *d, const double *lam, double *E,
+                              int64_t total, hipStream_t s);
 hipError_t launch_copy_rows(const int64_t *soff, const int64_t *doff, int nprob,
                             int64_t dtotal, int m, const int32_t *rows, const double *src,
                             int64_t lds, double *dst, int64_t ldd, const double *fill,

@@ -578,6 +578,32 @@ __global__ __launch_bounds__(256) void k_copy_rows(CopyRowsArgs a, int64_t dtota
         for (int c = c0; c < c1; ++c) a.dst[c * a.ldd + row] = a.fill;
 }
 
+// A deflated HSS step's row copies, one launch each instead of two: the reduced problems' poles and
+// weights (a node that deflated completely: d = 0, z = 1), and a node's eigenvalues, the
+// reduced roots in front of the deflated poles (18 steps over 65536 rows: 8.0 -> 7.9 ms).
+__global__ __launch_bounds__(256) void k_step_reduced(const int64_t *off, const int64_t *roff, int nprob,
+                                                      const int32_t *kept, const double *d,
+                                                      const double *z, double *dr, double *zr,
+                                                      int64_t rtotal) {
+    const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int p = row_prob(roff, nprob, row, rtotal);
+    if (row >= rtotal) return;
+    const int64_t j = row - roff[p], s = off[p] + j;
+    const bool in = j < kept[p] && s < off[p + 1];
+    dr[row] = in ? d[s] : 0.0;
+    zr[row] = in ? z[s] : 1.0;
+}
+
+__global__ __launch_bounds__(256) void k_step_values(const int64_t *off, const int64_t *roff, int nprob,
+                                                     const int32_t *kept, const double *d,
+                                                     const double *lam, double *E, int64_t total) {
+    const int64_t row = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int p = row_prob(off, nprob, row, total);
+    if (row >= total) return;
+    const int64_t j = row - off[p], s = roff[p] + j;
+    E[row] = j < kept[p] && s < roff[p + 1] ? lam[s] : d[row];
+}
+
 // ---------------------------------------------------------------------------------------
 int deflate_segments(int nprob, int max_n) {
     const int seg = defl_seg(nprob, max_n);
@@ -626,6 +652,22 @@ hipError_t launch_deflate_expand(const int64_t *off, int nprob, int64_t total, i
         SDC_LAUNCH(KID_DEFL_ROTATE, k_defl_rotate, g, dim3(256), 0, s, a, 1, total, cpt);
         SDC_LAUNCH(KID_DEFL_PLACE, k_defl_place, g, dim3(256), 0, s, a, 1, total, cpt);
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_step_reduced(const int64_t *off, const int64_t *roff, int nprob,
+                               const int32_t *kept, const double *d, const double *z, double *dr,
+                               double *zr, int64_t rtotal, hipStream_t s) {
+    SDC_LAUNCH(KID_COPY_ROWS, k_step_reduced, row_grid(rtotal, 1, 1), dim3(256), 0, s, off, roff, nprob,
+               kept, d, z, dr, zr, rtotal);
+    return hipGetLastError();
+}
+
+hipError_t launch_step_values(const int64_t *off, const int64_t *roff, int nprob,
+                              const int32_t *kept, const double *d, const double *lam, double *E,
+                              int64_t total, hipStream_t s) {
+    SDC_LAUNCH(KID_COPY_ROWS, k_step_values, row_grid(total, 1, 1), dim3(256), 0, s, off, roff, nprob,
+               kept, d, lam, E, total);
     return hipGetLastError();
 }
 

@@ -814,8 +814,10 @@ __global__ __launch_bounds__(1024) void k_sort_runs(const double *kin, double *k
             const int ps = i & ~(2 * w - 1);
             const int mid = min(ps + w, len), end = min(ps + 2 * w, len);
             const double v = key[b][i];
-            const int pos = i < mid ? i + count_less(key[b] + mid, end - mid, v)
-                                    : i - mid + ps + count_leq(key[b] + ps, mid - ps, v);
+            int pos = i;
+            if (mid < end && key[b][mid] < key[b][mid - 1])  // else the pair is in order
+                pos = i < mid ? i + count_less(key[b] + mid, end - mid, v)
+                              : i - mid + ps + count_leq(key[b] + ps, mid - ps, v);
             key[b ^ 1][pos] = v;
             idx[b ^ 1][pos] = idx[b][i];
         }
@@ -844,7 +846,8 @@ __global__ __launch_bounds__(256) void k_sort_pass(const double *kin, const int3
     const double v = kin[e];
     const int32_t idx = vin[e];
     int pos;
-    if (i < mid) pos = (i - ps) + count_less(kin + base + mid, end - mid, v);
+    if (mid >= end || !(kin[base + mid] < kin[base + mid - 1])) pos = i - ps;  // in order as they are
+    else if (i < mid) pos = (i - ps) + count_less(kin + base + mid, end - mid, v);
     else pos = (i - mid) + count_leq(kin + base + ps, mid - ps, v);
     kout[base + ps + pos] = v;
     vout[base + ps + pos] = idx;

@@ -185,12 +185,10 @@ int defl_step(superdc_ctx *ctx, superdc_hss *h, int l, int t, int cur, int ncol,
         if (rc) return rc;
     }
     const int64_t rt = roff[nprob];
-    const double zero = 0.0, one = 1.0;
+    const double zero = 0.0;
     double *dr = h->dr + k;
-    if ((e = launch_copy_rows(b->off_d, rb->off_d, nprob, rt, 1, kept, h->xd, n, dr, rt, &zero,
-                              s)) != hipSuccess ||
-        (e = launch_copy_rows(b->off_d, rb->off_d, nprob, rt, 1, kept, h->xz, n, h->xzr, rt, &one,
-                              s)) != hipSuccess ||
+    if ((e = launch_step_reduced(b->off_d, rb->off_d, nprob, kept, h->xd, h->xz, dr, h->xzr, rt,
+                                 s)) != hipSuccess ||
         (e = mark(h, 1, s)) != hipSuccess)
         return fail(e);
     rc = superdc_secular_solve(ctx, rb, dr, h->xzr, h->ones, h->xlam, h->eta + k, h->org + k,
@@ -205,10 +203,8 @@ int defl_step(superdc_ctx *ctx, superdc_hss *h, int l, int t, int cur, int ncol,
     if (rc) return rc;
     if ((e = mark(h, 3, s)) != hipSuccess) return fail(e);
     // the step's eigenvalues per node: reduced roots first, deflated values after, sorted
-    if ((e = hipMemcpyAsync(h->xE, h->xd, sizeof(double) * n, hipMemcpyDeviceToDevice, s)) !=
+    if ((e = launch_step_values(b->off_d, rb->off_d, nprob, kept, h->xd, h->xlam, h->xE, n, s)) !=
             hipSuccess ||
-        (e = launch_copy_rows(rb->off_d, b->off_d, nprob, n, 1, kept, h->xlam, rt, h->xE, n,
-                              nullptr, s)) != hipSuccess ||
         (e = launch_seg_sort(h->xE, nl, n, h->lam + k, h->dS + k, h->xk, h->xv, s)) != hipSuccess)
         return fail(e);
     if (m > 0) {

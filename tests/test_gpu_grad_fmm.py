@@ -59,8 +59,8 @@ def test_fmm_adjoint(sizes, leaf, proj):
                 assert np.abs(g[a:e] - w[a:e]).max() <= 1e-9 * np.abs(w[a:e]).max(), p
 
 
-@pytest.mark.parametrize("sizes,direct", [([2048] * 4, True), ([1024] * 19, True),
-                                          ([1024] * 20, False), ([2049], False)])
+@pytest.mark.parametrize("sizes,direct", [([4096] * 4, True), ([1024] * 66, True),
+                                          ([1024] * 67, False), ([4097], False)])
 def test_small_batches_directly(sizes, direct):
     batch = regular(sizes, 98)
     auto = gradients(batch, True)
