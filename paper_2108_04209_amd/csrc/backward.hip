@@ -178,7 +178,7 @@ __global__ __launch_bounds__(1024) void k_bwd(BwdArgs a) {
 // gamma) the poles' six.  One lane per target, S wavefronts per item of 64 targets; the far
 // field of the boxes away from the targets' interval goes through its nodes (fmm_far.h).
 // Bound by the FP64 pipe, as the direct sums: 1024 problems of 256 to 4096 roots with
-// projections took those 7.7 ms at 93 % of it; here 1.2 ms, 0.5 ms for the weights of the boxes
+// projections took those 7.7 ms at 93 % of it; here 1.0 ms, 0.3 ms for the weights of the boxes
 // and 0.3 ms for the problems below the crossover.
 // ---------------------------------------------------------------------------------------
 template <bool PROJ, int PASS>
@@ -290,17 +290,42 @@ __device__ void bwd_fmm_item(const BwdArgs &a, const FmmArgs &f, const FmmVec &v
             }
             for (; i < hi; ++i) pole(i, rcp_nr((d[i] - x0) - x1));
         } else {
-#pragma unroll 2
-            for (int k = lo; k < hi; ++k) {
-                const double4 q = rk[k];
+            // four roots to a set of scalar loads, the next set's in flight
+            struct Set {
+                double4 q[4];
+                double g[4];
+            };
+            auto load = [&](Set &s, int k) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    s.q[u] = rk[k + u];
+                    s.g[u] = PROJ ? gk[k + u] : 0.0;
+                }
+            };
+            auto root = [&](const double4 &q, double g) {
                 double w[NW];
                 w[0] = q.z;
                 if constexpr (PROJ) {
                     w[1] = q.w;
-                    w[2] = gk[k];
+                    w[2] = g;
                 }
                 Far::add(rcp_nr((x0 - q.x) - q.y), w, acc);
+            };
+            int k = lo;
+            if (k + 8 <= hi) {
+                Set s0, s1;
+                load(s0, k);
+                do {
+                    load(s1, k + 4);
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) root(s0.q[u], s0.g[u]);
+                    load(s0, min(k + 8, hi - 4));  // past the last turn: in the range, not used
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) root(s1.q[u], s1.g[u]);
+                    k += 8;
+                } while (k + 8 <= hi);
             }
+            for (; k < hi; ++k) root(rk[k], PROJ ? gk[k] : 0.0);
         }
     };
     if (nn < 0) {  // lists overflowed: every source directly, split over the wavefronts

