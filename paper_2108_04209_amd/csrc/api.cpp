@@ -680,6 +680,10 @@ int loewner_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const
     a.zhat = zhat;
     a.bnorm = bnorm;
     superdc_batch *bm = const_cast<superdc_batch *>(b);
+    if (fmm_b && o.persistent && b->max_n <= VS_N && b->max_n < fmm_crossover_of(b, o)) {
+        SDC_HIP(launch_vectors_small(a, b->nprob, b->max_n, s));
+        return SUPERDC_OK;
+    }
     const TileList *L = tile_list(bm, TILE);
     if (!L) return SUPERDC_ENOMEM;
     // large problems: zhat and b through the FMM (far boxes by moment expansions of the

@@ -318,6 +318,9 @@ struct VecArgs {
     double *zhat, *bnorm;
 };
 // pack = false: the (d_K, eta) pairs were packed already (launch_pack_ke)
+// zhat and b at once, batches of problems of at most VS_N poles
+constexpr int VS_N = 192;
+hipError_t launch_vectors_small(const VecArgs &a, int nprob, int max_n, hipStream_t s);
 hipError_t launch_loewner(const VecArgs &a, int split, hipStream_t s,
                           bool pack = true);
 hipError_t launch_pack_ke(const VecArgs &a, hipStream_t s);

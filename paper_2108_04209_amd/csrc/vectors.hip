@@ -392,6 +392,117 @@ __device__ void bnorm_tile(const VecArgs &a, Tile t, double4 *red) {
     if (active && wv == 0) a.bnorm[base + j] = 1.0 / sqrt(sum);
 }
 
+// zhat and b of a whole problem of at most VS_N poles in one workgroup, for batches of such
+// problems: the packed roots, the poles and zhat stay in LDS.  Four wavefronts (eight beyond
+// 128 poles), in as many shares of the factors (terms) as there are wavefronts to a tile of 64
+// poles (roots).  The three launches it replaces took longer to issue than to run: one problem
+// of 100 poles 16.7 -> 12.7 us a call, 512 of 128 19.4 -> 12.1, 4096 of 128 95 -> 56; at 256
+// poles a single problem is slower this way (16 -> 18), so the line is below.
+constexpr int VS_W = 8;  // wavefronts, at most
+__global__ __launch_bounds__(WAVE * VS_W) void k_vectors_small(VecArgs a) {
+    __shared__ double2 ke[VS_N];
+    __shared__ double dd[VS_N], zh[VS_N];
+    __shared__ double3 red[VS_W][WAVE];
+    const int p = blockIdx.x, tid = threadIdx.x, lane = lane_id();
+    const int64_t base = a.off[p];
+    const int n = (int)(a.off[p + 1] - base);
+    if (a.status[p] & ~SUPERDC_ST_NOCONV) {
+        for (int j = tid; j < n; j += blockDim.x) a.zhat[base + j] = a.bnorm[base + j] = __builtin_nan("");
+        return;
+    }
+    for (int j = tid; j < n; j += blockDim.x) {
+        dd[j] = a.d[base + j];
+        ke[j] = make_double2(a.d[base + clamp_idx(a.origin[base + j], n)], a.eta[base + j]);
+    }
+    __syncthreads();
+    const int tiles = (n + WAVE - 1) / WAVE, S = (int)(blockDim.x / WAVE) / tiles;
+    const int wv = wave_uniform(tid / WAVE), tile = wv / S, sh = wv % S;
+    const int i = tile * WAVE + lane, ii = min(i, n - 1);
+    const int j0 = n * sh / S, j1 = tile < tiles ? n * (sh + 1) / S : 0;
+    // Loewner products (as loewner_tile; a problem in range has es = 0 and sg = 1, exact)
+    const double2 kl = ke[n - 1];
+    const int ex = __builtin_amdgcn_frexp_exp((kl.x - dd[0]) + kl.y);
+    const int es = wave_uniform(ex < -32 || ex > 32 ? ex : 0);
+    const double sg = __builtin_ldexp(1.0, -es);
+    const double di = dd[ii];
+    double na = 1.0, da = 1.0, nb = 1.0, db = 1.0;
+    int E = 0, j = j0;
+    auto factor = [&](int u, double &nu, double &de) {
+        const double2 k = ke[u];
+        nu *= ((k.x - di) + k.y) * sg;
+        de *= u == ii ? 1.0 : (dd[u] - di) * sg;
+    };
+    for (; j + 16 <= j1; j += 16) {
+#pragma unroll
+        for (int u = 0; u < 16; u += 2) {
+            factor(j + u, na, da);
+            factor(j + u + 1, nb, db);
+        }
+        renorm(na, da, E);
+        renorm(nb, db, E);
+    }
+    for (; j + 2 <= j1; j += 2) {  // at most 7 factors more per chain
+        factor(j, na, da);
+        factor(j + 1, nb, db);
+    }
+    if (j < j1) factor(j, na, da);
+    renorm(na, da, E);
+    renorm(nb, db, E);
+    double num = na * nb, den = da * db;
+    renorm(num, den, E);
+    if (S > 1) {
+        red[wv][lane] = make_double3(num, den, (double)E);
+        __syncthreads();
+        if (sh == 0)
+            for (int w = 1; w < S; ++w) {
+                const double3 v = red[wv + w][lane];
+                num *= v.x;
+                den *= v.y;
+                E += (int)v.z;
+                renorm(num, den, E);
+            }
+    }
+    if (sh == 0 && i < n) {
+        const double R = ldexp(num / den, E + es);
+        const double v = copysign(sqrt(R / a.rho[p]), a.z[base + i]);
+        a.zhat[base + i] = v;
+        zh[i] = v;
+    }
+    __syncthreads();
+    // b_i = (sum_j zhat_j^2 / (d_j - lambda_i)^2)^(-1/2) (as bnorm_tile)
+    const double2 kv = ke[ii];
+    double s0 = 0.0, s1 = 0.0;
+    j = j0;
+    const double tmax = fmax(fabs((dd[0] - kv.x) - kv.y), fabs((dd[n - 1] - kv.x) - kv.y));
+    if (__ballot(!(fabs(kv.y) >= 0x1p-300 && tmax <= 0x1p300)) == 0ull) {
+#pragma unroll 4
+        for (; j + 2 <= j1; j += 2) {
+            const double t0 = (dd[j] - kv.x) - kv.y, t1 = (dd[j + 1] - kv.x) - kv.y;
+            const double R = rcp_nr(t0 * t1);
+            const double u0 = zh[j] * t1, u1 = zh[j + 1] * t0;
+            s0 = __builtin_fma(__builtin_fma(u0, u0, u1 * u1) * R, R, s0);
+        }
+    }
+    for (; j < j1; ++j) {
+        const double q = zh[j] * rcp_nr((dd[j] - kv.x) - kv.y);
+        s1 = __builtin_fma(q, q, s1);
+    }
+    double sum = s0 + s1;
+    if (S > 1) {
+        red[wv][lane] = make_double3(sum, 0.0, 0.0);
+        __syncthreads();
+        if (sh == 0)
+            for (int w = 1; w < S; ++w) sum += red[wv + w][lane].x;
+    }
+    if (sh == 0 && i < n) a.bnorm[base + i] = 1.0 / sqrt(sum);
+}
+
+hipError_t launch_vectors_small(const VecArgs &a, int nprob, int max_n, hipStream_t s) {
+    if (max_n > VS_N) return hipErrorInvalidValue;
+    SDC_LAUNCH(KID_LOEWNER, k_vectors_small, dim3(nprob), dim3(WAVE * (max_n <= 128 ? 4 : VS_W)), 0, s, a);
+    return hipGetLastError();
+}
+
 // blockDim.x = 64 S; dynamic LDS: one double4 per thread when S > 1
 __global__ __launch_bounds__(1024) void k_loewner(VecArgs a) {
     extern __shared__ double4 red4[];

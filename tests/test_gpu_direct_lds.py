@@ -108,3 +108,29 @@ def test_fmm_solver_in_lds(kind, n, leaf):
         span = batch.d[e - 1] - batch.d[s] + batch.rho[p] * np.sum(batch.z[s:e] ** 2)
         tol = 4.0 * native.default_opts().stop_c * (e - s) * 2.0 ** -52 * span
         assert np.max(np.abs(fmm["lam"][s:e] - direct["lam"][s:e])) <= tol
+
+
+@pytest.mark.parametrize("sizes", [[1], [2, 1, 63, 64, 65], [128, 127, 17], [192, 129, 191, 15], [192] * 5])
+@pytest.mark.parametrize("scale", [1.0, 1e-200, 1e150])
+def test_small_vectors_in_one_launch(sizes, scale):
+    """zhat and b of batches of at most 192 poles (one launch) against the separate kernels
+    (persistent = 0) on the same roots: products of up to 192 factors and sums of as many
+    positive terms in another order, 4 n eps relative.  A refused problem stays NaN."""
+    from paper_2108_04209_amd import native
+    from tests import gpu_pipeline as gp
+    batch = gen.small_batch(sizes, seed=107)
+    batch.d *= scale
+    batch.rho *= scale
+    if len(sizes) > 2:
+        batch.rho[1] = -1.0
+    ctx = gp.context()
+    b = native.Batch(ctx, batch.off)
+    d, z, rho = gp.to_dev(batch.d), gp.to_dev(batch.z), gp.to_dev(batch.rho)
+    s = native.secular_solve(ctx, b, d, z, rho)
+    res = [[x.cpu().numpy() for x in native.loewner(ctx, b, d, z, rho, s["eta"], s["origin"], s["status"],
+                                                    opts=native.default_opts(persistent=p))]
+           for p in (1, 0)]
+    for got, want in zip(*res):
+        assert np.array_equal(np.isnan(got), np.isnan(want))
+        ok = ~np.isnan(want)
+        assert np.all(np.abs(got[ok] - want[ok]) <= 4 * 192 * 2.0 ** -52 * np.abs(want[ok]))
