@@ -197,13 +197,16 @@ __global__ __launch_bounds__(EQ ? 2 * WAVE : WAVE) void k_fmm_lists(FmmArgs f) {
     int32_t *far_r = f.far_r + (int64_t)L * FMM_FAR_MAX;
     int32_t *near_lo = f.near_lo + (int64_t)L * FMM_NEAR_MAX;
     int32_t *near_hi = f.near_hi + (int64_t)L * FMM_NEAR_MAX;
-    int hidx = 0, ncand = 1;  // the root
+    // from level 2 on: the root and its children are as wide as half the spectrum, so far from a
+    // target only where clusters leave gaps wider than that (their two or four parts then are)
+    const int h0 = min(2, H);
+    int hidx = (1 << h0) - 1 + lane, ncand = 1 << h0;
     int nn = 0, nl = 0, nr = 0, ndl = 0, ndr = 0, nel = 0, ner = 0;
     bool overflow = false;
-    for (int h = 0; h <= H && ncand > 0 && !overflow; ++h) {
+    for (int h = h0; h <= H && ncand > 0 && !overflow; ++h) {
         const bool valid = lane < ncand;
-        const int g = f.box_off[q] + hidx;
-        const int i = hidx - ((1 << h) - 1);
+        const int g = f.box_off[q] + (valid ? hidx : 0);
+        const int i = (valid ? hidx : (1 << h) - 1) - ((1 << h) - 1);
         const int64_t span = (int64_t)f.leaf << (H - h);
         const int lo = (int)min((int64_t)n, i * span), hi = (int)min((int64_t)n, (i + 1) * span);
         const bool live = valid && lo < hi;  // empty boxes are dropped
@@ -321,11 +324,11 @@ __global__ __launch_bounds__(EQ ? 2 * WAVE : WAVE) void k_fmm_lists(FmmArgs f) {
 // nodes of the target interval [xa, xb] (which holds every iterate of the leaf's roots) and
 // turned into Chebyshev coefficients, so that the solver evaluates four short series per
 // root and iteration instead of the sources one by one.  Every source is at least sep_loc
-// interval widths from the interval.  Thread (node m, part u) sums the boxes e = u (mod
-// LOC_PARTS), two sources per reciprocal (all on one side of the node), and every
-// LOC_PARTS-th pole of the flagged ranges; the parts are added in order.
+// interval widths from the interval.  The sources go through LDS; thread (node m, part u) sums
+// every LOC_PARTS-th pair of them, and the parts are added in order.
 // cos(j pi / 2 FMM_PL), j = 0 .. 4 FMM_PL - 1: T_k at node m is entry k (2m + 1) mod 4 FMM_PL (the
-// cosines were a tenth of the launch: a level of 4096 problems 840 -> 750 us)
+// cosines were a tenth of the launch: a level of 4096 problems 840 -> 750 us, with the sources
+// through LDS in pairs instead of boxes read by every thread 625)
 __constant__ double LOC_COS[4 * FMM_PL] = {
     1.0, 0.996917333733128, 0.9876883405951378, 0.9723699203976766,
     0.9510565162951535, 0.9238795325112867, 0.8910065241883679, 0.8526401643540922,
@@ -349,10 +352,15 @@ __constant__ double LOC_COS[4 * FMM_PL] = {
     0.9510565162951535, 0.9723699203976766, 0.9876883405951378, 0.996917333733128
 };
 constexpr int LOC_PARTS = 16;
+constexpr int LOC_ROUND = 768;  // sources staged at a time (most leaves list fewer)
+static_assert(LOC_ROUND % 2 == 0, "pairs do not cross rounds");
 __global__ __launch_bounds__(FMM_PL * LOC_PARTS) void k_fmm_local(FmmArgs f) {
     __shared__ double part[LOC_PARTS][4][FMM_PL];  // [part][function][node]
     __shared__ double val[4][FMM_PL];              // [function][node]
     __shared__ double Tkm[FMM_PL][FMM_PL];         // T_k(t_m) = cos(k (2m + 1) pi / 2P)
+    __shared__ double2 src[LOC_ROUND];             // a round's sources
+    __shared__ int4 rng[FMM_NEAR_MAX];  // flagged near ranges: first pole, poles, place, left
+    __shared__ int box[2 * FMM_FAR_MAX], cntl, cntr;
     const int L = blockIdx.x;
     const int tid = threadIdx.x;
     for (int e = tid; e < FMM_PL * FMM_PL; e += blockDim.x)
@@ -369,55 +377,80 @@ __global__ __launch_bounds__(FMM_PL * LOC_PARTS) void k_fmm_local(FmmArgs f) {
     const double tm = LOC_COS[2 * m + 1];
     const double x = cw.x + cw.y * tm;
     double ps = 0.0, dps = 0.0, ph = 0.0, dph = 0.0;
-    for (int e = u; e < nel + ner; e += LOC_PARTS) {
-        const bool left = e < nel;
-        const int k = left ? e : e - nel;
-        const int g = (left ? f.far_ld : f.far_rd)[(int64_t)L * FMM_FAR_MAX + FMM_FAR_MAX - 1 - k];
-        const double2 *eq = f.eq + (int64_t)g * FMM_P;
-        double s0 = 0.0, s1 = 0.0;
-#pragma unroll 2
-        for (int r = 0; r < FMM_P; r += 2) {
-            // w0/t0 + w1/t1 = (w0 t1 + w1 t0)/(t0 t1), and the squares likewise
-            const double2 a = eq[r], b = eq[r + 1];
+    // the sources left of the leaf (far boxes' equivalent sources, then flagged poles) and those
+    // right of it, each side padded to an even number; ranges by the first wavefront
+    const int64_t base = f.off[p];
+    const double2 *dw = f.dw + base;
+    if (tid < WAVE) {
+        const int i0 = (L - f.leaf_off[q]) * f.leaf;
+        int lo = 0, len = 0;
+        bool left = false;
+        if (tid < nn && f.near_lf[(int64_t)L * FMM_NEAR_MAX + tid]) {
+            lo = f.near_lo[(int64_t)L * FMM_NEAR_MAX + tid];
+            const int hi = f.near_hi[(int64_t)L * FMM_NEAR_MAX + tid];
+            len = hi - lo;
+            left = hi <= i0;
+        }
+        int el = left ? len : 0, er = left ? 0 : len;
+        static_assert(FMM_NEAR_MAX <= 32, "the scan below covers 32 lanes");
+        for (int o = 1; o < 32; o <<= 1) {
+            const int vl = __shfl_up(el, o), vr = __shfl_up(er, o);
+            if (tid >= o) {
+                el += vl;
+                er += vr;
+            }
+        }
+        if (tid < nn) rng[tid] = make_int4(lo, len, (left ? el : er) - len, left);
+        if (tid == FMM_NEAR_MAX - 1) {
+            cntl = el;
+            cntr = er;
+        }
+    }
+    for (int e = tid; e < nel + ner; e += blockDim.x)
+        box[e] = e < nel ? f.far_ld[(int64_t)L * FMM_FAR_MAX + FMM_FAR_MAX - 1 - e]
+                         : f.far_rd[(int64_t)L * FMM_FAR_MAX + FMM_FAR_MAX - 1 - (e - nel)];
+    __syncthreads();
+    const int nleft = nel * FMM_P + cntl, nright = ner * FMM_P + cntr;
+    const int pl = (nleft + 1) & ~1, total = pl + ((nright + 1) & ~1);
+    for (int c0 = 0; c0 < total; c0 += LOC_ROUND) {
+        const int cnt = min(LOC_ROUND, total - c0);
+        if (c0) __syncthreads();  // the round before has been read
+        for (int e = tid; e < cnt; e += blockDim.x) {
+            const bool left = c0 + e < pl;
+            int s = left ? c0 + e : c0 + e - pl;
+            const int have = left ? nleft : nright, nbox = (left ? nel : ner) * FMM_P;
+            const bool pad = s >= have;  // the last source again, without weight
+            s -= pad;
+            double2 v;
+            if (s < nbox) {
+                v = f.eq[(int64_t)box[(left ? 0 : nel) + s / FMM_P] * FMM_P + s % FMM_P];
+            } else {
+                s -= nbox;
+                int r = 0;  // the range of this side that holds it
+                while (rng[r].w != (int)left || s < rng[r].z || s >= rng[r].z + rng[r].y) ++r;
+                v = dw[rng[r].x + s - rng[r].z];
+            }
+            src[e] = make_double2(v.x, pad ? 0.0 : v.y);
+        }
+        __syncthreads();
+        // two sources with one reciprocal: w0/t0 + w1/t1 = (w0 t1 + w1 t0)/(t0 t1), and the squares
+        // likewise
+        for (int e = 2 * u; e < cnt; e += 2 * LOC_PARTS) {
+            const double2 a = src[e], b = src[e + 1];
             const double t0 = a.x - x, t1 = b.x - x;
             const double pr = fabs(t0 * t1);
+            double s0, s1;
             if (pr > 0x1p-900 && pr < 0x1p900) {
                 const double R = rcp_nr(t0 * t1);
                 const double u0 = a.y * t1, u1 = b.y * t0;
-                s0 = __builtin_fma(u0 + u1, R, s0);
-                s1 = __builtin_fma(__builtin_fma(u0, t1, u1 * t0) * R, R, s1);
+                s0 = (u0 + u1) * R;
+                s1 = __builtin_fma(u0, t1, u1 * t0) * R * R;
             } else {  // the product would leave the exponent range: one source at a time
                 const double r0 = rcp_nr(t0), r1 = rcp_nr(t1);
-                s0 += a.y * r0 + b.y * r1;
-                s1 += a.y * r0 * r0 + b.y * r1 * r1;
+                s0 = a.y * r0 + b.y * r1;
+                s1 = a.y * r0 * r0 + b.y * r1 * r1;
             }
-        }
-        if (left) {
-            ps += s0;
-            dps += s1;
-        } else {
-            ph += s0;
-            dph += s1;
-        }
-    }
-    // flagged near ranges: their poles, left of the leaf into psi, right of it into phi
-    {
-        const int64_t base = f.off[p];
-        const int i0 = (L - f.leaf_off[q]) * f.leaf;
-        const double2 *dw = f.dw + base;
-        for (int e = 0; e < nn; ++e) {
-            if (!f.near_lf[(int64_t)L * FMM_NEAR_MAX + e]) continue;
-            const int lo = f.near_lo[(int64_t)L * FMM_NEAR_MAX + e];
-            const int hi = f.near_hi[(int64_t)L * FMM_NEAR_MAX + e];
-            double s0 = 0.0, s1 = 0.0;
-            for (int j = lo + u; j < hi; j += LOC_PARTS) {
-                const double2 pw = dw[j];
-                const double r = rcp_nr(pw.x - x);
-                const double wr = pw.y * r;
-                s0 += wr;
-                s1 = __builtin_fma(wr, r, s1);
-            }
-            if (hi <= i0) {
+            if (c0 + e < pl) {
                 ps += s0;
                 dps += s1;
             } else {
