@@ -573,8 +573,9 @@ int superdc_hss_apply(superdc_ctx *ctx, superdc_hss *h, int trans, int32_t m, co
         }
     }
     // one step of a deflated pass (see defl_step): trans 1 applies S (Qhat^T (+) I) P^T G
-    // to T0, trans 0 G^T P (Qhat (+) I) S^T; the result is left in T0
-    auto defl_apply = [&](int l, int t, int tr) -> int {
+    // to A, trans 0 G^T P (Qhat (+) I) S^T; the result goes to C (which may be A)
+    auto defl_apply = [&](int l, int t, int tr, const double *A, int64_t lda, double *C,
+                          int64_t ldc) -> int {
         superdc_batch *b = h->batch[l], *rb = h->rb[(size_t)l * r + t];
         const int nprob = b->nprob, nl = (int)(n >> l);
         const int64_t rt = rb->total;
@@ -585,10 +586,10 @@ int superdc_hss_apply(superdc_ctx *ctx, superdc_hss *h, int trans, int32_t m, co
         hipError_t ee;
         if (tr == 1) {
             if ((ee = launch_deflate_expand(b->off_d, nprob, n, m, h->dperm + k, h->drr + k,
-                                            h->drl + k, h->dc + k, h->ds + k, 1, T0, n, T1, n, Tx,
+                                            h->drl + k, h->dc + k, h->ds + k, 1, A, lda, T1, n, Tx,
                                             s)) != hipSuccess)
                 return fail(ee);
-        } else if ((ee = launch_permute(h->dS + k, nl, n, m, T0, n, T1, n, 1, s)) != hipSuccess) {
+        } else if ((ee = launch_permute(h->dS + k, nl, n, m, A, lda, T1, n, 1, s)) != hipSuccess) {
             return fail(ee);
         }
         if ((ee = launch_copy_rows(b->off_d, rb->off_d, nprob, rt, m, kept, T1, n, R0, rt, &zero,
@@ -600,10 +601,10 @@ int superdc_hss_apply(superdc_ctx *ctx, superdc_hss *h, int trans, int32_t m, co
         if ((ee = launch_copy_rows(rb->off_d, b->off_d, nprob, n, m, kept, R1, rt, T1, n, nullptr,
                                    s)) != hipSuccess)
             return fail(ee);
-        if (tr == 1) ee = launch_permute(h->dS + k, nl, n, m, T1, n, T0, n, 0, s);
+        if (tr == 1) ee = launch_permute(h->dS + k, nl, n, m, T1, n, C, ldc, 0, s);
         else
             ee = launch_deflate_expand(b->off_d, nprob, n, m, h->dperm + k, h->drr + k, h->drl + k,
-                                       h->dc + k, h->ds + k, 0, T1, n, T0, n, Tx, s);
+                                       h->dc + k, h->ds + k, 0, T1, n, C, ldc, Tx, s);
         return ee == hipSuccess ? SUPERDC_OK : fail(ee);
     };
     if (trans == 1) {
@@ -617,43 +618,39 @@ int superdc_hss_apply(superdc_ctx *ctx, superdc_hss *h, int trans, int32_t m, co
                 return fail(e);
             std::swap(T0, T1);
             for (int t = 0; t < r; ++t) {
+                const bool last = l == 0 && t == r - 1;  // straight into Y
+                double *C = last ? Y : h->defl ? T0 : T1;
+                const int64_t ldc = last ? ldy : n;
                 if (h->defl) {
-                    int rc = defl_apply(l, t, 1);
+                    int rc = defl_apply(l, t, 1, T0, n, C, ldc);
                     if (rc) return rc;
                     continue;
                 }
                 int rc = superdc_cauchy_apply(ctx, h->batch[l], h->poles(l, t),
                                               h->zhat + h->idx(l, t), h->bn + h->idx(l, t),
                                               h->eta + h->idx(l, t), h->org + h->idx(l, t),
-                                              h->st(l, t), 1, m, T0, n, T1, n, &o, stream);
+                                              h->st(l, t), 1, m, T0, n, C, ldc, &o, stream);
                 if (rc) return rc;
                 std::swap(T0, T1);
             }
         }
-        for (int c = 0; c < m; ++c) {
-            e = hipMemcpyAsync(Y + c * ldy, T0 + c * n, sizeof(double) * n,
-                               hipMemcpyDeviceToDevice, s);
-            if (e != hipSuccess) return fail(e);
-        }
     } else {
         // Q X: per level Qhat_r .. Qhat_1 then P^T, from the root down; leaves last
-        for (int c = 0; c < m; ++c) {
-            e = hipMemcpyAsync(T0 + c * n, X + c * ldx, sizeof(double) * n,
-                               hipMemcpyDeviceToDevice, s);
-            if (e != hipSuccess) return fail(e);
-        }
         for (int l = 0; l < D; ++l) {
             const int nl = (int)(n >> l);
             for (int t = r - 1; t >= 0; --t) {
+                const bool first = l == 0 && t == r - 1;  // straight from X
+                const double *A = first ? X : T0;
+                const int64_t lda = first ? ldx : n;
                 if (h->defl) {
-                    int rc = defl_apply(l, t, 0);
+                    int rc = defl_apply(l, t, 0, A, lda, T0, n);
                     if (rc) return rc;
                     continue;
                 }
                 int rc = superdc_cauchy_apply(ctx, h->batch[l], h->poles(l, t),
                                               h->zhat + h->idx(l, t), h->bn + h->idx(l, t),
                                               h->eta + h->idx(l, t), h->org + h->idx(l, t),
-                                              h->st(l, t), 0, m, T0, n, T1, n, &o, stream);
+                                              h->st(l, t), 0, m, A, lda, T1, n, &o, stream);
                 if (rc) return rc;
                 std::swap(T0, T1);
             }
