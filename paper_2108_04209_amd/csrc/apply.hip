@@ -88,7 +88,8 @@ __device__ __forceinline__ void apply_store(int n, int s0, int ncols, int tid,
 // NCT: 16-column blocks per pass (the pass width is 16 NCT columns); this item's pass starts
 // at column c0.  FB: form b beside the columns.  TEAMS teams of four wavefronts take the
 // reduction's chunks in turn and add their sums in team order, for launches with too few items
-// to fill the chip (the levels of a 1024-row HSS conquer: 6.2 -> 5.3 us a launch on average)
+// to fill the chip, up to two per CU (the levels of a 1024-row HSS conquer: 6.2 -> 5.3 us a
+// launch on average; 8192 rows of 64 columns, 512 items: problems of 128 to 1024, 23 -> 21)
 template <int NCT>
 struct ApplyTeam {
     double Xs[2][16 * NCT * AP_LD];
@@ -334,7 +335,7 @@ hipError_t launch_apply(const ApplyArgs &a0, int use_mfma, int max_n, int num_cu
         auto items = [&] { return a.ntiles * ((a.m + 16 * nct - 1) / (16 * nct)); };
         while (nct > 1 && items() < 2 * num_cu) nct /= 2;
         const dim3 g(items());
-        const bool teams = nct == 1 && items() < 2 * num_cu && max_n > 2 * AP_K;
+        const bool teams = nct == 1 && items() <= 2 * num_cu && max_n > 2 * AP_K;
 #define SDC_APPLY_MFMA(T, C, FB, K)                                                         \
     SDC_LAUNCH(KID_APPLY_MFMA, (k_apply_mfma<T, C, FB, K>), g, dim3(256 * K), 0, s, a)
         if (a.trans) {
