@@ -209,8 +209,8 @@ int superdc_loewner(superdc_ctx *ctx, const superdc_batch *batch, const double *
  * X and Y are total x m column-major with leading dimensions ldx, ldy >= total; they
  * must not overlap.  m >= 1.  With trans = 1, problems that use the FMM (as for the
  * solver) are applied through the eigenvector-side triangular FMM (Sec. 4.3, Alg. 3
- * Z-update) in passes of 16 columns; the others, and every trans = 0 product, use the
- * FP64 MFMA kernel (m >= 4) or the VALU kernel.
+ * Z-update), with trans = 0 through one over the roots; the others use the FP64 MFMA kernel or,
+ * for few columns, the VALU kernel.
  */
 int superdc_cauchy_apply(superdc_ctx *ctx, const superdc_batch *batch, const double *d,
                          const double *zhat, const double *bnorm, const double *eta,
@@ -225,6 +225,8 @@ int superdc_cauchy_apply(superdc_ctx *ctx, const superdc_batch *batch, const dou
  *   in : d, z, rho, eta, origin, status, g_lam[total] = dL/dlambda (may be NULL),
  *        g_proj[total] = dL/dp (may be NULL), u[total] (NULL iff g_proj is NULL)
  *   out: g_d[total] = dL/dd, g_z[total] = dL/dz, g_rho[nprob] = dL/drho.
+ * Large batches take their sums through the FMM (opts->persistent, method and crossover as for
+ * the solver), the others and every problem below the crossover directly.
  */
 int superdc_secular_backward(superdc_ctx *ctx, const superdc_batch *batch, const double *d,
                              const double *z, const double *rho, const double *eta,

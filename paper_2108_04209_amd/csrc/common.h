@@ -258,8 +258,8 @@ int noalloc_init(int device);
 
 namespace sdc {
 // Loewner/b and the Cauchy apply behind superdc_loewner / superdc_cauchy_apply.
-// reuse_lists: the batch's FMM interaction lists were built by a solve on the same poles
-// d (internal callers that know it).  fmm_b = false leaves b to the next apply_run with
+// reuse_lists: the batch's FMM interaction lists and the roots' (d_K, eta) pairs were left by a
+// solve on the same poles d just before (internal callers that know it).  fmm_b = false leaves b to the next apply_run with
 // fuse_b = true (Qhat^T X, 1 <= m < 16 columns, on the MFMA kernels), whose products form
 // b beside the columns (from the same equivalent sources for the FMM problems) and write
 // it to bnorm.

@@ -326,6 +326,7 @@ __global__ __launch_bounds__(EQ ? 2 * WAVE : WAVE) void k_fmm_lists(FmmArgs f) {
 // root and iteration instead of the sources one by one.  Every source is at least sep_loc
 // interval widths from the interval.  The sources go through LDS; thread (node m, part u) sums
 // every LOC_PARTS-th pair of them, and the parts are added in order.
+
 // cos(j pi / 2 FMM_PL), j = 0 .. 4 FMM_PL - 1: T_k at node m is entry k (2m + 1) mod 4 FMM_PL (the
 // cosines were a tenth of the launch: a level of 4096 problems 840 -> 750 us, with the sources
 // through LDS in pairs instead of boxes read by every thread 625)
