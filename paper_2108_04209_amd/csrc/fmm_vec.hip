@@ -525,6 +525,13 @@ __global__ __launch_bounds__(512) void k_fmmv_eval(SolveArgs it, FmmArgs f, FmmV
 // sums in team order (n = 1024, 16 items: 23 -> 12 us).
 // ---------------------------------------------------------------------------------------
 constexpr int FV_K = 64;            // sources per chunk
+// Two blocks of 16 columns an item (one generates the Cauchy entries and builds the lists of both)
+// from so many items per CU on.  Measured, one -> two blocks, us a launch, Q^T X: 64 columns of
+// 65536 roots (8 a CU) 142 -> 126 (four blocks: 133, two workgroups a CU by LDS), of 16384 (2 a CU)
+// 40.0 -> 38.5, 32 columns of 16384 (1 a CU) 27.3 -> 29.3.  With three blocks a quarter of the
+// matrix work is padding: 48 columns, 2 a CU 32 -> 37.5, 8 a CU 110 -> 125, 64 a CU 685 -> 609.
+constexpr int FV_WIDE_PER_CU = 2;
+constexpr int FV_WIDE3_PER_CU = 32;
 constexpr int FV_LD = FV_K + 4;     // LDS row: the 16 columns x 4 sources of a step fall on
                                     // different banks
 
@@ -543,17 +550,18 @@ static_assert(FMM_NEAR_MAX <= WAVE, "a lane per near range");
 // store.  Near sources: thread t holds source t % 64 in columns t / 64 + 4 i (a wavefront
 // reads 64 consecutive entries of a column of X) and its scale; far sources: source t / 16 of
 // box i in column t % 16 (their weights are source-major: 16 threads read a source's row).
+template <int NC>
 struct FvStage {
     double2 sd;    // (first wavefront) source position and, with b formed beside the columns,
                    // zhat (near) or the weight of zhat^2 (far); TRANS 0: (d_K, eta) (near) or
                    // (node, 0) (far)
-    double w[4];
+    double w[4 * NC];
     double sc;
 };
 
-template <int TRANS, bool FB>
-__device__ __forceinline__ void fv_fetch(const FmmVec &v, int64_t base, const int *fbox,
-                                         int4 ch, int tid, int g0, int mg, int mx, FvStage &st) {
+template <int TRANS, bool FB, int NC>
+__device__ __forceinline__ void fv_fetch(const FmmVec &v, int64_t base, const int *fbox, int4 ch,
+                                         int tid, int g0, int mg, int mx, FvStage<NC> &st) {
     const int m = v.m;
     const bool first = wave_uniform(tid / WAVE) == 0;
     if (ch.x == 0) {
@@ -561,7 +569,7 @@ __device__ __forceinline__ void fv_fetch(const FmmVec &v, int64_t base, const in
         const double *xs = v.X + j + (int64_t)g0 * v.ldx;
         st.sc = v.scale[j];
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < 4 * NC; ++i)
             st.w[i] = xs[(int64_t)min(tid / FV_K + 4 * i, mx - 1) * v.ldx];
         if (first) {
             if (TRANS == 0) st.sd = v.ke[j];
@@ -569,11 +577,13 @@ __device__ __forceinline__ void fv_fetch(const FmmVec &v, int64_t base, const in
         }
     } else {
         // far chunk: box i of the chunk holds its FMM_P = 16 sources r16
-        const int c = min(tid & 15, mg - 1), r16 = tid >> 4;
+        const int r16 = tid >> 4;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int64_t sq = (int64_t)fbox[ch.y + min(i, ch.z - 1)] * FMM_P + r16;
-            st.w[i] = v.vw[sq * m + g0 + c];
+#pragma unroll
+            for (int b = 0; b < NC; ++b)
+                st.w[4 * b + i] = v.vw[sq * m + g0 + min(16 * b + (tid & 15), mg - 1)];
         }
         if (first) {
             const int64_t sq = (int64_t)fbox[ch.y + min(tid / FMM_P, ch.z - 1)] * FMM_P + tid % FMM_P;
@@ -584,44 +594,49 @@ __device__ __forceinline__ void fv_fetch(const FmmVec &v, int64_t base, const in
 
 // Padding (past a partial chunk's sources or the group's columns) is stored as weight zero at
 // the position of one of the chunk's own sources.
-template <bool FB>
-__device__ __forceinline__ void fv_store(int4 ch, int tid, int mg, int mx, const FvStage &st,
+template <bool FB, int NC>
+__device__ __forceinline__ void fv_store(int4 ch, int tid, int mg, int mx, const FvStage<NC> &st,
                                          double *Xs, double2 *Sd) {
     const int cnt = ch.x == 0 ? ch.z : ch.z * FMM_P;
     if (ch.x == 0) {
         const int sl = tid & (FV_K - 1), c0 = tid / FV_K;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
+        for (int i = 0; i < 4 * NC; ++i)
             Xs[(c0 + 4 * i) * FV_LD + sl] =
                 sl < ch.z && c0 + 4 * i < mx ? st.sc * st.w[i] : 0.0;
     } else {
         const int c = tid & 15, r16 = tid >> 4;
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            Xs[c * FV_LD + r16 + 16 * i] = i < ch.z && c < mg ? st.w[i] : 0.0;
+        for (int b = 0; b < NC; ++b)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                Xs[(16 * b + c) * FV_LD + r16 + 16 * i] =
+                    i < ch.z && 16 * b + c < mg ? st.w[4 * b + i] : 0.0;
     }
     if (wave_uniform(tid / WAVE) == 0)
         Sd[tid] = make_double2(st.sd.x, FB && tid >= cnt ? 0.0 : st.sd.y);
 }
 
+template <int NC>
 struct FvTeam {
-    double Xs[2][16 * FV_LD];
+    double Xs[2][16 * NC * FV_LD];
     double2 Sd[2][FV_K];
 };
 
-template <int TEAMS>
+template <int TEAMS, int NC>
 struct FvShared {
-    FvTeam team[TEAMS];
+    FvTeam<NC> team[TEAMS];
     int4 ctab[FV_MAXCH];
     int fbox[2 * FMM_FAR_MAX];
     int nch, nexp;
     double node[FMM_P], bary[FMM_P];  // FV_NODE and FV_BARY (read by lane)
 };
 
-// gi: the group of FMMV_MAX_M columns of the pass
-template <int TRANS, bool FB, int TEAMS>
+// gi: the group of NC blocks of FMMV_MAX_M columns of the pass
+template <int TRANS, bool FB, int TEAMS, int NC>
 __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmVec &v, Tile t,
-                               int gi, FvShared<TEAMS> &sh) {
+                               int gi, FvShared<TEAMS, NC> &sh) {
+    static_assert(NC == 1 || (TEAMS == 1 && !FB), "one block of columns for teams and b");
     const int p = t.prob;
     const int64_t base = it.off[p];
     const int n = (int)(it.off[p + 1] - base);
@@ -630,8 +645,8 @@ __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmV
     const int tm = wave >> 2, wv = wave & 3;      // team, wavefront of the team
     const int tid = threadIdx.x & 255;            // thread of the team
     const int o0 = t.row0;
-    const int g0 = gi * FMMV_MAX_M;
-    const int mg = min(FMMV_MAX_M, v.m - g0);  // columns of the group
+    const int g0 = gi * (NC * FMMV_MAX_M);
+    const int mg = min(NC * FMMV_MAX_M, v.m - g0);  // columns of the group
     const int mo = mg - (FB ? 1 : 0);          // output columns
     if (f.status[p] & ~SUPERDC_ST_NOCONV) {
         const double nan = __builtin_nan("");
@@ -691,16 +706,18 @@ __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmV
     const int oc = min(o0 + wv * 16 + (lane & 15), n - 1);
     double ra = TRANS ? v.d[base + clamp_idx(v.origin[base + oc], n)] : v.d[base + oc];
     double rb = TRANS ? v.eta[base + oc] : 0.0;
-    v4d_f acc = v4d_f{0.0, 0.0, 0.0, 0.0};
+    v4d_f acc[NC];
+#pragma unroll
+    for (int b = 0; b < NC; ++b) acc[b] = v4d_f{0.0, 0.0, 0.0, 0.0};
     // FB: this lane's share of b's sum for its Cauchy row (the sources it generates entries
     // for), on the VALU beside the multiply: one column does not need the MFMA
     double bsum = 0.0;
-    FvStage st;
+    FvStage<NC> st;
     const int rounds = (nch + TEAMS - 1) / TEAMS;
     int4 cur = make_int4(0, 0, 0, 0);
     if (tm < nch) {
         cur = chunk(tm);
-        fv_fetch<TRANS, FB>(v, base, sh.fbox, cur, tid, g0, mg, mo, st);
+        fv_fetch<TRANS, FB, NC>(v, base, sh.fbox, cur, tid, g0, mg, mo, st);
     }
     asm volatile("" : "+v"(ra), "+v"(rb), "+v"(iv.x), "+v"(iv.y));  // loaded here, not in the loop
     for (int rd = 0; rd < rounds; ++rd) {
@@ -708,12 +725,12 @@ __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmV
         double2 *Sd = sh.team[tm].Sd[rd & 1];
         const int ci = rd * TEAMS + tm;
         const bool live = ci < nch;
-        if (live) fv_store<FB>(cur, tid, mg, mo, st, Xs, Sd);
+        if (live) fv_store<FB, NC>(cur, tid, mg, mo, st, Xs, Sd);
         __syncthreads();
         const bool near = cur.x == 0;
         if (ci + TEAMS < nch) {  // the next chunk's loads, in flight during the multiply
             cur = chunk(ci + TEAMS);
-            fv_fetch<TRANS, FB>(v, base, sh.fbox, cur, tid, g0, mg, mo, st);
+            fv_fetch<TRANS, FB, NC>(v, base, sh.fbox, cur, tid, g0, mg, mo, st);
         }
         if (!live) continue;
         // a step of 4 sources: the Cauchy entry of this lane's row (one reciprocal with a
@@ -724,8 +741,11 @@ __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmV
                 const int sl = kk + (lane >> 4);
                 const double2 sd = Sd[sl];
                 const double av = rcp_nr1(TRANS ? (sd.x - ra) - rb : (ra - sd.x) - sd.y);
-                const double bv = Xs[(lane & 15) * FV_LD + sl];
-                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
+#pragma unroll
+                for (int b = 0; b < NC; ++b) {
+                    const double bv = Xs[(16 * b + (lane & 15)) * FV_LD + sl];
+                    acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc[b], 0, 0, 0);
+                }
                 if (FB) {
                     if (is_near.value) {  // (zhat / t)^2: squared after the division
                         const double qv = av * sd.y;
@@ -744,19 +764,23 @@ __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmV
         // The expansion: the Cauchy rows are the interval's nodes.  Wavefront w takes the boxes
         // w, w + 4, ..., their operands straight from memory (step s of a box: source
         // 4 s + lane / 16, column lane % 16), the next box's in flight.
-        const int c = min(lane & 15, mg - 1);
         const double off = iv.y * sh.node[lane & 15];
-        v4d_f g = v4d_f{0.0, 0.0, 0.0, 0.0};
+        v4d_f g[NC];
+#pragma unroll
+        for (int b = 0; b < NC; ++b) g[b] = v4d_f{0.0, 0.0, 0.0, 0.0};
         double gb = 0.0;  // FB: sum of W / t^2 at this lane's node over its sources
         struct Box {
-            double w[4], x[4], b[4];
+            double w[4 * NC], x[4], b[4];
         };
         auto fetch = [&](int e, Box &o) {
             const int64_t s0 = (int64_t)sh.fbox[2 * FMM_FAR_MAX - 1 - e] * FMM_P + (lane >> 4);
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 o.x[k] = v.vnode[s0 + 4 * k];
-                o.w[k] = v.vw[(s0 + 4 * k) * v.m + g0 + c];
+#pragma unroll
+                for (int b = 0; b < NC; ++b)
+                    o.w[4 * b + k] =
+                        v.vw[(s0 + 4 * k) * v.m + g0 + min(16 * b + (lane & 15), mg - 1)];
                 if (FB) o.b[k] = v.vw[(s0 + 4 * k) * v.m + v.m - 1];
             }
         };
@@ -765,7 +789,9 @@ __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmV
             for (int k = 0; k < 4; ++k) {
                 const double t = (o.x[k] - iv.x) - off;
                 const double av = rcp_nr1(TRANS ? t : -t);
-                g = __builtin_amdgcn_mfma_f64_16x16x4f64(av, o.w[k], g, 0, 0, 0);
+#pragma unroll
+                for (int b = 0; b < NC; ++b)
+                    g[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, o.w[4 * b + k], g[b], 0, 0, 0);
                 if (FB) gb = fma(av * av, o.b[k], gb);
             }
             mfma_drain();
@@ -786,7 +812,9 @@ __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmV
         double *pb = (double *)sh.team[0].Sd[rounds & 1];
         static_assert(4 * 4 * WAVE <= 16 * FV_LD && 4 * FMM_P <= 2 * FV_K, "the sums fit the buffer");
 #pragma unroll
-        for (int k = 0; k < 4; ++k) part[(wv * 4 + k) * WAVE + lane] = g[k];
+        for (int b = 0; b < NC; ++b)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) part[((b * 4 + wv) * 4 + k) * WAVE + lane] = g[b][k];
         if (FB) {
             gb += __shfl_xor(gb, 16);
             gb += __shfl_xor(gb, 32);
@@ -808,10 +836,13 @@ __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmV
         const double iden = 1.0 / den;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            double gk = part[k * WAVE + lane];
 #pragma unroll
-            for (int u = 1; u < 4; ++u) gk += part[(u * 4 + k) * WAVE + lane];
-            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(lq[k] * iden, gk, acc, 0, 0, 0);
+            for (int b = 0; b < NC; ++b) {
+                double gk = part[(b * 16 + k) * WAVE + lane];
+#pragma unroll
+                for (int u = 1; u < 4; ++u) gk += part[((b * 4 + u) * 4 + k) * WAVE + lane];
+                acc[b] = __builtin_amdgcn_mfma_f64_16x16x4f64(lq[k] * iden, gk, acc[b], 0, 0, 0);
+            }
             if (FB) {
                 const int q = 4 * k + (lane >> 4);
                 double bk = pb[q];
@@ -843,7 +874,7 @@ __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmV
         __syncthreads();
         if (tm > 0) {
 #pragma unroll
-            for (int r = 0; r < 4; ++r) mine[r * WAVE + lane] = acc[r];
+            for (int r = 0; r < 4; ++r) mine[r * WAVE + lane] = acc[0][r];
             if (FB) mine[4 * WAVE + lane] = bsum;
         }
         __syncthreads();
@@ -851,7 +882,7 @@ __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmV
         for (int u = 1; u < TEAMS; ++u) {
             const double *o = &sh.team[u].Xs[0][0] + wv * 5 * WAVE;
 #pragma unroll
-            for (int r = 0; r < 4; ++r) acc[r] += o[r * WAVE + lane];
+            for (int r = 0; r < 4; ++r) acc[0][r] += o[r * WAVE + lane];
             if (FB) bsum += o[4 * WAVE + lane];
         }
     }
@@ -859,29 +890,34 @@ __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmV
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
         const int row = o0 + wv * 16 + 4 * r + (lane >> 4);
-        const int col = lane & 15;
         double post;
         if (FB) {  // b's sum of this row is held by the lanes that generated its entries
             post = 1.0 / sqrt(__shfl(bsum, 4 * r + (lane >> 4)));
-            if (row < n && col == 0) v.bout[base + row] = post;
+            if (row < n && (lane & 15) == 0) v.bout[base + row] = post;
         } else {
             post = row < n ? v.post[base + row] : 0.0;
         }
-        if (row < n && col < mo) v.Y[base + row + (int64_t)(g0 + col) * v.ldy] = post * acc[r];
+#pragma unroll
+        for (int b = 0; b < NC; ++b) {
+            const int col = 16 * b + (lane & 15);
+            if (row < n && col < mo)
+                v.Y[base + row + (int64_t)(g0 + col) * v.ldy] = post * acc[b][r];
+        }
     }
 }
 
-template <int TRANS, bool FB, int TEAMS>
-__global__ __launch_bounds__(256 * TEAMS, 4) void k_fmmv_eval_mfma(SolveArgs it, FmmArgs f,
-                                                                   FmmVec v) {
-    __shared__ FvShared<TEAMS> sh;
+template <int TRANS, bool FB, int TEAMS, int NC>
+__global__ __launch_bounds__(256 * TEAMS, NC == 1 ? 4 : 3) void k_fmmv_eval_mfma(SolveArgs it,
+                                                                                 FmmArgs f,
+                                                                                 FmmVec v) {
+    __shared__ FvShared<TEAMS, NC> sh;
     if (TEAMS == 1 && threadIdx.x < FMM_P) {
         sh.node[threadIdx.x] = FV_NODE[threadIdx.x];
         sh.bary[threadIdx.x] = FV_BARY[threadIdx.x];
     }
     // the column groups of a tile are neighbouring items: they read the same lists and poles
-    const int ng = (v.m + FMMV_MAX_M - 1) / FMMV_MAX_M;
-    fmmv_item_mfma<TRANS, FB, TEAMS>(it, f, v, it.tiles[blockIdx.x / ng], blockIdx.x % ng, sh);
+    const int ng = (v.m + NC * FMMV_MAX_M - 1) / (NC * FMMV_MAX_M);
+    fmmv_item_mfma<TRANS, FB, TEAMS, NC>(it, f, v, it.tiles[blockIdx.x / ng], blockIdx.x % ng, sh);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1162,11 +1198,23 @@ hipError_t launch_fmmv_eval(const SolveArgs &it, const FmmArgs &f, const FmmVec 
     const bool mfma = v.kern == 1 && (v.m >= 4 || v.fuse_b || v.trans == 0);
     v.work = trace_work(mfma ? KID_FMMV_EVAL_MFMA : KID_FMMV_EVAL);
     if (mfma) {
-        const int items = it.ntiles * ((v.m + FMMV_MAX_M - 1) / FMMV_MAX_M);
+        const int groups = (v.m + FMMV_MAX_M - 1) / FMMV_MAX_M, items = it.ntiles * groups;
+        const int wide = (groups + 1) / 2;
+        if (!v.fuse_b && groups > 1 &&
+            it.ntiles * wide >= (groups == 3 ? FV_WIDE3_PER_CU : FV_WIDE_PER_CU) * num_cu) {
+            const dim3 gw(it.ntiles * wide);
+            if (v.trans == 0)
+                SDC_LAUNCH(KID_FMMV_EVAL_MFMA, (k_fmmv_eval_mfma<0, false, 1, 2>), gw, dim3(256), 0,
+                           s, it, f, v);
+            else
+                SDC_LAUNCH(KID_FMMV_EVAL_MFMA, (k_fmmv_eval_mfma<1, false, 1, 2>), gw, dim3(256), 0,
+                           s, it, f, v);
+            return hipGetLastError();
+        }
         const int teams = items >= FV_EXPAND_PER_CU * num_cu ? 1 : items >= num_cu ? 2 : 4;
         const dim3 g(items);
 #define SDC_FV(T, FB, K) \
-    SDC_LAUNCH(KID_FMMV_EVAL_MFMA, (k_fmmv_eval_mfma<T, FB, K>), g, dim3(256 * K), 0, s, it, f, v)
+    SDC_LAUNCH(KID_FMMV_EVAL_MFMA, (k_fmmv_eval_mfma<T, FB, K, 1>), g, dim3(256 * K), 0, s, it, f, v)
 #define SDC_FV_TEAMS(T, FB)              \
     {                                    \
         if (teams == 1) SDC_FV(T, FB, 1);     \
