@@ -221,8 +221,8 @@ template <int TRANS, int NCT, bool FB, int TEAMS>
 __global__ __launch_bounds__(256 * TEAMS) void k_apply_mfma(ApplyArgs a) {
     __shared__ ApplyTeam<NCT> sh[TEAMS];
     const int np = (a.m + 16 * NCT - 1) / (16 * NCT);  // passes of a tile: neighbouring items
-    apply_tile_mfma<TRANS, NCT, FB, TEAMS>(a, a.tiles[blockIdx.x / np],
-                                           blockIdx.x % np * (16 * NCT), sh);
+    const int item = xcd_item();
+    apply_tile_mfma<TRANS, NCT, FB, TEAMS>(a, a.tiles[item / np], item % np * (16 * NCT), sh);
 }
 
 // ---------------------------------------------------------------------------------------

@@ -167,8 +167,8 @@ __device__ void bwd_poles_tile(const BwdArgs &a, Tile t, double4 *red) {
 template <bool PROJ, int PASS>
 __global__ __launch_bounds__(1024) void k_bwd(BwdArgs a) {
     extern __shared__ double4 red4[];
-    if (PASS == 1) bwd_roots_tile<PROJ>(a, a.tiles[blockIdx.x], red4);
-    else bwd_poles_tile<PROJ>(a, a.tiles[blockIdx.x], red4);
+    if (PASS == 1) bwd_roots_tile<PROJ>(a, a.tiles[xcd_item()], red4);
+    else bwd_poles_tile<PROJ>(a, a.tiles[xcd_item()], red4);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -433,7 +433,7 @@ template <bool PROJ, int PASS>
 __global__ __launch_bounds__(512) void k_bwd_fmm(BwdArgs a, FmmArgs f, FmmVec v) {
     extern __shared__ double red[];
     __shared__ BwdFar<PROJ, PASS> sh;
-    bwd_fmm_item<PROJ, PASS>(a, f, v, a.tiles[blockIdx.x], sh, red);
+    bwd_fmm_item<PROJ, PASS>(a, f, v, a.tiles[xcd_item()], sh, red);
 }
 
 // g_rho[p] = sum_k alpha_k / rho_p^2, fixed-order block reduction

@@ -112,6 +112,23 @@ __device__ __forceinline__ void wave_sync() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// The item of this workgroup: the dispatcher deals workgroups out over the eight XCDs in turn, each
+// with an L2 of its own, and neighbouring items (tiles of one problem, leaves side by side)
+// read the same poles, columns, lists and boxes.  So the items go to the XCDs in runs of XCD_RUN,
+// still about longest first; those past the last whole set of runs stay where they are.
+// Measured, single items -> runs of 4 -> 16 -> 32, us a pass: a level of 4096 problems 11260 ->
+// 11025 -> 10920 -> 10920, an HSS conquer of 65536 rows 15860 -> 15740 -> 15590 -> 15550, 1024
+// problems with their adjoint 4995 -> 4855 -> 4770 -> 4760, deflated levels 4000 -> 3970 -> 3920
+// -> 3980, 64 columns of 8192 rows 3940 -> 3940 -> 3830 -> 3790.
+constexpr int XCDS = 8;
+constexpr int XCD_RUN = 16;
+__device__ __forceinline__ int xcd_item() {
+    const unsigned b = blockIdx.x, set = XCDS * XCD_RUN;
+    if (b >= gridDim.x / set * set) return (int)b;
+    const unsigned r = b % set;
+    return (int)(b - r + r % XCDS * XCD_RUN + r / XCDS);
+}
+
 // columns [c0, c1) of one row, up to eight loads in flight
 __device__ __forceinline__ void copy_cols(const double *x, int64_t ldx, double *y, int64_t ldy,
                                           int c0, int c1) {

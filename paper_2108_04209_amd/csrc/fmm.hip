@@ -158,7 +158,7 @@ template <bool EQ>
 __global__ __launch_bounds__(EQ ? 2 * WAVE : WAVE) void k_fmm_lists(FmmArgs f) {
     __shared__ int slot[WAVE];
     __shared__ double part[EQ ? WAVE * (FMM_P + 1) : 1];
-    const int L = blockIdx.x;
+    const int L = xcd_item();
     // EQ (the solver's lists): a second wavefront compresses the leaf itself meanwhile
     if (EQ && threadIdx.x >= WAVE) {
         box_sources<true, true>(f, f.leaf_box[L], part, nullptr, threadIdx.x - WAVE, WAVE);
@@ -362,7 +362,7 @@ __global__ __launch_bounds__(FMM_PL * LOC_PARTS) void k_fmm_local(FmmArgs f) {
     __shared__ double2 src[LOC_ROUND];             // a round's sources
     __shared__ int4 rng[FMM_NEAR_MAX];  // flagged near ranges: first pole, poles, place, left
     __shared__ int box[2 * FMM_FAR_MAX], cntl, cntr;
-    const int L = blockIdx.x;
+    const int L = xcd_item();
     const int tid = threadIdx.x;
     for (int e = tid; e < FMM_PL * FMM_PL; e += blockDim.x)
         Tkm[e / FMM_PL][e % FMM_PL] = LOC_COS[(e / FMM_PL) * (2 * (e % FMM_PL) + 1) % (4 * FMM_PL)];

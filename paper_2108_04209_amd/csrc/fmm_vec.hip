@@ -496,7 +496,7 @@ template <int KERN, int NC>
 __global__ __launch_bounds__(512) void k_fmmv_eval(SolveArgs it, FmmArgs f, FmmVec v) {
     extern __shared__ double red[];
     __shared__ FvEvalShared<NC> sh;
-    fmmv_item<KERN, NC>(it, f, v, it.tiles[blockIdx.x], sh, red);
+    fmmv_item<KERN, NC>(it, f, v, it.tiles[xcd_item()], sh, red);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -917,7 +917,8 @@ __global__ __launch_bounds__(256 * TEAMS, NC == 1 ? 4 : 3) void k_fmmv_eval_mfma
     }
     // the column groups of a tile are neighbouring items: they read the same lists and poles
     const int ng = (v.m + NC * FMMV_MAX_M - 1) / (NC * FMMV_MAX_M);
-    fmmv_item_mfma<TRANS, FB, TEAMS, NC>(it, f, v, it.tiles[blockIdx.x / ng], blockIdx.x % ng, sh);
+    const int item = xcd_item();
+    fmmv_item_mfma<TRANS, FB, TEAMS, NC>(it, f, v, it.tiles[item / ng], item % ng, sh);
 }
 
 // ---------------------------------------------------------------------------------------

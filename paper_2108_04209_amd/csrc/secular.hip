@@ -1259,13 +1259,13 @@ __device__ void secular_fmm_item(const SolveArgs &a, Tile t, const FmmArgs &f, d
 // dynamic LDS: 16 bytes per pole of the launch's largest problem
 __global__ __launch_bounds__(512, 4) void k_secular_lds(SolveArgs a) {
     extern __shared__ double2 poles[];
-    secular_lds_item(a, a.tiles[blockIdx.x], poles);
+    secular_lds_item(a, a.tiles[xcd_item()], poles);
 }
 
 // dynamic LDS: 16 bytes per staged entry (cap of them) and the local expansion
 __global__ __launch_bounds__(512, 4) void k_secular_fmm_lds(SolveArgs a, FmmArgs f, int cap) {
     extern __shared__ double2 poles[];
-    secular_fmm_item(a, a.tiles[blockIdx.x], f, poles, cap);
+    secular_fmm_item(a, a.tiles[xcd_item()], f, poles, cap);
 }
 
 // the same problems' unshifted and hybrid ablations; blockDim.x = 64 S with the same dynamic

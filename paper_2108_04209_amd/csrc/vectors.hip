@@ -506,17 +506,17 @@ hipError_t launch_vectors_small(const VecArgs &a, int nprob, int max_n, hipStrea
 // blockDim.x = 64 S; dynamic LDS: one double4 per thread when S > 1
 __global__ __launch_bounds__(1024) void k_loewner(VecArgs a) {
     extern __shared__ double4 red4[];
-    loewner_tile(a, a.tiles[blockIdx.x], red4);
+    loewner_tile(a, a.tiles[xcd_item()], red4);
 }
 
 __global__ __launch_bounds__(1024) void k_bnorm(VecArgs a) {
     extern __shared__ double4 red4[];
-    bnorm_tile(a, a.tiles[blockIdx.x], red4);
+    bnorm_tile(a, a.tiles[xcd_item()], red4);
 }
 
 __global__ __launch_bounds__(1024) void k_loewner_fmm(VecArgs a, FmmArgs f, FmmlArgs l) {
     extern __shared__ double4 red4[];
-    loewner_fmm_tile(a, f, l, a.tiles[blockIdx.x], red4);
+    loewner_fmm_tile(a, f, l, a.tiles[xcd_item()], red4);
 }
 
 hipError_t launch_pack_ke(const VecArgs &a, hipStream_t s) {
