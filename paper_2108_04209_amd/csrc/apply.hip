@@ -5,8 +5,8 @@
 //   Y = Qhat^T X : Y_j = b_j    sum_i C_ij (zhat_i X_i)    (Alg. 3 Z-update, Alg. 4)
 //
 // The product is a dense contraction whose left factor is generated, never stored.
-// MFMA kernel: a workgroup of 4 wavefronts owns 64 output rows (16 per wavefront) and
-// all right-hand sides in blocks of 64 columns.  The reduction runs over 64-entry chunks:
+// MFMA kernel: a team of 4 wavefronts owns 64 output rows (16 per wavefront) and a pass of 16,
+// 32 or 64 columns; in small launches four teams share an item's reduction.  The reduction runs over 64-entry chunks:
 // the scaled right-hand sides (b_s X_s or zhat_s X_s) and the per-entry pole data are
 // staged in LDS, then each wavefront generates its 16x4 slice of C with one reciprocal
 // per lane and feeds v_mfma_f64_16x16x4f64 against 4x16 slices of the staged block.

@@ -8,10 +8,12 @@
 // are split at k: poles j <= k feed psi, poles j > k feed phi (eq. flu, lower and strictly
 // upper triangle), so each partial sum has terms of one sign.
 //
-// One wavefront owns a tile of 64 consecutive roots of one problem, one root per lane.
-// The pole loop index is wave-uniform, so (d_j, w_j) pairs come through the scalar data
-// cache and each pair feeds 64 roots.  Pole ranges entirely left of the tile go to psi,
-// entirely right to phi; only the 64 poles under the tile are routed per lane.
+// Two forms.  In LDS (batched launches): a workgroup stages what its roots sum, and teams of
+// lanes that hold a root share its poles.  By scalar fetches (single launches, problems too
+// large for LDS, the ablations): a wavefront owns a tile of 64 consecutive roots, one to a
+// lane; the pole loop index is wave-uniform, so (d_j, w_j) pairs come through the scalar data
+// cache and each pair feeds 64 roots.  In both, pole ranges entirely left of the live roots
+// go to psi, entirely right to phi; only the poles between them are routed one by one.
 //
 // The iteration (Alg. 2) runs to convergence inside the kernel:
 //   pass 0 : sums at the interval midpoint with origin k; the sign of f there picks the
