@@ -1134,6 +1134,7 @@ __device__ void secular_lds_item(const SolveArgs &a, Tile t, double2 *P) {
     // phi, its own by sign
     const int nw = blockDim.x / WAVE, share = (i1 - i0 + nw - 1) / nw;
     const int c0 = min(i1, i0 + wv * share), c1 = min(i1, c0 + share);
+    if (c0 >= c1) return;  // no roots left for this wavefront (and no pole c0 staged)
     const double d0 = P[0].x, dn = P[n - 1].x;
     const double dl = P[max(c0 - 1, 0)].x, dr = P[min(c1, n - 1)].x;  // beside the window
     secular_teams(a, p, base, n, c0, c1, (unsigned long long)n, [&](int j) { return P[j].x; },
