@@ -95,16 +95,10 @@ class Upload {
   public:
     template <typename T>
     void add(T **dst, const std::vector<T> &v) {
-        const size_t at = space(dst, v.size());
-        if (!v.empty()) std::memcpy(buf_.data() + at, v.data(), sizeof(T) * v.size());
-    }
-    // room for count entries, not initialised
-    template <typename T>
-    size_t space(T **dst, size_t count) {
         const size_t at = (buf_.size() + 255) & ~(size_t)255;
-        buf_.resize(at + std::max<size_t>(1, sizeof(T) * count));
+        buf_.resize(at + std::max<size_t>(1, sizeof(T) * v.size()));
         fix_.push_back({(void **)dst, at});
-        return at;
+        if (!v.empty()) std::memcpy(buf_.data() + at, v.data(), sizeof(T) * v.size());
     }
     // the device memory that holds them all (nullptr on failure; *err: why)
     void *commit(hipError_t *err) {
@@ -122,6 +116,24 @@ class Upload {
 
   private:
     std::vector<char> buf_;
+    std::vector<std::pair<void **, size_t>> fix_;
+};
+
+// Arrays laid out one behind the other in a block that is not initialised
+class Layout {
+  public:
+    template <typename T>
+    void add(T **dst, size_t count) {
+        fix_.push_back({(void **)dst, size_});
+        size_ += (sizeof(T) * std::max<size_t>(1, count) + 255) & ~(size_t)255;
+    }
+    size_t size() const { return size_; }
+    void place(void *mem) const {
+        for (const auto &f : fix_) *f.first = (char *)mem + f.second;
+    }
+
+  private:
+    size_t size_ = 0;
     std::vector<std::pair<void **, size_t>> fix_;
 };
 
@@ -249,9 +261,11 @@ int lds_chunk(const superdc_batch *b, int64_t below) {
 constexpr double FMM_SEP = 1.5;
 constexpr double FMM_SEP_LOC = 0.75;
 
-void fmm_free(FmmPlan *fp) {
+// synced: the current device has been waited for
+void fmm_free(FmmPlan *fp, superdc_batch *b, bool synced) {
     if (!fp) return;
     if (fp->mem) (void)hipFree(fp->mem);
+    if (fp->work) b->spare->give(fp->work, fp->work_cap, synced);
     for (void *p : fp->allocs) (void)hipFree(p);
     delete fp;
 }
@@ -291,57 +305,59 @@ bool dir_list(const superdc_batch *b, FmmPlan *fp, int C, SolveArgs &a) {
     return true;
 }
 
-// The per-call arrays of a layout (equivalent sources, lists, moments) in the context's
-// workspace: every call writes what it reads, but for the lists that a solve leaves to the
-// Loewner and apply calls that follow it inside the library on the same batch.  The use flags
-// have a buffer of their own, whose every entry is the number of some lists build (numbers
-// rise through the context's life), zero at first: a stale flag never equals a new number.
-bool fmm_scratch(FmmPlan *fp, superdc_ctx *ctx) {
-    const size_t nb = std::max(1, fp->nboxes), nl = std::max(1, fp->nleaves);
-    size_t at = 0;
-    std::vector<std::pair<void **, size_t>> fix;
-    auto room = [&](auto **dst, size_t count) {
-        fix.push_back({(void **)dst, at});
-        at += (sizeof(**dst) * count + 255) & ~(size_t)255;
-    };
-    room(&fp->eq, nb * FMM_P);
-    room(&fp->vnode, nb * FMM_P);
-    room(&fp->lgeo, nb);
-    room(&fp->lmom, nb * FMML_K);
-    room(&fp->loc, nl * FMM_LOC);
+// Columns per set of launches: in small batches up to FMMV_MAX_PASS at once, so that the
+// 16-column groups fill the chip together (one 8192-root problem has 128 items for 256 CUs: 64
+// columns in four sets of launches took 264 us, in one 73 us; of one 65536-root problem, 560 and
+// 317 us); 16 where the wider pass's equivalent weights (2 KiB a box and group) would exceed 64
+// MiB -- such a batch has items enough for every CU.
+int fmmv_max_pass(const FmmPlan *fp) {
+    const int64_t groups = ((int64_t)64 << 20) / ((int64_t)std::max(1, fp->nboxes) * FMM_P * FMMV_MAX_M * 8);
+    return FMMV_MAX_M * (int)std::min<int64_t>(FMMV_MAX_PASS / FMMV_MAX_M, std::max<int64_t>(1, groups));
+}
+
+// The per-call arrays of a layout: equivalent sources, lists, moments, and the equivalent weights
+// of up to 16 columns.  They are the layout's own: a captured call holds their addresses, and
+// stays valid while the batch does, whatever other batches of the context run afterwards.  Every
+// call writes what it reads, but for the lists that a solve leaves to the Loewner and apply
+// calls that follow it inside the library on the same batch, and for the use flags, which start
+// below every number of a lists build.  False: out of memory (*err: why).
+bool fmm_arrays(FmmPlan *fp, superdc_batch *b, hipError_t *err) {
+    Layout up;
+    const size_t nb = fp->nboxes, nl = fp->nleaves;
+    up.add(&fp->eq, nb * FMM_P);
+    up.add(&fp->vnode, nb * FMM_P);
+    up.add(&fp->lgeo, nb);
+    up.add(&fp->lmom, nb * FMML_K);
+    up.add(&fp->loc, nl * FMM_LOC);
+    up.add(&fp->vw[0], nb * FMM_P * FMMV_MAX_M);
+    up.add(&fp->vpart[0], (size_t)fp->nslot * FMM_P * FMMV_MAX_M);
     for (FmmLists *l : {&fp->own, &fp->roots}) {
-        room(&l->near_lo, nl * FMM_NEAR_MAX);
-        room(&l->near_hi, nl * FMM_NEAR_MAX);
-        room(&l->near_lf, nl * FMM_NEAR_MAX);
-        room(&l->far_l, nl * FMM_FAR_MAX);
-        room(&l->far_r, nl * FMM_FAR_MAX);
-        room(&l->far_ld, nl * FMM_FAR_MAX);
-        room(&l->far_rd, nl * FMM_FAR_MAX);
-        room(&l->cnt, nl * 3);
-        room(&l->cntd, nl * 2);
-        room(&l->loc_ab, nl);
+        up.add(&l->near_lo, nl * FMM_NEAR_MAX);
+        up.add(&l->near_hi, nl * FMM_NEAR_MAX);
+        up.add(&l->near_lf, nl * FMM_NEAR_MAX);
+        up.add(&l->far_l, nl * FMM_FAR_MAX);
+        up.add(&l->far_r, nl * FMM_FAR_MAX);
+        up.add(&l->far_ld, nl * FMM_FAR_MAX);
+        up.add(&l->far_rd, nl * FMM_FAR_MAX);
+        up.add(&l->cnt, nl * 3);
+        up.add(&l->cntd, nl * 2);
+        up.add(&l->loc_ab, nl);
     }
-    char *mem = (char *)ws_get(ctx, WS_FMM, at);
-    const size_t flags = sizeof(int32_t) * 2 * nb;
-    const bool grow = ctx->ws_cap[WS_FMM_USED] < flags;
-    int32_t *used = (int32_t *)ws_get(ctx, WS_FMM_USED, flags);
-    if (!mem || !used) return false;
-    if (grow && (hipMemset(used, 0, ctx->ws_cap[WS_FMM_USED]) != hipSuccess ||
-                 hipDeviceSynchronize() != hipSuccess))
-        return false;
-    for (const auto &f : fix) *f.first = mem + f.second;
-    fp->own.used = used;
-    fp->roots.used = used + nb;
+    fp->work = b->spare->take(up.size(), &fp->work_cap);
+    if (!fp->work) {
+        *err = hipMalloc(&fp->work, up.size());
+        if (*err != hipSuccess) return false;
+        fp->work_cap = up.size();
+    }
+    up.place(fp->work);
     return true;
 }
 
 // The FMM layout of a batch: which problems use it, their leaf trees and work lists.
 // Rebuilt only when the leaf size or the crossover changes.
 FmmPlan *fmm_plan(superdc_batch *b, int leaf, int crossover) {
-    if (b->fmm && b->fmm->leaf == leaf && b->fmm->crossover == crossover)
-        return fmm_scratch(b->fmm, b->ctx) ? b->fmm : nullptr;
-    (void)hipDeviceSynchronize();
-    fmm_free(b->fmm);
+    if (b->fmm && b->fmm->leaf == leaf && b->fmm->crossover == crossover) return b->fmm;
+    fmm_free(b->fmm, b, hipDeviceSynchronize() == hipSuccess);
     b->fmm = nullptr;
     FmmPlan *fp = new (std::nothrow) FmmPlan();
     if (!fp) return nullptr;
@@ -483,9 +499,10 @@ FmmPlan *fmm_plan(superdc_batch *b, int leaf, int crossover) {
     up.add(&fp->sitem_lpt, slpt);
     // direct chunks of the other problems: the cut lengths in use now
     for (int C : {(int)TILE, fp->lds_chunk, b->sec.chunk}) dir_add(b, fp, C, up);
+    for (FmmLists *l : {&fp->own, &fp->roots}) up.add(&l->used, std::vector<int32_t>(fp->nboxes, 0));
     hipError_t e;
-    if (!(fp->mem = up.commit(&e)) || !fmm_scratch(fp, b->ctx)) {
-        fmm_free(fp);
+    if (!(fp->mem = up.commit(&e)) || !fmm_arrays(fp, b, &e)) {
+        fmm_free(fp, b, true);
         return nullptr;
     }
     b->fmm = fp;
@@ -580,25 +597,24 @@ FmmPlan *fmm_for(superdc_batch *b, const superdc_opts &o, int &rc, double pairs 
     return fp->nfmm > 0 ? fp : nullptr;
 }
 
-// Columns per set of launches for m columns: in small batches up to FMMV_MAX_PASS at once, so
-// that the 16-column groups fill the chip together (one 8192-root problem has 128 items for
-// 256 CUs: 64 columns in four sets of launches took 264 us, in one 73 us; of one 65536-root
-// problem, 560 and 317 us);
-// 16 where the wider pass's equivalent weights (2 KiB a box and group) would exceed 64 MiB --
-// such a batch has items enough for every CU.
-int fmmv_pass(const FmmPlan *fp, int m) {
-    const int64_t groups = ((int64_t)64 << 20) / ((int64_t)std::max(1, fp->nboxes) * FMM_P * FMMV_MAX_M * 8);
-    return std::min<int64_t>(m, FMMV_MAX_M * std::min<int64_t>(FMMV_MAX_PASS / FMMV_MAX_M,
-                                                               std::max<int64_t>(1, groups)));
-}
-
-// workspace for the equivalent weights of a pass of `cols` columns; false: out of memory
-bool fmmv_space(superdc_ctx *ctx, const FmmPlan *fp, int cols, FmmArgs &f, FmmVec &v) {
-    const int ng = (cols + FMMV_MAX_M - 1) / FMMV_MAX_M;
+// the arrays for the equivalent weights of a pass of `cols` columns: those of wide passes are
+// allocated, for the widest, by the batch's first such call; false: out of memory
+bool fmmv_space(FmmPlan *fp, int cols, FmmArgs &f, FmmVec &v) {
+    const int wide = cols > FMMV_MAX_M;
+    if (wide && !fp->vw[1]) {
+        const int most = fmmv_max_pass(fp);
+        Layout w;
+        w.add(&fp->vw[1], (size_t)fp->nboxes * FMM_P * most);
+        w.add(&fp->vpart[1], (size_t)fp->nslot * FMM_P * most);
+        void *mem = nullptr;
+        if (hipMalloc(&mem, w.size()) != hipSuccess) return false;
+        fp->allocs.push_back(mem);
+        w.place(mem);
+    }
     v.vnode = fp->vnode;
-    v.vw = (double *)ws_get(ctx, WS_VW, sizeof(double) * fp->nboxes * FMM_P * cols);
-    f.vpart = (double *)ws_get(ctx, WS_VPART, sizeof(double) * fp->nslot * ng * FMM_P * FMMV_MAX_M);
-    return v.vw && f.vpart;
+    v.vw = fp->vw[wide];
+    f.vpart = fp->vpart[wide];
+    return true;
 }
 
 // Run the eigenvector-side FMM over every FMM problem of the batch for the v.m columns of
@@ -627,6 +643,38 @@ hipError_t fmmv_run(superdc_ctx *ctx, const superdc_batch *b, const FmmPlan *fp,
 }  // namespace
 
 namespace sdc {
+void *SpareBlock::take(size_t bytes, size_t *cap) {
+    std::lock_guard<std::mutex> g(mu_);
+    int dev = -1;
+    if (!p_ || cap_ < bytes || hipGetDevice(&dev) != hipSuccess || dev != device_) return nullptr;
+    void *p = p_;
+    *cap = cap_;
+    p_ = nullptr;
+    cap_ = 0;
+    return p;
+}
+
+void SpareBlock::give(void *p, size_t cap, bool synced) {
+    {
+        std::lock_guard<std::mutex> g(mu_);
+        int dev = -1;
+        if (synced && !closed_ && cap <= SPARE_MAX && cap > cap_ && hipGetDevice(&dev) == hipSuccess &&
+            dev == device_) {
+            std::swap(p, p_);
+            cap_ = cap;
+        }
+    }
+    if (p) (void)hipFree(p);
+}
+
+void SpareBlock::close() {
+    std::lock_guard<std::mutex> g(mu_);
+    if (p_) (void)hipFree(p_);
+    p_ = nullptr;
+    cap_ = 0;
+    closed_ = true;
+}
+
 void *ws_get(superdc_ctx *ctx, int slot, size_t bytes) {
     if (bytes == 0) bytes = 256;
     if (ctx->ws_cap[slot] >= bytes) return ctx->ws[slot];
@@ -717,7 +765,7 @@ int loewner_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const
         v.bout = bnorm;
         v.zh = zhat;
         f = fmm_vec_args(fp, b, d, eta, origin, status);
-        if (fmm_b && !fmmv_space(ctx, fp, 1, f, v)) return SUPERDC_ENOMEM;
+        if (fmm_b && !fmmv_space(fp, 1, f, v)) return SUPERDC_ENOMEM;
         lf.pd = pairs;
         lf.geo = fp->lgeo;
         lf.mom = fp->lmom;
@@ -726,7 +774,7 @@ int loewner_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const
         // leaves' launch packs the pairs itself
         if (!reuse_lists) {
             SDC_HIP(launch_fmml_pack(pk, s));
-            f.gen = fp->own.gen = ++ctx->lists_gen;
+            f.gen = ++fp->own.gen;
             SDC_HIP(launch_fmm_lists(f, s));
         } else {
             lf.pack = 1;
@@ -857,7 +905,7 @@ int apply_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const d
     bool lists = !reuse_lists;
     FmmArgs f{};
     if (trans == 0) {
-        double *pos = (double *)ws_get(ctx, WS_VPAIR, sizeof(double) * b->total);
+        double *pos = (double *)ws_get(ctx, WS_VPAIR, sizeof(double2) * b->total);
         double2 *ke = (double2 *)ws_get(ctx, WS_KE, sizeof(double2) * b->total);
         if (!pos || !ke) return SUPERDC_ENOMEM;
         FmmvPackArgs pk{};
@@ -872,14 +920,14 @@ int apply_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const d
         v.ke = ke;
         SDC_HIP(launch_fmmv_pos(pk, s));
         f = fmm_roots_args(fp, b, pos, status, d);
-        f.gen = fp->roots.gen = ++ctx->lists_gen;  // built with the first columns below
+        f.gen = ++fp->roots.gen;  // built with the first columns below
         lists = true;
     } else {
         f = fmm_vec_args(fp, b, d, eta, origin, status);
-        if (lists) f.gen = fp->own.gen = ++ctx->lists_gen;  // built with the first columns below
+        if (lists) f.gen = ++fp->own.gen;  // built with the first columns below
     }
-    const int pass = fmmv_pass(fp, m + v.fuse_b);  // one pass when fused
-    if (!fmmv_space(ctx, fp, pass, f, v)) return SUPERDC_ENOMEM;
+    const int pass = std::min(m + v.fuse_b, fmmv_max_pass(fp));  // one pass when fused
+    if (!fmmv_space(fp, pass, f, v)) return SUPERDC_ENOMEM;
     for (int c0 = 0; c0 < m; c0 += pass) {
         v.m = std::min(pass, m + v.fuse_b - c0);
         v.X = X + (int64_t)c0 * ldx;
@@ -932,6 +980,12 @@ int superdc_create(superdc_ctx **out) {
     if (!ctx) return SUPERDC_ENOMEM;
     ctx->device = dev;
     ctx->num_cu = prop.multiProcessorCount;
+    try {
+        ctx->spare = std::make_shared<SpareBlock>(dev);
+    } catch (const std::bad_alloc &) {
+        delete ctx;
+        return SUPERDC_ENOMEM;
+    }
     {
         const int rc = noalloc_init(dev);
         if (rc != SUPERDC_OK) {
@@ -948,6 +1002,7 @@ void superdc_destroy(superdc_ctx *ctx) {
     (void)hipDeviceSynchronize();
     for (int i = 0; i < kNumWs; ++i)
         if (ctx->ws[i]) (void)hipFree(ctx->ws[i]);
+    ctx->spare->close();
     delete ctx;
 }
 
@@ -965,6 +1020,7 @@ int superdc_batch_create(superdc_ctx *ctx, int32_t nprob, const int64_t *off_hos
     superdc_batch *b = new (std::nothrow) superdc_batch();
     if (!b) return SUPERDC_ENOMEM;
     b->ctx = ctx;
+    b->spare = ctx->spare;
     b->nprob = nprob;
     b->total = off_host[nprob];
     b->max_n = max_n;
@@ -991,8 +1047,8 @@ int superdc_batch_create(superdc_ctx *ctx, int32_t nprob, const int64_t *off_hos
     up.add(&b->off_d, b->off_h);
     for (int C : {(int)TILE, b->sec.chunk, b->lds_chunk}) list_add(b, C, up);
     if (b->vsplit > 1) {
-        up.space(&b->vsum, (size_t)nprob * b->vsplit);
-        up.space(&b->vst, (size_t)nprob * b->vsplit);
+        up.add(&b->vsum, std::vector<double>((size_t)nprob * b->vsplit));
+        up.add(&b->vst, std::vector<int32_t>((size_t)nprob * b->vsplit));
     }
     hipError_t e;
     void *mem = up.commit(&e);
@@ -1008,8 +1064,7 @@ int superdc_batch_create(superdc_ctx *ctx, int32_t nprob, const int64_t *off_hos
 
 void superdc_batch_destroy(superdc_batch *b) {
     if (!b) return;
-    (void)hipDeviceSynchronize();
-    fmm_free(b->fmm);
+    fmm_free(b->fmm, b, hipDeviceSynchronize() == hipSuccess);
     for (void *p : b->mem) (void)hipFree(p);
     delete b;
 }
@@ -1055,7 +1110,7 @@ int superdc_secular_solve(superdc_ctx *ctx, const superdc_batch *b, const double
     FmmArgs f{};
     if (fp) {
         f = fmm_args(fp, b, a, o);
-        f.gen = fp->own.gen = ++ctx->lists_gen;  // the lists this solve builds
+        f.gen = ++fp->own.gen;  // the lists this solve builds
     }
     if (o.persistent) {
         // one launch over the chunks of the direct problems, longest first,
@@ -1179,9 +1234,9 @@ int superdc_secular_backward(superdc_ctx *ctx, const superdc_batch *b, const dou
         FmmArgs f{};
         FmmVec v{};
         if (fp) {
-            pos = (double *)ws_get(ctx, WS_VPAIR, sizeof(double) * b->total);
+            pos = (double *)ws_get(ctx, WS_VPAIR, sizeof(double2) * b->total);
             ke = (double2 *)ws_get(ctx, WS_KE, sizeof(double2) * b->total);
-            if (!pos || !ke || !fmmv_space(ctx, fp, g_proj ? 3 : 1, f, v)) fp = nullptr;
+            if (!pos || !ke || !fmmv_space(fp, g_proj ? 3 : 1, f, v)) fp = nullptr;
         }
         a.tiles = fp ? fp->dir_lpt[chunk_slot(TILE)] : L->lpt;
         a.ntiles = fp ? fp->dir_count[chunk_slot(TILE)] : L->count;
@@ -1203,7 +1258,7 @@ int superdc_secular_backward(superdc_ctx *ctx, const superdc_batch *b, const dou
             v.trans = 1;
             f = fmm_vec_args(fp, b, d, eta, origin, status);
             f.vpart = part;
-            f.gen = fp->own.gen = ++ctx->lists_gen;
+            f.gen = ++fp->own.gen;
             SDC_HIP(launch_fmm_lists(f, s));
             SDC_HIP(launch_fmmv_sources(f, v, s));
             SDC_HIP(launch_backward_fmm(a, f, v, fp->split, ctx->num_cu, s));
@@ -1223,7 +1278,7 @@ int superdc_secular_backward(superdc_ctx *ctx, const superdc_batch *b, const dou
             v.trans = 0;
             f = fmm_roots_args(fp, b, pos, status, d);
             f.vpart = part;
-            f.gen = fp->roots.gen = ++ctx->lists_gen;
+            f.gen = ++fp->roots.gen;
             SDC_HIP(launch_fmm_lists(f, s));
             SDC_HIP(launch_fmmv_sources(f, v, s));
             SDC_HIP(launch_backward_fmm(a, f, v, fp->split, ctx->num_cu, s));

@@ -96,8 +96,8 @@ struct FmmLists {
     int gen = 0;
 };
 
-// Host side: the FMM layout of one batch for one leaf size.  The index arrays are device
-// buffers owned here; the per-call arrays are the context's workspace, set on every use.
+// Host side: the FMM layout of one batch for one leaf size.  The device arrays, those
+// of the layout and those written on every call, are owned here.
 struct FmmPlan {
     int leaf = 0;
     int crossover = 0;               // problems with n >= crossover use the FMM
@@ -113,8 +113,9 @@ struct FmmPlan {
     int2 *split_box = nullptr;
     int nupper_item = 0, nitem_big = 0, nsplit = 0, nslot = 0;
     int upper_cls[7] = {0};          // see FmmArgs
-    double2 *eq = nullptr;           // per-call arrays (fmm_scratch)
+    double2 *eq = nullptr;           // per-call arrays (fmm_arrays)
     double *loc = nullptr, *vnode = nullptr;
+    double *vw[2] = {nullptr}, *vpart[2] = {nullptr};  // passes of up to 16 columns; wider ones
     double2 *lgeo = nullptr;
     double *lmom = nullptr;
     FmmLists own;                    // lists of the poles' targets
@@ -140,6 +141,8 @@ struct FmmPlan {
     int32_t dir_count[kNumChunks] = {0};
     bool dir_built[kNumChunks] = {false};
     void *mem = nullptr;               // the arrays above that hold the layout
+    void *work = nullptr;              // the per-call arrays
+    size_t work_cap = 0;
     std::vector<void *> allocs;        // direct chunks added later
 };
 
