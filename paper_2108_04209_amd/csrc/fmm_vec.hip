@@ -353,15 +353,17 @@ __device__ void fmmv_item(const SolveArgs &it, const FmmArgs &f, const FmmVec &v
             for (; i + 2 <= hi; i += 2) {
                 const double t0 = (dd[i] - dK) - eta, t1 = (dd[i + 1] - dK) - eta;
                 const double R = rcp_nr(t0 * t1);
-                const double u0 = sc[i] * t1, u1 = sc[i + 1] * t0;  // scale_i / t_i = u_i R
+                // scale_i / t_i, divided before any further product: scale times t can leave the
+                // range where the quotient does not
+                const double q0 = sc[i] * t1 * R, q1 = sc[i + 1] * t0 * R;
                 if (KERN == 1) {
 #pragma unroll
                     for (int c = 0; c < NC; ++c) {
                         const const_double_ptr x = X + i + (int64_t)c * v.ldx;
-                        acc[c] = __builtin_fma(__builtin_fma(u0, x[0], u1 * x[1]), R, acc[c]);
+                        acc[c] = __builtin_fma(q0, x[0], __builtin_fma(q1, x[1], acc[c]));
                     }
-                } else {  // u0^2 + u1^2 over (t0 t1)^2, applied as (num R) R
-                    acc[0] = __builtin_fma(__builtin_fma(u0, u0, u1 * u1) * R, R, acc[0]);
+                } else {
+                    acc[0] = __builtin_fma(q0, q0, __builtin_fma(q1, q1, acc[0]));
                 }
             }
         }

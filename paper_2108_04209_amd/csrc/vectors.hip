@@ -345,9 +345,9 @@ __device__ void bnorm_tile(const VecArgs &a, Tile t, double4 *red) {
     int p0, p1;
     split_range(n, p0, p1);
     // two poles share one reciprocal (the FP64 reciprocal issues at a quarter of the FMA
-    // rate): zhat0^2/t0^2 + zhat1^2/t1^2 = ((zhat0 t1)^2 + (zhat1 t0)^2) / (t0 t1)^2, a sum
-    // of two squares over a square, applied as (num R) R.  The products need every |t| inside
-    // [2^-300, 2^300] (the range the solver's shared reciprocals use);
+    // rate): zhat0/t0 = zhat0 t1 R and zhat1/t1 = zhat1 t0 R with R = 1/(t0 t1), squared after
+    // the division (zhat^2 t^2 leaves the range where the quotient does not).  The products need
+    // every |t| inside [2^-300, 2^300] (the range the solver's shared reciprocals use);
     // the smallest |t| of a root is |eta| (its origin is its nearest pole) and the largest
     // is at an end of the pole range.  A wavefront with a root outside takes one
     // reciprocal per pole.
@@ -364,9 +364,9 @@ __device__ void bnorm_tile(const VecArgs &a, Tile t, double4 *red) {
             const double2 q0v = dz[i], q1v = dz[i + 1];
             const double t0 = (q0v.x - kv.x) - kv.y, t1 = (q1v.x - kv.x) - kv.y;
             const double R = rcp_nr(t0 * t1);
-            const double u0 = q0v.y * t1, u1 = q1v.y * t0;
-            const double num = __builtin_fma(u0, u0, u1 * u1);
-            s0 = __builtin_fma(num * R, R, s0);
+            const double q0 = q0v.y * t1 * R, q1 = q1v.y * t0 * R;
+            s0 = __builtin_fma(q0, q0, s0);
+            s1 = __builtin_fma(q1, q1, s1);
         }
     }
     for (; i + 2 <= p1; i += 2) {
@@ -479,8 +479,9 @@ __global__ __launch_bounds__(WAVE * VS_W) void k_vectors_small(VecArgs a) {
         for (; j + 2 <= j1; j += 2) {
             const double t0 = (dd[j] - kv.x) - kv.y, t1 = (dd[j + 1] - kv.x) - kv.y;
             const double R = rcp_nr(t0 * t1);
-            const double u0 = zh[j] * t1, u1 = zh[j + 1] * t0;
-            s0 = __builtin_fma(__builtin_fma(u0, u0, u1 * u1) * R, R, s0);
+            const double q0 = zh[j] * t1 * R, q1 = zh[j + 1] * t0 * R;
+            s0 = __builtin_fma(q0, q0, s0);
+            s1 = __builtin_fma(q1, q1, s1);
         }
     }
     for (; j < j1; ++j) {
