@@ -260,6 +260,11 @@ int lds_chunk(const superdc_batch *b, int64_t below) {
 // test's tolerance is n eps (1 + |psi| + |phi|) >= 1.1e-13 relative for the FMM's n >= 1024)
 constexpr double FMM_SEP = 1.5;
 constexpr double FMM_SEP_LOC = 0.75;
+// The adjoint's sums run over 1/t, 1/t^2 and 1/t^3, which nodes at a distance of 1.5 widths
+// interpolate to 9e-15, 2e-13 and worse (gradients of single eigenvalues, entry by entry: g_d off by
+// 2.0e-13, by direct sums 1.3e-15); 3 widths leave less than the rounding of the terms (8 boxes of
+// poles a target instead of 5: 1024 problems with their gradients 4.75 -> 5.1 ms).
+constexpr double FMM_SEP_BWD = 3.0;
 
 // synced: the current device has been waited for
 void fmm_free(FmmPlan *fp, superdc_batch *b, bool synced) {
@@ -326,6 +331,7 @@ bool fmm_arrays(FmmPlan *fp, superdc_batch *b, hipError_t *err) {
     const size_t nb = fp->nboxes, nl = fp->nleaves;
     up.add(&fp->eq, nb * FMM_P);
     up.add(&fp->vnode, nb * FMM_P);
+    up.add(&fp->vcen, nb);
     up.add(&fp->lgeo, nb);
     up.add(&fp->lmom, nb * FMML_K);
     up.add(&fp->loc, nl * FMM_LOC);
@@ -1251,12 +1257,14 @@ int superdc_secular_backward(superdc_ctx *ctx, const superdc_batch *b, const dou
             v.u = u;
             v.rk = a.rk;
             v.gk = a.gk;
+            v.vcen = fp->vcen;
             double *const part = f.vpart;
             // the roots' sums over the poles
             v.kern = 3;
             v.m = nw;
             v.trans = 1;
             f = fmm_vec_args(fp, b, d, eta, origin, status);
+            f.sep = FMM_SEP_BWD;
             f.vpart = part;
             f.gen = ++fp->own.gen;
             SDC_HIP(launch_fmm_lists(f, s));
@@ -1277,6 +1285,7 @@ int superdc_secular_backward(superdc_ctx *ctx, const superdc_batch *b, const dou
             v.m = g_proj ? 3 : 1;
             v.trans = 0;
             f = fmm_roots_args(fp, b, pos, status, d);
+            f.sep = FMM_SEP_BWD;
             f.vpart = part;
             f.gen = ++fp->roots.gen;
             SDC_HIP(launch_fmm_lists(f, s));

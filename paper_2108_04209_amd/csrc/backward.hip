@@ -178,8 +178,12 @@ __global__ __launch_bounds__(1024) void k_bwd(BwdArgs a) {
 // gamma) the poles' six.  One lane per target, S wavefronts per item of 64 targets; the far
 // field of the boxes away from the targets' interval goes through its nodes (fmm_far.h).
 // Bound by the FP64 pipe, as the direct sums: 1024 problems of 256 to 4096 roots with
-// projections took those 7.7 ms at 93 % of it; here 1.0 ms, 0.3 ms for the weights of the boxes
-// and 0.3 ms for the problems below the crossover.
+// projections took those 7.7 ms at 93 % of it; here 1.4 ms, 0.3 ms for the weights of the boxes
+// and 0.3 ms for the problems below the crossover.  The boxes lie 3 widths away and their nodes
+// are offsets from their centres, so that the far field is as exact as the direct sums: gradients
+// of single eigenvalues of 2048 to 8192 roots, entry by entry against long double, g_d off by
+// 2.3e-15 at most and 4.7e-16 rms (direct 3.2e-15 and 6.0e-16), g_z 2.2e-15 and 4.6e-16 (3.0e-15
+// and 5.8e-16); with boxes from 1.5 widths on, 2.0e-13 and 8.9e-15 at most.
 // ---------------------------------------------------------------------------------------
 template <bool PROJ, int PASS>
 struct BwdFar {
@@ -353,13 +357,14 @@ __device__ void bwd_fmm_item(const BwdArgs &a, const FmmArgs &f, const FmmVec &v
             for (int c = 0; c < NF; ++c) gs[c] = 0.0;
             for (int e = wv; e < ne; e += S) {
                 const int64_t g = sh.fbox[2 * FMM_FAR_MAX - 1 - e];
+                const double c = v.vcen[g] - iv.x;
 #pragma unroll
                 for (int k = 0; k < 4; ++k) {
                     const int64_t sq = g * FMM_P + 4 * k + (lane >> 4);
                     double w[NW];
 #pragma unroll
                     for (int c = 0; c < NW; ++c) w[c] = v.vw[sq * NW + c];
-                    Far::add(sg * rcp_nr((v.vnode[sq] - iv.x) - off), w, gs);
+                    Far::add(sg * rcp_nr((c + v.vnode[sq]) - off), w, gs);
                 }
             }
 #pragma unroll
@@ -393,13 +398,14 @@ __device__ void bwd_fmm_item(const BwdArgs &a, const FmmArgs &f, const FmmVec &v
             const int g = wave_uniform(sh.fbox[e]);
             const const_double_ptr nd = as_const(v.vnode + (int64_t)g * FMM_P);
             const const_double_ptr ww = as_const(v.vw + (int64_t)g * FMM_P * NW);
+            const double c = (v.vcen[g] - x0) - x1;
             ent += FMM_P;
 #pragma unroll 4
             for (int q = 0; q < FMM_P; ++q) {
                 double w[NW];
 #pragma unroll
                 for (int c = 0; c < NW; ++c) w[c] = ww[q * NW + c];
-                Far::add(sg * rcp_nr((nd[q] - x0) - x1), w, acc);
+                Far::add(sg * rcp_nr(c + nd[q]), w, acc);
             }
         }
     }
@@ -477,6 +483,7 @@ hipError_t launch_backward_fmm(const BwdArgs &a, const FmmArgs &f, const FmmVec 
     FmmVec v = v0;
     if (v.m != (v.kern == 3 ? (proj ? 2 : 1) : (proj ? 3 : 1)) || split > 8) return hipErrorInvalidValue;
     v.work = trace_work(KID_BWD_FMM);
+    v.sep_t = FV_SEP_BWD;
     v.expand = a.ntiles >= FV_EXPAND_PER_CU * num_cu;
     const dim3 g(a.ntiles), blk(WAVE * split);
 #define SDC_BWD(P, K)                                                                   \

@@ -114,7 +114,7 @@ struct FmmPlan {
     int nupper_item = 0, nitem_big = 0, nsplit = 0, nslot = 0;
     int upper_cls[7] = {0};          // see FmmArgs
     double2 *eq = nullptr;           // per-call arrays (fmm_arrays)
-    double *loc = nullptr, *vnode = nullptr;
+    double *loc = nullptr, *vnode = nullptr, *vcen = nullptr;
     double *vw[2] = {nullptr}, *vpart[2] = {nullptr};  // passes of up to 16 columns; wider ones
     double2 *lgeo = nullptr;
     double *lmom = nullptr;
@@ -165,6 +165,8 @@ struct FmmVec {
     int64_t ldx;
     const double *scale;
     double *vnode;            // [boxes][FMM_P] equivalent source nodes
+    double *vcen;             // when set (the adjoint), [boxes] their boxes' centres, and the nodes
+                              // are held as offsets from those
     double *vw;               // [boxes][FMM_P][m] equivalent source weights
     const double *d;          // poles
     const int32_t *origin;    // roots' origins (local indices)
@@ -179,6 +181,7 @@ struct FmmVec {
                               // it to bout and scales the other m - 1 columns by it
     int expand;               // VALU evaluation: far boxes through the targets' interval (set
                               // by launch_fmmv_eval)
+    double sep_t;             // interval widths from which a far box goes through it (set there)
     const double *zh;         // fuse_b: zhat, for b's near terms (zhat / t)^2
     const double *u;          // kern 3: u (scale: z)
     const double4 *rk;        // kern 4: (d_K, eta, alpha, beta) per root

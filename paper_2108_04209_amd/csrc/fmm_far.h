@@ -15,8 +15,12 @@ namespace sdc {
 // the others stay with the direct sums (entries per row, level of 4096 problems: 541 -> 387;
 // evaluation 3.25 -> 2.60 ms, b 1.75 -> 1.54 ms).  Node positions are kept as offsets from the
 // interval's centre, so a difference s - x_m = (s - centre) - offset_m is as accurate as the
-// shifted differences of the targets themselves.
+// shifted differences of the targets themselves.  Against long double, with and without the
+// expansion: single entries of Q (5 problems of 8192, 40 of 2048) 1.0e-14 and 9.9e-15 off at most,
+// what the boxes' own nodes leave; b of the last root, whose far field is all of it, 8.8e-16 and
+// 6.7e-16; a last root with 97 % of its weight in one box 1.5 intervals away 3.8e-16 and 5.7e-16.
 constexpr double FV_SEP_T = 1.5;
+constexpr double FV_SEP_BWD = 3.0;  // the adjoint's, as its lists' (1/t^2 and 1/t^3 lose more)
 constexpr int FV_MIN_EXP = 4;  // fewer boxes: the interpolation costs more than it saves
 // A launch uses the expansion once its items give every CU two workgroups: from there the
 // FP64 pipe is the bound (1024 items, one problem of 65536 with 64 columns: 232 -> 173 us with
@@ -71,8 +75,9 @@ __device__ __forceinline__ int fv_split_far(const FmmArgs &f, const FmmVec &v, i
             // the box's end sources: its nodes descend (a leaf of few poles keeps them
             // ascending instead, but that is a problem's last leaf, whose nearest is the first)
             const double *nd2 = v.vnode + (int64_t)g * FMM_P;
-            const double dist = fmin(fabs(nd2[0] - iv.x), fabs(nd2[FMM_P - 1] - iv.x)) - iv.y;
-            ex = expand && iv.y > 0.0 && dist >= FV_SEP_T * 2.0 * iv.y;
+            const double c = v.vcen ? v.vcen[g] - iv.x : -iv.x;
+            const double dist = fmin(fabs(nd2[0] + c), fabs(nd2[FMM_P - 1] + c)) - iv.y;
+            ex = expand && iv.y > 0.0 && dist >= v.sep_t * 2.0 * iv.y;
         }
         const unsigned long long md = __ballot(in && !ex), me = __ballot(ex);
         auto rank = [&](unsigned long long mk) {

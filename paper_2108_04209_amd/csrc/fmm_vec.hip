@@ -112,12 +112,25 @@ __global__ __launch_bounds__(LEAVES ? 64 : 256, LEAVES ? 1 : 4) void k_fmmv_sour
     };
     const double a = d[lo], b = d[hi - 1];
     const double cc = 0.5 * (a + b), hw = 0.5 * (b - a);
+    // the adjoint's nodes are offsets from cc (rounded as positions, they would lie eps |d| off
+    // their place, which shows at a distance of 64 poles), its points' from the roots' own pairs
+    const bool rel = v.vcen != nullptr;
+    const double nc = rel ? 0.0 : cc;
+    const double lim = rel ? 1.0 + 0x1p-20 : 1.0;  // the ends were rounded as positions
+    auto point = [&](int k) {  // pole or root k of a leaf, from cc
+        if (v.kern != 4) return d[k] - cc;
+        const double4 r = v.rk[base + k];
+        return (r.x - cc) + r.y;
+    };
     double *node = v.vnode + (int64_t)g * FMM_P;
     double *w = v.vw + (int64_t)g * FMM_P * m + g0;
     if (LEAVES && hi - lo <= FMM_P) {  // few poles: they are their own equivalent sources
         if (tid < FMM_P) {
             const bool in = lo + tid < hi;
-            if (blockIdx.y == 0) node[tid] = in ? d[lo + tid] : cc;
+            if (blockIdx.y == 0) {
+                node[tid] = !in ? nc : rel ? point(lo + tid) : d[lo + tid];
+                if (rel && tid == 0) v.vcen[g] = cc;
+            }
             for (int c = 0; c < mg; ++c) {
                 int st;
                 const double *wc = column(c, st);
@@ -178,9 +191,16 @@ __global__ __launch_bounds__(LEAVES ? 64 : 256, LEAVES ? 1 : 4) void k_fmmv_sour
         }
         const int k = k0 + tid;
         if (k < pk1) {
-            const double x = LEAVES ? d[lo + k]
-                                    : v.vnode[(int64_t)(f.box_off[qf] + leaf0) * FMM_P + k];
-            const double t = fmin(1.0, fmax(-1.0, (x - cc) * ihw));
+            double x;  // the point from cc
+            if (LEAVES) {
+                x = point(lo + k);
+            } else {
+                const int64_t b0 = f.box_off[qf] + leaf0;
+                x = v.vnode[b0 * FMM_P + k];
+                x = rel ? (v.vcen[b0 + k / FMM_P] - cc) + x : x - cc;
+            }
+            // (a box of one position: ihw is infinite, and every node lies there)
+            const double t = fmin(lim, fmax(-lim, x * ihw));
             int hit = -1;
             double inv[FMM_P], den = 0.0;
 #pragma unroll
@@ -236,7 +256,10 @@ __global__ __launch_bounds__(LEAVES ? 64 : 256, LEAVES ? 1 : 4) void k_fmmv_sour
             else if (cn < mg)
                 w[qn * m + cn] = s2;
         }
-        if (it.y == 0 && blockIdx.y == 0 && tid < FMM_P) node[tid] = cc + hw * tq[tid];
+        if (it.y == 0 && blockIdx.y == 0 && tid < FMM_P) {
+            node[tid] = nc + hw * tq[tid];
+            if (rel && tid == 0) v.vcen[g] = cc;
+        }
         return;
     }
     mfma_drain();
@@ -1197,6 +1220,7 @@ hipError_t launch_fmmv_eval(const SolveArgs &it, const FmmArgs &f, const FmmVec 
                             int num_cu, hipStream_t s) {
     if (it.ntiles <= 0) return hipSuccess;
     FmmVec v = v0;
+    v.sep_t = FV_SEP_T;
     // the MFMA for a dense enough block of columns, and for every sum over the roots
     const bool mfma = v.kern == 1 && (v.m >= 4 || v.fuse_b || v.trans == 0);
     v.work = trace_work(mfma ? KID_FMMV_EVAL_MFMA : KID_FMMV_EVAL);
