@@ -868,8 +868,11 @@ int apply_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const d
     superdc_batch *bm = const_cast<superdc_batch *>(b);
     const TileList *L = tile_list(bm, TILE);
     if (!L) return SUPERDC_ENOMEM;
-    // few columns: the VALU kernel does less work, the MFMA kernel is the faster alone (one
-    // problem of 100 roots and one column: 3 against 9 us)
+    // few columns: the VALU kernel does less work, but in launches of less than two tiles a CU a
+    // wavefront's chain of sources bounds it, and the MFMA kernel's teams are the faster up to the
+    // line whatever the sizes (VALU against MFMA, one column, us a call: one problem of 100
+    // roots 11.7 and 9.2, 511 of 64 12.4 and 9.4, 100 of 300 20.7 and 13.7, 31 of 1000 45 and 32,
+    // 7 of 4096 168 and 109)
     const int use_mfma = fuse_b || o.apply_kernel == 2 ||
                          (o.apply_kernel == 0 && (m >= 4 || L->count < 2 * ctx->num_cu));
     // Y = Qhat^T X of the large problems by the eigenvector-side FMM (the sums run over the

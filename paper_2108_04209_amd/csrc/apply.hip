@@ -85,6 +85,7 @@ __device__ __forceinline__ void apply_store(int n, int s0, int ncols, int tid,
     }
 }
 
+// FEW: one to three columns, as exact as the VALU kernel that takes them in larger launches.
 // NCT: 16-column blocks per pass (the pass width is 16 NCT columns); this item's pass starts
 // at column c0.  FB: form b beside the columns.  TEAMS teams of four wavefronts take the
 // reduction's chunks in turn and add their sums in team order, for launches with too few items
@@ -96,7 +97,7 @@ struct ApplyTeam {
     double2 Sd[2][AP_K];
 };
 
-template <int TRANS, int NCT, bool FB, int TEAMS>
+template <int TRANS, int NCT, bool FB, int TEAMS, bool FEW>
 __device__ void apply_tile_mfma(const ApplyArgs &a, Tile t, int c0, ApplyTeam<NCT> *sh) {
     const int p = t.prob;
     const int64_t base = a.off[p];
@@ -148,13 +149,14 @@ __device__ void apply_tile_mfma(const ApplyArgs &a, Tile t, int c0, ApplyTeam<NC
             apply_fetch<TRANS, NCT>(a, base, n, (ci + TEAMS) * AP_K, c0, ncols, tid, st);
         if (!live) continue;
         // one step of 4 sources: this lane's Cauchy entry (one reciprocal with a Newton
-        // step) into the MFMA of every column tile; padding entries have weight zero at the
-        // position of the problem's last source
+        // step, FEW: with two) into the MFMA of every column tile; padding entries have weight
+        // zero at the position of the problem's last source
 #pragma unroll 4
         for (int kk = 0; kk < AP_K; kk += 4) {
             const int sl = kk + (lane >> 4);
             const double2 sd = Sb[sl];
-            const double av = rcp_nr1(TRANS ? (sd.x - ra) - rb : (ra - sd.x) - sd.y);
+            const double t = TRANS ? (sd.x - ra) - rb : (ra - sd.x) - sd.y;
+            const double av = FEW ? rcp_nr(t) : rcp_nr1(t);
 #pragma unroll
             for (int ct = 0; ct < NCT; ++ct) {
                 const double bv = Xb[(ct * 16 + (lane & 15)) * AP_LD + sl];
@@ -217,12 +219,12 @@ __device__ void apply_tile_mfma(const ApplyArgs &a, Tile t, int c0, ApplyTeam<NC
     }
 }
 
-template <int TRANS, int NCT, bool FB, int TEAMS>
+template <int TRANS, int NCT, bool FB, int TEAMS, bool FEW>
 __global__ __launch_bounds__(256 * TEAMS) void k_apply_mfma(ApplyArgs a) {
     __shared__ ApplyTeam<NCT> sh[TEAMS];
     const int np = (a.m + 16 * NCT - 1) / (16 * NCT);  // passes of a tile: neighbouring items
     const int item = xcd_item();
-    apply_tile_mfma<TRANS, NCT, FB, TEAMS>(a, a.tiles[item / np], item % np * (16 * NCT), sh);
+    apply_tile_mfma<TRANS, NCT, FB, TEAMS, FEW>(a, a.tiles[item / np], item % np * (16 * NCT), sh);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -337,7 +339,19 @@ hipError_t launch_apply(const ApplyArgs &a0, int use_mfma, int max_n, int num_cu
         const dim3 g(items());
         const bool teams = nct == 1 && items() <= 2 * num_cu && max_n > 2 * AP_K;
 #define SDC_APPLY_MFMA(T, C, FB, K)                                                         \
-    SDC_LAUNCH(KID_APPLY_MFMA, (k_apply_mfma<T, C, FB, K>), g, dim3(256 * K), 0, s, a)
+    SDC_LAUNCH(KID_APPLY_MFMA, (k_apply_mfma<T, C, FB, K, false>), g, dim3(256 * K), 0, s, a)
+#define SDC_APPLY_FEW(T, K) \
+    SDC_LAUNCH(KID_APPLY_MFMA, (k_apply_mfma<T, 1, false, K, true>), g, dim3(256 * K), 0, s, a)
+        if (a.m < 4 && !a.fuse_b) {
+            if (a.trans) {
+                if (teams) SDC_APPLY_FEW(1, 4);
+                else SDC_APPLY_FEW(1, 1);
+            } else {
+                if (teams) SDC_APPLY_FEW(0, 4);
+                else SDC_APPLY_FEW(0, 1);
+            }
+            return hipGetLastError();
+        }
         if (a.trans) {
             if (a.fuse_b && teams) SDC_APPLY_MFMA(1, 1, true, 4);
             else if (a.fuse_b) SDC_APPLY_MFMA(1, 1, true, 1);
@@ -351,6 +365,7 @@ hipError_t launch_apply(const ApplyArgs &a0, int use_mfma, int max_n, int num_cu
             else if (nct == 2) SDC_APPLY_MFMA(0, 2, false, 1);
             else SDC_APPLY_MFMA(0, 4, false, 1);
         }
+#undef SDC_APPLY_FEW
 #undef SDC_APPLY_MFMA
     } else {
         const dim3 g(a.ntiles);

@@ -657,8 +657,9 @@ struct FvShared {
     double node[FMM_P], bary[FMM_P];  // FV_NODE and FV_BARY (read by lane)
 };
 
-// gi: the group of NC blocks of FMMV_MAX_M columns of the pass
-template <int TRANS, bool FB, int TEAMS, int NC>
+// gi: the group of NC blocks of FMMV_MAX_M columns of the pass.  FEW: the last block has one to three
+// columns, which are as exact as fmmv_item's, that takes so few alone
+template <int TRANS, bool FB, int TEAMS, int NC, bool FEW>
 __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmVec &v, Tile t,
                                int gi, FvShared<TEAMS, NC> &sh) {
     static_assert(NC == 1 || (TEAMS == 1 && !FB), "one block of columns for teams and b");
@@ -759,13 +760,14 @@ __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmV
         }
         if (!live) continue;
         // a step of 4 sources: the Cauchy entry of this lane's row (one reciprocal with a
-        // Newton step) into the MFMA
+        // Newton step, FEW: with two) into the MFMA
         auto multiply = [&](auto is_near) {
 #pragma unroll 4
             for (int kk = 0; kk < FV_K; kk += 4) {
                 const int sl = kk + (lane >> 4);
                 const double2 sd = Sd[sl];
-                const double av = rcp_nr1(TRANS ? (sd.x - ra) - rb : (ra - sd.x) - sd.y);
+                const double t = TRANS ? (sd.x - ra) - rb : (ra - sd.x) - sd.y;
+                const double av = FEW ? rcp_nr(t) : rcp_nr1(t);
 #pragma unroll
                 for (int b = 0; b < NC; ++b) {
                     const double bv = Xs[(16 * b + (lane & 15)) * FV_LD + sl];
@@ -931,7 +933,7 @@ __device__ void fmmv_item_mfma(const SolveArgs &it, const FmmArgs &f, const FmmV
     }
 }
 
-template <int TRANS, bool FB, int TEAMS, int NC>
+template <int TRANS, bool FB, int TEAMS, int NC, bool FEW>
 __global__ __launch_bounds__(256 * TEAMS, NC == 1 ? 4 : 3) void k_fmmv_eval_mfma(SolveArgs it,
                                                                                  FmmArgs f,
                                                                                  FmmVec v) {
@@ -943,7 +945,7 @@ __global__ __launch_bounds__(256 * TEAMS, NC == 1 ? 4 : 3) void k_fmmv_eval_mfma
     // the column groups of a tile are neighbouring items: they read the same lists and poles
     const int ng = (v.m + NC * FMMV_MAX_M - 1) / (NC * FMMV_MAX_M);
     const int item = xcd_item();
-    fmmv_item_mfma<TRANS, FB, TEAMS, NC>(it, f, v, it.tiles[item / ng], item % ng, sh);
+    fmmv_item_mfma<TRANS, FB, TEAMS, NC, FEW>(it, f, v, it.tiles[item / ng], item % ng, sh);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1227,30 +1229,29 @@ hipError_t launch_fmmv_eval(const SolveArgs &it, const FmmArgs &f, const FmmVec 
     if (mfma) {
         const int groups = (v.m + FMMV_MAX_M - 1) / FMMV_MAX_M, items = it.ntiles * groups;
         const int wide = (groups + 1) / 2;
+        const bool few = v.trans && !v.fuse_b && (v.m - 1) % FMMV_MAX_M < 3;
+#define SDC_FV(T, FB, K, N, FEW)                                                                   \
+    SDC_LAUNCH(KID_FMMV_EVAL_MFMA, (k_fmmv_eval_mfma<T, FB, K, N, FEW>), g, dim3(256 * K), 0, s, it, f, v)
         if (!v.fuse_b && groups > 1 &&
             it.ntiles * wide >= (groups == 3 ? FV_WIDE3_PER_CU : FV_WIDE_PER_CU) * num_cu) {
-            const dim3 gw(it.ntiles * wide);
-            if (v.trans == 0)
-                SDC_LAUNCH(KID_FMMV_EVAL_MFMA, (k_fmmv_eval_mfma<0, false, 1, 2>), gw, dim3(256), 0,
-                           s, it, f, v);
-            else
-                SDC_LAUNCH(KID_FMMV_EVAL_MFMA, (k_fmmv_eval_mfma<1, false, 1, 2>), gw, dim3(256), 0,
-                           s, it, f, v);
+            const dim3 g(it.ntiles * wide);
+            if (v.trans == 0) SDC_FV(0, false, 1, 2, false);
+            else if (few) SDC_FV(1, false, 1, 2, true);
+            else SDC_FV(1, false, 1, 2, false);
             return hipGetLastError();
         }
         const int teams = items >= FV_EXPAND_PER_CU * num_cu ? 1 : items >= num_cu ? 2 : 4;
         const dim3 g(items);
-#define SDC_FV(T, FB, K) \
-    SDC_LAUNCH(KID_FMMV_EVAL_MFMA, (k_fmmv_eval_mfma<T, FB, K, 1>), g, dim3(256 * K), 0, s, it, f, v)
-#define SDC_FV_TEAMS(T, FB)              \
-    {                                    \
-        if (teams == 1) SDC_FV(T, FB, 1);     \
-        else if (teams == 2) SDC_FV(T, FB, 2); \
-        else SDC_FV(T, FB, 4);           \
+#define SDC_FV_TEAMS(T, FB, FEW)                     \
+    {                                                \
+        if (teams == 1) SDC_FV(T, FB, 1, 1, FEW);    \
+        else if (teams == 2) SDC_FV(T, FB, 2, 1, FEW); \
+        else SDC_FV(T, FB, 4, 1, FEW);               \
     }
-        if (v.trans == 0) SDC_FV_TEAMS(0, false)
-        else if (v.fuse_b) SDC_FV_TEAMS(1, true)
-        else SDC_FV_TEAMS(1, false)
+        if (v.trans == 0) SDC_FV_TEAMS(0, false, false)
+        else if (v.fuse_b) SDC_FV_TEAMS(1, true, false)
+        else if (few) SDC_FV_TEAMS(1, false, true)
+        else SDC_FV_TEAMS(1, false, false)
 #undef SDC_FV_TEAMS
 #undef SDC_FV
         return hipGetLastError();
