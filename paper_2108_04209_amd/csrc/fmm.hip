@@ -378,10 +378,14 @@ __global__ __launch_bounds__(FMM_PL * LOC_PARTS) void k_fmm_local(FmmArgs f) {
     const double tm = LOC_COS[2 * m + 1];
     const double x = cw.x + cw.y * tm;
     double ps = 0.0, dps = 0.0, ph = 0.0, dph = 0.0;
-    // the sources left of the leaf (far boxes' equivalent sources, then flagged poles) and those
-    // right of it, each side padded to an even number; ranges by the first wavefront
+    // two sources share a reciprocal while every |t| lies inside [2^-300, 2^300], as in the solver
+    // (w t^2 has to stay in range): at least sep_loc interval widths, and what the poles span
     const int64_t base = f.off[p];
     const double2 *dw = f.dw + base;
+    const double tmax = fmax(cw.x + cw.y - dw[0].x, dw[f.off[p + 1] - base - 1].x - (cw.x - cw.y));
+    const bool pairs = 2.0 * f.sep_loc * cw.y >= 0x1p-300 && tmax <= 0x1p300;
+    // the sources left of the leaf (far boxes' equivalent sources, then flagged poles) and those
+    // right of it, each side padded to an even number; ranges by the first wavefront
     if (tid < WAVE) {
         const int i0 = (L - f.leaf_off[q]) * f.leaf;
         int lo = 0, len = 0;
@@ -439,14 +443,13 @@ __global__ __launch_bounds__(FMM_PL * LOC_PARTS) void k_fmm_local(FmmArgs f) {
         for (int e = 2 * u; e < cnt; e += 2 * LOC_PARTS) {
             const double2 a = src[e], b = src[e + 1];
             const double t0 = a.x - x, t1 = b.x - x;
-            const double pr = fabs(t0 * t1);
             double s0, s1;
-            if (pr > 0x1p-900 && pr < 0x1p900) {
+            if (pairs) {
                 const double R = rcp_nr(t0 * t1);
                 const double u0 = a.y * t1, u1 = b.y * t0;
                 s0 = (u0 + u1) * R;
                 s1 = __builtin_fma(u0, t1, u1 * t0) * R * R;
-            } else {  // the product would leave the exponent range: one source at a time
+            } else {  // one source at a time
                 const double r0 = rcp_nr(t0), r1 = rcp_nr(t1);
                 s0 = a.y * r0 + b.y * r1;
                 s1 = a.y * r0 * r0 + b.y * r1 * r1;
