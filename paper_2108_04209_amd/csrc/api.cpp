@@ -101,9 +101,9 @@ class Upload {
         if (!v.empty()) std::memcpy(buf_.data() + at, v.data(), sizeof(T) * v.size());
     }
     // the device memory that holds them all (nullptr on failure; *err: why)
-    void *commit(hipError_t *err) {
+    void *commit(superdc_ctx *ctx, hipError_t *err) {
         void *mem = nullptr;
-        *err = hipMalloc(&mem, buf_.size());
+        *err = dev_alloc(ctx, &mem, buf_.size());
         if (*err != hipSuccess) return nullptr;
         *err = hipMemcpy(mem, buf_.data(), buf_.size(), hipMemcpyHostToDevice);
         if (*err != hipSuccess) {
@@ -166,7 +166,7 @@ const TileList *tile_list(superdc_batch *b, int chunk) {
     Upload up;
     list_add(b, chunk, up);
     hipError_t e;
-    void *mem = up.commit(&e);
+    void *mem = up.commit(b->ctx, &e);
     if (!mem) {
         l.count = 0;
         return nullptr;
@@ -298,7 +298,7 @@ bool dir_list(const superdc_batch *b, FmmPlan *fp, int C, SolveArgs &a) {
         Upload up;
         dir_add(b, fp, C, up);
         hipError_t e;
-        void *mem = up.commit(&e);
+        void *mem = up.commit(b->ctx, &e);
         if (!mem) {
             fp->dir_built[slot] = false;
             return false;
@@ -351,8 +351,11 @@ bool fmm_arrays(FmmPlan *fp, superdc_batch *b, hipError_t *err) {
     }
     fp->work = b->spare->take(up.size(), &fp->work_cap);
     if (!fp->work) {
-        *err = hipMalloc(&fp->work, up.size());
-        if (*err != hipSuccess) return false;
+        *err = dev_alloc(b->ctx, &fp->work, up.size());
+        if (*err != hipSuccess) {
+            fp->work = nullptr;
+            return false;
+        }
         fp->work_cap = up.size();
     }
     up.place(fp->work);
@@ -507,7 +510,7 @@ FmmPlan *fmm_plan(superdc_batch *b, int leaf, int crossover) {
     for (int C : {(int)TILE, fp->lds_chunk, b->sec.chunk}) dir_add(b, fp, C, up);
     for (FmmLists *l : {&fp->own, &fp->roots}) up.add(&l->used, std::vector<int32_t>(fp->nboxes, 0));
     hipError_t e;
-    if (!(fp->mem = up.commit(&e)) || !fmm_arrays(fp, b, &e)) {
+    if (!(fp->mem = up.commit(b->ctx, &e)) || !fmm_arrays(fp, b, &e)) {
         fmm_free(fp, b, true);
         return nullptr;
     }
@@ -605,7 +608,7 @@ FmmPlan *fmm_for(superdc_batch *b, const superdc_opts &o, int &rc, double pairs 
 
 // the arrays for the equivalent weights of a pass of `cols` columns: those of wide passes are
 // allocated, for the widest, by the batch's first such call; false: out of memory
-bool fmmv_space(FmmPlan *fp, int cols, FmmArgs &f, FmmVec &v) {
+bool fmmv_space(superdc_ctx *ctx, FmmPlan *fp, int cols, FmmArgs &f, FmmVec &v) {
     const int wide = cols > FMMV_MAX_M;
     if (wide && !fp->vw[1]) {
         const int most = fmmv_max_pass(fp);
@@ -613,7 +616,10 @@ bool fmmv_space(FmmPlan *fp, int cols, FmmArgs &f, FmmVec &v) {
         w.add(&fp->vw[1], (size_t)fp->nboxes * FMM_P * most);
         w.add(&fp->vpart[1], (size_t)fp->nslot * FMM_P * most);
         void *mem = nullptr;
-        if (hipMalloc(&mem, w.size()) != hipSuccess) return false;
+        if (dev_alloc(ctx, &mem, w.size()) != hipSuccess) {
+            fp->vw[1] = fp->vpart[1] = nullptr;
+            return false;
+        }
         fp->allocs.push_back(mem);
         w.place(mem);
     }
@@ -649,6 +655,12 @@ hipError_t fmmv_run(superdc_ctx *ctx, const superdc_batch *b, const FmmPlan *fp,
 }  // namespace
 
 namespace sdc {
+hipError_t dev_alloc(superdc_ctx *ctx, void **p, size_t bytes) {
+    const hipError_t e = hipMalloc(p, bytes > ctx->alloc_limit ? (size_t)1 << 60 : bytes);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e;
+}
+
 void *SpareBlock::take(size_t bytes, size_t *cap) {
     std::lock_guard<std::mutex> g(mu_);
     int dev = -1;
@@ -692,7 +704,7 @@ void *ws_get(superdc_ctx *ctx, int slot, size_t bytes) {
     }
     size_t cap = std::max(bytes, ctx->ws_cap[slot] + ctx->ws_cap[slot] / 2);
     void *p = nullptr;
-    if (hipMalloc(&p, cap) != hipSuccess) return nullptr;
+    if (dev_alloc(ctx, &p, cap) != hipSuccess) return nullptr;
     ctx->ws[slot] = p;
     ctx->ws_cap[slot] = cap;
     return p;
@@ -771,7 +783,7 @@ int loewner_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const
         v.bout = bnorm;
         v.zh = zhat;
         f = fmm_vec_args(fp, b, d, eta, origin, status);
-        if (fmm_b && !fmmv_space(fp, 1, f, v)) return SUPERDC_ENOMEM;
+        if (fmm_b && !fmmv_space(ctx, fp, 1, f, v)) return SUPERDC_ENOMEM;
         lf.pd = pairs;
         lf.geo = fp->lgeo;
         lf.mom = fp->lmom;
@@ -936,7 +948,7 @@ int apply_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const d
         if (lists) f.gen = ++fp->own.gen;  // built with the first columns below
     }
     const int pass = std::min(m + v.fuse_b, fmmv_max_pass(fp));  // one pass when fused
-    if (!fmmv_space(fp, pass, f, v)) return SUPERDC_ENOMEM;
+    if (!fmmv_space(ctx, fp, pass, f, v)) return SUPERDC_ENOMEM;
     for (int c0 = 0; c0 < m; c0 += pass) {
         v.m = std::min(pass, m + v.fuse_b - c0);
         v.X = X + (int64_t)c0 * ldx;
@@ -962,6 +974,9 @@ void superdc_opts_default(superdc_opts *o) {
     o->persistent = 1;
     o->apply_kernel = 0;
 }
+
+// for tests (not in the header): device allocations of more than `bytes` fail on this context
+void superdc_test_alloc_limit(superdc_ctx *ctx, size_t bytes) { ctx->alloc_limit = bytes; }
 
 const char *superdc_strerror(int code) {
     switch (code) {
@@ -1060,7 +1075,7 @@ int superdc_batch_create(superdc_ctx *ctx, int32_t nprob, const int64_t *off_hos
         up.add(&b->vst, std::vector<int32_t>((size_t)nprob * b->vsplit));
     }
     hipError_t e;
-    void *mem = up.commit(&e);
+    void *mem = up.commit(ctx, &e);
     if (!mem) {
         superdc_batch_destroy(b);
         return hip_fail(e);
@@ -1245,7 +1260,7 @@ int superdc_secular_backward(superdc_ctx *ctx, const superdc_batch *b, const dou
         if (fp) {
             pos = (double *)ws_get(ctx, WS_VPAIR, sizeof(double2) * b->total);
             ke = (double2 *)ws_get(ctx, WS_KE, sizeof(double2) * b->total);
-            if (!pos || !ke || !fmmv_space(fp, g_proj ? 3 : 1, f, v)) fp = nullptr;
+            if (!pos || !ke || !fmmv_space(ctx, fp, g_proj ? 3 : 1, f, v)) fp = nullptr;
         }
         a.tiles = fp ? fp->dir_lpt[chunk_slot(TILE)] : L->lpt;
         a.ntiles = fp ? fp->dir_count[chunk_slot(TILE)] : L->count;

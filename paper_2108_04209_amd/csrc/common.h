@@ -238,6 +238,7 @@ struct superdc_ctx {
     size_t ws_cap[kNumWs] = {0};
     int fmm_crossover = 1024;      // automatic method: FMM for problems at least this large (measured)
     std::shared_ptr<sdc::SpareBlock> spare;
+    size_t alloc_limit = ~(size_t)0;  // larger requests fail (dev_alloc; set by tests alone)
 };
 
 namespace sdc {
@@ -318,6 +319,9 @@ int apply_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const d
               double *Y, int64_t ldy, const superdc_opts *opts, void *stream, bool reuse_lists,
               bool fuse_b = false);
 
+// hipMalloc for the library's own arrays.  A failure leaves no error behind in the runtime: the
+// launches that follow, of a fallback or of a caller's next attempt, ask for the last error
+hipError_t dev_alloc(superdc_ctx *ctx, void **p, size_t bytes);
 // grow a workspace slot to at least `bytes`; returns nullptr on allocation failure
 void *ws_get(superdc_ctx *ctx, int slot, size_t bytes);
 

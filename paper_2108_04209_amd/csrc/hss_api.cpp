@@ -89,7 +89,7 @@ namespace {
 template <typename T>
 hipError_t alloc(superdc_hss *h, T **p, size_t count) {
     void *q = nullptr;
-    hipError_t e = hipMalloc(&q, sizeof(T) * std::max<size_t>(count, 1));
+    hipError_t e = dev_alloc(h->ctx, &q, sizeof(T) * std::max<size_t>(count, 1));
     if (e == hipSuccess) {
         h->allocs.push_back(q);
         *p = (T *)q;
@@ -476,8 +476,8 @@ int superdc_hss_autotune(superdc_ctx *ctx, superdc_hss *h, const double *leaf_D,
     if (opts && opts->hss_tau != 0.0) return SUPERDC_EINVAL;  // deflated batches vary per pass
     double *lam = nullptr;
     int32_t *st = nullptr;
-    hipError_t e = hipMalloc(&lam, sizeof(double) * (size_t)h->n);
-    if (e == hipSuccess) e = hipMalloc(&st, sizeof(int32_t));
+    hipError_t e = dev_alloc(ctx, (void **)&lam, sizeof(double) * (size_t)h->n);
+    if (e == hipSuccess) e = dev_alloc(ctx, (void **)&st, sizeof(int32_t));
     int rc = e == hipSuccess ? SUPERDC_OK : fail(e);
     if (rc == SUPERDC_OK) {
         h->tune = true;

@@ -117,15 +117,15 @@ int superdc_autotune(superdc_ctx *ctx, superdc_batch *b, const double *d, const 
     double *lam = nullptr, *eta = nullptr, *zh = nullptr, *bn = nullptr, *gd = nullptr,
            *gz = nullptr, *gr = nullptr;
     int32_t *org = nullptr, *st = nullptr;
-    hipError_t e = hipMalloc(&lam, sizeof(double) * n);
-    if (e == hipSuccess) e = hipMalloc(&eta, sizeof(double) * n);
-    if (e == hipSuccess) e = hipMalloc(&zh, sizeof(double) * n);
-    if (e == hipSuccess) e = hipMalloc(&bn, sizeof(double) * n);
-    if (e == hipSuccess) e = hipMalloc(&gd, sizeof(double) * n);
-    if (e == hipSuccess) e = hipMalloc(&gz, sizeof(double) * n);
-    if (e == hipSuccess) e = hipMalloc(&gr, sizeof(double) * b->nprob);
-    if (e == hipSuccess) e = hipMalloc(&org, sizeof(int32_t) * n);
-    if (e == hipSuccess) e = hipMalloc(&st, sizeof(int32_t) * b->nprob);
+    hipError_t e = dev_alloc(ctx, (void **)&lam, sizeof(double) * n);
+    if (e == hipSuccess) e = dev_alloc(ctx, (void **)&eta, sizeof(double) * n);
+    if (e == hipSuccess) e = dev_alloc(ctx, (void **)&zh, sizeof(double) * n);
+    if (e == hipSuccess) e = dev_alloc(ctx, (void **)&bn, sizeof(double) * n);
+    if (e == hipSuccess) e = dev_alloc(ctx, (void **)&gd, sizeof(double) * n);
+    if (e == hipSuccess) e = dev_alloc(ctx, (void **)&gz, sizeof(double) * n);
+    if (e == hipSuccess) e = dev_alloc(ctx, (void **)&gr, sizeof(double) * b->nprob);
+    if (e == hipSuccess) e = dev_alloc(ctx, (void **)&org, sizeof(int32_t) * n);
+    if (e == hipSuccess) e = dev_alloc(ctx, (void **)&st, sizeof(int32_t) * b->nprob);
     int rc = e == hipSuccess ? SUPERDC_OK : SUPERDC_ENOMEM;
     const int reps = 2;
     if (rc == SUPERDC_OK) {
