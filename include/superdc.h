@@ -130,13 +130,14 @@ int64_t superdc_batch_total(const superdc_batch *batch);
 
 /*
  * Autotune the batch's launch shapes on representative data (d, z, rho as for
- * superdc_secular_solve): the secular solver's work-item length (64..512 roots) and split
- * (wavefronts sharing one work item, 1..16), the split of the FMM solver's work items
- * (1..8) when opts select the FMM for some problem, and the splits of the Loewner/b and
- * adjoint kernels, each timed on `stream`.  Synchronises the stream and allocates scratch; call it
- * once, before capturing graphs.  With SUPERDC_TUNE_CACHE set to a file path the choice is
- * read from / appended to that file, keyed by the problem sizes and the CU count.
- * Without tuning a heuristic shape is used.  Results of the solver can differ in the last
+ * superdc_secular_solve): the work-item length (64..512 roots) and split (wavefronts sharing
+ * one work item, 1..16) of the solver that takes direct problems above 4096 roots and the
+ * ablations, the wavefronts of the FMM solver's work items (1..8), and the splits of the
+ * Loewner/b and adjoint kernels, each timed on `stream` where opts have some launch read it
+ * (the solver of direct problems up to 4096 roots takes a shape of its own).  Synchronises the
+ * stream and allocates scratch; call it once, before capturing graphs.  With SUPERDC_TUNE_CACHE
+ * set to a file path the choice is read from / appended to that file, keyed by the problem
+ * sizes and the CU count.  Without tuning a heuristic shape is used.  Results of the solver can differ in the last
  * bits between shapes (the near/far split of some pole-root pairs moves).
  */
 int superdc_autotune(superdc_ctx *ctx, superdc_batch *batch, const double *d, const double *z,

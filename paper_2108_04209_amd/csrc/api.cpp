@@ -80,6 +80,33 @@ int fmm_crossover_of(const superdc_batch *b, const superdc_opts &o, double pairs
     return direct ? 0x7fffffff : b->ctx->fmm_crossover;
 }
 
+namespace {
+double bwd_pairs(const superdc_batch *b) { return b->max_n <= DIRECT_BWD_N ? DIRECT_BWD_PAIRS : 1.0; }
+
+int largest_below(const superdc_batch *b, const superdc_opts &o, int crossover) {
+    if (b->max_n < crossover) return b->max_n;
+    int64_t most = 0;
+    for (int p = 0; p < b->nprob; ++p) {
+        const int64_t n = b->off_h[p + 1] - b->off_h[p];
+        if (n < crossover || n < 2 * o.fmm_leaf) most = std::max(most, n);
+    }
+    return (int)most;
+}
+}  // namespace
+
+int largest_direct(const superdc_batch *b, const superdc_opts &o) {
+    return largest_below(b, o, fmm_crossover_of(b, o));
+}
+int largest_direct_bwd(const superdc_batch *b, const superdc_opts &o) {
+    return largest_below(b, o, fmm_crossover_of(b, o, bwd_pairs(b)));
+}
+bool solve_in_lds(int max_dir, const superdc_opts &o) {
+    return max_dir <= SECL_MAX_N && !o.unshifted && !o.interp;
+}
+bool vectors_in_one(const superdc_batch *b, const superdc_opts &o) {
+    return o.persistent && b->max_n <= VS_N && b->max_n < fmm_crossover_of(b, o);
+}
+
 int chunk_slot(int chunk) {
     for (int i = 0; i < kNumChunks; ++i)
         if (chunk == MIN_CHUNK << i) return i;
@@ -746,7 +773,7 @@ int loewner_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const
     a.zhat = zhat;
     a.bnorm = bnorm;
     superdc_batch *bm = const_cast<superdc_batch *>(b);
-    if (fmm_b && o.persistent && b->max_n <= VS_N && b->max_n < fmm_crossover_of(b, o)) {
+    if (fmm_b && vectors_in_one(b, o)) {
         SDC_HIP(launch_vectors_small(a, b->nprob, b->max_n, s));
         return SUPERDC_OK;
     }
@@ -1141,7 +1168,7 @@ int superdc_secular_solve(superdc_ctx *ctx, const superdc_batch *b, const double
         // and one over the target leaves of the FMM problems
         const LaunchShape sh = b->sec;
         const int max_dir = fp ? fp->max_dir : b->max_n;  // largest direct problem
-        const bool lds = max_dir <= SECL_MAX_N && !o.unshifted && !o.interp;
+        const bool lds = solve_in_lds(max_dir, o);
         a.chunk = !lds ? sh.chunk : fp ? fp->lds_chunk : b->lds_chunk;
         if (fp) {
             if (!dir_list(b, fp, a.chunk, a)) return SUPERDC_ENOMEM;
@@ -1251,7 +1278,7 @@ int superdc_secular_backward(superdc_ctx *ctx, const superdc_batch *b, const dou
         // the large problems through the FMM; all of them directly where its workspace does
         // not fit
         int rc;
-        FmmPlan *fp = fmm_for(bm, o, rc, b->max_n <= DIRECT_BWD_N ? DIRECT_BWD_PAIRS : 1.0);
+        FmmPlan *fp = fmm_for(bm, o, rc, bwd_pairs(b));
         const int nw = g_proj ? 2 : 1;  // weights of a pole; of a root one more with projections
         double *pos = nullptr;
         double2 *ke = nullptr;

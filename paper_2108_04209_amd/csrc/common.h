@@ -295,6 +295,15 @@ int opts_check(const superdc_opts *o);
 // problems of at least this many roots use the triangular FMM under these options: in the solver,
 // Loewner and b calls, and (apply) in the Cauchy applies
 int fmm_crossover_of(const superdc_batch *b, const superdc_opts &o, double pairs = 0.0);
+// the largest problem that these options solve (and form zhat and b of) by direct sums, or that the
+// adjoint sums directly; 0: none
+int largest_direct(const superdc_batch *b, const superdc_opts &o);
+int largest_direct_bwd(const superdc_batch *b, const superdc_opts &o);
+// batched launches: direct problems of at most max_dir roots are solved in LDS, the others (and the
+// ablations) by the solver that reads superdc_batch::sec
+bool solve_in_lds(int max_dir, const superdc_opts &o);
+// zhat and b in one launch, which reads no split (superdc_batch::vec)
+bool vectors_in_one(const superdc_batch *b, const superdc_opts &o);
 // launch shape of the plain (one launch per problem) direct solve of an n-root problem
 ::LaunchShape plain_shape(const superdc_ctx *ctx, int64_t n);
 // the allocation-free solve's scratch array: its address on `device` is looked up once

@@ -92,7 +92,7 @@ extern "C" int superdc_secular_solve_noalloc(superdc_ctx *ctx, const superdc_bat
     hipError_t e = hipSuccess;
     if (o.persistent) {
         const LaunchShape sh = b->sec;
-        const bool lds = b->max_n <= SECL_MAX_N && !o.unshifted && !o.interp;
+        const bool lds = solve_in_lds(b->max_n, o);
         a.chunk = lds ? b->lds_chunk : sh.chunk;
         const TileList &L = b->lists[chunk_slot(a.chunk)];
         if (!L.lpt) return SUPERDC_EINVAL;  // built with the batch (or by the autotuner)

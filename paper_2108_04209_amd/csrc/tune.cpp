@@ -1,10 +1,11 @@
 // tune.cpp -- autotuner for the launch shapes of a batch.
 //
-// For the secular solver the candidates are the chunk length (64..512 roots per work
-// item) times the split (1..16 wavefronts per item sharing the pole range), and for the
-// problems that use the triangular FMM the split of its work items (1..8); for the
-// Loewner/b and adjoint kernels the split.  Each candidate is run on the caller's data
-// and timed with HIP events on the caller's stream; the fastest is kept in the batch.
+// Candidates: for the solver by scalar fetches the chunk length (64..512 roots per work item) times
+// the split (1..16 wavefronts per item sharing the pole range); for the problems that use the
+// triangular FMM the wavefronts of its work items (1..8); for the Loewner/b and adjoint kernels
+// the split.  Each candidate is run on the caller's data and timed with HIP events on the
+// caller's stream; the fastest is kept in the batch.  A shape that no launch of these options reads
+// (the solver in LDS takes its own from the batch) keeps its heuristic.
 // Results can be kept across processes in a text cache (environment variable
 // SUPERDC_TUNE_CACHE), one line per batch signature.
 #include <hip/hip_runtime.h>
@@ -35,8 +36,10 @@ uint64_t signature(const superdc_batch *b, int num_cu) {
     return h;
 }
 
-// one line per batch: "<key> <chunk> <split> <loewner split> <adjoint split> <fmm split>"
-// (fmm split 0: the heuristic); lines in any other form are skipped
+// one line per batch: "<key> <chunk> <split> <loewner split> <adjoint split> <fmm split> <version>"
+// (fmm split 0: the heuristic); lines in any other form are skipped.  Version 2: those without one
+// held shapes timed on launches that did not read them.
+constexpr int CACHE_VERSION = 2;
 bool cache_load(superdc_batch *b, uint64_t key) {
     const char *path = std::getenv("SUPERDC_TUNE_CACHE");
     if (!path) return false;
@@ -46,9 +49,10 @@ bool cache_load(superdc_batch *b, uint64_t key) {
     bool found = false;
     while (std::fgets(line, sizeof line, f)) {
         unsigned long long k;
-        int sc, ss, vs, bs, fs;
-        if (std::sscanf(line, "%llx %d %d %d %d %d", &k, &sc, &ss, &vs, &bs, &fs) != 6) continue;
-        if (k == key && sc >= 64 && sc <= 512 && ss >= 1 && ss <= 16 && vs >= 1 && vs <= 16 &&
+        int sc, ss, vs, bs, fs, version;
+        if (std::sscanf(line, "%llx %d %d %d %d %d %d", &k, &sc, &ss, &vs, &bs, &fs, &version) != 7)
+            continue;
+        if (version == CACHE_VERSION && k == key && sc >= 64 && sc <= 512 && ss >= 1 && ss <= 16 && vs >= 1 && vs <= 16 &&
             bs >= 1 && bs <= 16 && fs >= 0 && fs <= 8) {
             b->sec = LaunchShape{sc, ss};
             b->vec = LaunchShape{TILE, vs};
@@ -66,8 +70,8 @@ void cache_store(const superdc_batch *b, uint64_t key) {
     if (!path) return;
     FILE *f = std::fopen(path, "a");
     if (!f) return;
-    std::fprintf(f, "%llx %d %d %d %d %d\n", (unsigned long long)key, b->sec.chunk, b->sec.split,
-                 b->vec.split, b->bwd.split, b->fmm_ssplit);
+    std::fprintf(f, "%llx %d %d %d %d %d %d\n", (unsigned long long)key, b->sec.chunk, b->sec.split,
+                 b->vec.split, b->bwd.split, b->fmm_ssplit, CACHE_VERSION);
     std::fclose(f);
 }
 
@@ -132,8 +136,9 @@ int superdc_autotune(superdc_ctx *ctx, superdc_batch *b, const double *d, const 
         // secular solver: chunk x split
         float best = 1e30f;
         LaunchShape bs = b->sec;
-        for (int S = 1; S <= 16; S *= 2) {
-            if (S > 1 && b->max_n / S < 128) break;
+        const int max_dir = largest_direct(b, o);
+        for (int S = 1; S <= 16 && max_dir > 0 && !solve_in_lds(max_dir, o); S *= 2) {
+            if (S > 1 && max_dir / S < 128) break;
             for (int C = 512; C >= TILE; C /= 2) {
                 long wg = 0;
                 for (int p = 0; p < b->nprob; ++p) wg += (b->off_h[p + 1] - b->off_h[p] + C - 1) / C;
@@ -175,12 +180,15 @@ int superdc_autotune(superdc_ctx *ctx, superdc_batch *b, const double *d, const 
     if (rc == SUPERDC_OK) {
         float best = 1e30f;
         int bsplit = b->vec.split;
-        for (int S = 1; S <= 16; S *= 2) {
-            if (S > 1 && b->max_n / S < 16) break;
+        // (where zhat and b take one launch, zhat alone: what HSS steps run, b coming with the apply)
+        const int vec_n = largest_direct(b, o);
+        for (int S = 1; S <= 16 && vec_n > 0; S *= 2) {
+            if (S > 1 && vec_n / S < 16) break;
             b->vec.split = S;
             bool ok = true;
             const float t = time_best([&] {
-                return superdc_loewner(ctx, b, d, z, rho, eta, org, st, zh, bn, &o, stream);
+                return loewner_run(ctx, b, d, z, rho, eta, org, st, zh, bn, &o, stream, false,
+                                   !vectors_in_one(b, o));
             }, s, reps, ok);
             if (ok && t < best) {
                 best = t;
@@ -190,8 +198,9 @@ int superdc_autotune(superdc_ctx *ctx, superdc_batch *b, const double *d, const 
         b->vec.split = bsplit;
         best = 1e30f;
         bsplit = b->bwd.split;
-        for (int S = 1; S <= 16; S *= 2) {
-            if (S > 1 && b->max_n / S < 16) break;
+        const int bwd_n = largest_direct_bwd(b, o);
+        for (int S = 1; S <= 16 && bwd_n > 0; S *= 2) {
+            if (S > 1 && bwd_n / S < 16) break;
             b->bwd.split = S;
             bool ok = true;
             const float t = time_best([&] {
