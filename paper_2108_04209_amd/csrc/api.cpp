@@ -66,9 +66,12 @@ constexpr double DIRECT_APPLY_PAIRS = 9e6;
 // through all its poles), its FMM eleven launches more: direct against FMM, 16 problems of 1024
 // roots 40 and 72 us, 4 of 2048 62 and 77, 1 of 4096 108 and 84, 64 of 1024 172 and 113, 1 of
 // 8192 202 and 97, 128 of 1024 435 and 192.  The line lies where the FMM also gains on a
-// program that issues the calls itself (30 us of launches more).
+// program that issues the calls itself (30 us of launches more).  It lies there for every method,
+// since the adjoint's results don't depend on the solver's: with larger leaves, which leave more
+// to sum directly, in proportion (leaves of 256, direct against FMM: 1 problem of 4097 112 and
+// 135 us, 20 of 1100 83 and 120; 1 of 600 roots and leaves of 64 56 and 75).
 constexpr double DIRECT_BWD_PAIRS = 7e7;
-constexpr int DIRECT_BWD_N = 4096;
+constexpr int DIRECT_BWD_LEAVES = 64;  // 4096 roots in leaves of 64
 
 int fmm_crossover_of(const superdc_batch *b, const superdc_opts &o, double pairs) {
     if (o.method == 1) return 0x7fffffff;
@@ -81,7 +84,16 @@ int fmm_crossover_of(const superdc_batch *b, const superdc_opts &o, double pairs
 }
 
 namespace {
-double bwd_pairs(const superdc_batch *b) { return b->max_n <= DIRECT_BWD_N ? DIRECT_BWD_PAIRS : 1.0; }
+// whether the adjoint of the batch goes through the FMM where the options allow it
+bool bwd_by_fmm(const superdc_batch *b, const superdc_opts &o) {
+    if (b->max_n > DIRECT_BWD_LEAVES * o.fmm_leaf) return true;
+    double pairs = 0.0;
+    for (int p = 0; p < b->nprob; ++p) {
+        const double n = (double)(b->off_h[p + 1] - b->off_h[p]);
+        if (n >= DIRECT_BWD_LEAVES / 4 * o.fmm_leaf) pairs += n * n;
+    }
+    return pairs > DIRECT_BWD_PAIRS * o.fmm_leaf / 64;
+}
 
 int largest_below(const superdc_batch *b, const superdc_opts &o, int crossover) {
     if (b->max_n < crossover) return b->max_n;
@@ -98,7 +110,7 @@ int largest_direct(const superdc_batch *b, const superdc_opts &o) {
     return largest_below(b, o, fmm_crossover_of(b, o));
 }
 int largest_direct_bwd(const superdc_batch *b, const superdc_opts &o) {
-    return largest_below(b, o, fmm_crossover_of(b, o, bwd_pairs(b)));
+    return bwd_by_fmm(b, o) ? largest_below(b, o, fmm_crossover_of(b, o, 1.0)) : b->max_n;
 }
 bool solve_in_lds(int max_dir, const superdc_opts &o) {
     return max_dir <= SECL_MAX_N && !o.unshifted && !o.interp;
@@ -1278,7 +1290,7 @@ int superdc_secular_backward(superdc_ctx *ctx, const superdc_batch *b, const dou
         // the large problems through the FMM; all of them directly where its workspace does
         // not fit
         int rc;
-        FmmPlan *fp = fmm_for(bm, o, rc, bwd_pairs(b));
+        FmmPlan *fp = bwd_by_fmm(b, o) ? fmm_for(bm, o, rc, 1.0) : nullptr;
         const int nw = g_proj ? 2 : 1;  // weights of a pole; of a root one more with projections
         double *pos = nullptr;
         double2 *ke = nullptr;
