@@ -74,7 +74,6 @@ def unmet_levels(it):
     """Per level, the largest share (percent) over the steps of roots whose iteration ended
     before the stopping test held, over the roots of the problems solved."""
     return _per_level((it & (ITER_UNMET | ITER_CAP)) != 0, (it & ITER_SKIPPED) == 0)
-MFMA_MIN_M = 4           # the library's automatic VALU/MFMA apply switch (columns)
 
 
 MFMA_KERNELS = ("k_apply_mfma", "k_fmmv_eval_mfma")  # FP64 matrix-core kernels
@@ -951,8 +950,8 @@ def conquer_kernel_flops(tree, iters, crossover=FMM_CROSSOVER):
         for t in range(r):
             m = ncol - t - 1
             if m > 0:
-                key = "k_apply_mfma" if m >= MFMA_MIN_M else "k_apply_valu"
-                k[key] += (2 * m + 3) * n * nl + 2 * n * m
+                # b is formed beside the columns, on the matrix cores whatever their number
+                k["k_apply_mfma"] += (2 * m + 3) * n * nl + 2 * n * m
     return k
 
 

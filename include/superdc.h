@@ -89,12 +89,14 @@ typedef struct {
     int32_t fmm_leaf;    /* FMM leaf size; default 64, a multiple of 64, at most 1024     */
     int32_t persistent;  /* 1: one launch per phase for the whole batch;
                             0: one launch per problem per phase (the "plain" baseline)    */
-    int32_t apply_kernel;/* Cauchy apply: 0 auto (MFMA for m >= 4), 1 VALU, 2 FP64 MFMA    */
+    int32_t apply_kernel;/* direct Cauchy apply: 0 auto (MFMA for m >= 4, and for fewer columns
+                            in batches of less than two 64-row tiles per CU), 1 VALU,
+                            2 FP64 MFMA                                                   */
     int32_t fmm_crossover;/* method 0: problems with at least this many roots use the FMM
-                            (solver, b, Qhat^T X); 0 = the context's default: 1024, and
-                            direct sums for every problem of a batch too small to gain
-                            from it (none above 4096 roots, sum of n^2 up to 4e7; applies
-                            9e6)                                                          */
+                            (solver, zhat, b, Qhat^T X, Qhat X); 0 = the context's default:
+                            1024, and direct sums for every problem of a batch too small
+                            to gain from it (none above 4096 roots, and the sum of n^2 over
+                            those of 1024 and more up to 4e7; applies 9e6)                */
     int32_t unshifted;   /* 1: ablation of the local shifting (Sec. 4.2.2): the iterate is
                             kept as lambda itself and every pole difference is formed as
                             d_j - lambda (f evaluated at lambda with no shift); the
@@ -196,8 +198,8 @@ int superdc_secular_solve_noalloc(superdc_ctx *ctx, const superdc_batch *batch,
  *        bnorm_j = (sum_i zhat_i^2 / (d_i - lambda_j)^2)^(-1/2) > 0.
  * Problems that use the FMM (opts.method / opts.fmm_crossover, as for the solver) get b
  * through the eigenvector-side triangular FMM (Sec. 4.3: near poles in the shifted form,
- * far boxes through Chebyshev equivalent sources), the others by direct sums; zhat is
- * always formed by direct products.
+ * far boxes through Chebyshev equivalent sources) and zhat from near products and the far
+ * boxes' moments, the others by direct sums and products.
  */
 int superdc_loewner(superdc_ctx *ctx, const superdc_batch *batch, const double *d,
                     const double *z, const double *rho, const double *eta,
@@ -226,8 +228,10 @@ int superdc_cauchy_apply(superdc_ctx *ctx, const superdc_batch *batch, const dou
  *   in : d, z, rho, eta, origin, status, g_lam[total] = dL/dlambda (may be NULL),
  *        g_proj[total] = dL/dp (may be NULL), u[total] (NULL iff g_proj is NULL)
  *   out: g_d[total] = dL/dd, g_z[total] = dL/dz, g_rho[nprob] = dL/drho.
- * Large batches take their sums through the FMM (opts->persistent, method and crossover as for
- * the solver), the others and every problem below the crossover directly.
+ * Large batches -- some problem above 64 leaves, or a sum of n^2 over those of 16 leaves and
+ * more above 7e7 (fmm_leaf 64; in proportion for others) -- take the sums of the problems that
+ * use the FMM through it (opts->persistent, method and crossover as for the solver; direct
+ * sums where its arrays do not fit the memory), the others take direct sums.
  */
 int superdc_secular_backward(superdc_ctx *ctx, const superdc_batch *batch, const double *d,
                              const double *z, const double *rho, const double *eta,

@@ -15,11 +15,6 @@
 #include "common.h"
 #include "fmm.h"
 
-// waves per CU the FMM solver's split aims at (its items times the split)
-#ifndef SDC_FMM_WAVES_PER_CU
-#define SDC_FMM_WAVES_PER_CU 16
-#endif
-
 using namespace sdc;
 
 namespace {
@@ -505,7 +500,6 @@ FmmPlan *fmm_plan(superdc_batch *b, int leaf, int crossover) {
         fp->split *= 2;
     // the solver's items (pieces of ssub roots that never cross a leaf)
     std::vector<Tile> snat, slpt;
-    fp->ssub = TILE;
     fp->sitem_off_h.push_back(0);
     for (int q = 0; q < fp->nfmm; ++q) {
         const int p = fp->fmm_prob_h[q];
@@ -572,8 +566,7 @@ void set_lists(FmmArgs &f, const FmmLists &l) {
     f.gen = l.gen;
 }
 
-FmmArgs fmm_args(const FmmPlan *fp, const superdc_batch *b, const SolveArgs &a,
-                 const superdc_opts &o) {
+FmmArgs fmm_args(const FmmPlan *fp, const superdc_batch *b, const SolveArgs &a) {
     FmmArgs f{};
     f.off = b->off_d;
     f.leaf = fp->leaf;
@@ -603,7 +596,6 @@ FmmArgs fmm_args(const FmmPlan *fp, const superdc_batch *b, const SolveArgs &a,
     std::copy(fp->upper_cls, fp->upper_cls + 7, f.upper_cls);
     f.split_box = fp->split_box;
     f.nsplit = fp->nsplit;
-    (void)o;
     return f;
 }
 // The eigenvector-side FMM of one call: the list geometry comes from this call's poles and
@@ -612,9 +604,7 @@ FmmArgs fmm_vec_args(const FmmPlan *fp, const superdc_batch *b, const double *d,
                      const double *eta, const int32_t *origin, const int32_t *status) {
     SolveArgs a{};
     a.status = const_cast<int32_t *>(status);
-    superdc_opts o;
-    superdc_opts_default(&o);
-    FmmArgs f = fmm_args(fp, b, a, o);
+    FmmArgs f = fmm_args(fp, b, a);
     f.pos = d;
     f.tail = nullptr;
     f.teta = eta;
@@ -851,7 +841,7 @@ int loewner_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const
             a.tiles = fp->dir_lpt[chunk_slot(TILE)];
             a.ntiles = fp->dir_count[chunk_slot(TILE)];
         }
-        SDC_HIP(launch_loewner(a, S, s, false));
+        SDC_HIP(launch_loewner(a, S, s));
         if (fp) {
             VecArgs af = a;
             af.tiles = fp->leaf_lpt;
@@ -875,7 +865,7 @@ int loewner_run(superdc_ctx *ctx, const superdc_batch *b, const double *d, const
             }
             a.tiles = L->nat + L->begin[p];
             a.ntiles = L->begin[p + 1] - L->begin[p];
-            SDC_HIP(launch_loewner(a, S, s, false));
+            SDC_HIP(launch_loewner(a, S, s));
             if (fmm_b) SDC_HIP(launch_bnorm(a, S, s));
         }
         if (fp && fmm_b) SDC_HIP(fmmv_run(ctx, b, fp, f, v, false, false, s));
@@ -1120,7 +1110,6 @@ int superdc_batch_create(superdc_ctx *ctx, int32_t nprob, const int64_t *off_hos
         return hip_fail(e);
     }
     b->mem.push_back(mem);
-    b->app = LaunchShape{TILE, 1};
     *out = b;
     return SUPERDC_OK;
 }
@@ -1172,7 +1161,7 @@ int superdc_secular_solve(superdc_ctx *ctx, const superdc_batch *b, const double
     }
     FmmArgs f{};
     if (fp) {
-        f = fmm_args(fp, b, a, o);
+        f = fmm_args(fp, b, a);
         f.gen = ++fp->own.gen;  // the lists this solve builds
     }
     if (o.persistent) {

@@ -182,8 +182,8 @@ __global__ __launch_bounds__(1024) void k_bwd(BwdArgs a) {
 // and 0.3 ms for the problems below the crossover.  The boxes lie 3 widths away and their nodes
 // are offsets from their centres, so that the far field is as exact as the direct sums: gradients
 // of single eigenvalues of 2048 to 8192 roots, entry by entry against long double, g_d off by
-// 2.3e-15 at most and 4.7e-16 rms (direct 3.2e-15 and 6.0e-16), g_z 2.2e-15 and 4.6e-16 (3.0e-15
-// and 5.8e-16); with boxes from 1.5 widths on, 2.0e-13 and 8.9e-15 at most.
+// 2.4e-15 at most and 5.2e-16 rms (direct 3.2e-15 and 6.8e-16), g_z 2.2e-15 and 4.9e-16 (3.0e-15
+// and 6.6e-16); with boxes from 1.5 widths on, 2.0e-13 and 8.9e-15 at most.
 // ---------------------------------------------------------------------------------------
 template <bool PROJ, int PASS>
 struct BwdFar {

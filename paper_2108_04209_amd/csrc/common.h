@@ -272,7 +272,7 @@ struct superdc_batch {
     double big_pairs = 0.0;             // sum of n^2 over the problems of the FMM's sizes
     TileList lists[sdc::kNumChunks];    // by cut length
     // chosen launch shapes (heuristic, or set by the autotuner): batched launches
-    LaunchShape sec, vec, app, bwd;
+    LaunchShape sec, vec, bwd;
     int lds_chunk = 64;                 // roots per work item of the direct solver in LDS
     int fmm_ssplit = 0;                 // FMM solver: wavefronts per work item (0: heuristic)
     bool tuned = false;
@@ -375,12 +375,11 @@ struct VecArgs {
     double2 *dz;   // workspace (d_i, zhat_i) per pole
     double *zhat, *bnorm;
 };
-// pack = false: the (d_K, eta) pairs were packed already (launch_pack_ke)
 // zhat and b at once, batches of problems of at most VS_N poles
 constexpr int VS_N = 192;
 hipError_t launch_vectors_small(const VecArgs &a, int nprob, int max_n, hipStream_t s);
-hipError_t launch_loewner(const VecArgs &a, int split, hipStream_t s,
-                          bool pack = true);
+// zhat from the pairs (d_K, eta) that launch_pack_ke, or a solve, wrote to ke
+hipError_t launch_loewner(const VecArgs &a, int split, hipStream_t s);
 hipError_t launch_pack_ke(const VecArgs &a, hipStream_t s);
 hipError_t launch_bnorm(const VecArgs &a, int split, hipStream_t s);
 
@@ -413,7 +412,6 @@ struct BwdArgs {
     const int32_t *origin, *status;
     const double *g_lam, *g_proj, *u;
     double *g_d, *g_z, *g_rho;
-    double4 *pz;    // workspace (d_i, z_i, u_i, 0) per pole
     double4 *rk;    // workspace (d_K, eta, alpha, beta) per root
     double *gk;     // workspace gamma per root
 };

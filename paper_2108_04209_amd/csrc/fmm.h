@@ -128,9 +128,9 @@ struct FmmPlan {
     std::vector<int32_t> item_off_h;   // FMM problem q owns items [item_off[q], item_off[q+1])
     Tile *leaf_lpt = nullptr;          // work items, longest problems first
     Tile *leaf_nat = nullptr;          // ... in problem order
-    // the solver's work items: longer pieces (ssub roots), so a wavefront refills lanes whose
-    // roots converged instead of idling until its slowest root is done
-    int ssub = 2 * TILE;
+    // the solver's work items: ssub roots of a leaf, shared by ssplit wavefronts (the solver in LDS
+    // gives each its own roots, the ablations' its share of every root's sources)
+    int ssub = TILE;
     int snitems = 0;
     int ssplit = 1;
     std::vector<int32_t> sitem_off_h;
@@ -208,13 +208,11 @@ struct FmmlArgs {
     double2 *pd;              // (d_j, delta_j) per entry (pole and its root's offset)
     double2 *geo;             // [boxes] (c, hw)
     double *mom;              // [boxes][FMML_K] coefficients (-1)^(k+1) M_k / k, k = 1 .. K
-    // pack != 0: the leaves' launch packs its poles itself (when the lists already exist, as
-    // the separate packing launch would): (d_j, delta_j) into pd, (d_{K_j}, eta_j) into ke
-    // when ke is set
+    // pack != 0: the leaves' launch packs its poles' (d_j, delta_j) into pd itself (when the lists
+    // already exist, as the separate packing launch would)
     int pack;
     const double *d, *eta;
     const int32_t *origin;
-    double2 *ke;
 };
 hipError_t launch_fmml_moments(const FmmArgs &f, const FmmlArgs &l, hipStream_t s);
 

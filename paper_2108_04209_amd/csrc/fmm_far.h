@@ -18,7 +18,8 @@ namespace sdc {
 // shifted differences of the targets themselves.  Against long double, with and without the
 // expansion: single entries of Q (5 problems of 8192, 40 of 2048) 1.0e-14 and 9.9e-15 off at most,
 // what the boxes' own nodes leave; b of the last root, whose far field is all of it, 8.8e-16 and
-// 6.7e-16; a last root with 97 % of its weight in one box 1.5 intervals away 3.8e-16 and 5.7e-16.
+// 6.7e-16; a last root with all but 1e-9 of its weight in boxes 1.5 intervals away and more 3.8e-16
+// and 5.7e-16.
 constexpr double FV_SEP_T = 1.5;
 constexpr double FV_SEP_BWD = 3.0;  // the adjoint's, as its lists' (1/t^2 and 1/t^3 lose more)
 constexpr int FV_MIN_EXP = 4;  // fewer boxes: the interpolation costs more than it saves

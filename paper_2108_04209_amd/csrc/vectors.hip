@@ -535,11 +535,9 @@ hipError_t launch_loewner_fmm(const VecArgs &a, const FmmArgs &f, const FmmlArgs
     return hipGetLastError();
 }
 
-hipError_t launch_loewner(const VecArgs &a, int split, hipStream_t s,
-                          bool pack) {
+hipError_t launch_loewner(const VecArgs &a, int split, hipStream_t s) {
     if (a.ntiles <= 0) return hipSuccess;
     const size_t lds = split > 1 ? sizeof(double4) * WAVE * split : 0;
-    if (pack) SDC_LAUNCH(KID_PACK, k_pack_ke, dim3(a.ntiles), dim3(64), 0, s, a);
     SDC_LAUNCH(KID_LOEWNER, k_loewner, dim3(a.ntiles), dim3(WAVE * split), lds, s, a);
     return hipGetLastError();
 }
